@@ -536,6 +536,7 @@ int ee_prefill(const ee_model* m, ee_kv* kv, ee_batch* b, const int32_t* dev_tok
     hipStream_t s = as_stream(stream);
     int rc = launch_prefill_begin(m, kv, b, dev_tok, dev_pos, dev_seq, n, s);
     b->kv_seq = b->wsp<int32_t>(b->W.kv_seq);      // the layers address the cache through the entry's row
+    b->long_runs = true;
     bool x_ready = false;
     for (int l = 1; l <= R && rc == EE_OK; ++l) {
         if (c.dtype == EE_BF16) {
@@ -548,6 +549,7 @@ int ee_prefill(const ee_model* m, ee_kv* kv, ee_batch* b, const int32_t* dev_tok
         }
     }
     b->kv_seq = nullptr;
+    b->long_runs = false;
     return rc;
 }
 

@@ -863,7 +863,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
                    const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos,
                    const float* __restrict__ rope, int max_pos, KvView kv, bf16_t* __restrict__ q_hi,
                    bf16_t* __restrict__ q_lo, int32_t* __restrict__ status, int64_t z_stride,
-                   int32_t* __restrict__ order, int splits, int64_t plane) {
+                   int32_t* __restrict__ order, int tile_entries, int splits, int64_t plane) {
     int i = blockIdx.x;
     int n = min(*n_ptr, B);
     if (i >= n) return;
@@ -871,18 +871,22 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
     kv.layer0 += blockIdx.z;
     int b = idx[i];
     int p = pos[b];
-    if (order != nullptr && blockIdx.y == 0 && threadIdx.x < 64) {
-        // launch order of the attention workgroups: list entries by falling context length (ties by
-        // entry), so that the longest rows start first and the last wave of workgroups is short.
-        // rank of this entry = how many entries come before it; the ranks form a permutation.
+    if (order != nullptr && blockIdx.y == 0 && threadIdx.x < 64 && i % tile_entries == 0) {
+        // launch order of the attention workgroups: tiles of tile_entries list entries (one in a decode
+        // step) by falling context length (that of a tile's last entry, as a context comes in rising
+        // order; ties by tile), so that the longest start first and the last round of workgroups is short.
+        // Rank of this tile = how many tiles come before it; the ranks form a permutation.
+        auto key = [&](int tile) { return pos[idx[min(n, (tile + 1) * tile_entries) - 1]]; };
+        const int tile = i / tile_entries, tiles = (n + tile_entries - 1) / tile_entries;
+        const int mine = key(tile);
         int before = 0;
-        for (int j = threadIdx.x; j < n; j += 64) {
-            int pj = pos[idx[j]];
-            before += (pj > p || (pj == p && j < i)) ? 1 : 0;
+        for (int j = threadIdx.x; j < tiles; j += 64) {
+            const int kj = key(j);
+            before += (kj > mine || (kj == mine && j < tile)) ? 1 : 0;
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
-        if (threadIdx.x == 0) order[before] = i;
+        if (threadIdx.x == 0) order[before] = tile;
     }
     const int hd = 128, half = 64;
     int Hkv = kv.n_kv_heads;
@@ -970,36 +974,22 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
 // The result registers of the score MFMAs are, lane for lane, the P operand
 // of the value MFMAs (the grouped V layout is chosen to make that so).
 // q and P enter as bf16 (hi, lo) pairs: two MFMAs each, fp32-grade products.
-template <bool PAIR>
-__global__ void __launch_bounds__(256, PAIR ? 3 : 2)
-k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
-            const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr, int B,
-            const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao, int KB_ao, int n_splits,
-            float* __restrict__ part, const int32_t* __restrict__ order) {
-    __shared__ float sm_m[4][16];
-    __shared__ float sm_l[4][16];
-    __shared__ float sm_o[4][16][128];
-    const int g = blockIdx.x;
-    const int n = min(*n_ptr, B);
+// The work of one workgroup: list entries first .. first + cnt - 1 of kv head g, share `share` of n_splits of
+// the position groups.  AHEAD: a wave asks for its next group before it works on the current one.
+struct AttnShared {
+    float m[4][16];
+    float l[4][16];
+    float o[4][16][128];
+};
+
+template <bool PAIR, bool AHEAD>
+__device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo,
+                                             int Hq, const int32_t* __restrict__ idx, const int32_t* __restrict__ pos,
+                                             const KvView& kv, uint4* __restrict__ ao, int KB_ao, int n_splits, int share,
+                                             float* __restrict__ part, int g, int first, int cnt) {
     const int G = Hq / kv.n_kv_heads;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int n16 = lane & 15, gq = lane >> 4;
-    // PAIR (context pass and other passes over list entries, 2 G <= 16): the workgroup serves the E = 16 / G
-    // list entries E y .. E y + E - 1.  Consecutive entries that read the same cache row (a context passed
-    // in rising position order) share its K/V stream: entry j of such a run has its G heads in the MFMA
-    // columns G j .. G j + G - 1, each column masked at its own entry's position.  With one query head per
-    // kv head 16 entries share a stream, with eight heads two.  A change of cache row inside the E entries
-    // starts another run, served after the first.
-    int first, cnt = 1;
-    if (PAIR) {
-        const int E = 16 / G;
-        first = E * (int)blockIdx.y;
-        if (first >= n) return;
-        cnt = min(E, n - first);
-    } else {
-        if ((int)blockIdx.y >= n) return;
-        first = order[blockIdx.y];            // longest contexts first
-    }
     for (int r0 = 0; r0 < cnt;) {
     const int sq = kv_row(kv, idx[first + r0]);
     int r1 = r0 + 1;
@@ -1032,9 +1022,9 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     for (int hb = 0; hb < 8; ++hb) O[hb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const int n_groups = (n_pos + 31) >> 5;
-    // with n_splits > 1 this workgroup covers the blockIdx.z-th share of the position groups
-    const int g_lo = (int)(((int64_t)n_groups * blockIdx.z) / n_splits);
-    const int g_hi = (int)(((int64_t)n_groups * (blockIdx.z + 1)) / n_splits);
+    // with n_splits > 1 this workgroup covers the share-th share of the position groups
+    const int g_lo = (int)(((int64_t)n_groups * share) / n_splits);
+    const int g_hi = (int)(((int64_t)n_groups * (share + 1)) / n_splits);
     // K and V tiles of one 32-position group as this lane holds them for the MFMAs
     struct KVTiles { uint4 k[2][4]; uint4 v[8]; };
     auto load_kv = [&](int t) -> KVTiles {
@@ -1057,15 +1047,15 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     // equal at 256).  Context pass with two entries per workgroup: three workgroups, no prefetch
     // (0.8 % faster there).
     KVTiles nxt;
-    if constexpr (!PAIR) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has
+    if constexpr (AHEAD) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has
     for (int t = g_lo + w; t < g_hi; t += 4) {
         const int p0 = t << 5;
         KVTiles cur;
-        if constexpr (PAIR) {
-            cur = load_kv(t);
-        } else {
+        if constexpr (AHEAD) {
             cur = nxt;
             if (t + 4 < g_hi) nxt = load_kv(t + 4);
+        } else {
+            cur = load_kv(t);
         }
         floatx4 S0 = {0.f, 0.f, 0.f, 0.f}, S1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1129,27 +1119,27 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     // O[hb][r]: feature 16 hb + 4 gq + r of head n16 (unnormalised), this wave's positions
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
-    if (gq == 0) { sm_m[w][n16] = m_run; sm_l[w][n16] = l_run; }
+    if (gq == 0) { sm.m[w][n16] = m_run; sm.l[w][n16] = l_run; }
 #pragma unroll
     for (int hb = 0; hb < 8; ++hb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sm_o[w][n16][16 * hb + 4 * gq + r] = O[hb][r];
+        for (int r = 0; r < 4; ++r) sm.o[w][n16][16 * hb + 4 * gq + r] = O[hb][r];
     __syncthreads();
     {
         const int head = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;     // head = MFMA column
         if (head < n_col) {
             const int i = first + r0 + head / G;
             const int hq = head % G;
-            float M = fmaxf(fmaxf(sm_m[0][head], sm_m[1][head]), fmaxf(sm_m[2][head], sm_m[3][head]));
+            float M = fmaxf(fmaxf(sm.m[0][head], sm.m[1][head]), fmaxf(sm.m[2][head], sm.m[3][head]));
             float wgt[4], Lsum = 0.f;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { wgt[k] = __expf(sm_m[k][head] - M); Lsum += sm_l[k][head] * wgt[k]; }
+            for (int k = 0; k < 4; ++k) { wgt[k] = __expf(sm.m[k][head] - M); Lsum += sm.l[k][head] * wgt[k]; }
             float o[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 float acc = 0.f;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) acc += sm_o[k][head][c0 + j] * wgt[k];
+                for (int k = 0; k < 4; ++k) acc += sm.o[k][head][c0 + j] * wgt[k];
                 o[j] = acc;
             }
             if (n_splits == 1) {
@@ -1159,7 +1149,7 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
                 ao[afrag_chunk(i, col, KB_ao)] = pk;
             } else {
                 // unnormalised share: [i][kv head][split][head][130] = 128 features, max, sum
-                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * n_splits + blockIdx.z) * 16 + hq) * 130;
+                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * n_splits + share) * 16 + hq) * 130;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) p[c0 + j] = o[j];
                 if (c0 == 0) { p[128] = M; p[129] = Lsum; }
@@ -1169,6 +1159,303 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     r0 = r1;
     if (r0 < cnt) __syncthreads();         // the merge has read the shared arrays before the next run writes them
     }
+}
+
+template <bool PAIR>
+__global__ void __launch_bounds__(256, PAIR ? 3 : 2)
+k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
+            const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr, int B,
+            const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao, int KB_ao, int n_splits,
+            float* __restrict__ part, const int32_t* __restrict__ order) {
+    __shared__ AttnShared sm;
+    const int n = min(*n_ptr, B);
+    // PAIR (context pass and other passes over list entries, 2 G <= 16): the workgroup serves the E = 16 / G
+    // list entries E y .. E y + E - 1.  Consecutive entries that read the same cache row (a context passed
+    // in rising position order) share its K/V stream: entry j of such a run has its G heads in the MFMA
+    // columns G j .. G j + G - 1, each column masked at its own entry's position.  With one query head per
+    // kv head 16 entries share a stream, with eight heads two.  A change of cache row inside the E entries
+    // starts another run, served after the first.
+    int first, cnt = 1;
+    if (PAIR) {
+        const int E = 16 / (Hq / kv.n_kv_heads);
+        first = E * (int)blockIdx.y;
+        if (first >= n) return;
+        cnt = min(E, n - first);
+    } else {
+        if ((int)blockIdx.y >= n) return;
+        first = order[blockIdx.y];            // longest contexts first
+    }
+    attn_streams<PAIR, !PAIR>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, n_splits, blockIdx.z, part, blockIdx.x, first, cnt);
+}
+
+// ------------------------------------------------------------------ context-pass attention
+// What bounds the kernel above in a context pass: 16 MFMA columns per workgroup, so with eight query heads
+// per kv head two entries share a pass over the keys and values and a 2000-entry call streams them 1000
+// times.  Here a workgroup serves a tile of 4 C 16-column blocks (C per wave; 4 C E entries with E = 16 / G):
+// the keys and values of its cache row go through LDS in stages of 64 positions, two stage buffers filled by
+// LDS-DMA loads, and every wave works through all of them for its own columns, so no merge follows.  Scores
+// and P V take the same operands as above (queries and probabilities as bf16 pairs hi + lo).  Exponentials
+// are base 2 with the scale folded in, and a column's running maximum is only raised (and its sums rescaled)
+// when it grows by more than 2^8, which leaves the sums in fp32 range and the result unchanged.
+// Measured (70B shape, 1999 entries of three contexts of 1400 to 2200 positions): 585 -> 275 us, at 2 us of
+// MFMAs in 4.3 us per stage and pair of waves; what is left is the softmax arithmetic, which the other wave
+// of the SIMD covers in part, at the 1.65 GHz the power limit leaves beside the products of the layer.  7B
+// shape, 1024 entries of four prompts (C = 1): 73 -> 35 us.  All eight K reads of a group are asked for
+// before its first MFMA and the V reads before the softmax; with a read in front of each product C = 2 took
+// 315 us, and with one register too many (a spill's reload waits for the stage just requested) up to 760.
+// Entries of a tile that name more than two cache rows are served by attn_streams instead, one workgroup per
+// E entries as above: the workgroups y = sub * tiles + t, sub = 0 .. 4 C - 1, exist for that; on a tile of
+// one or two rows only sub = 0 works.
+#define CTX_STAGE 2048                        /* uint4 of a stage: two groups of 32 positions, 16 KiB each */
+
+__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b) {     // round to nearest even, a in the low half
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
+}
+
+// maximum over the four lanes that hold a column (lane, lane ^ 16, lane ^ 32, lane ^ 48)
+__device__ __forceinline__ float column_max(float v) {
+    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+template <int C>
+__device__ __forceinline__ void attn_tile(uint4* lds, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
+                                          const int32_t* __restrict__ idx, const int32_t* __restrict__ pos, const KvView& kv,
+                                          uint4* __restrict__ ao, int KB_ao, int g, int first, int cnt) {
+    const int G = Hq / kv.n_kv_heads, E = 16 / G;
+    const int lane = threadIdx.x & 63, n16 = lane & 15, gq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned lane_bytes = (unsigned)lane * 16u, lds0 = (unsigned)(size_t)lds;
+    const float scale2 = (1.0f / sqrtf(128.0f)) * 1.44269504088896340736f;    // exp(x) = 2^(x log2 e)
+    const float NEG = -1.0e30f;
+    for (int r0 = 0; r0 < cnt;) {
+        const int sq = __builtin_amdgcn_readfirstlane(kv_row(kv, idx[first + r0]));
+        int r1 = r0 + 1;
+        while (r1 < cnt && __builtin_amdgcn_readfirstlane(kv_row(kv, idx[first + r1])) == sq) ++r1;
+        const int cap = kv.cap[sq];
+        int n_pos = 1;                                       // positions read: the longest of the run
+        for (int j = r0 + lane; j < r1; j += 64) n_pos = max(n_pos, min(pos[idx[first + j]] + 1, cap));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n_pos = max(n_pos, __shfl_xor(n_pos, o, 64));
+        n_pos = __builtin_amdgcn_readfirstlane(n_pos);
+        const uint4* Kb = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(kv.pool) + kv_block(kv, sq, g, cap));
+        const uint64_t kv_base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)Kb >> 32)) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(uint64_t)Kb);
+        const int n_groups = (n_pos + 31) >> 5, n_st = (n_groups + 1) >> 1;
+
+        // this lane's column of each block: entry, head, positions (0: a column without an entry of the run)
+        int ent[C], np[C];
+        bf16x8 qh[C][4], ql[C][4];
+        int lo_np = 0x7fffffff, hi_np = 0;                   // over the wave's live columns
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const int e = (w * C + j) * E + n16 / G;
+            const bool live = n16 < E * G && e >= r0 && e < r1;
+            ent[j] = live ? first + e : -1;
+            np[j] = live ? max(1, min(pos[idx[first + e]] + 1, cap)) : 0;
+            const uint4 z = make_uint4(0, 0, 0, 0);
+            const int64_t qo = ((int64_t)(first + (live ? e : r0)) * Hq + (int64_t)g * G + n16 % G) * 128 + 8 * gq;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                qh[j][c] = as_bf16x8(live ? *reinterpret_cast<const uint4*>(q_hi + qo + 32 * c) : z);
+                ql[j][c] = as_bf16x8(live ? *reinterpret_cast<const uint4*>(q_lo + qo + 32 * c) : z);
+            }
+            int l = live ? np[j] : 0x7fffffff, h = np[j];
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) { l = min(l, __shfl_xor(l, o, 64)); h = max(h, __shfl_xor(h, o, 64)); }
+            lo_np = min(lo_np, l);
+            hi_np = max(hi_np, h);
+        }
+        lo_np = __builtin_amdgcn_readfirstlane(lo_np);
+        hi_np = __builtin_amdgcn_readfirstlane(hi_np);
+        float m_run[C], l_run[C];
+        floatx4 O[C][8];
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            m_run[j] = NEG; l_run[j] = 0.f;
+#pragma unroll
+            for (int hb = 0; hb < 8; ++hb) O[j][hb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+
+        // wave w sends pieces 8 w .. 8 w + 7 (1 KiB each) of a stage; a group past the last one of the row is
+        // replaced by the last one (its positions are masked)
+        auto issue = [&](int t) {
+            const int grp = min(2 * t + (w >> 1), n_groups - 1);
+            const uint4* src = reinterpret_cast<const uint4*>(kv_base + ((uint64_t)grp << 14) + ((w & 1) << 13));
+            const unsigned dst = lds0 + (unsigned)((t & 1) * CTX_STAGE + w * 512) * 16u;
+#pragma unroll
+            for (int p = 0; p < 8; ++p) dma_tile(src + p * 64, lane_bytes, dst + (unsigned)p * 1024u);
+        };
+        // the queries are in registers before the first LDS-DMA load: a wait for them inside the loop would wait
+        // for the stage that has just been asked for
+#pragma unroll
+        for (int j = 0; j < C; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(qh[j][c]), "+v"(ql[j][c]));
+        __syncthreads();                                     // an earlier run's last stage has been read
+        issue(0);
+        for (int t = 0; t < n_st; ++t) {
+            // this wave's pieces of stage t have landed; after the barrier everybody's have, and the other
+            // buffer (stage t - 1) has been read by all waves
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (t + 1 < n_st) issue(t + 1);
+            const int p0 = t << 6;
+            if (p0 >= hi_np) continue;                       // no column of this wave reaches this stage
+            const uint4* st = lds + (t & 1) * CTX_STAGE + lane;
+            const bool edge = p0 + 64 > lo_np;               // a column of the wave ends inside this stage
+#pragma unroll 1
+            for (int q = 0; q < 2; ++q) {                    // 32 positions from pg on, their K and V at kvg
+                const uint4* kvg = st + q * 1024;
+                const int pg = p0 + 32 * q;
+                if (pg >= hi_np) break;
+                bf16x8 kf[8];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { kf[c] = as_bf16x8(kvg[c * 64]); kf[4 + c] = as_bf16x8(kvg[256 + c * 64]); }
+                floatx4 S[C][2];                             // [pb][r]: position pg + 16 pb + 4 gq + r of column n16
+#pragma unroll
+                for (int j = 0; j < C; ++j) S[j][0] = S[j][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+                __builtin_amdgcn_sched_barrier(0);           // all eight K reads are under way before the first MFMA
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        S[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[c], qh[j][c], S[j][0], 0, 0, 0);
+                        S[j][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[4 + c], qh[j][c], S[j][1], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        S[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[c], ql[j][c], S[j][0], 0, 0, 0);
+                        S[j][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[4 + c], ql[j][c], S[j][1], 0, 0, 0);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                uint4 vf[8];                                 // under way during the softmax
+#pragma unroll
+                for (int hb = 0; hb < 8; ++hb) vf[hb] = kvg[512 + hb * 64];
+                __builtin_amdgcn_sched_barrier(0);
+                if (edge) {
+                    asm volatile("");                        // a branch, not 8 C selects in every group
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        const int end = np[j] - pg - 4 * gq; // the lane's positions 16 pb + r from here on are masked
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            if (16 * (i >> 2) + (i & 3) >= end) S[j][i >> 2][i & 3] = NEG;
+                    }
+                }
+                float mx[C];
+                bool raise = false;
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    mx[j] = NEG;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) mx[j] = fmaxf(mx[j], S[j][i >> 2][i & 3]);
+                    mx[j] = column_max(mx[j]) * scale2;
+                    raise = raise || mx[j] > m_run[j] + 8.0f;
+                }
+                if (__any(raise)) {
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        const float m_new = mx[j] > m_run[j] + 8.0f ? mx[j] : m_run[j];
+                        const float alpha = __builtin_amdgcn_exp2f(m_run[j] - m_new);
+                        m_run[j] = m_new;
+                        l_run[j] *= alpha;
+#pragma unroll
+                        for (int hb = 0; hb < 8; ++hb) O[j][hb] = O[j][hb] * alpha;
+                    }
+                }
+                uint4 ph[C], pl[C];
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    float pv[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) pv[i] = __builtin_amdgcn_exp2f(fmaf(S[j][i >> 2][i & 3], scale2, -m_run[j]));
+                    l_run[j] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
+                    uint32_t hw[4], lw[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        hw[i] = cvt2_bf16(pv[2 * i], pv[2 * i + 1]);
+                        lw[i] = cvt2_bf16(pv[2 * i] - __uint_as_float(hw[i] << 16), pv[2 * i + 1] - __uint_as_float(hw[i] & 0xffff0000u));
+                    }
+                    ph[j] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+                    pl[j] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+                }
+                if (pg + 32 > n_pos) {                       // what lies beyond the row's positions was never written
+                    const int end = n_pos - pg - 4 * gq;     // element e of a lane's chunk is position e (e < 4) or 12 + e
+#pragma unroll
+                    for (int hb = 0; hb < 8; ++hb) {
+                        uint32_t* vw = reinterpret_cast<uint32_t*>(&vf[hb]);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if ((e < 4 ? e : 12 + e) >= end) vw[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                    for (int j = 0; j < C; ++j)
+#pragma unroll
+                        for (int u = 4 * half; u < 4 * half + 4; ++u)
+                            O[j][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vf[u]), as_bf16x8(ph[j]), O[j][u], 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < C; ++j)
+#pragma unroll
+                        for (int u = 4 * half; u < 4 * half + 4; ++u)
+                            O[j][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vf[u]), as_bf16x8(pl[j]), O[j][u], 0, 0, 0);
+                }
+            }
+        }
+        // O[j][hb][r]: feature 16 hb + 4 gq + r of column n16 of block j
+        int chunk0 = (g * G + n16 % G) * 128;
+        asm volatile("" : "+v"(chunk0));                     // the addresses below are not worth registers in the loop
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            float l = l_run[j];
+            l += __shfl_xor(l, 16, 64);
+            l += __shfl_xor(l, 32, 64);
+            if (ent[j] < 0) continue;
+            const float inv = 1.0f / l;
+#pragma unroll
+            for (int hb = 0; hb < 8; ++hb) {
+                const int col = chunk0 + 16 * hb + 4 * gq;
+                uint2* dst = reinterpret_cast<uint2*>(ao + afrag_chunk(ent[j], col & ~7, KB_ao)) + ((col >> 2) & 1);
+                *dst = make_uint2(cvt2_bf16(O[j][hb][0] * inv, O[j][hb][1] * inv), cvt2_bf16(O[j][hb][2] * inv, O[j][hb][3] * inv));
+            }
+        }
+        r0 = r1;
+    }
+}
+
+template <int C>
+__global__ void __launch_bounds__(256, 2)
+k_bf16_attn_ctx(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq, const int32_t* __restrict__ idx,
+                const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao,
+                int KB_ao, const int32_t* __restrict__ order) {
+    __shared__ uint4 lds[2 * CTX_STAGE];
+    static_assert(sizeof(AttnShared) <= sizeof(lds), "the merge arrays share the stage buffers");
+    const int n = min(*n_ptr, B);
+    const int E = 16 / (Hq / kv.n_kv_heads), TE = 4 * C * E;
+    const int tiles = gridDim.y / (4 * C);                   // of the batch's capacity; n entries fill the first ones
+    const int sub = blockIdx.y / tiles, t = blockIdx.y % tiles;
+    if (t * TE >= n) return;
+    const int first = order[t] * TE, cnt = min(TE, n - first);
+    const int lane = threadIdx.x & 63;
+    int changes = 0;                                         // cache-row changes inside the tile
+    for (int j = lane; j + 1 < cnt; j += 64) changes += kv_row(kv, idx[first + j]) != kv_row(kv, idx[first + j + 1]) ? 1 : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) changes += __shfl_xor(changes, o, 64);
+    if (__builtin_amdgcn_readfirstlane(changes) <= 1) {
+        if (sub == 0) attn_tile<C>(lds, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, blockIdx.x, first, cnt);
+        return;
+    }
+    if (sub * E >= cnt) return;
+    attn_streams<true, true>(*reinterpret_cast<AttnShared*>(lds), q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr,
+                             blockIdx.x, first + sub * E, min(E, cnt - sub * E));
 }
 
 // merges the position shares of k_bf16_attn in share order: one workgroup per (kv head, list entry)
@@ -1437,6 +1724,26 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     return true;
 }
 
+// How the attention of a context pass is tiled: C 16-column blocks per wave (0: not tiled), entries per tile.
+// Two blocks per wave read each K and V operand from LDS half as often, one block gives twice the
+// workgroups: two where that still leaves two workgroups per CU (70B shape, 1999 entries: 275 us against 310
+// with one), one from one workgroup per CU on (256 entries, 1500 cached: layer 558 -> 539 us; 600 entries of
+// four contexts: 1284 -> 1239 us).  Below that the kernel that splits a row's positions over its waves stays.
+// Speculative rounds keep it too: their runs are a few drafts long.
+struct CtxTiles { int C = 0, tile_entries = 1, tiles = 0; };
+static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
+    CtxTiles r;
+    const int G = c.n_q_heads / c.n_kv_heads, E = 16 / G;
+    if (!b->long_runs) return r;
+    for (int C = 2; C >= 1; --C) {
+        const int te = 4 * C * E, tiles = (b->B + te - 1) / te;
+        if (tiles * c.n_kv_heads < 256 * C || tiles * 4 * C > 65535) continue;
+        r.C = C; r.tile_entries = te; r.tiles = tiles;
+        break;
+    }
+    return r;
+}
+
 // x_ready: the operand matrix already holds RMSNorm(h; attention gain of this layer).
 // tail_gain (with x_done): if the last product of the layer is finished from K-slice planes, that
 // kernel also leaves RMSNorm(h; tail_gain) in the operand matrix and sets *x_done.
@@ -1455,6 +1762,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     uint4* ao = b->wsp<uint4>(b->W.ao);
     bf16_t* act = b->wsp<bf16_t>(b->W.act);
     KvView view = make_view(m, kv, layer, b);
+    const CtxTiles ctx = ctx_tiles(c, b);
 
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
@@ -1476,7 +1784,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         hipLaunchKernelGGL(k_bf16_rope_append, dim3(B, 4), dim3(256), 0, s, src, qkv_n, c.n_q_heads, idx, n_ptr, B,
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
-                           b->wsp<int32_t>(b->W.attn_order), qkv_splits, (int64_t)b->Mpad * qkv_n);
+                           b->wsp<int32_t>(b->W.attn_order), ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * qkv_n);
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
@@ -1488,7 +1796,13 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         // context pass: 16 / G entries per workgroup, which share the K/V stream where they sit in the same cache row
         const int G = c.n_q_heads / c.n_kv_heads;
         const bool pair = b->kv_seq != nullptr && n_splits == 1 && 2 * G <= 16;
-        if (pair)
+        if (ctx.C) {
+            n_splits = 1;
+            auto kern = ctx.C == 2 ? k_bf16_attn_ctx<2> : k_bf16_attn_ctx<1>;
+            hipLaunchKernelGGL(kern, dim3(c.n_kv_heads, ctx.tiles * 4 * ctx.C), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
+                               b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
+                               qd / 16, b->wsp<int32_t>(b->W.attn_order));
+        } else if (pair)
             hipLaunchKernelGGL(k_bf16_attn<true>, dim3(c.n_kv_heads, (B + 16 / G - 1) / (16 / G), 1), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
                                qd / 16, 1, b->wsp<float>(b->W.attn_part), b->wsp<int32_t>(b->W.attn_order));
@@ -1586,7 +1900,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(B, 1, nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, 1, (int64_t)0);
+                       (int32_t*)nullptr, 1, 1, (int64_t)0);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
