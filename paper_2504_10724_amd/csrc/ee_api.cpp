@@ -276,6 +276,7 @@ int ee_kv_bind(const ee_model* m, void* dev_pool, size_t pool_bytes, int n_resid
     kv->B = B;
     kv->T = T;
     kv->h_cap.assign(host_capacity, host_capacity + B);
+    for (int b = 0; b < B; ++b) kv->max_cap = host_capacity[b] > kv->max_cap ? host_capacity[b] : kv->max_cap;
     kv->h_off.resize(B);
     int64_t acc = 0;
     for (int b = 0; b < B; ++b) { kv->h_off[b] = acc; acc += host_capacity[b]; }
@@ -375,9 +376,9 @@ static void lay_workspace(const ee_model* m, int B, WsLayout* W) {
         W->gemm_part_bytes = Mpad * ((size_t)384 << 10);   // K-slice planes: 96 MiB at 256 rows
         W->gemm_part = take(W->gemm_part_bytes);
         size_t pairs = Mpad * (size_t)c.n_kv_heads;   // position shares only when there are few pairs
-        W->attn_part_bytes = pairs < 512 + 32 * (size_t)c.n_kv_heads ? pairs * 16 * 16 * 130 * 4 : 0;
+        W->attn_part_bytes = pairs < 512 + 32 * (size_t)c.n_kv_heads ? pairs * 16 * 16 * 132 * 4 : 0;
         W->attn_part = take(W->attn_part_bytes);
-        W->attn_order = take(Mpad * 4);
+        W->attn_order = take(Mpad * 32);
         W->kv_seq = take(Mpad * 4);
         W->gone_idx = take(Mpad * 4);
         W->n_gone = take(4);

@@ -56,6 +56,15 @@ __device__ __forceinline__ int64_t afrag_chunk(int row, int c, int KB /* K/16 */
     return ((int64_t)mb * KB + kb) * 64 + lane;
 }
 
+// Which list entry a block of a per-entry launch takes.  Blocks go to the 8 XCDs round-robin and each XCD has its
+// own L2; neighbouring entries write neighbouring 16-byte pieces of the same lines (operand tiles, cached keys and
+// values), so `near` consecutive entries go to blocks 8 apart: one XCD completes their lines.  The grid is
+// rounded up to a multiple of 8 near (entry_grid); near = 1: block b takes entry b.
+__device__ __forceinline__ int entry_of_block(int b, int near) {
+    const int span = 8 * near;
+    return near == 1 ? b : b / span * span + (b & 7) * near + (b % span >> 3);
+}
+
 template <int THREADS>
 __device__ __forceinline__ float block_sum(float v, float* smem /* THREADS/64 floats */) {
 #pragma unroll

@@ -35,6 +35,7 @@ struct ee_kv {
     int      n_layers = 0;
     int      B = 0;
     int64_t  T = 0;                         // total positions over all rows
+    int32_t  max_cap = 0;                   // largest row capacity
     int32_t* d_cap = nullptr;               // device [B]
     int64_t* d_off = nullptr;               // device [B]: T_b
     std::vector<int32_t> h_cap;
@@ -46,7 +47,7 @@ struct WsLayout {
     size_t x, qkv, q_hi, q_lo, ao, act, part_max, part_sum, part_arg, logits, fill_x, fill_kv, total;
     size_t gemm_part, gemm_part_bytes;                            // K-slice partial planes
     size_t attn_part, attn_part_bytes;                            // attention position shares
-    size_t attn_order;                                            // int32 [Mpad]: list entries, longest context first
+    size_t attn_order;                                            // 32 bytes [Mpad]: what the attention workgroups take, longest context first
     size_t kv_seq;                                                // int32 [Mpad]: cache row of each entry (context pass)
     size_t gone_idx, n_gone;                                      // int32 [Mpad], int32: rows that left at any exit of the running step
 };
@@ -88,6 +89,12 @@ struct TimedScope {
     TimedScope(int k, hipStream_t st) : kind(k), s(st), on((g_ee_timing_mask >> k) & 1u) { if (on) ee_timing_mark(kind, s, true); }
     ~TimedScope() { if (on) ee_timing_mark(kind, s, false); }
 };
+
+// Entries whose blocks go to one XCD (entry_of_block), and the launch size that goes with it.  A 128-byte line of
+// an operand tile holds 8 rows, a group of the key/value pool 32 positions; fewer rows than there are such groups
+// for 8 XCDs keep one entry per block in turn.
+static inline int entry_near(int B) { return B >= 1024 ? 32 : (B >= 128 ? 8 : 1); }
+static inline unsigned entry_grid(int B) { const int n = entry_near(B), span = 8 * n; return n == 1 ? B : (B + span - 1) / span * span; }
 
 // Per-(layer,row,head) addressing of the key/value pool, passed by value to kernels.
 struct KvView {

@@ -53,6 +53,26 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
     const float4* hr = reinterpret_cast<const float4*>(hr_);
     const float4* g4 = reinterpret_cast<const float4*>(gain);
     int n8 = d >> 3;
+    int KB = d >> 4;
+    if (n8 <= NORM_THREADS) {
+        // one chunk per thread (d <= 8192): it stays in registers; same arithmetic, same bits as below
+        const int c = threadIdx.x;
+        const bool has = c < n8;
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, ga = a, gb = a;
+        if (has) { a = hr[2 * c]; b = hr[2 * c + 1]; ga = g4[2 * c]; gb = g4[2 * c + 1]; }
+        float ss = 0.f;
+        if (has) ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
+        ss = block_sum<NORM_THREADS>(ss, red);
+        const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+        if (!has) return;
+        uint4 o;
+        o.x = pack2((a.x * inv) * ga.x, (a.y * inv) * ga.y);
+        o.y = pack2((a.z * inv) * ga.z, (a.w * inv) * ga.w);
+        o.z = pack2((b.x * inv) * gb.x, (b.y * inv) * gb.y);
+        o.w = pack2((b.z * inv) * gb.z, (b.w * inv) * gb.w);
+        out[afrag_chunk(i, c * 8, KB)] = o;
+        return;
+    }
     float ss = 0.f;
     for (int c = threadIdx.x; c < n8; c += NORM_THREADS) {
         float4 a = hr[2 * c], b = hr[2 * c + 1];
@@ -60,7 +80,6 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
     }
     ss = block_sum<NORM_THREADS>(ss, red);
     float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    int KB = d >> 4;
     for (int c = threadIdx.x; c < n8; c += NORM_THREADS) {
         float4 a = hr[2 * c], b = hr[2 * c + 1];
         float4 ga = g4[2 * c], gb = g4[2 * c + 1];
@@ -76,9 +95,9 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
 // one block per list entry i; out is the [Mpad][d] activation matrix in tile order
 __global__ void __launch_bounds__(NORM_THREADS)
 k_bf16_rmsnorm(const float* __restrict__ h, const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr,
-               int B, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ out, ZBatch zb) {
+               int B, int near, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ out, ZBatch zb) {
     __shared__ float red[NORM_THREADS / 64];
-    int i = blockIdx.x;
+    int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
     if (i >= n) return;
     if (zb.g_tab) gain = zb.g_tab[zb.z0 + blockIdx.z];
@@ -852,6 +871,18 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     else cols_wave<EPI, NT, 1>(c, 2 * (NT - 4) + (wn - (NT - 4)), ep);
 }
 
+// What a workgroup of the decode attention has to know before its first load from the cache.  The RoPE kernel
+// leaves one per list entry, in launch order, so that the attention kernel starts with a single load instead of
+// the chain order -> row -> position -> cache row -> capacity, offset (each a trip to memory).
+struct AttnJob {
+    int32_t entry;      // list entry
+    int32_t n_pos;      // positions read
+    int32_t cap;        // capacity of the cache row
+    int32_t pad;
+    int64_t off;        // positions of the rows before it
+    int64_t pad2;
+};
+
 // ------------------------------------------------------------------ RoPE + cache append
 // buf[i] = [q (n_q heads, may be 0) | k (Hkv heads) | v (Hkv heads)], fp32, hd = 128.
 // Queries are rotated and written as a bf16 pair (hi, lo) with hi + lo = q to 16
@@ -860,18 +891,20 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 // appended; values are rounded and appended in the grouped layout.
 __global__ void __launch_bounds__(256)
 k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t* __restrict__ idx,
-                   const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos,
+                   const int32_t* __restrict__ n_ptr, int B, int near, const int32_t* __restrict__ pos,
                    const float* __restrict__ rope, int max_pos, KvView kv, bf16_t* __restrict__ q_hi,
                    bf16_t* __restrict__ q_lo, int32_t* __restrict__ status, int64_t z_stride,
-                   int32_t* __restrict__ order, int tile_entries, int splits, int64_t plane) {
-    int i = blockIdx.x;
+                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int tile_entries, int splits, int64_t plane) {
+    int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
     if (i >= n) return;
     buf += (int64_t)blockIdx.z * z_stride;     // several layers in one launch: blockIdx.z = layer offset
     kv.layer0 += blockIdx.z;
     int b = idx[i];
     int p = pos[b];
-    if (order != nullptr && blockIdx.y == 0 && threadIdx.x < 64 && i % tile_entries == 0) {
+    const int sq = kv_row(kv, b);
+    const int cap = kv.cap[sq];
+    if ((order != nullptr || jobs != nullptr) && blockIdx.y == 0 && threadIdx.x < 64 && i % tile_entries == 0) {
         // launch order of the attention workgroups: tiles of tile_entries list entries (one in a decode
         // step) by falling context length (that of a tile's last entry, as a context comes in rising
         // order; ties by tile), so that the longest start first and the last round of workgroups is short.
@@ -886,12 +919,13 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
-        if (threadIdx.x == 0) order[before] = tile;
+        if (threadIdx.x == 0) {
+            if (jobs != nullptr) jobs[before] = AttnJob{tile, max(1, min(p + 1, cap)), cap, 0, kv.off[sq], 0};
+            else order[before] = tile;
+        }
     }
     const int hd = 128, half = 64;
     int Hkv = kv.n_kv_heads;
-    const int sq = kv_row(kv, b);
-    int cap = kv.cap[sq];
     if (p < 0 || p >= cap || p >= max_pos) {
         if (threadIdx.x == 0) atomicOr(status, 1);
         return;
@@ -915,7 +949,9 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
     // The work of a row, in items of four rotation pairs (q, k) or four values (v), is dealt out over
     // the threads of the gridDim.y blocks that share the row: items [0, nq4) rotate queries, the next
     // nk4 rotate and append keys, the last nv4 append values.
-    const int nq4 = n_q * (half / 4), nk4 = Hkv * (half / 4), nv4 = Hkv * (hd / 4);
+    // A thread of the value items takes the values f, f + 64, f + 128, f + 192 of a block of 256, so that a wave's
+    // 2-byte stores (16 bytes apart in the cache) touch 8 lines per store instead of 32.
+    const int nq4 = n_q * (half / 4), nk4 = Hkv * (half / 4), nv4 = (Hkv * hd + 255) / 256 * 64;
     const int kin = n_q * hd;
     const int vin = kin + Hkv * hd;
     for (int t = blockIdx.y * 256 + threadIdx.x; t < nq4 + nk4 + nv4; t += 256 * gridDim.y) {
@@ -952,13 +988,24 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
             }
         } else {
             const int u = t - nq4 - nk4;
-            const int g = u >> 5, j0 = (u & 31) * 4;
-            const float4 v = rd4(vin + g * hd + j0);
-            bf16_t* base = reinterpret_cast<bf16_t*>(kv.pool) + kv_block(kv, sq, g, cap);
-            base[v_bf16_offset(p, j0, hd)] = f32_to_bf16(v.x);
-            base[v_bf16_offset(p, j0 + 1, hd)] = f32_to_bf16(v.y);
-            base[v_bf16_offset(p, j0 + 2, hd)] = f32_to_bf16(v.z);
-            base[v_bf16_offset(p, j0 + 3, hd)] = f32_to_bf16(v.w);
+            const int f0 = (u >> 6) * 256 + (u & 63);
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int f = f0 + 64 * k;
+                v[k] = 0.f;
+                if (f < Hkv * hd) {
+                    v[k] = r0[vin + f];
+                    for (int q = 1; q < splits; ++q) v[k] += r0[vin + f + (int64_t)q * plane];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int f = f0 + 64 * k;
+                if (f >= Hkv * hd) break;
+                bf16_t* base = reinterpret_cast<bf16_t*>(kv.pool) + kv_block(kv, sq, f >> 7, cap);
+                base[v_bf16_offset(p, f & 127, hd)] = f32_to_bf16(v[k]);
+            }
         }
     }
 }
@@ -976,6 +1023,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
 // q and P enter as bf16 (hi, lo) pairs: two MFMAs each, fp32-grade products.
 // The work of one workgroup: list entries first .. first + cnt - 1 of kv head g, share `share` of n_splits of
 // the position groups.  AHEAD: a wave asks for its next group before it works on the current one.
+#define ATTN_SHARE 132      /* floats of one head's share of a row: a multiple of four, so that they move 16 bytes at a time */
 struct AttnShared {
     float m[4][16];
     float l[4][16];
@@ -986,40 +1034,33 @@ template <bool PAIR, bool AHEAD>
 __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo,
                                              int Hq, const int32_t* __restrict__ idx, const int32_t* __restrict__ pos,
                                              const KvView& kv, uint4* __restrict__ ao, int KB_ao, int n_splits, int share,
-                                             float* __restrict__ part, int g, int first, int cnt) {
+                                             float* __restrict__ part, int g, int first, int cnt, const AttnJob& job = AttnJob{}) {
     const int G = Hq / kv.n_kv_heads;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int n16 = lane & 15, gq = lane >> 4;
     for (int r0 = 0; r0 < cnt;) {
-    const int sq = kv_row(kv, idx[first + r0]);
-    int r1 = r0 + 1;
-    if (PAIR) while (r1 < cnt && kv_row(kv, idx[first + r1]) == sq) ++r1;
-    const int n_col = (r1 - r0) * G;                       // live MFMA columns
-    const int cap = kv.cap[sq];
-    int n_pos = 1;                                         // positions read: the longest of the run
-    for (int j = r0; j < r1; ++j) n_pos = max(n_pos, min(pos[idx[first + j]] + 1, cap));
-    const int my_ent = n16 < n_col ? n16 / G : 0;          // this lane's column: entry, head, positions
+    int r1 = r0 + 1, cap, n_pos;                            // n_pos: positions read, the longest of the run
+    const bf16_t* Kb;
+    int my_ent = 0, my_np, n_col = G;
+    if constexpr (PAIR) {
+        const int sq = kv_row(kv, idx[first + r0]);
+        while (r1 < cnt && kv_row(kv, idx[first + r1]) == sq) ++r1;
+        n_col = (r1 - r0) * G;                               // live MFMA columns
+        cap = kv.cap[sq];
+        n_pos = 1;
+        for (int j = r0; j < r1; ++j) n_pos = max(n_pos, min(pos[idx[first + j]] + 1, cap));
+        my_ent = n16 < n_col ? n16 / G : 0;                  // this lane's column: entry, head, positions
+        my_np = n16 < n_col ? max(1, min(pos[idx[first + r0 + my_ent]] + 1, cap)) : 0;
+        Kb = reinterpret_cast<const bf16_t*>(kv.pool) + kv_block(kv, sq, g, cap);
+    } else {
+        cap = job.cap;
+        n_pos = job.n_pos;
+        my_np = n16 < n_col ? n_pos : 0;
+        Kb = reinterpret_cast<const bf16_t*>(kv.pool) +
+             ((int64_t)kv.layer0 * kv.T + job.off) * (2LL * kv.n_kv_heads * 128) + (int64_t)g * 2LL * cap * 128;
+    }
     const int my_e = first + r0 + my_ent;
     const int my_head = n16 - my_ent * G;
-    const int my_np = n16 < n_col ? max(1, min(pos[idx[my_e]] + 1, cap)) : 0;
-    const bf16_t* Kb = reinterpret_cast<const bf16_t*>(kv.pool) + kv_block(kv, sq, g, cap);
-
-    bf16x8 qh[4], ql[4];
-    {
-        uint4 z = make_uint4(0, 0, 0, 0);
-        const int64_t qo = ((int64_t)my_e * Hq + (int64_t)g * G + my_head) * 128 + 8 * gq;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            qh[c] = as_bf16x8(n16 < n_col ? *reinterpret_cast<const uint4*>(q_hi + qo + 32 * c) : z);
-            ql[c] = as_bf16x8(n16 < n_col ? *reinterpret_cast<const uint4*>(q_lo + qo + 32 * c) : z);
-        }
-    }
-    const float inv_sqrt = 1.0f / sqrtf(128.0f);
-    const float NEG = -1.0e30f;
-    float m_run = NEG, l_run = 0.f;
-    floatx4 O[8];
-#pragma unroll
-    for (int hb = 0; hb < 8; ++hb) O[hb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const int n_groups = (n_pos + 31) >> 5;
     // with n_splits > 1 this workgroup covers the share-th share of the position groups
@@ -1047,7 +1088,25 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     // equal at 256).  Context pass with two entries per workgroup: three workgroups, no prefetch
     // (0.8 % faster there).
     KVTiles nxt;
-    if constexpr (AHEAD) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has
+    if constexpr (AHEAD) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has; before the queries
+
+    bf16x8 qh[4], ql[4];
+    {
+        uint4 z = make_uint4(0, 0, 0, 0);
+        const int64_t qo = ((int64_t)my_e * Hq + (int64_t)g * G + my_head) * 128 + 8 * gq;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            qh[c] = as_bf16x8(n16 < n_col ? *reinterpret_cast<const uint4*>(q_hi + qo + 32 * c) : z);
+            ql[c] = as_bf16x8(n16 < n_col ? *reinterpret_cast<const uint4*>(q_lo + qo + 32 * c) : z);
+        }
+    }
+    const float inv_sqrt = 1.0f / sqrtf(128.0f);
+    const float NEG = -1.0e30f;
+    float m_run = NEG, l_run = 0.f;
+    floatx4 O[8];
+#pragma unroll
+    for (int hb = 0; hb < 8; ++hb) O[hb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
     for (int t = g_lo + w; t < g_hi; t += 4) {
         const int p0 = t << 5;
         KVTiles cur;
@@ -1148,10 +1207,10 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
                 int col = (g * G + hq) * 128 + c0;
                 ao[afrag_chunk(i, col, KB_ao)] = pk;
             } else {
-                // unnormalised share: [i][kv head][split][head][130] = 128 features, max, sum
-                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * n_splits + share) * 16 + hq) * 130;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) p[c0 + j] = o[j];
+                // unnormalised share: [i][kv head][split][head][132] = 128 features, max, sum, two unused
+                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * n_splits + share) * 16 + hq) * ATTN_SHARE;
+                *reinterpret_cast<float4*>(p + c0) = make_float4(o[0], o[1], o[2], o[3]);
+                *reinterpret_cast<float4*>(p + c0 + 4) = make_float4(o[4], o[5], o[6], o[7]);
                 if (c0 == 0) { p[128] = M; p[129] = Lsum; }
             }
         }
@@ -1166,7 +1225,7 @@ __global__ void __launch_bounds__(256, PAIR ? 3 : 2)
 k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
             const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr, int B,
             const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao, int KB_ao, int n_splits,
-            float* __restrict__ part, const int32_t* __restrict__ order) {
+            float* __restrict__ part, const AttnJob* __restrict__ jobs) {
     __shared__ AttnShared sm;
     const int n = min(*n_ptr, B);
     // PAIR (context pass and other passes over list entries, 2 G <= 16): the workgroup serves the E = 16 / G
@@ -1175,17 +1234,17 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     // columns G j .. G j + G - 1, each column masked at its own entry's position.  With one query head per
     // kv head 16 entries share a stream, with eight heads two.  A change of cache row inside the E entries
     // starts another run, served after the first.
-    int first, cnt = 1;
-    if (PAIR) {
-        const int E = 16 / (Hq / kv.n_kv_heads);
-        first = E * (int)blockIdx.y;
+    if constexpr (PAIR) {
+        const int E = 16 / (Hq / kv.n_kv_heads), first = E * (int)blockIdx.y;
         if (first >= n) return;
-        cnt = min(E, n - first);
+        attn_streams<true, false>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, n_splits, blockIdx.z, part, blockIdx.x, first,
+                                  min(E, n - first));
     } else {
+        const AttnJob job = jobs[blockIdx.y];  // longest contexts first; slots from n on are not read further
         if ((int)blockIdx.y >= n) return;
-        first = order[blockIdx.y];            // longest contexts first
+        attn_streams<false, true>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, n_splits, blockIdx.z, part, blockIdx.x, job.entry,
+                                  1, job);
     }
-    attn_streams<PAIR, !PAIR>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, n_splits, blockIdx.z, part, blockIdx.x, first, cnt);
 }
 
 // ------------------------------------------------------------------ context-pass attention
@@ -1468,16 +1527,29 @@ k_bf16_attn_merge(const float* __restrict__ part, int Hq, int Hkv, int n_splits,
     const int G = Hq / Hkv;
     const int head = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;
     if (head >= G) return;
-    const float* base = part + (((int64_t)i * Hkv + g) * n_splits * 16 + head) * 130;
+    // all maxima and sums at once, then all values: two trips to memory whatever the number of shares
+    const float* base = part + (((int64_t)i * Hkv + g) * n_splits * 16 + head) * ATTN_SHARE;
+    float ms[16], ls[16];
     float M = -1.0e30f;
-    for (int q = 0; q < n_splits; ++q) M = fmaxf(M, base[(int64_t)q * 16 * 130 + 128]);
-    float L = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int q = 0; q < n_splits; ++q) {
-        const float* p = base + (int64_t)q * 16 * 130;
-        float wq = __expf(p[128] - M);
-        L += p[129] * wq;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) o[j] += p[c0 + j] * wq;
+    for (int q = 0; q < 16; ++q) {
+        ms[q] = -1.0e30f; ls[q] = 0.f;
+        if (q < n_splits) {
+            const float2 ml = *reinterpret_cast<const float2*>(base + (int64_t)q * 16 * ATTN_SHARE + 128);
+            ms[q] = ml.x; ls[q] = ml.y;
+        }
+        M = fmaxf(M, ms[q]);
+    }
+    float L = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        if (q >= n_splits) break;
+        const float* p = base + (int64_t)q * 16 * ATTN_SHARE + c0;
+        const float4 u = *reinterpret_cast<const float4*>(p), v = *reinterpret_cast<const float4*>(p + 4);
+        const float wq = __expf(ms[q] - M);
+        L += ls[q] * wq;
+        o[0] += u.x * wq; o[1] += u.y * wq; o[2] += u.z * wq; o[3] += u.w * wq;
+        o[4] += v.x * wq; o[5] += v.y * wq; o[6] += v.z * wq; o[7] += v.w * wq;
     }
     uint4 pk = make_uint4(pack2(o[0] / L, o[1] / L), pack2(o[2] / L, o[3] / L), pack2(o[4] / L, o[5] / L),
                           pack2(o[6] / L, o[7] / L));
@@ -1541,11 +1613,11 @@ k_splitk_finish(const float* __restrict__ partial, int64_t plane, int ld, int sp
 // of the updated row straight into the operand matrix of the next product.
 __global__ void __launch_bounds__(NORM_THREADS)
 k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, int splits, int N,
-                    const int32_t* __restrict__ n_ptr, int B, float* h, int ldh, const int32_t* __restrict__ idx,
+                    const int32_t* __restrict__ n_ptr, int B, int near, float* h, int ldh, const int32_t* __restrict__ idx,
                     const float* gain, float eps, uint4* xout) {
     __shared__ float red[NORM_THREADS / 64];
     const int n = min(*n_ptr, B);
-    const int i = blockIdx.x;
+    const int i = entry_of_block(blockIdx.x, near);
     if (i >= n) return;
     float* hrow = h + (int64_t)idx[i] * ldh;
     const float* prow = partial + (int64_t)i * ld;
@@ -1712,8 +1784,8 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     if (tail.splits_out) *tail.splits_out = splits;
     if (splits > 1) {
         if (EPI == EPI_RESID) {
-            hipLaunchKernelGGL(k_splitk_resid_norm, dim3(B), dim3(NORM_THREADS), 0, s, b->wsp<float>(b->W.gemm_part),
-                               (int64_t)Mpad * N, N, splits, N, n_ptr, B, ep.out, ep.ldo, ep.idx, tail.norm_gain,
+            hipLaunchKernelGGL(k_splitk_resid_norm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->wsp<float>(b->W.gemm_part),
+                               (int64_t)Mpad * N, N, splits, N, n_ptr, B, entry_near(B), ep.out, ep.ldo, ep.idx, tail.norm_gain,
                                tail.eps, tail.norm_out);
             if (tail.norm_gain && tail.norm_done) *tail.norm_done = true;
         } else if (!tail.defer_store) {
@@ -1766,7 +1838,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
 
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(B), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, w.g_attn, c.rms_eps, d, x, ZBatch{});
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_attn, c.rms_eps, d, x, ZBatch{});
     }
     EpiArgs e1{};
     e1.out = qkv; e1.ldo = qkv_n; e1.idx = idx;
@@ -1780,19 +1852,23 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     }
     {
         TimedScope t(EE_K_ROPE_APPEND, s);
+        // neighbouring entries share lines of the cache only where they are positions of one row (context pass)
+        const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
         const float* src = qkv_splits > 1 ? b->wsp<float>(b->W.gemm_part) : qkv;
-        hipLaunchKernelGGL(k_bf16_rope_append, dim3(B, 4), dim3(256), 0, s, src, qkv_n, c.n_q_heads, idx, n_ptr, B,
+        hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 4), dim3(256), 0, s, src, qkv_n, c.n_q_heads, idx, n_ptr, B, near,
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
-                           b->wsp<int32_t>(b->W.attn_order), ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * qkv_n);
+                           ctx.C ? b->wsp<int32_t>(b->W.attn_order) : nullptr, ctx.C ? nullptr : b->wsp<AttnJob>(b->W.attn_order),
+                           ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * qkv_n);
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
         // few (row, kv head) pairs: also split the positions, so that the chip has workgroups to run
         int pairs = c.n_kv_heads * B;
         int n_splits = pairs >= 512 ? 1 : (1024 + pairs - 1) / pairs;
-        if (n_splits > 16) n_splits = 16;
-        while (n_splits > 1 && (size_t)b->Mpad * c.n_kv_heads * n_splits * 16 * 130 * 4 > b->W.attn_part_bytes) --n_splits;
+        // at most 16, and no more than leave every wave of the longest row's workgroups a group of 32 positions
+        n_splits = std::min({n_splits, 16, std::max(1, kv->max_cap / 128)});
+        while (n_splits > 1 && (size_t)b->Mpad * c.n_kv_heads * n_splits * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --n_splits;
         // context pass: 16 / G entries per workgroup, which share the K/V stream where they sit in the same cache row
         const int G = c.n_q_heads / c.n_kv_heads;
         const bool pair = b->kv_seq != nullptr && n_splits == 1 && 2 * G <= 16;
@@ -1805,11 +1881,11 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         } else if (pair)
             hipLaunchKernelGGL(k_bf16_attn<true>, dim3(c.n_kv_heads, (B + 16 / G - 1) / (16 / G), 1), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
-                               qd / 16, 1, b->wsp<float>(b->W.attn_part), b->wsp<int32_t>(b->W.attn_order));
+                               qd / 16, 1, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
         else
             hipLaunchKernelGGL(k_bf16_attn<false>, dim3(c.n_kv_heads, B, n_splits), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
-                               qd / 16, n_splits, b->wsp<float>(b->W.attn_part), b->wsp<int32_t>(b->W.attn_order));
+                               qd / 16, n_splits, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
         if (n_splits > 1)
             hipLaunchKernelGGL(k_bf16_attn_merge, dim3(c.n_kv_heads, B), dim3(256), 0, s, b->wsp<float>(b->W.attn_part),
                                c.n_q_heads, c.n_kv_heads, n_splits, n_ptr, B, ao, qd / 16);
@@ -1826,7 +1902,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     }
     if (!ffn_x_done) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(B), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, w.g_ffn, c.rms_eps, d, x, ZBatch{});
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_ffn, c.rms_eps, d, x, ZBatch{});
     }
     EpiArgs e3{};
     e3.act = act; e3.KB_act = F / 16; e3.idx = idx;
@@ -1856,7 +1932,7 @@ int bf16_exit_head(const ee_model* m, int e, float th, int force, ee_batch* b, f
     uint4* x = b->wsp<uint4>(b->W.x);
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(B), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B,
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
                            m->exits[e].gain, c.rms_eps, d, x, ZBatch{});
     }
     EpiArgs ep{};
@@ -1889,7 +1965,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     ZBatch zb{};
     zb.w_tab = m->d_wqkv_tab; zb.g_tab = m->d_gattn_tab; zb.z0 = from_excl;
     zb.x_stride = (int64_t)b->Mpad * d / 8; zb.out_stride = (int64_t)b->Mpad * kv_n;
-    hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(B, 1, nl), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B,
+    hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B), 1, nl), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
                        (const float*)nullptr, c.rms_eps, d, x, zb);
     // key and value rows are the last 2*H_kv*hd rows of W_qkv: tile-rows H_q*hd/32 onwards
     EpiArgs ep{};
@@ -1897,10 +1973,11 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     int NBs = (c.n_q_heads + 2 * c.n_kv_heads) * hd / 32, nb_off = c.n_q_heads * hd / 32;
     if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl))
         gemm<1, EPI_STORE>(x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl);
-    hipLaunchKernelGGL(k_bf16_rope_append, dim3(B, 1, nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B,
+    const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
+    hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 1, nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, 1, 1, (int64_t)0);
+                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, (int64_t)0);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
