@@ -375,13 +375,27 @@ __device__ __forceinline__ void epilogue_one(const EpiArgs& ep, const floatx16& 
         const uint32_t r0 = __shfl_xor(h ? d[0] : d[2], 32, 64), r1 = __shfl_xor(h ? d[1] : d[3], 32, 64);
         const uint4 o = h ? make_uint4(r0, d[2], r1, d[3]) : make_uint4(d[0], r0, d[1], r1);
         if (row < n) reinterpret_cast<uint4*>(ep.act)[afrag_chunk(row, 16 * nb + 8 * h, ep.KB_act)] = o;
+    } else if constexpr (EPI == EPI_RESID) {
+        // h[row id] += v.  All row ids, then all old values, then the stores: taken one result at a time (the stores
+        // may alias the loads, so the compiler cannot) the 128 results of a lane were 128 trips to memory, 90 of
+        // the 306 us of the O projection of 1999 entries at the 70B shape.
+        float* at[16];
+        float old[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = row0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            at[r] = ep.out + (int64_t)ep.idx[min(row, n - 1)] * ep.ldo + 32 * nb + cl;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) old[r] = *at[r];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (row0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) < n) *at[r] = old[r] + v[r];
     } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int row = row0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            if (row >= n) continue;
-            if constexpr (EPI == EPI_STORE) ep.out[(int64_t)row * ep.ldo + 32 * nb + cl] = v[r];
-            else ep.out[(int64_t)ep.idx[row] * ep.ldo + 32 * nb + cl] += v[r];      // EPI_RESID
+            if (row < n) ep.out[(int64_t)row * ep.ldo + 32 * nb + cl] = v[r];      // EPI_STORE
         }
     }
 }
@@ -894,7 +908,8 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
                    const int32_t* __restrict__ n_ptr, int B, int near, const int32_t* __restrict__ pos,
                    const float* __restrict__ rope, int max_pos, KvView kv, bf16_t* __restrict__ q_hi,
                    bf16_t* __restrict__ q_lo, int32_t* __restrict__ status, int64_t z_stride,
-                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int tile_entries, int splits, int64_t plane) {
+                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int tile_entries, int splits, int64_t plane,
+                   const float* __restrict__ planes, int ld_planes, int from) {
     int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
     if (i >= n) return;
@@ -930,16 +945,24 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
         if (threadIdx.x == 0) atomicOr(status, 1);
         return;
     }
-    // buf holds `splits` K-slice planes of the product (plane floats apart): their sum in slice
-    // order is the value; splits = 1 is a finished matrix
+    // columns before `from` are finished in buf; those from there on are `splits` K-slice planes of the product
+    // (plane floats apart, ld_planes wide): their sum in slice order is the value
     const float* r0 = buf + (int64_t)i * ld;
-    // four consecutive values at once (x is a multiple of 4: 16-byte loads from every plane)
+    const float* rp = planes + (int64_t)i * ld_planes - from;
+    // four consecutive values at once (x is a multiple of 4, from of 128: 16-byte loads from every plane)
     auto rd4 = [&](int x) -> float4 {
-        float4 v = *reinterpret_cast<const float4*>(r0 + x);
+        if (x < from) return *reinterpret_cast<const float4*>(r0 + x);
+        float4 v = *reinterpret_cast<const float4*>(rp + x);
         for (int q = 1; q < splits; ++q) {
-            const float4 u = *reinterpret_cast<const float4*>(r0 + x + (int64_t)q * plane);
+            const float4 u = *reinterpret_cast<const float4*>(rp + x + (int64_t)q * plane);
             v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
         }
+        return v;
+    };
+    auto rd1 = [&](int x) -> float {
+        if (x < from) return r0[x];
+        float v = rp[x];
+        for (int q = 1; q < splits; ++q) v += rp[x + (int64_t)q * plane];
         return v;
     };
     auto pack4 = [](float a, float b, float c, float d) -> uint2 {
@@ -993,11 +1016,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int f = f0 + 64 * k;
-                v[k] = 0.f;
-                if (f < Hkv * hd) {
-                    v[k] = r0[vin + f];
-                    for (int q = 1; q < splits; ++q) v[k] += r0[vin + f + (int64_t)q * plane];
-                }
+                v[k] = f < Hkv * hd ? rd1(vin + f) : 0.f;
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -1687,6 +1706,7 @@ struct SliceTail {
     bool*        norm_done = nullptr;   // set when that happened
     bool         defer_store = false;   // STORE: leave the planes to the caller ...
     int*         splits_out = nullptr;  // ... who gets their number (1 = the result is in out already)
+    int*         from_out = nullptr;    // ... and the first column that is in planes (those before it are in out)
 };
 
 // the 256-row tile kernels, 128 or 256 columns wide, K sliced so that about one workgroup per CU
@@ -1699,9 +1719,12 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     // One product at a time: the tile kernels at every batch size (at 1 to 32 rows, measured on the
     // 70B shapes against the weight-streaming kernel plus the normalisation launch that the finish of
     // a sliced product saves: QKV 36 against 46 us, O 34 against 37, down 84 against 87, exit head 94
-    // against 95-100, and 99 against 149 at 64 rows).  Several layers in one launch (K/V of skipped
-    // layers): from 65 rows up.
-    if (nz > 1 && B < 65) return false;
+    // against 95-100, and 99 against 149 at 64 rows).  Several layers in one launch (K/V of skipped layers)
+    // are not sliced: up to 128 rows the tile kernel needs the 256-column tiles of all layers to fill the
+    // chip (rule `wide` below).  Seven layers of the 7B shape (224 tiles): 17 rows 73 against 83 us, 40 rows
+    // 74 against 102; three layers of the 70B shape (48 tiles of 128): 64 rows 67 against 29 us, 100 rows 72
+    // against 63.
+    if (nz > 1 && B <= 128 && !(N % 256 == 0 && N / 256 * nz >= 200)) return false;
     int row_groups = (B + 255) / 256;
     int Mpad = (B + 31) / 32 * 32;
     int KS = K / 32;
@@ -1771,6 +1794,26 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     }
     int n_tiles = wide ? N / 256 : N / 128;
     if (splits == 0) splits = sliceable && n_tiles * row_groups < 200 ? fit_slices(slices_for(n_tiles * row_groups)) : 1;
+    if (tail.from_out) *tail.from_out = 0;
+    if (EPI == EPI_STORE && tail.defer_store && tail.from_out && wide && splits == 1 && row_groups > 1 && nz == 1) {
+        // More tiles than fit whole rounds of 256 workgroups: the column tiles that do run unsliced, the rest in
+        // a second launch, K-sliced so that it fills one short round (QKV of 1999 entries at the 70B shape: 320
+        // tiles, two rounds 372 us; 256 tiles and 64 in four slices 262 us).
+        const int full = n_tiles * row_groups / 256 * 256 / row_groups, rest = n_tiles - full;
+        const int N2 = rest * 256;
+        int sp = full > 0 && rest > 0 ? std::min({4, 256 / (rest * row_groups), KS / 16}) : 1;
+        while (sp > 1 && (size_t)sp * Mpad * N2 * sizeof(float) > b->W.gemm_part_bytes) --sp;
+        if (sp > 1) {
+            hipLaunchKernelGGL((k_bf16_gemm_dma8<EPI>), dim3((full + 7) / 8 * 8 * row_groups), dim3(512), 0, s, (const uint4*)X,
+                               (const uint4*)W, K / 16, NBs, nb_off, full, 1, n_ptr, B, (float*)nullptr, (int64_t)0, 0, ep, zb);
+            hipLaunchKernelGGL((k_bf16_gemm_dma8<EPI>), dim3((rest * sp + 7) / 8 * 8 * row_groups), dim3(512), 0, s, (const uint4*)X,
+                               (const uint4*)W, K / 16, NBs, nb_off + full * 8, rest, sp, n_ptr, B, b->wsp<float>(b->W.gemm_part),
+                               (int64_t)Mpad * N2, N2, ep, zb);
+            *tail.splits_out = sp;
+            *tail.from_out = full * 256;
+            return true;
+        }
+    }
     dim3 grid(n_tiles * splits, row_groups, nz);
     if (row_groups > 1) grid = dim3((n_tiles * splits + 7) / 8 * 8 * row_groups, 1, nz);   // see tile_of_block
     if (wide)
@@ -1842,11 +1885,11 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     }
     EpiArgs e1{};
     e1.out = qkv; e1.ldo = qkv_n; e1.idx = idx;
-    int qkv_splits = 1;
+    int qkv_splits = 1, qkv_from = 0;
     {
         TimedScope t(EE_K_GEMM_QKV, s);
         SliceTail st;                  // K-slice planes of q|k|v are added up by the RoPE kernel
-        st.defer_store = true; st.splits_out = &qkv_splits;
+        st.defer_store = true; st.splits_out = &qkv_splits; st.from_out = &qkv_from;
         if (!gemm_tiled<EPI_STORE>(b, x, w.w_qkv, qkv_n, d, qkv_n / 32, 0, n_ptr, B, e1, s, ZBatch{}, 1, st))
             gemm<1, EPI_STORE>(x, w.w_qkv, qkv_n, d, qkv_n / 32, 0, n_ptr, B, e1, s);
     }
@@ -1854,12 +1897,13 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         TimedScope t(EE_K_ROPE_APPEND, s);
         // neighbouring entries share lines of the cache only where they are positions of one row (context pass)
         const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
-        const float* src = qkv_splits > 1 ? b->wsp<float>(b->W.gemm_part) : qkv;
-        hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 4), dim3(256), 0, s, src, qkv_n, c.n_q_heads, idx, n_ptr, B, near,
+        if (qkv_splits == 1) qkv_from = qkv_n;         // nothing is in planes
+        hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 4), dim3(256), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B, near,
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
                            ctx.C ? b->wsp<int32_t>(b->W.attn_order) : nullptr, ctx.C ? nullptr : b->wsp<AttnJob>(b->W.attn_order),
-                           ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * qkv_n);
+                           ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * (qkv_n - qkv_from), b->wsp<float>(b->W.gemm_part),
+                           qkv_n - qkv_from, qkv_from);
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
@@ -1977,7 +2021,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 1, nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, (int64_t)0);
+                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, (int64_t)0, kvb, kv_n, kv_n);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
