@@ -12,13 +12,8 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t b) {
     return __uint_as_float(((uint32_t)b) << 16);
 }
 
-// round to nearest even; inf/nan pass through
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (bf16_t)(u >> 16);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
+// round to nearest even (v_cvt_pk_bf16_f32; the same bits as the integer form for every value that is no NaN)
+__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 // element offset (in elements of the model dtype) of the (layer, row, kv-head) block
 // cache row that batch row b reads and appends to

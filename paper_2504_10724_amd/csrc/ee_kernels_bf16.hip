@@ -37,8 +37,18 @@ struct ZBatch {
     int64_t out_stride;            // floats between the layers' output matrices
 };
 
+// two values rounded to nearest even, a in the low half: one v_cvt_pk_bf16_f32
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
-    return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
+}
+
+// g / (1 + exp(-g)) * u on the hardware's exponential and reciprocal (1 ulp each; the product is rounded to bf16).
+// With expf and an IEEE division, 64 of them per lane, the SwiGLU epilogue took 11 us of every round of
+// workgroups; now 4.
+__device__ __forceinline__ float silu_mul(float g, float u) {
+    return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
 // ------------------------------------------------------------------ RMSNorm -> A tiles
@@ -277,7 +287,7 @@ k_bf16_gemm(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, 
                 for (int ns = 0; ns < NS; ++ns) {
                     const float mine = v[ns][ii], other = __shfl_xor(mine, 1, 64);
                     const float gt = (cl & 1) ? other : mine, up = (cl & 1) ? mine : other;
-                    const float a = (gt / (1.0f + expf(-gt))) * up;
+                    const float a = silu_mul(gt, up);
                     const int col = 16 * (nb0 + ns) + (cl >> 1);
                     if (live && !(cl & 1)) ep.act[afrag_chunk(row, col & ~7, ep.KB_act) * 8 + (col & 7)] = f32_to_bf16(a);
                 }
@@ -345,8 +355,19 @@ __device__ __forceinline__ void epilogue_one(const EpiArgs& ep, const floatx16& 
         for (int r = 0; r < 16; ++r) {
             const int col = col0 + 8 * (r >> 2) + (r & 3);        // rising with r: > keeps the lowest column
             z[r] = v[r] * sc;
-            if (live && ep.dbg_logits) ep.dbg_logits[(int64_t)row * ep.ldo + col] = z[r];
             if (z[r] > mx) { mx = z[r]; arg = col; }
+        }
+        if (ep.dbg_logits && live) {
+            // registers 4 q .. 4 q + 3 are neighbouring columns of this lane's row: 16 bytes per store (V is a
+            // multiple of 32; single values where the caller's array is not aligned for that)
+            float* zp = ep.dbg_logits + (int64_t)row * ep.ldo + col0;
+            if (((uintptr_t)ep.dbg_logits & 15) == 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(zp + 8 * q) = make_float4(z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) zp[8 * (r >> 2) + (r & 3)] = z[r];
+            }
         }
         const float m2 = __shfl_xor(mx, 32, 64);
         const int a2 = __shfl_xor(arg, 32, 64);
@@ -370,7 +391,7 @@ __device__ __forceinline__ void epilogue_one(const EpiArgs& ep, const floatx16& 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float g0 = v[4 * q], u0 = v[4 * q + 1], g1 = v[4 * q + 2], u1 = v[4 * q + 3];
-            d[q] = pack2((g0 / (1.0f + expf(-g0))) * u0, (g1 / (1.0f + expf(-g1))) * u1);
+            d[q] = pack2(silu_mul(g0, u0), silu_mul(g1, u1));
         }
         const uint32_t r0 = __shfl_xor(h ? d[0] : d[2], 32, 64), r1 = __shfl_xor(h ? d[1] : d[3], 32, 64);
         const uint4 o = h ? make_uint4(r0, d[2], r1, d[3]) : make_uint4(d[0], r0, d[1], r1);
@@ -965,9 +986,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
         for (int q = 1; q < splits; ++q) v += rp[x + (int64_t)q * plane];
         return v;
     };
-    auto pack4 = [](float a, float b, float c, float d) -> uint2 {
-        return make_uint2(f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16), f32_to_bf16(c) | ((uint32_t)f32_to_bf16(d) << 16));
-    };
+    auto pack4 = [](float a, float b, float c, float d) -> uint2 { return make_uint2(pack2(a, b), pack2(c, d)); };
     const float* cs = rope + (int64_t)p * half * 2;
     // The work of a row, in items of four rotation pairs (q, k) or four values (v), is dealt out over
     // the threads of the gridDim.y blocks that share the row: items [0, nq4) rotate queries, the next
@@ -1286,12 +1305,6 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
 // one or two rows only sub = 0 works.
 #define CTX_STAGE 2048                        /* uint4 of a stage: two groups of 32 positions, 16 KiB each */
 
-__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b) {     // round to nearest even, a in the low half
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
-}
-
 // maximum over the four lanes that hold a column (lane, lane ^ 16, lane ^ 32, lane ^ 48)
 __device__ __forceinline__ float column_max(float v) {
     auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -1456,8 +1469,8 @@ __device__ __forceinline__ void attn_tile(uint4* lds, const bf16_t* __restrict__
                     uint32_t hw[4], lw[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        hw[i] = cvt2_bf16(pv[2 * i], pv[2 * i + 1]);
-                        lw[i] = cvt2_bf16(pv[2 * i] - __uint_as_float(hw[i] << 16), pv[2 * i + 1] - __uint_as_float(hw[i] & 0xffff0000u));
+                        hw[i] = pack2(pv[2 * i], pv[2 * i + 1]);
+                        lw[i] = pack2(pv[2 * i] - __uint_as_float(hw[i] << 16), pv[2 * i + 1] - __uint_as_float(hw[i] & 0xffff0000u));
                     }
                     ph[j] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
                     pl[j] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
@@ -1502,7 +1515,7 @@ __device__ __forceinline__ void attn_tile(uint4* lds, const bf16_t* __restrict__
             for (int hb = 0; hb < 8; ++hb) {
                 const int col = chunk0 + 16 * hb + 4 * gq;
                 uint2* dst = reinterpret_cast<uint2*>(ao + afrag_chunk(ent[j], col & ~7, KB_ao)) + ((col >> 2) & 1);
-                *dst = make_uint2(cvt2_bf16(O[j][hb][0] * inv, O[j][hb][1] * inv), cvt2_bf16(O[j][hb][2] * inv, O[j][hb][3] * inv));
+                *dst = make_uint2(pack2(O[j][hb][0] * inv, O[j][hb][1] * inv), pack2(O[j][hb][2] * inv, O[j][hb][3] * inv));
             }
         }
         r0 = r1;
@@ -1907,11 +1920,13 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
-        // few (row, kv head) pairs: also split the positions, so that the chip has workgroups to run
+        // few (row, kv head) pairs: also split the positions, to at most the 512 workgroups that run at a time (two
+        // per CU) and 16 shares, and no further than two groups of 32 positions per wave of the longest row.
+        // Attention with its merge: 16 rows of the 70B shape 37 us at twice the workgroups, 32 at 512; 48 rows
+        // 64 -> 57 (no merge); 20 rows of 4 kv heads 31 -> 23; 37 rows of 2 kv heads, up to 900 positions: 21 with
+        // one group per wave and 1024 workgroups, 18 with 512, 16 with two groups.
         int pairs = c.n_kv_heads * B;
-        int n_splits = pairs >= 512 ? 1 : (1024 + pairs - 1) / pairs;
-        // at most 16, and no more than leave every wave of the longest row's workgroups a group of 32 positions
-        n_splits = std::min({n_splits, 16, std::max(1, kv->max_cap / 128)});
+        int n_splits = std::min({std::max(1, 512 / pairs), 16, std::max(1, kv->max_cap / 256)});
         while (n_splits > 1 && (size_t)b->Mpad * c.n_kv_heads * n_splits * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --n_splits;
         // context pass: 16 / G entries per workgroup, which share the K/V stream where they sit in the same cache row
         const int G = c.n_q_heads / c.n_kv_heads;
