@@ -45,8 +45,8 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 }
 
 // g / (1 + exp(-g)) * u on the hardware's exponential and reciprocal (1 ulp each; the product is rounded to bf16).
-// With expf and an IEEE division, 64 of them per lane, the SwiGLU epilogue took 11 us of every round of
-// workgroups; now 4.
+// With expf and an IEEE division, 64 of them per lane, a round of 256 workgroups took 4.5 us longer (gate/up of
+// 1999 entries at the 70B shape, seven rounds: 1422 -> 1391 us).
 __device__ __forceinline__ float silu_mul(float g, float u) {
     return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
