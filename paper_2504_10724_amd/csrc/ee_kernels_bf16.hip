@@ -1593,6 +1593,16 @@ static KvView make_view(const ee_model* m, const ee_kv* kv, int layer, const ee_
     return KvView{kv->pool, kv->d_cap, kv->d_off, kv->T, m->cfg.n_kv_heads, m->cfg.head_dim, layer - 1, b->kv_seq};
 }
 
+// Blocks that share a row in k_bf16_rope_append: one item per thread, up to eight blocks, as long as the launch stays
+// within 8192 blocks (four rounds on the chip: each block first waits for its entry's row, position and cache row),
+// but four.  7B shape: 64 rows 8.5 us with four blocks, 8.1 with eight, 1024 context entries 32 and 22; seven
+// skipped layers of 32 rows 12.2 with one block, 9.0 with six.  70B shape: 256 rows 14.6 with four, 13.7 with six,
+// 1999 context entries 40 and 48.
+static int rope_blocks(int n_q, int n_kv, int rows) {
+    const int items = n_q * 16 + n_kv * 16 + (n_kv * 128 + 255) / 256 * 64;
+    return std::min({8, (items + 255) / 256, std::max(4, 8192 / rows)});
+}
+
 template <int MS, int NS, int WK, int WN, int EPI>
 static void gemm_launch(const void* X, const void* W, int K, int NB_total, int NBs, int nb_off, const int32_t* n_ptr,
                         int B, int row_groups, const EpiArgs& ep, hipStream_t s, const ZBatch& zb, int nz) {
@@ -1911,7 +1921,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         // neighbouring entries share lines of the cache only where they are positions of one row (context pass)
         const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
         if (qkv_splits == 1) qkv_from = qkv_n;         // nothing is in planes
-        hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 4), dim3(256), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B, near,
+        hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(c.n_q_heads, c.n_kv_heads, B)), dim3(256), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B, near,
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
                            ctx.C ? b->wsp<int32_t>(b->W.attn_order) : nullptr, ctx.C ? nullptr : b->wsp<AttnJob>(b->W.attn_order),
@@ -2033,7 +2043,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl))
         gemm<1, EPI_STORE>(x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl);
     const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
-    hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, 1, nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
+    hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(0, c.n_kv_heads, B * nl), nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
                        (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, (int64_t)0, kvb, kv_n, kv_n);

@@ -641,11 +641,32 @@ k_exit_decide(const float* __restrict__ part_max, const float* __restrict__ part
     int n = *n_active;
     if (n > B) n = B;
     if (i >= n) return;
-    Stat st{-FLT_MAX, 0.f, 0x7fffffff};
     int64_t base = (int64_t)i * n_part;
-    for (int t = threadIdx.x; t < n_part; t += 256) {
-        Stat p{part_max[base + t], part_sum[base + t], part_arg[base + t]};
-        st = stat_merge(st, p);
+    // A thread's own partials (four at a time, their loads in flight together): the maximum first, then one
+    // exponential per partial; merged one by one each cost two, in a chain.
+    Stat st{-FLT_MAX, 0.f, 0x7fffffff};
+    for (int t0 = threadIdx.x; t0 < n_part; t0 += 1024) {
+        float m[4], s[4];
+        int a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = t0 + 256 * u;
+            const bool in = t < n_part;
+            m[u] = in ? part_max[base + t] : -FLT_MAX;
+            s[u] = in ? part_sum[base + t] : 0.f;
+            a[u] = in ? part_arg[base + t] : 0x7fffffff;
+        }
+        float mx = st.m;
+        int arg = st.a;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            arg = m[u] > mx ? a[u] : (m[u] == mx ? min(arg, a[u]) : arg);
+            mx = fmaxf(mx, m[u]);
+        }
+        float sum = st.s * expf(st.m - mx);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += s[u] * expf(m[u] - mx);
+        st = Stat{mx, sum, arg};
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
