@@ -535,10 +535,11 @@ int ee_prefill(const ee_model* m, ee_kv* kv, ee_batch* b, const int32_t* dev_tok
     if (!m->emb) return ee_fail(EE_ERR_INVALID_ARG, "ee_prefill: embedding not set");
     const ee_model_config& c = m->cfg;
     hipStream_t s = as_stream(stream);
-    int rc = launch_prefill_begin(m, kv, b, dev_tok, dev_pos, dev_seq, n, s);
+    bool x_ready = false;
+    int rc = c.dtype == EE_BF16 ? bf16_prefill_begin(m, kv, b, dev_tok, dev_pos, dev_seq, n, s, &x_ready)
+                                : launch_prefill_begin(m, kv, b, dev_tok, dev_pos, dev_seq, n, s);
     b->kv_seq = b->wsp<int32_t>(b->W.kv_seq);      // the layers address the cache through the entry's row
     b->long_runs = true;
-    bool x_ready = false;
     for (int l = 1; l <= R && rc == EE_OK; ++l) {
         if (c.dtype == EE_BF16) {
             const float* tail_gain = l < R ? (const float*)m->layers[l].g_attn : nullptr;
@@ -600,9 +601,8 @@ int ee_backfill_kv(const ee_model* m, int from_layer_excl, int to_layer_incl, ee
 // layers first .. last on the batch's active rows, the way the decode step chains them: the kernel that
 // finishes a layer leaves the normalised operand of what comes next (next layer, or the head `then_gain`)
 static int run_layers(const ee_model* m, int first, int last, ee_kv* kv, ee_batch* b, const float* then_gain,
-                      hipStream_t s, bool* x_ready_out) {
+                      hipStream_t s, bool* x_ready_out, bool x_ready = false) {
     int rc = EE_OK;
-    bool x_ready = false;
     for (int l = first; l <= last && rc == EE_OK; ++l) {
         if (m->cfg.dtype == EE_BF16) {
             const float* tail_gain = l < last ? (const float*)m->layers[l].g_attn : then_gain;
@@ -650,9 +650,9 @@ int ee_draft_step(const ee_model* m, ee_kv* kv, ee_batch* b, int draft_exit, int
     rc = check_speculation("ee_draft_step", m, kv, draft_exit, &Le, &R, &last_exit);
     if (rc != EE_OK) return rc;
     hipStream_t s = as_stream(stream);
-    rc = ee_batch_begin_step(m, b, stream);
     bool x_ready = false;
-    if (rc == EE_OK) rc = run_layers(m, 1, Le, kv, b, (const float*)m->exits[draft_exit].gain, s, &x_ready);
+    rc = m->cfg.dtype == EE_BF16 ? bf16_begin_step(m, b, s, &x_ready) : launch_begin_step(m, b, s);
+    if (rc == EE_OK) rc = run_layers(m, 1, Le, kv, b, (const float*)m->exits[draft_exit].gain, s, &x_ready, x_ready);
     if (rc == EE_OK) rc = head_on(m, draft_exit, b, s, x_ready);
     if (rc == EE_OK) rc = ee_compact_active(b, draft_exit, Le, stream);          // every row leaves: out_tok = its draft
     if (rc == EE_OK) rc = launch_end_step(b, s);
@@ -752,11 +752,13 @@ static int check_step(const char* who, const ee_model* m, const ee_kv* kv, const
 // exit head there, the compaction, and the K/V of the layers up to the next exit for the rows that have left.
 static int step_segment(const ee_model* m, ee_kv* kv, ee_batch* b, const float* host_thresholds, int e, int R, void* s) {
     const ee_model_config& c = m->cfg;
-    int rc = e == 0 ? ee_batch_begin_step(m, b, s) : EE_OK;
-    const int first = e == 0 ? 1 : c.exit_layers[e - 1] + 1, last = c.exit_layers[e];
     // bf16: the kernel that finishes a layer can leave the normalised operand of whatever comes
-    // next (the exit head, or the next layer when no compaction lies between): one launch less
+    // next (the exit head, or the next layer when no compaction lies between), and the kernel that
+    // begins the step that of the first layer: one launch less
     bool x_ready = false;
+    int rc = EE_OK;
+    if (e == 0) rc = c.dtype == EE_BF16 ? bf16_begin_step(m, b, as_stream(s), &x_ready) : launch_begin_step(m, b, as_stream(s));
+    const int first = e == 0 ? 1 : c.exit_layers[e - 1] + 1, last = c.exit_layers[e];
     for (int l = first; l <= last && rc == EE_OK; ++l) {
         if (c.dtype == EE_BF16) {
             const float* tail_gain = l == last ? (const float*)m->exits[e].gain : (const float*)m->layers[l].g_attn;

@@ -58,6 +58,26 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 // (1024 threads: one chunk each at d = 8192; the kernels here are latency bound, and every
 // user of this routine takes the same thread count so that all give the same bits.)
 #define NORM_THREADS 1024
+// the row as one 8-float chunk (a, b) per thread (d <= 8 NORM_THREADS; zeros in threads past the row)
+__device__ __forceinline__ void rmsnorm_chunk(const float4& a, const float4& b, const float* gain, float eps, int d, uint4* out, int i,
+                                              float* red) {
+    const int c = threadIdx.x;
+    const bool has = c < (d >> 3);
+    float4 ga = make_float4(0.f, 0.f, 0.f, 0.f), gb = ga;
+    if (has) { ga = reinterpret_cast<const float4*>(gain)[2 * c]; gb = reinterpret_cast<const float4*>(gain)[2 * c + 1]; }
+    float ss = 0.f;
+    if (has) ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
+    ss = block_sum<NORM_THREADS>(ss, red);
+    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+    if (!has) return;
+    uint4 o;
+    o.x = pack2((a.x * inv) * ga.x, (a.y * inv) * ga.y);
+    o.y = pack2((a.z * inv) * ga.z, (a.w * inv) * ga.w);
+    o.z = pack2((b.x * inv) * gb.x, (b.y * inv) * gb.y);
+    o.w = pack2((b.z * inv) * gb.z, (b.w * inv) * gb.w);
+    out[afrag_chunk(i, c * 8, d >> 4)] = o;
+}
+
 __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain, float eps, int d, uint4* out, int i,
                                             float* red /* NORM_THREADS / 64 floats */) {
     const float4* hr = reinterpret_cast<const float4*>(hr_);
@@ -67,20 +87,9 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
     if (n8 <= NORM_THREADS) {
         // one chunk per thread (d <= 8192): it stays in registers; same arithmetic, same bits as below
         const int c = threadIdx.x;
-        const bool has = c < n8;
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a, ga = a, gb = a;
-        if (has) { a = hr[2 * c]; b = hr[2 * c + 1]; ga = g4[2 * c]; gb = g4[2 * c + 1]; }
-        float ss = 0.f;
-        if (has) ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
-        ss = block_sum<NORM_THREADS>(ss, red);
-        const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-        if (!has) return;
-        uint4 o;
-        o.x = pack2((a.x * inv) * ga.x, (a.y * inv) * ga.y);
-        o.y = pack2((a.z * inv) * ga.z, (a.w * inv) * ga.w);
-        o.z = pack2((b.x * inv) * gb.x, (b.y * inv) * gb.y);
-        o.w = pack2((b.z * inv) * gb.z, (b.w * inv) * gb.w);
-        out[afrag_chunk(i, c * 8, KB)] = o;
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+        if (c < n8) { a = hr[2 * c]; b = hr[2 * c + 1]; }
+        rmsnorm_chunk(a, b, gain, eps, d, out, i, red);
         return;
     }
     float ss = 0.f;
@@ -113,6 +122,58 @@ k_bf16_rmsnorm(const float* __restrict__ h, const int32_t* __restrict__ idx, con
     if (zb.g_tab) gain = zb.g_tab[zb.z0 + blockIdx.z];
     out += (int64_t)blockIdx.z * zb.x_stride;
     rmsnorm_row(h + (int64_t)idx[i] * d, gain, eps, d, out, i, red);
+}
+
+// ------------------------------------------------------------------ step begin and first norm in one launch
+// What k_begin_step (CTX = false) and k_prefill_begin (CTX = true) do for row or entry i, and the operand row of the
+// first layer's q|k|v product, RMSNorm of the embedding that was just read: one launch and one pass over h less
+// (1999 entries of 8192 values: 22 + 25 us as two launches).  d <= 8 NORM_THREADS.
+struct BeginArgs {
+    const int32_t* tok; const int32_t* pos; const int32_t* seq;      // pos, seq: context pass
+    int n, n_seq, V;
+    const uint4* emb;
+    float* h;
+    int32_t *s_tok, *s_pos, *kv_seq, *active_idx, *n_active, *n_exited, *out_layer, *status;
+};
+
+template <bool CTX>
+__global__ void __launch_bounds__(NORM_THREADS)
+k_bf16_begin_norm(BeginArgs g, int near, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ xout) {
+    __shared__ float red[NORM_THREADS / 64];
+    const int i = entry_of_block(blockIdx.x, near);
+    if (i >= g.n) return;
+    int t = g.tok[i];
+    const bool bad = t < 0 || t >= g.V;
+    if (threadIdx.x == 0) {
+        if (bad) atomicOr(g.status, 2);
+        if constexpr (CTX) {
+            int p = g.pos[i], sq = g.seq[i];
+            if (sq < 0 || sq >= g.n_seq) {
+                atomicOr(g.status, 1);
+                sq = 0;
+                p = -1;
+            }
+            g.s_tok[i] = bad ? 0 : t;
+            g.s_pos[i] = p;
+            g.kv_seq[i] = sq;
+        } else {
+            g.out_layer[i] = 0;
+        }
+        g.active_idx[i] = i;
+        if (i == 0) { *g.n_active = g.n; *g.n_exited = 0; }
+    }
+    if (bad) t = 0;
+    const int c = threadIdx.x;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    if (c < (d >> 3)) {
+        const uint4 v = g.emb[(int64_t)t * (d >> 3) + c];
+        a = make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+        b = make_float4(__uint_as_float(v.z << 16), __uint_as_float(v.z & 0xffff0000u), __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xffff0000u));
+        float4* hp = reinterpret_cast<float4*>(g.h + (int64_t)i * d + c * 8);
+        hp[0] = a;
+        hp[1] = b;
+    }
+    rmsnorm_chunk(a, b, gain, eps, d, xout, i, red);
 }
 
 // ------------------------------------------------------------------ weight-streaming MFMA GEMM
@@ -1821,7 +1882,7 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     if (EPI == EPI_STORE && tail.defer_store && tail.from_out && wide && splits == 1 && row_groups > 1 && nz == 1) {
         // More tiles than fit whole rounds of 256 workgroups: the column tiles that do run unsliced, the rest in
         // a second launch, K-sliced so that it fills one short round (QKV of 1999 entries at the 70B shape: 320
-        // tiles, two rounds 372 us; 256 tiles and 64 in four slices 262 us).
+        // tiles, two rounds 372 us; 256 tiles 215 us and 64 in four slices 62, with 10 more where they are added).
         const int full = n_tiles * row_groups / 256 * 256 / row_groups, rest = n_tiles - full;
         const int N2 = rest * 256;
         int sp = full > 0 && rest > 0 ? std::min({4, 256 / (rest * row_groups), KS / 16}) : 1;
@@ -1880,6 +1941,42 @@ static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
         break;
     }
     return r;
+}
+
+static bool begin_norm_fits(const ee_model* m) {
+    return m->cfg.d_model <= 8 * NORM_THREADS && (uintptr_t)m->emb % 16 == 0;
+}
+
+int bf16_begin_step(const ee_model* m, ee_batch* b, hipStream_t s, bool* x_ready) {
+    *x_ready = begin_norm_fits(m);
+    if (!*x_ready) return launch_begin_step(m, b, s);
+    const ee_batch_layout& L = b->L;
+    TimedScope t(EE_K_EMBED, s);
+    BeginArgs g{};
+    g.tok = b->st<int32_t>(L.tok_in); g.n = b->B; g.V = m->cfg.vocab; g.emb = (const uint4*)m->emb; g.h = b->st<float>(L.h);
+    g.active_idx = b->st<int32_t>(L.active_idx); g.n_active = b->st<int32_t>(L.n_active);
+    g.n_exited = b->st<int32_t>(L.n_exited); g.out_layer = b->st<int32_t>(L.out_layer); g.status = b->st<int32_t>(L.status);
+    hipLaunchKernelGGL(k_bf16_begin_norm<false>, dim3(entry_grid(b->B)), dim3(NORM_THREADS), 0, s, g, entry_near(b->B),
+                       (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x));
+    EE_LAUNCH_CHECK();
+    return EE_OK;
+}
+
+int bf16_prefill_begin(const ee_model* m, const ee_kv* kv, ee_batch* b, const int32_t* tok, const int32_t* pos,
+                       const int32_t* seq, int n, hipStream_t s, bool* x_ready) {
+    *x_ready = begin_norm_fits(m);
+    if (!*x_ready) return launch_prefill_begin(m, kv, b, tok, pos, seq, n, s);
+    const ee_batch_layout& L = b->L;
+    TimedScope t(EE_K_EMBED, s);
+    BeginArgs g{};
+    g.tok = tok; g.pos = pos; g.seq = seq; g.n = n; g.n_seq = kv->B; g.V = m->cfg.vocab; g.emb = (const uint4*)m->emb;
+    g.h = b->st<float>(L.h); g.s_tok = b->st<int32_t>(L.tok_in); g.s_pos = b->st<int32_t>(L.pos);
+    g.kv_seq = b->wsp<int32_t>(b->W.kv_seq); g.active_idx = b->st<int32_t>(L.active_idx);
+    g.n_active = b->st<int32_t>(L.n_active); g.n_exited = b->st<int32_t>(L.n_exited); g.status = b->st<int32_t>(L.status);
+    hipLaunchKernelGGL(k_bf16_begin_norm<true>, dim3(entry_grid(n)), dim3(NORM_THREADS), 0, s, g, entry_near(n),
+                       (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x));
+    EE_LAUNCH_CHECK();
+    return EE_OK;
 }
 
 // x_ready: the operand matrix already holds RMSNorm(h; attention gain of this layer).
