@@ -58,6 +58,15 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 // (1024 threads: one chunk each at d = 8192; the kernels here are latency bound, and every
 // user of this routine takes the same thread count so that all give the same bits.)
 #define NORM_THREADS 1024
+// Sum of the squares of a chunk, its fused multiply-adds written out: every kernel that normalises a row (here, the
+// finish of a sliced product, the step begin) has to give the same bits, and left to the compiler which of the
+// products of a sum are fused differs from kernel to kernel.
+__device__ __forceinline__ float sum_sq8(const float4& a, const float4& b) {
+    float s = a.x * a.x;
+    s = fmaf(a.y, a.y, s); s = fmaf(a.z, a.z, s); s = fmaf(a.w, a.w, s);
+    s = fmaf(b.x, b.x, s); s = fmaf(b.y, b.y, s); s = fmaf(b.z, b.z, s); s = fmaf(b.w, b.w, s);
+    return s;
+}
 // the row as one 8-float chunk (a, b) per thread (d <= 8 NORM_THREADS; zeros in threads past the row)
 __device__ __forceinline__ void rmsnorm_chunk(const float4& a, const float4& b, const float* gain, float eps, int d, uint4* out, int i,
                                               float* red) {
@@ -66,7 +75,7 @@ __device__ __forceinline__ void rmsnorm_chunk(const float4& a, const float4& b, 
     float4 ga = make_float4(0.f, 0.f, 0.f, 0.f), gb = ga;
     if (has) { ga = reinterpret_cast<const float4*>(gain)[2 * c]; gb = reinterpret_cast<const float4*>(gain)[2 * c + 1]; }
     float ss = 0.f;
-    if (has) ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
+    if (has) ss += sum_sq8(a, b);
     ss = block_sum<NORM_THREADS>(ss, red);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
     if (!has) return;
@@ -95,7 +104,7 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
     float ss = 0.f;
     for (int c = threadIdx.x; c < n8; c += NORM_THREADS) {
         float4 a = hr[2 * c], b = hr[2 * c + 1];
-        ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w + b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
+        ss += sum_sq8(a, b);
     }
     ss = block_sum<NORM_THREADS>(ss, red);
     float inv = 1.0f / sqrtf(ss / (float)d + eps);
@@ -1748,7 +1757,7 @@ k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, in
         }
         if (gain == nullptr) return;
         float ss = 0.f;
-        if (has) ss += o0.x * o0.x + o0.y * o0.y + o0.z * o0.z + o0.w * o0.w + o1.x * o1.x + o1.y * o1.y + o1.z * o1.z + o1.w * o1.w;
+        if (has) ss += sum_sq8(o0, o1);
         ss = block_sum<NORM_THREADS>(ss, red);
         const float inv = 1.0f / sqrtf(ss / (float)N + eps);
         if (has) {
