@@ -287,24 +287,26 @@ k_f32_exit_decide(const float* __restrict__ logits, int V, const int32_t* __rest
     int n = min(*n_ptr, B);
     if (i >= n) return;
     const float* z = logits + (int64_t)i * V;
-    float m = -INFINITY;
+    // Maximum and column as stat_merge takes them: a logit that is NaN is never the maximum (fmaxf), and the row's
+    // token is the largest of the others; the sum below is NaN then, and the row meets no threshold.
+    float m = -FLT_MAX;
     int a = 0x7fffffff;
+    auto take = [&](float m2, int a2) {
+        a = m > m2 ? a : (m2 > m ? a2 : min(a, a2));
+        m = fmaxf(m, m2);
+    };
 #pragma unroll 4
-    for (int j = threadIdx.x; j < V; j += 256) {
-        const float v = z[j];
-        if (v > m || a == 0x7fffffff) { m = v; a = j; }       // rising j: > keeps the lowest column
-    }
+    for (int j = threadIdx.x; j < V; j += 256) take(z[j], j);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const float m2 = __shfl_xor(m, o, 64);
         const int a2 = __shfl_xor(a, o, 64);
-        if (m2 > m || (m2 == m && a2 < a)) { m = m2; a = a2; }
+        take(m2, a2);
     }
     if ((threadIdx.x & 63) == 0) { s_m[threadIdx.x >> 6] = m; s_a[threadIdx.x >> 6] = a; }
     __syncthreads();
     m = s_m[0]; a = s_a[0];
-    for (int w = 1; w < 4; ++w)
-        if (s_m[w] > m || (s_m[w] == m && s_a[w] < a)) { m = s_m[w]; a = s_a[w]; }
+    for (int w = 1; w < 4; ++w) take(s_m[w], s_a[w]);
     float sum = 0.f;
 #pragma unroll 4
     for (int j = threadIdx.x; j < V; j += 256) sum += expf(z[j] - m);
