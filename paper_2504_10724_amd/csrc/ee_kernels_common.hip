@@ -660,7 +660,7 @@ k_exit_decide(const float* __restrict__ part_max, const float* __restrict__ part
         int arg = st.a;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            arg = m[u] > mx ? a[u] : (m[u] == mx ? min(arg, a[u]) : arg);
+            arg = mx > m[u] ? arg : (m[u] > mx ? a[u] : min(arg, a[u]));       // as stat_merge, also where m[u] is NaN
             mx = fmaxf(mx, m[u]);
         }
         float sum = st.s * expf(st.m - mx);

@@ -51,3 +51,21 @@ def test_f32_head_with_non_finite_columns(cols, value):
         assert torch.isnan(conf).all() and not leaves.any()
     else:
         assert torch.allclose(conf.double(), torch.softmax(z, -1).max(-1).values, rtol=1e-4) and leaves.all()
+
+
+# weight-streaming kernel (no multiple of 128) with one and several column tiles, tile kernel; a row of NaN among others
+@pytest.mark.parametrize("dtype,V", [("bf16", 32), ("bf16", 96), ("bf16", 512), ("f32", 300)])
+def test_a_row_of_nan_logits_gives_token_0(dtype, V):
+    print(f"[case] {dtype} head, V = {V}, a row of NaN", flush=True)
+    gen = torch.Generator().manual_seed(6)
+    d, rows = 64, 5
+    emb, W = torch.randn(V, d, generator=gen), torch.randn(V, d, generator=gen)
+    m = _head_only(dtype, d, V, W, emb)
+    tok, conf, leaves = _ask(m, rows)
+    assert leaves.all()
+    emb[2, 7] = float("nan")
+    m.set_embed(emb.to(m.tdtype))
+    tok2, conf2, leaves2 = _ask(m, rows)
+    others = [0, 1, 3, 4]
+    assert torch.equal(tok2[others], tok[others]) and torch.equal(conf2[others], conf[others]) and leaves2[others].all()
+    assert int(tok2[2]) == 0 and torch.isnan(conf2[2]) and not leaves2[2]
