@@ -1170,10 +1170,23 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     const int my_e = first + r0 + my_ent;
     const int my_head = n16 - my_ent * G;
 
+    bf16x8 qh[4], ql[4];
+    {
+        // Columns without a head read head 0 (their results are not written): eight 16-byte loads.  With a condition
+        // on them they became 32 loads of 4 bytes, each with a branch of its own, at the start of every run of
+        // entries: 1024 rows of 30 to 100 positions at the 7B shape 438 us, 362 now; 16 rows of the 70B shape in
+        // eight shares with their merge 36.4, 33.9; long contexts within 1 %.
+        const int64_t qo = ((int64_t)my_e * Hq + (int64_t)g * G + (n16 < n_col ? my_head : 0)) * 128 + 8 * gq;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            qh[c] = as_bf16x8(*reinterpret_cast<const uint4*>(q_hi + qo + 32 * c));
+            ql[c] = as_bf16x8(*reinterpret_cast<const uint4*>(q_lo + qo + 32 * c));
+        }
+    }
     const int n_groups = (n_pos + 31) >> 5;
-    // with n_splits > 1 this workgroup covers the share-th share of the position groups
-    const int g_lo = (int)(((int64_t)n_groups * share) / n_splits);
-    const int g_hi = (int)(((int64_t)n_groups * (share + 1)) / n_splits);
+    // with n_splits > 1 this workgroup covers the share-th share of the position groups (at most 2^26 of them, 16 shares)
+    const int g_lo = (int)((unsigned)(n_groups * share) / (unsigned)n_splits);
+    const int g_hi = (int)((unsigned)(n_groups * (share + 1)) / (unsigned)n_splits);
     // K and V tiles of one 32-position group as this lane holds them for the MFMAs
     struct KVTiles { uint4 k[2][4]; uint4 v[8]; };
     auto load_kv = [&](int t) -> KVTiles {
@@ -1196,18 +1209,8 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     // equal at 256).  Context pass with two entries per workgroup: three workgroups, no prefetch
     // (0.8 % faster there).
     KVTiles nxt;
-    if constexpr (AHEAD) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has; before the queries
+    if constexpr (AHEAD) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has
 
-    bf16x8 qh[4], ql[4];
-    {
-        uint4 z = make_uint4(0, 0, 0, 0);
-        const int64_t qo = ((int64_t)my_e * Hq + (int64_t)g * G + my_head) * 128 + 8 * gq;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            qh[c] = as_bf16x8(n16 < n_col ? *reinterpret_cast<const uint4*>(q_hi + qo + 32 * c) : z);
-            ql[c] = as_bf16x8(n16 < n_col ? *reinterpret_cast<const uint4*>(q_lo + qo + 32 * c) : z);
-        }
-    }
     const float inv_sqrt = 1.0f / sqrtf(128.0f);
     const float NEG = -1.0e30f;
     float m_run = NEG, l_run = 0.f;
