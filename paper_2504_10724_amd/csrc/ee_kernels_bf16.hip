@@ -1376,6 +1376,10 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
 // Entries of a tile that name more than two cache rows are served by attn_streams instead, one workgroup per
 // E entries as above: the workgroups y = sub * tiles + t, sub = 0 .. 4 C - 1, exist for that; on a tile of
 // one or two rows only sub = 0 works.
+// A column's probability is 0 at the positions it is masked at, but 0 times a value that is infinite or NaN is NaN,
+// and the entries of a tile read each other's positions: a tile with such a result is served again entry group
+// by entry group, so that a token with a NaN, or an entry refused for its position, reaches no further among
+// the entries of its call than it did when all calls went that way.
 #define CTX_STAGE 2048                        /* uint4 of a stage: two groups of 32 positions, 16 KiB each */
 
 // maximum over the four lanes that hold a column (lane, lane ^ 16, lane ^ 32, lane ^ 48)
@@ -1386,8 +1390,9 @@ __device__ __forceinline__ float column_max(float v) {
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Returns, alike in all waves, whether a result came out infinite or NaN.
 template <int C>
-__device__ __forceinline__ void attn_tile(uint4* lds, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
+__device__ __forceinline__ bool attn_tile(uint4* lds, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
                                           const int32_t* __restrict__ idx, const int32_t* __restrict__ pos, const KvView& kv,
                                           uint4* __restrict__ ao, int KB_ao, int g, int first, int cnt) {
     const int G = Hq / kv.n_kv_heads, E = 16 / G;
@@ -1396,6 +1401,7 @@ __device__ __forceinline__ void attn_tile(uint4* lds, const bf16_t* __restrict__
     const unsigned lane_bytes = (unsigned)lane * 16u, lds0 = (unsigned)(size_t)lds;
     const float scale2 = (1.0f / sqrtf(128.0f)) * 1.44269504088896340736f;    // exp(x) = 2^(x log2 e)
     const float NEG = -1.0e30f;
+    float odd = 0.f;                                         // NaN once a result is infinite or NaN
     for (int r0 = 0; r0 < cnt;) {
         const int sq = __builtin_amdgcn_readfirstlane(kv_row(kv, idx[first + r0]));
         int r1 = r0 + 1;
@@ -1587,12 +1593,15 @@ __device__ __forceinline__ void attn_tile(uint4* lds, const bf16_t* __restrict__
 #pragma unroll
             for (int hb = 0; hb < 8; ++hb) {
                 const int col = chunk0 + 16 * hb + 4 * gq;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) odd = fmaf(O[j][hb][r] * inv, 0.f, odd);
                 uint2* dst = reinterpret_cast<uint2*>(ao + afrag_chunk(ent[j], col & ~7, KB_ao)) + ((col >> 2) & 1);
                 *dst = make_uint2(pack2(O[j][hb][0] * inv, O[j][hb][1] * inv), pack2(O[j][hb][2] * inv, O[j][hb][3] * inv));
             }
         }
         r0 = r1;
     }
+    return __syncthreads_or(odd != 0.f);
 }
 
 template <int C>
@@ -1613,13 +1622,17 @@ k_bf16_attn_ctx(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo
     for (int j = lane; j + 1 < cnt; j += 64) changes += kv_row(kv, idx[first + j]) != kv_row(kv, idx[first + j + 1]) ? 1 : 0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) changes += __shfl_xor(changes, o, 64);
+    int k = sub, k_end = sub + 1;                            // entry groups this workgroup serves one by one
     if (__builtin_amdgcn_readfirstlane(changes) <= 1) {
-        if (sub == 0) attn_tile<C>(lds, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, blockIdx.x, first, cnt);
-        return;
+        if (sub != 0 || !attn_tile<C>(lds, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, blockIdx.x, first, cnt)) return;
+        k_end = 4 * C;
+        __syncthreads();                                     // what the tile wrote comes before what follows
     }
-    if (sub * E >= cnt) return;
-    attn_streams<true, true>(*reinterpret_cast<AttnShared*>(lds), q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr,
-                             blockIdx.x, first + sub * E, min(E, cnt - sub * E));
+    for (; k < k_end && k * E < cnt; ++k) {
+        attn_streams<true, true>(*reinterpret_cast<AttnShared*>(lds), q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr,
+                                 blockIdx.x, first + k * E, min(E, cnt - k * E));
+        __syncthreads();                                     // the merge has read the shared arrays
+    }
 }
 
 // merges the position shares of k_bf16_attn in share order: one workgroup per (kv head, list entry)
