@@ -44,12 +44,11 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{a, b}), b2));
 }
 
-// g / (1 + exp(-g)) * u on the hardware's exponential and reciprocal (1 ulp each; the product is rounded to bf16).
-// With expf and an IEEE division, 64 of them per lane, a round of 256 workgroups took 4.5 us longer (gate/up of
-// 1999 entries at the 70B shape, seven rounds: 1422 -> 1391 us).
-__device__ __forceinline__ float silu_mul(float g, float u) {
-    return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-}
+// silu(g) u: expf and an IEEE division, which stay within 1e-7 of the value before it is rounded to bf16.  On the
+// hardware's exponential and reciprocal a round of 256 workgroups takes 3 to 5 us less (gate/up of 256 rows at the
+// 70B shape 193 against 198 us, of 1024 entries at the 7B shape 175 against 183), but there the exponential's argument
+// is rounded as a product with log2 e, an error that grows with |g|: 2.5e-6 of the value at -80.
+__device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
 // ------------------------------------------------------------------ RMSNorm -> A tiles
 // The NORM_THREADS threads of a block normalise one row (hr: d floats) and write it as list entry
