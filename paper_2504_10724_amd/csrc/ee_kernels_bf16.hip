@@ -1588,14 +1588,14 @@ __device__ __forceinline__ bool attn_tile(uint4* lds, const bf16_t* __restrict__
             l += __shfl_xor(l, 16, 64);
             l += __shfl_xor(l, 32, 64);
             if (ent[j] < 0) continue;
-            const float inv = 1.0f / l;
 #pragma unroll
             for (int hb = 0; hb < 8; ++hb) {
                 const int col = chunk0 + 16 * hb + 4 * gq;
+                O[j][hb] = O[j][hb] / l;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) odd = fmaf(O[j][hb][r] * inv, 0.f, odd);
+                for (int r = 0; r < 4; ++r) odd = fmaf(O[j][hb][r], 0.f, odd);
                 uint2* dst = reinterpret_cast<uint2*>(ao + afrag_chunk(ent[j], col & ~7, KB_ao)) + ((col >> 2) & 1);
-                *dst = make_uint2(pack2(O[j][hb][0] * inv, O[j][hb][1] * inv), pack2(O[j][hb][2] * inv, O[j][hb][3] * inv));
+                *dst = make_uint2(pack2(O[j][hb][0], O[j][hb][1]), pack2(O[j][hb][2], O[j][hb][3]));
             }
         }
         r0 = r1;

@@ -57,3 +57,34 @@ def test_context_attention_tiles(hq, hkv, lengths):
         for got, ref in ((K, o.kv.K), (V, o.kv.V)):
             worst, ok = rows_close(got.reshape(1, -1), ref[1, i, :, :lengths[r]].reshape(1, -1), TOL["bf16"])
             assert ok, f"cache row {r}: worst cache error {worst:.2e}"
+
+
+@pytest.mark.parametrize("n", [515, 1100])                  # one and two blocks of columns per wave
+def test_mean_of_two_values_is_rounded_once(n):
+    """All scores 0, values 254/128 and 255/128 in turn: the mean over an even number of positions lies half way between
+    these two bf16 neighbours and has to become 254/128 (the even one) for every number of positions; a result that is
+    off by one unit of fp32 before it is rounded becomes 255/128 for some of them."""
+    print(f"[case] mean over 1 .. {n} positions", flush=True)
+    d, heads = 64, 32
+    m = S.Model(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=heads, head_dim=128, d_ffn=64, vocab=32, dtype="bf16",
+                exit_layers=[1], max_pos=2048)
+    # two tokens with one value each; the gain makes their normalised value 1
+    emb = torch.zeros(32, d)
+    emb[0, 0] = emb[1, 1] = 1.0
+    W_qkv, W_o = torch.zeros(3 * heads * 128, d), torch.zeros(d, heads * 128)
+    W_qkv[2 * heads * 128:, 0], W_qkv[2 * heads * 128:, 1] = 254 / 128, 255 / 128
+    W_o[torch.arange(heads) + 2, torch.arange(heads) * 129 % (heads * 128)] = 1.0       # one feature of each head
+    b16 = lambda t: t.bfloat16()      # noqa: E731
+    m.set_layer(1, g_attn=torch.full((d,), float(np.sqrt(1.0 / d + 1e-5))), W_qkv=b16(W_qkv), W_o=b16(W_o), g_ffn=torch.ones(d),
+                W_gate=b16(torch.zeros(64, d)), W_up=b16(torch.zeros(64, d)), W_down=b16(torch.zeros(d, 64)))
+    m.set_embed(b16(emb))
+    kv, b = S.KVCache(m, 1, [(n + 31) // 32 * 32]), S.Batch(m, n)
+    b.reset(np.zeros(n, np.int32), np.zeros(n, np.int32), None)
+    i = np.arange(n, dtype=np.int32)
+    assert S.prefill(m, kv, b, i % 2, i, np.zeros(n, np.int32)) == 0
+    got = b.field("h").cpu().numpy()[:, 2:2 + heads]
+    even = i % 2 == 1                                       # an even number of positions
+    assert np.array_equal(got[even], np.full((even.sum(), heads), 254 / 128, np.float32)), i[even][(got[even] != 254 / 128).any(-1)] + 1
+    mean = (254 + ((i + 1) // 2) / (i + 1.0)) / 128
+    want = torch.from_numpy(mean).float().bfloat16().float().numpy()
+    assert np.array_equal(got[~even], np.repeat(want[~even, None], heads, 1))
