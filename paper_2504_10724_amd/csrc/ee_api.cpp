@@ -539,7 +539,7 @@ int ee_prefill(const ee_model* m, ee_kv* kv, ee_batch* b, const int32_t* dev_tok
     int rc = c.dtype == EE_BF16 ? bf16_prefill_begin(m, kv, b, dev_tok, dev_pos, dev_seq, n, s, &x_ready)
                                 : launch_prefill_begin(m, kv, b, dev_tok, dev_pos, dev_seq, n, s);
     b->kv_seq = b->wsp<int32_t>(b->W.kv_seq);      // the layers address the cache through the entry's row
-    b->long_runs = true;
+    b->n_entries = n;
     for (int l = 1; l <= R && rc == EE_OK; ++l) {
         if (c.dtype == EE_BF16) {
             const float* tail_gain = l < R ? (const float*)m->layers[l].g_attn : nullptr;
@@ -551,7 +551,7 @@ int ee_prefill(const ee_model* m, ee_kv* kv, ee_batch* b, const int32_t* dev_tok
         }
     }
     b->kv_seq = nullptr;
-    b->long_runs = false;
+    b->n_entries = 0;
     return rc;
 }
 

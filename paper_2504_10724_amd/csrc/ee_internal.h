@@ -61,7 +61,7 @@ struct ee_batch {
     ee_batch_layout L;
     WsLayout W;
     const int32_t* kv_seq = nullptr;        // device [Mpad], set only while a context pass runs: entry -> cache row
-    bool long_runs = false;                 // set beside kv_seq in ee_prefill: neighbouring entries mostly share a cache row
+    int n_entries = 0;                      // set beside kv_seq in ee_prefill: entries of the call, of which neighbours mostly share a cache row
     template <class T> T* st(size_t off) const { return reinterpret_cast<T*>(state + off); }
     template <class T> T* wsp(size_t off) const { return reinterpret_cast<T*>(ws + off); }
 };

@@ -1952,14 +1952,16 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
 // workgroups: two where that still leaves two workgroups per CU (70B shape, 1999 entries: 275 us against 310
 // with one), one from one workgroup per CU on (256 entries, 1500 cached: layer 558 -> 539 us; 600 entries of
 // four contexts: 1284 -> 1239 us).  Below that the kernel that splits a row's positions over its waves stays.
+// What counts is the entries of the call, not the batch's capacity: 64 entries at positions from 1936 on take 41 us
+// in a batch of 2048 (79 as four tiles of 16, 32 workgroups), 100 of two contexts of 3000 in a batch of 1024 61 (197).
 // Speculative rounds keep it too: their runs are a few drafts long.
 struct CtxTiles { int C = 0, tile_entries = 1, tiles = 0; };
 static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
     CtxTiles r;
     const int G = c.n_q_heads / c.n_kv_heads, E = 16 / G;
-    if (!b->long_runs) return r;
+    if (b->n_entries == 0) return r;
     for (int C = 2; C >= 1; --C) {
-        const int te = 4 * C * E, tiles = (b->B + te - 1) / te;
+        const int te = 4 * C * E, tiles = (b->n_entries + te - 1) / te;
         if (tiles * c.n_kv_heads < 256 * C || tiles * 4 * C > 65535) continue;
         r.C = C; r.tile_entries = te; r.tiles = tiles;
         break;

@@ -1,0 +1,66 @@
+"""What a call costs follows the rows it has, not the capacity of the batch or the cache it runs in.  Each test times
+one class of kernels (HIP events inside the library, median of 15 runs) on two sides that do the same work; the bound
+lies between what they differ by and what a launch rule that goes by the capacity made of it."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_10724_amd import capi
+from paper_2504_10724_amd import session as S
+
+pytestmark = pytest.mark.gpu
+
+ATTENTION, QKV = (1 << capi.KERNEL_CLASSES.index(k) for k in ("attention", "gemm_qkv"))
+SHAPES = {"70b": (8192, 64, 8), "7b": (4096, 32, 32)}      # d, query heads, kv heads (the FFN is kept small)
+
+
+def _model(shape, layers=1):
+    d, hq, hkv = SHAPES[shape]
+    m = S.Model(n_layers=layers, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ffn=256, vocab=512, dtype="bf16",
+                exit_layers=[layers], max_pos=4096)
+    rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02)      # noqa: E731
+    one = torch.ones(d, device="cuda")
+    for l in range(1, layers + 1):
+        m.set_layer(l, g_attn=one, W_qkv=rnd((hq + 2 * hkv) * 128, d), W_o=rnd(d, hq * 128), g_ffn=one, W_gate=rnd(256, d),
+                    W_up=rnd(256, d), W_down=rnd(d, 256))
+    m.set_exit(0, g=one, W=rnd(512, d))
+    m.set_embed(rnd(512, d))
+    return m
+
+
+def _time(call, kernels):
+    """microseconds of the launches of one class in a call"""
+    lib, n, ms, got = capi.load(), C.c_int(), C.c_float(), []
+    capi.check(lib.ee_timing_enable(kernels))
+    try:
+        for k in range(20):
+            capi.check(lib.ee_timing_reset())
+            call()
+            capi.check(lib.ee_timing_read(kernels.bit_length() - 1, C.byref(n), C.byref(ms)))
+            got.append(ms.value * 1e3)
+    finally:
+        lib.ee_timing_enable(0)
+    return float(np.median(got[5:]))
+
+
+def _context_call(m, batch, lengths, start):
+    """one call of lengths[r] tokens for cache row r, which holds `start` positions"""
+    kv, b, n = S.KVCache(m, 1, [(start + x + 31) // 32 * 32 for x in lengths]), S.Batch(m, batch), sum(lengths)
+    kv.pool.view(torch.bfloat16).normal_()
+    b.reset(np.zeros(batch, np.int32), np.zeros(batch, np.int32), None)
+    dev = lambda x: torch.as_tensor(np.asarray(x, np.int32)).cuda()      # noqa: E731
+    tok, seq = dev(np.arange(n) % 512), dev(np.repeat(np.arange(len(lengths)), lengths))
+    pos = dev(np.concatenate([start + np.arange(x) for x in lengths]))
+    return lambda: capi.check(S.prefill(m, kv, b, tok, pos, seq))
+
+
+@pytest.mark.parametrize("shape,batch,lengths,start", [("70b", 1024, [50, 50], 3000), ("70b", 2048, [64], 1936),
+                                                       ("7b", 2048, [64], 1936)])
+def test_context_attention_of_a_short_call(shape, batch, lengths, start):
+    m = _model(shape)
+    small = _time(_context_call(m, sum(lengths), lengths, start), ATTENTION)
+    large = _time(_context_call(m, batch, lengths, start), ATTENTION)
+    print(f"[case] attention of {sum(lengths)} entries, {shape}: {small:.1f} us alone, {large:.1f} in a batch of {batch}", flush=True)
+    assert large <= 1.5 * small

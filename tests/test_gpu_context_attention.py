@@ -59,6 +59,35 @@ def test_context_attention_tiles(hq, hkv, lengths):
             assert ok, f"cache row {r}: worst cache error {worst:.2e}"
 
 
+# a batch of 1152 entries takes the whole context but its last tokens in one call, those in the next: the
+# tiling goes by the call's entries (1088 of them: C = 2, 64: not tiled; 700 and 300: C = 1; G = 1, 800: C = 1, 330: not tiled)
+@pytest.mark.parametrize("hq,hkv,first,rest", [(64, 8, 1088, 64), (64, 8, 700, 300), (32, 32, 800, 330)])
+def test_short_call_in_a_large_batch(hq, hkv, first, rest):
+    n = first + rest
+    s = BASE.with_(name=f"short_{hq}_{hkv}_{n}", n_q_heads=hq, n_kv_heads=hkv, batch=1, ctx_lo=1, ctx_hi=n)
+    print(f"[case] {rest} entries after {first} in a batch of 1152", flush=True)
+    o = OracleSide(s, rows=[0], cap=n, fill_ctx=False)
+    g = GpuSide(s, weights=o.weights, synth_rows=[], max_pos=2048)
+    kv, b = S.KVCache(g.model, s.resident, [(n + 31) // 32 * 32]), S.Batch(g.model, 1152)
+    kv.pool.view(torch.bfloat16).fill_(float("nan"))
+    b.reset(np.zeros(1152, np.int32), np.zeros(1152, np.int32), None)
+    toks = synth.context_tokens(s, 0, n)
+    got = []
+    for lo, hi in ((0, first), (first, n)):
+        i = np.arange(lo, hi, dtype=np.int32)
+        assert S.prefill(g.model, kv, b, np.asarray(toks[lo:hi], np.int32), i, np.zeros(hi - lo, np.int32)) == 0
+        got.append(b.field("h").cpu().numpy()[:hi - lo])
+    assert int(b.field("status").cpu()[0]) == 0
+    rc, want = orc.prefill(o.model, o.kv, 0, toks, want_h=True)
+    assert rc == 0
+    worst, ok = rows_close(np.concatenate(got), want, TOL["bf16"])
+    assert ok, f"worst entry error {worst:.2e}"
+    K, V = kv.read_context(2, 0, n)
+    for a, ref in ((K, o.kv.K), (V, o.kv.V)):
+        worst, ok = rows_close(a.reshape(1, -1), ref[1, 0, :, :n].reshape(1, -1), TOL["bf16"])
+        assert ok, f"worst cache error {worst:.2e}"
+
+
 @pytest.mark.parametrize("n", [515, 1100])                  # one and two blocks of columns per wave
 def test_mean_of_two_values_is_rounded_once(n):
     """All scores 0, values 254/128 and 255/128 in turn: the mean over an even number of positions lies half way between
