@@ -1903,13 +1903,17 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     int n_tiles = wide ? N / 256 : N / 128;
     if (splits == 0) splits = sliceable && n_tiles * row_groups < 200 ? fit_slices(slices_for(n_tiles * row_groups)) : 1;
     if (tail.from_out) *tail.from_out = 0;
-    if (EPI == EPI_STORE && tail.defer_store && tail.from_out && wide && splits == 1 && row_groups > 1 && nz == 1) {
+    // row groups that have rows: known in a context pass; in a decode step the rows that have left may leave one
+    const int live_groups = (b->n_entries + 255) / 256;
+    if (EPI == EPI_STORE && tail.defer_store && tail.from_out && wide && splits == 1 && live_groups > 1 && nz == 1) {
         // More tiles than fit whole rounds of 256 workgroups: the column tiles that do run unsliced, the rest in
         // a second launch, K-sliced so that it fills one short round (QKV of 1999 entries at the 70B shape: 320
         // tiles, two rounds 372 us; 256 tiles 215 us and 64 in four slices 62, with 10 more where they are added).
-        const int full = n_tiles * row_groups / 256 * 256 / row_groups, rest = n_tiles - full;
+        // By the batch's capacity instead of the call's entries, 64 entries in a batch of 2048 (7B shape) took two
+        // launches for 48 tiles: 79 us instead of 52.
+        const int full = n_tiles * live_groups / 256 * 256 / live_groups, rest = n_tiles - full;
         const int N2 = rest * 256;
-        int sp = full > 0 && rest > 0 ? std::min({4, 256 / (rest * row_groups), KS / 16}) : 1;
+        int sp = full > 0 && rest > 0 ? std::min({4, 256 / (rest * live_groups), KS / 16}) : 1;
         while (sp > 1 && (size_t)sp * Mpad * N2 * sizeof(float) > b->W.gemm_part_bytes) --sp;
         if (sp > 1) {
             hipLaunchKernelGGL((k_bf16_gemm_dma8<EPI>), dim3((full + 7) / 8 * 8 * row_groups), dim3(512), 0, s, (const uint4*)X,

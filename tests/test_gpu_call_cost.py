@@ -64,3 +64,12 @@ def test_context_attention_of_a_short_call(shape, batch, lengths, start):
     large = _time(_context_call(m, batch, lengths, start), ATTENTION)
     print(f"[case] attention of {sum(lengths)} entries, {shape}: {small:.1f} us alone, {large:.1f} in a batch of {batch}", flush=True)
     assert large <= 1.5 * small
+
+
+def test_qkv_of_a_short_call():
+    """2048 rows of the 7B shape have more 256-column tiles than fit a round of workgroups, 1025 have not"""
+    m = _model("7b")
+    small = _time(_context_call(m, 1025, [64], 0), QKV)
+    large = _time(_context_call(m, 2048, [64], 0), QKV)
+    print(f"[case] q|k|v of 64 entries: {small:.1f} us in a batch of 1025, {large:.1f} in one of 2048", flush=True)
+    assert large <= 1.25 * small
