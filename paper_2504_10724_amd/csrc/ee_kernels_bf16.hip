@@ -1905,10 +1905,15 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     if (tail.from_out) *tail.from_out = 0;
     // row groups that have rows: known in a context pass; in a decode step the rows that have left may leave one
     const int live_groups = (b->n_entries + 255) / 256;
-    if (EPI == EPI_STORE && tail.defer_store && tail.from_out && wide && splits == 1 && live_groups > 1 && nz == 1) {
+    if (EPI == EPI_STORE && tail.defer_store && tail.from_out && wide && splits == 1 && nz == 1 && live_groups > 1 &&
+        32 % live_groups == 0) {
         // More tiles than fit whole rounds of 256 workgroups: the column tiles that do run unsliced, the rest in
         // a second launch, K-sliced so that it fills one short round (QKV of 1999 entries at the 70B shape: 320
-        // tiles, two rounds 372 us; 256 tiles 215 us and 64 in four slices 62, with 10 more where they are added).
+        // tiles, two rounds 360 us; 256 tiles 215 us and 64 in four slices 62, with 14 more where they are added).
+        // Only where the row groups of whole column tiles fill an XCD's 32 CUs (32 % live_groups): tile_of_block
+        // keeps a column tile on one XCD, so with seven groups 36 column tiles are 35 workgroups on some XCDs and
+        // 28 on others, two rounds again (1600 entries: 345 + 39 us against 298 + 31 unsplit; 7B shape, 1600
+        // entries 220 against 183, 3072 364 against 296).
         // By the batch's capacity instead of the call's entries, 64 entries in a batch of 2048 (7B shape) took two
         // launches for 48 tiles: 79 us instead of 52.
         const int full = n_tiles * live_groups / 256 * 256 / live_groups, rest = n_tiles - full;

@@ -73,3 +73,13 @@ def test_qkv_of_a_short_call():
     large = _time(_context_call(m, 2048, [64], 0), QKV)
     print(f"[case] q|k|v of 64 entries: {small:.1f} us in a batch of 1025, {large:.1f} in one of 2048", flush=True)
     assert large <= 1.25 * small
+
+
+@pytest.mark.parametrize("shape", ["70b", "7b"])
+def test_qkv_does_not_rise_below_2048_entries(shape):
+    """eight row groups: the column tiles of a full round run in one launch and the rest in slices; with seven groups
+    that would leave some XCDs with more workgroups than CUs"""
+    m = _model(shape)
+    t = {n: _time(_context_call(m, n, [n], 0), QKV) for n in (1600, 2048)}
+    print(f"[case] q|k|v, {shape}: {t[1600]:.1f} us for 1600 entries, {t[2048]:.1f} for 2048", flush=True)
+    assert t[1600] <= 1.15 * t[2048]

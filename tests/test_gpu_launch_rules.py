@@ -15,12 +15,14 @@ from paper_2504_10724_amd import session as S
 pytestmark = pytest.mark.gpu
 
 
-# 40 column tiles of 256: 6 row groups are 240 tiles (one launch), 7 are 280 (36 column tiles + 4 in slices, whose
-# border lies inside the values), the last row group with one entry
-@pytest.mark.parametrize("n", [1536, 1537, 1760])
-def test_qkv_of_a_context_pass_in_one_and_two_launches(n):
-    s = synth.CONFIGS["llama2_70b"].with_(name=f"qkv_{n}", n_layers=2, resident=2, d_model=1024, d_ffn=256, vocab=512,
-                                          exit_layers=(1, 2), thresholds=(0.5, 0.0), batch=40, ctx_lo=1, ctx_hi=44, steps=1)
+# 40 column tiles of 256: 6 row groups are 240 tiles, 7 are 280 (both one launch), 8 are 320 (32 column tiles, the
+# queries, + 8 in slices, the keys and values), the last row group with one entry and full; 48 column tiles: queries and
+# keys + 16 in slices, the values
+@pytest.mark.parametrize("n,hq,hkv", [(1536, 64, 8), (1537, 64, 8), (1760, 64, 8), (1793, 64, 8), (2048, 64, 8), (1793, 32, 32)])
+def test_qkv_of_a_context_pass_in_one_and_two_launches(n, hq, hkv):
+    s = synth.CONFIGS["llama2_70b"].with_(name=f"qkv_{n}_{hkv}", n_layers=2, resident=2, d_model=1024, n_q_heads=hq,
+                                          n_kv_heads=hkv, d_ffn=256, vocab=512, exit_layers=(1, 2), thresholds=(0.5, 0.0),
+                                          batch=40, ctx_lo=1, ctx_hi=52, steps=1)
     print(f"[case] {s.name}", flush=True)
     lengths = [n // 40 + (1 if r < n % 40 else 0) for r in range(40)]
     check = [0, 1, 25, 39]
