@@ -982,10 +982,22 @@ struct AttnJob {
     int32_t entry;      // list entry
     int32_t n_pos;      // positions read
     int32_t cap;        // capacity of the cache row
-    int32_t pad;
+    int32_t shares;     // workgroups that share its positions, per kv head
     int64_t off;        // positions of the rows before it
     int64_t pad2;
 };
+
+// Workgroups that share the positions of one list entry and kv head: as many as keep the live (entry, kv head) pairs
+// within the 512 that run at a time (two per CU), but two up to 384 pairs, and no more than leave each of the four
+// waves two groups of 32 positions.  `most`: what the host launched, from the capacity.  Taken on the device, because
+// only there it is known how many rows are left and how long they are: by the capacities alone, 4 of 16 rows of the
+// 70B shape took 24 us with their merge (19 now; 19 with twice the shares whatever is live), one row of 2000
+// positions 19 (16).  All rows live, attention and merge: 16 rows of the 70B shape 34 us at 1024 workgroups, 31
+// here; 37 rows of 2 kv heads, up to 900 positions, 27 and 17; 12 entries of four contexts at the 7B shape (384
+// pairs) 64 unshared, 55 in two; 60 entries (480 pairs) of the 70B shape 46 in two, 41 unshared.
+__device__ __forceinline__ int attn_shares(int pairs, int n_pos, int most) {
+    return max(1, min(min(most, n_pos >> 8), max(512 / pairs, pairs <= 384 ? 2 : 1)));
+}
 
 // ------------------------------------------------------------------ RoPE + cache append
 // buf[i] = [q (n_q heads, may be 0) | k (Hkv heads) | v (Hkv heads)], fp32, hd = 128.
@@ -998,7 +1010,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
                    const int32_t* __restrict__ n_ptr, int B, int near, const int32_t* __restrict__ pos,
                    const float* __restrict__ rope, int max_pos, KvView kv, bf16_t* __restrict__ q_hi,
                    bf16_t* __restrict__ q_lo, int32_t* __restrict__ status, int64_t z_stride,
-                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int tile_entries, int splits, int64_t plane,
+                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int most_shares, int tile_entries, int splits, int64_t plane,
                    const float* __restrict__ planes, int ld_planes, int from) {
     int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
@@ -1025,8 +1037,12 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
         if (threadIdx.x == 0) {
-            if (jobs != nullptr) jobs[before] = AttnJob{tile, max(1, min(p + 1, cap)), cap, 0, kv.off[sq], 0};
-            else order[before] = tile;
+            if (jobs != nullptr) {
+                const int n_pos = max(1, min(p + 1, cap));
+                jobs[before] = AttnJob{tile, n_pos, cap, attn_shares(n * kv.n_kv_heads, n_pos, most_shares), kv.off[sq], 0};
+            } else {
+                order[before] = tile;
+            }
         }
     }
     const int hd = 128, half = 64;
@@ -1141,7 +1157,8 @@ template <bool PAIR, bool AHEAD>
 __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo,
                                              int Hq, const int32_t* __restrict__ idx, const int32_t* __restrict__ pos,
                                              const KvView& kv, uint4* __restrict__ ao, int KB_ao, int n_splits, int share,
-                                             float* __restrict__ part, int g, int first, int cnt, const AttnJob& job = AttnJob{}) {
+                                             float* __restrict__ part, int most, int g, int first, int cnt,
+                                             const AttnJob& job = AttnJob{}) {
     const int G = Hq / kv.n_kv_heads;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int n16 = lane & 15, gq = lane >> 4;
@@ -1317,8 +1334,8 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
                 int col = (g * G + hq) * 128 + c0;
                 ao[afrag_chunk(i, col, KB_ao)] = pk;
             } else {
-                // unnormalised share: [i][kv head][split][head][132] = 128 features, max, sum, two unused
-                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * n_splits + share) * 16 + hq) * ATTN_SHARE;
+                // unnormalised share: [i][kv head][share, `most` of them][head][132] = 128 features, max, sum, two unused
+                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * most + share) * 16 + hq) * ATTN_SHARE;
                 *reinterpret_cast<float4*>(p + c0) = make_float4(o[0], o[1], o[2], o[3]);
                 *reinterpret_cast<float4*>(p + c0 + 4) = make_float4(o[4], o[5], o[6], o[7]);
                 if (c0 == 0) { p[128] = M; p[129] = Lsum; }
@@ -1334,7 +1351,7 @@ template <bool PAIR>
 __global__ void __launch_bounds__(256, PAIR ? 3 : 2)
 k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
             const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr, int B,
-            const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao, int KB_ao, int n_splits,
+            const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao, int KB_ao, int most,
             float* __restrict__ part, const AttnJob* __restrict__ jobs) {
     __shared__ AttnShared sm;
     const int n = min(*n_ptr, B);
@@ -1347,13 +1364,12 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     if constexpr (PAIR) {
         const int E = 16 / (Hq / kv.n_kv_heads), first = E * (int)blockIdx.y;
         if (first >= n) return;
-        attn_streams<true, false>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, n_splits, blockIdx.z, part, blockIdx.x, first,
-                                  min(E, n - first));
+        attn_streams<true, false>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr, 1, blockIdx.x, first, min(E, n - first));
     } else {
         const AttnJob job = jobs[blockIdx.y];  // longest contexts first; slots from n on are not read further
-        if ((int)blockIdx.y >= n) return;
-        attn_streams<false, true>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, n_splits, blockIdx.z, part, blockIdx.x, job.entry,
-                                  1, job);
+        if ((int)blockIdx.y >= n || (int)blockIdx.z >= job.shares) return;
+        attn_streams<false, true>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, job.shares, blockIdx.z, part, most, blockIdx.x,
+                                  job.entry, 1, job);
     }
 }
 
@@ -1629,42 +1645,31 @@ k_bf16_attn_ctx(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo
     }
     for (; k < k_end && k * E < cnt; ++k) {
         attn_streams<true, true>(*reinterpret_cast<AttnShared*>(lds), q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr,
-                                 blockIdx.x, first + k * E, min(E, cnt - k * E));
+                                 1, blockIdx.x, first + k * E, min(E, cnt - k * E));
         __syncthreads();                                     // the merge has read the shared arrays
     }
 }
 
 // merges the position shares of k_bf16_attn in share order: one workgroup per (kv head, list entry)
 __global__ void __launch_bounds__(256)
-k_bf16_attn_merge(const float* __restrict__ part, int Hq, int Hkv, int n_splits, const int32_t* __restrict__ n_ptr,
-                  int B, uint4* __restrict__ ao, int KB_ao) {
-    const int g = blockIdx.x, i = blockIdx.y;
+k_bf16_attn_merge(const float* __restrict__ part, int Hq, int Hkv, int most, const AttnJob* __restrict__ jobs,
+                  const int32_t* __restrict__ n_ptr, int B, uint4* __restrict__ ao, int KB_ao) {
+    const int g = blockIdx.x;
     const int n = min(*n_ptr, B);
-    if (i >= n) return;
+    const int i = jobs[blockIdx.y].entry, shares = jobs[blockIdx.y].shares;
+    if ((int)blockIdx.y >= n || shares == 1) return;         // a single share wrote the result itself
     const int G = Hq / Hkv;
     const int head = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;
     if (head >= G) return;
-    // all maxima and sums at once, then all values: two trips to memory whatever the number of shares
-    const float* base = part + (((int64_t)i * Hkv + g) * n_splits * 16 + head) * ATTN_SHARE;
-    float ms[16], ls[16];
+    const float* base = part + (((int64_t)i * Hkv + g) * most * 16 + head) * ATTN_SHARE;
     float M = -1.0e30f;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        ms[q] = -1.0e30f; ls[q] = 0.f;
-        if (q < n_splits) {
-            const float2 ml = *reinterpret_cast<const float2*>(base + (int64_t)q * 16 * ATTN_SHARE + 128);
-            ms[q] = ml.x; ls[q] = ml.y;
-        }
-        M = fmaxf(M, ms[q]);
-    }
+    for (int q = 0; q < shares; ++q) M = fmaxf(M, base[(int64_t)q * 16 * ATTN_SHARE + 128]);
     float L = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        if (q >= n_splits) break;
-        const float* p = base + (int64_t)q * 16 * ATTN_SHARE + c0;
-        const float4 u = *reinterpret_cast<const float4*>(p), v = *reinterpret_cast<const float4*>(p + 4);
-        const float wq = __expf(ms[q] - M);
-        L += ls[q] * wq;
+    for (int q = 0; q < shares; ++q) {
+        const float* p = base + (int64_t)q * 16 * ATTN_SHARE;
+        const float4 u = *reinterpret_cast<const float4*>(p + c0), v = *reinterpret_cast<const float4*>(p + c0 + 4);
+        const float wq = __expf(p[128] - M);
+        L += p[129] * wq;
         o[0] += u.x * wq; o[1] += u.y * wq; o[2] += u.z * wq; o[3] += u.w * wq;
         o[4] += v.x * wq; o[5] += v.y * wq; o[6] += v.z * wq; o[7] += v.w * wq;
     }
@@ -2033,6 +2038,10 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     bf16_t* act = b->wsp<bf16_t>(b->W.act);
     KvView view = make_view(m, kv, layer, b);
     const CtxTiles ctx = ctx_tiles(c, b);
+    // most workgroups per (row, kv head) of the decode attention (attn_shares)
+    const int pairs = c.n_kv_heads * B;
+    int most = pairs >= 512 ? 1 : std::min({16, (1024 + pairs - 1) / pairs, std::max(1, kv->max_cap / 256)});
+    while (most > 1 && (size_t)b->Mpad * c.n_kv_heads * most * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --most;
 
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
@@ -2057,24 +2066,15 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
                            ctx.C ? b->wsp<int32_t>(b->W.attn_order) : nullptr, ctx.C ? nullptr : b->wsp<AttnJob>(b->W.attn_order),
-                           ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * (qkv_n - qkv_from), b->wsp<float>(b->W.gemm_part),
+                           most, ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * (qkv_n - qkv_from), b->wsp<float>(b->W.gemm_part),
                            qkv_n - qkv_from, qkv_from);
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
-        // few (row, kv head) pairs: also split the positions, to at most the 512 workgroups that run at a time (two
-        // per CU) and 16 shares, and no further than two groups of 32 positions per wave of the longest row.
-        // Attention with its merge: 16 rows of the 70B shape 37 us at twice the workgroups, 32 at 512; 48 rows
-        // 64 -> 57 (no merge); 20 rows of 4 kv heads 31 -> 23; 37 rows of 2 kv heads, up to 900 positions: 21 with
-        // one group per wave and 1024 workgroups, 18 with 512, 16 with two groups.
-        int pairs = c.n_kv_heads * B;
-        int n_splits = std::min({std::max(1, 512 / pairs), 16, std::max(1, kv->max_cap / 256)});
-        while (n_splits > 1 && (size_t)b->Mpad * c.n_kv_heads * n_splits * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --n_splits;
         // context pass: 16 / G entries per workgroup, which share the K/V stream where they sit in the same cache row
         const int G = c.n_q_heads / c.n_kv_heads;
-        const bool pair = b->kv_seq != nullptr && n_splits == 1 && 2 * G <= 16;
+        const bool pair = b->kv_seq != nullptr && pairs >= 512 && 2 * G <= 16;
         if (ctx.C) {
-            n_splits = 1;
             auto kern = ctx.C == 2 ? k_bf16_attn_ctx<2> : k_bf16_attn_ctx<1>;
             hipLaunchKernelGGL(kern, dim3(c.n_kv_heads, ctx.tiles * 4 * ctx.C), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
@@ -2084,12 +2084,12 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
                                qd / 16, 1, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
         else
-            hipLaunchKernelGGL(k_bf16_attn<false>, dim3(c.n_kv_heads, B, n_splits), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
+            hipLaunchKernelGGL(k_bf16_attn<false>, dim3(c.n_kv_heads, B, most), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
-                               qd / 16, n_splits, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
-        if (n_splits > 1)
+                               qd / 16, most, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
+        if (most > 1 && ctx.C == 0)
             hipLaunchKernelGGL(k_bf16_attn_merge, dim3(c.n_kv_heads, B), dim3(256), 0, s, b->wsp<float>(b->W.attn_part),
-                               c.n_q_heads, c.n_kv_heads, n_splits, n_ptr, B, ao, qd / 16);
+                               c.n_q_heads, c.n_kv_heads, most, b->wsp<AttnJob>(b->W.attn_order), n_ptr, B, ao, qd / 16);
     }
     EpiArgs e2{};
     e2.out = h; e2.ldo = d; e2.idx = idx;
@@ -2178,7 +2178,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(0, c.n_kv_heads, B * nl), nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, (int64_t)0, kvb, kv_n, kv_n);
+                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, 1, (int64_t)0, kvb, kv_n, kv_n);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }

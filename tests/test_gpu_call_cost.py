@@ -83,3 +83,22 @@ def test_qkv_does_not_rise_below_2048_entries(shape):
     t = {n: _time(_context_call(m, n, [n], 0), QKV) for n in (1600, 2048)}
     print(f"[case] q|k|v, {shape}: {t[1600]:.1f} us for 1600 entries, {t[2048]:.1f} for 2048", flush=True)
     assert t[1600] <= 1.15 * t[2048]
+
+
+def _layer_call(m, batch, live, positions):
+    kv, b = S.KVCache(m, 1, [4096] * batch), S.Batch(m, batch)
+    kv.pool.view(torch.bfloat16).normal_()
+    b.reset(np.zeros(batch, np.int32), np.full(batch, positions - 1), None)
+    b.begin_step()
+    b.field("n_active").fill_(live)
+    return lambda: capi.check(S.layer_forward(m, 1, kv, b))
+
+
+@pytest.mark.parametrize("live,positions", [(1, 3900), (2, 3900)])
+def test_attention_of_the_rows_that_are_left(live, positions):
+    """rows that have left no longer count when the positions of the others are shared out"""
+    m = _model("70b")
+    small = _time(_layer_call(m, live, live, positions), ATTENTION)
+    large = _time(_layer_call(m, 16, live, positions), ATTENTION)
+    print(f"[case] attention of {live} rows: {small:.1f} us, as what is left of 16: {large:.1f}", flush=True)
+    assert large <= 1.4 * small

@@ -87,3 +87,36 @@ def test_skipped_layers_of_few_rows(layers, rows):
             for got, want in ((K[:, pos[r]], k[r]), (V[:, pos[r]], v[r])):
                 err = np.abs(got - want.numpy()).max() / np.abs(want.numpy()).max()
                 assert err <= 1e-2, (l, r, err)              # one bf16 rounding, as for every cache entry
+
+
+# 16 rows of 8 kv heads: up to 8 shares.  Rows of one to eleven groups of 256 positions beside each other, all live (4
+# shares), 6 (8 by the live pairs), one; 74 pairs of 2 kv heads; 40 rows of 8 (320 pairs: 2 shares)
+@pytest.mark.parametrize("rows,hq,hkv,live", [(16, 64, 8, 16), (16, 64, 8, 6), (16, 64, 8, 1), (37, 4, 2, 37), (40, 64, 8, 40),
+                                              (12, 32, 32, 12)])
+def test_shared_positions_against_unshared(rows, hq, hkv, live):
+    """the same rows in a batch whose capacity leaves every row to one workgroup: other sums only"""
+    print(f"[case] shares: {live} of {rows} rows, {hq}/{hkv} heads", flush=True)
+    gen = torch.Generator().manual_seed(9)
+    d = 512
+    rnd = lambda *shape: (torch.randn(*shape, generator=gen) * 0.02).bfloat16()      # noqa: E731
+    m = S.Model(n_layers=1, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ffn=64, vocab=64, dtype="bf16",
+                exit_layers=[1], max_pos=4096)
+    one = torch.ones(d)
+    m.set_layer(1, g_attn=one, W_qkv=rnd((hq + 2 * hkv) * 128, d), W_o=rnd(d, hq * 128), g_ffn=one, W_gate=rnd(64, d),
+                W_up=rnd(64, d), W_down=rnd(d, 64))
+    m.set_embed(rnd(64, d))
+    lengths = [(1, 31, 256, 511, 512, 513, 900, 1100, 1280, 1535, 2047, 2815)[r % 12] for r in range(rows)]
+    out = []
+    for B in (rows, (512 + hkv - 1) // hkv):
+        kv, b = S.KVCache(m, 1, [(x + 32) // 32 * 32 for x in lengths] + [32] * (B - rows)), S.Batch(m, B)
+        kv.pool.view(torch.bfloat16).normal_(0.0, 1.0, generator=torch.Generator(device="cuda").manual_seed(3))
+        b.reset(np.arange(B) % 64, np.array(lengths + [0] * (B - rows), np.int32), None)
+        b.begin_step()
+        b.field("n_active").fill_(live)
+        before = b.field("h")[:live].cpu().numpy().copy()
+        # the pool's layout goes by the capacities of the rows before: the first rows are the same in both
+        assert S.layer_forward(m, 1, kv, b) == 0
+        out.append(b.field("h")[:live].cpu().numpy() - before)
+    assert np.isfinite(out[0]).all()
+    worst, ok = rows_close(out[0], out[1], TOL["bf16"])
+    assert ok, worst
