@@ -1832,12 +1832,21 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     // One product at a time: the tile kernels at every batch size (at 1 to 32 rows, measured on the
     // 70B shapes against the weight-streaming kernel plus the normalisation launch that the finish of
     // a sliced product saves: QKV 36 against 46 us, O 34 against 37, down 84 against 87, exit head 94
-    // against 95-100, and 99 against 149 at 64 rows).  Several layers in one launch (K/V of skipped layers)
-    // are not sliced: up to 128 rows the tile kernel needs the 256-column tiles of all layers to fill the
-    // chip (rule `wide` below).  Seven layers of the 7B shape (224 tiles): 17 rows 73 against 83 us, 40 rows
-    // 74 against 102; three layers of the 70B shape (48 tiles of 128): 64 rows 67 against 29 us, 100 rows 72
-    // against 63.
-    if (nz > 1 && B <= 128 && !(N % 256 == 0 && N / 256 * nz >= 200)) return false;
+    // against 95-100, and 99 against 149 at 64 rows).
+    if (nz > 1) {
+        // Several layers in one launch (K/V of skipped layers) are not sliced.  The whole fill, streaming / tile
+        // kernel: up to 64 rows the tile kernel needs the 256-column tiles of all layers (rule `wide` below) to fill
+        // the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape (224 tiles) 1 row
+        // 90 / 79 us, 40 rows 144 / 94; nine (288, two rounds) 1 row 109 / 134, 40 rows 175 / 153; 40 layers of the
+        // 70B shape (320) 1 row 240 / 274, 16 rows 254 / 285, 40 rows 376 / 316.  From 65
+        // rows on the streaming kernel stays where the tiles are few: three layers of the 70B shape (48 tiles of
+        // 128) 40 of 65 rows 70 / 81, 128 rows 94 / 91; eight (128 tiles) 128 rows 112 / 103, ten 188 / 113; three
+        // layers of the 7B shape (192 tiles) 40 of 65 rows 76 / 52.
+        const int wide_tiles = N % 256 == 0 ? N / 256 * nz : 0;
+        const float fill = (float)wide_tiles / (float)((wide_tiles + 255) / 256 * 256);
+        if (B <= 64 && (wide_tiles < 200 || (B <= 32 && fill < 0.75f))) return false;
+        if (B > 64 && B <= 128 && N / 128 * nz <= 64) return false;
+    }
     int row_groups = (B + 255) / 256;
     int Mpad = (B + 31) / 32 * 32;
     int KS = K / 32;

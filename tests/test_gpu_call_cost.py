@@ -102,3 +102,34 @@ def test_attention_of_the_rows_that_are_left(live, positions):
     large = _time(_layer_call(m, 16, live, positions), ATTENTION)
     print(f"[case] attention of {live} rows: {small:.1f} us, as what is left of 16: {large:.1f}", flush=True)
     assert large <= 1.4 * small
+
+
+FILL = 1 << capi.KERNEL_CLASSES.index("fill_kv")
+
+
+def _fill_call(m, rows, left, layers):
+    kv, b = S.KVCache(m, layers + 1, [64] * rows), S.Batch(m, rows)
+    b.reset(np.zeros(rows, np.int32), np.arange(rows) % 60, None)
+    b.begin_step()
+    b.field("exited_idx").copy_(torch.arange(rows, dtype=torch.int32))
+    b.field("n_exited").fill_(left)
+    return lambda: capi.check(S.fill_skipped_kv(m, 1, layers + 1, kv, b))
+
+
+# 160 tiles of 128 columns and 192: more than the streaming kernel runs at a time with 65 rows and more
+@pytest.mark.parametrize("shape,layers,rows,left", [("70b", 10, 128, 128), ("7b", 3, 65, 40), ("7b", 6, 128, 30)])
+def test_fill_just_above_64_rows(shape, layers, rows, left):
+    """129 rows run on the tile kernel whatever the number of layers"""
+    m = _model(shape, layers + 1)
+    few = _time(_fill_call(m, rows, left, layers), FILL)
+    more = _time(_fill_call(m, 129, left, layers), FILL)
+    print(f"[case] fill of {layers} layers, {left} rows: {few:.1f} us in a batch of {rows}, {more:.1f} in one of 129", flush=True)
+    assert few <= 1.15 * more
+
+
+def test_fill_of_layers_that_spill_into_a_second_round():
+    """40 layers of the 70B shape are 320 tiles; one row of them costs no more than twice 20 layers"""
+    m = _model("70b", 41)
+    t = {n: _time(_fill_call(m, 16, 1, n), FILL) for n in (20, 40)}
+    print(f"[case] fill of one row: 20 layers {t[20]:.1f} us, 40 layers {t[40]:.1f}", flush=True)
+    assert t[40] <= 1.95 * t[20]

@@ -47,13 +47,13 @@ def test_qkv_of_a_context_pass_in_one_and_two_launches(n, hq, hkv):
             assert ok, f"cache row {r}: worst cache error {worst:.2e}"
 
 
-# 32 tiles of 256 per layer: 7 layers are 224 tiles (tile kernel from the first row on), 6 are 192 (streaming kernel
-# up to 128 rows, 128-column tiles above)
-@pytest.mark.parametrize("layers", [7, 8])
+# 32 tiles of 256 columns per layer: 7 layers are 224 (tile kernel from the first row on), 6 are 192 (streaming kernel up
+# to 64 rows), 10 are 320 (streaming up to 32 rows); of 8 kv heads 3 layers are 48 tiles of 128 (streaming up to 128 rows)
+@pytest.mark.parametrize("layers,hkv", [(7, 32), (8, 32), (11, 32), (4, 8)])
 @pytest.mark.parametrize("rows", [1, 33, 64, 65, 129])
-def test_skipped_layers_of_few_rows(layers, rows):
-    print(f"[case] fill of {layers - 1} layers, {rows} rows", flush=True)
-    d, hkv, hd = 256, 32, 128
+def test_skipped_layers_of_few_rows(layers, hkv, rows):
+    print(f"[case] fill of {layers - 1} layers, {hkv} kv heads, {rows} rows", flush=True)
+    d, hd = 256, 128
     gen = torch.Generator().manual_seed(rows * 100 + layers)
     rnd = lambda *shape, std=0.02: (torch.randn(*shape, generator=gen) * std).bfloat16()      # noqa: E731
     m = S.Model(n_layers=layers, d_model=d, n_q_heads=hkv, n_kv_heads=hkv, head_dim=hd, d_ffn=64, vocab=64, dtype="bf16",
