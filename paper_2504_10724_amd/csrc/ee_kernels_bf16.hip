@@ -1065,12 +1065,6 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
         }
         return v;
     };
-    auto rd1 = [&](int x) -> float {
-        if (x < from) return r0[x];
-        float v = rp[x];
-        for (int q = 1; q < splits; ++q) v += rp[x + (int64_t)q * plane];
-        return v;
-    };
     auto pack4 = [](float a, float b, float c, float d) -> uint2 { return make_uint2(pack2(a, b), pack2(c, d)); };
     const float* cs = rope + (int64_t)p * half * 2;
     // The work of a row, in items of four rotation pairs (q, k) or four values (v), is dealt out over
@@ -1116,11 +1110,21 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
         } else {
             const int u = t - nq4 - nk4;
             const int f0 = (u >> 6) * 256 + (u & 63);
+            // the four values of a plane are asked for together (value by value, each through its planes, 20 rows of
+            // 4 kv heads in four slices took 9.7 us between events instead of 7.8); past the last value the last one is read again
             float v[4];
+            int x[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int f = f0 + 64 * k;
-                v[k] = f < Hkv * hd ? rd1(vin + f) : 0.f;
+                x[k] = vin + min(f0 + 64 * k, Hkv * hd - 1);
+                v[k] = x[k] < from ? r0[x[k]] : rp[x[k]];
+            }
+            for (int q = 1; q < splits; ++q) {
+                float u[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) u[k] = x[k] < from ? 0.f : rp[x[k] + (int64_t)q * plane];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = x[k] < from ? v[k] : v[k] + u[k];
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
