@@ -247,7 +247,7 @@ int ee_exit_head(const ee_model* m, int exit_idx, float threshold, int force_exi
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same
  * results (bit for bit) and same outputs in the batch state as ee_exit_head without the debug
  * pointer, but what that call keeps in the batch's workspace (normalised operand rows, per-tile
- * softmax statistics, for EE_F32 also the logits) goes to a device array of EE_STATIC_SCRATCH_BYTES
+ * softmax statistics, for EE_F32 the logits instead) goes to a device array of EE_STATIC_SCRATCH_BYTES
  * that the library holds on every GPU it runs on until the process ends.  The call allocates
  * nothing and frees nothing (its first call on a device looks the array's address up); the
  * batch's own workspace is not touched.  Nothing in the array has to start at zero: every value

@@ -383,18 +383,19 @@ static void lay_workspace(const ee_model* m, int B, WsLayout* W) {
         W->gone_idx = take(Mpad * 4);
         W->n_gone = take(4);
     } else {
-        size_t wide = (size_t)c.vocab > 2 * (size_t)c.d_ffn ? (size_t)c.vocab : 2 * (size_t)c.d_ffn;
-        W->x = take(Mpad * c.d_model * 4);
+        // norms, SwiGLU and the exit decision happen inside the products and their epilogues: no operand rows, no
+        // gate/up matrix, no row statistics
+        W->x = take(0);
         W->qkv = take(Mpad * qkv * 4);
         W->q_hi = take(0);
         W->q_lo = take(0);
         W->ao = take(Mpad * qd * 4);
         W->act = take(Mpad * c.d_ffn * 4);
-        W->part_max = take(Mpad * 4);
-        W->part_sum = take(Mpad * 4);
-        W->part_arg = take(Mpad * 4);
-        W->logits = take(Mpad * wide * 4);
-        W->fill_x = take(Mpad * c.d_model * 4);
+        W->part_max = take(0);
+        W->part_sum = take(0);
+        W->part_arg = take(0);
+        W->logits = take(Mpad * c.vocab * 4);
+        W->fill_x = take(0);
         W->fill_kv = take(Mpad * kvn * 4);
         W->gemm_part_bytes = 0; W->gemm_part = take(0);
         W->attn_part_bytes = 0; W->attn_part = take(0);

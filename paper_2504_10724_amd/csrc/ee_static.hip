@@ -2,7 +2,7 @@
 // memory and bring no workspace (code under HIP graph capture, tight serving loops, harnesses
 // that forbid hipMalloc).  Same kernels as ee_exit_head; what that call keeps in the batch's
 // workspace (the normalised operand rows and the per-tile softmax statistics, for fp32 models
-// also the logits) lives here in a device array of the library's own, one copy per GPU.
+// the logits instead) lives here in a device array of the library's own, one copy per GPU.
 #include "ee_internal.h"
 
 #include <mutex>
@@ -47,8 +47,8 @@ extern "C" int ee_exit_head_static(const ee_model* m, int exit_idx, float thresh
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     const size_t Mpad = (size_t)b->Mpad;
-    const size_t n_part = bf16 ? (size_t)c.vocab / 32 : 1;
-    t.W.x = take(Mpad * c.d_model * (bf16 ? 2 : 4));
+    const size_t n_part = bf16 ? (size_t)c.vocab / 32 : 0;
+    t.W.x = take(bf16 ? Mpad * c.d_model * 2 : 0);
     t.W.part_max = take(Mpad * n_part * 4);
     t.W.part_sum = take(Mpad * n_part * 4);
     t.W.part_arg = take(Mpad * n_part * 4);

@@ -86,3 +86,27 @@ def test_static_exit_head_rejects_what_does_not_fit_and_bad_arguments():
     assert S.exit_head_static(m, 1, 0.5, 0, b) == ee.EE_ERR_EXIT_NOT_RESIDENT
     assert S.exit_head_static(m, 0, float("nan"), 0, b) == ee.EE_ERR_INVALID_ARG
     assert S.exit_head_static(m, 7, 0.5, 0, b) == ee.EE_ERR_INVALID_ARG
+
+
+def test_f32_scratch_holds_what_the_kernels_use_and_no_more():
+    """fp32: the logits are the only scratch of an exit head, so 1024 rows of 4000 logits (15.6 MiB) fit the array of
+    16 MiB whatever d is; the workspace holds q|k|v, attention rows, FFN rows, logits, K/V of the fill and three lists"""
+    print("[case] fp32 scratch", flush=True)
+    s = TINY.with_(name="f32_scratch", d_model=256, vocab=4000, batch=1024, exit_layers=(1,), thresholds=(0.0,))
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    m = S.Model.from_shape(s, max_pos=64)
+    m.set_exit_device(0, torch.ones(s.d_model, device="cuda"), torch.randn(s.vocab, s.d_model, device="cuda", generator=gen))
+    m.set_embed(torch.randn(s.vocab, s.d_model, device="cuda", generator=gen))
+    b = S.Batch(m, s.batch)
+    b.reset(np.arange(s.batch), np.zeros(s.batch, np.int32), None)
+    b.begin_step()
+    assert S.exit_head(m, 0, 0.5, 0, b) == 0
+    want = {k: b.field(k).cpu().clone() for k in HEAD}
+    for k in HEAD:
+        b.field(k).zero_()
+    assert S.exit_head_static(m, 0, 0.5, 0, b) == 0
+    for k in HEAD:
+        assert torch.equal(b.field(k).cpu(), want[k]), k
+    qd, kvd, rows = s.n_q_heads * s.head_dim, s.n_kv_heads * s.head_dim, s.batch
+    parts = [rows * 4 * x for x in (qd + 2 * kvd, qd, s.d_ffn, s.vocab, 2 * kvd, 1, 1)] + [4]
+    assert m.lib.ee_workspace_bytes(m.h, rows) == sum((x + 255) // 256 * 256 for x in parts)
