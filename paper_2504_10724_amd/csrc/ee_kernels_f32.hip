@@ -287,16 +287,19 @@ k_f32_exit_decide(const float* __restrict__ logits, int V, const int32_t* __rest
     int n = min(*n_ptr, B);
     if (i >= n) return;
     const float* z = logits + (int64_t)i * V;
-    // Maximum and column as stat_merge takes them: a logit that is NaN is never the maximum (fmaxf), and the row's
-    // token is the largest of the others; the sum below is NaN then, and the row meets no threshold.
+    // Maximum and column as stat_merge takes them: a logit that is NaN is never the maximum, and the row's token is
+    // the largest of the others (none: the lowest column); the sum below is NaN then, and the row meets no threshold.
     float m = -FLT_MAX;
-    int a = 0x7fffffff;
+    int a = threadIdx.x < V ? threadIdx.x : 0x7fffffff;
     auto take = [&](float m2, int a2) {
         a = m > m2 ? a : (m2 > m ? a2 : min(a, a2));
         m = fmaxf(m, m2);
     };
 #pragma unroll 4
-    for (int j = threadIdx.x; j < V; j += 256) take(z[j], j);
+    for (int j = threadIdx.x; j < V; j += 256) {
+        const float v = z[j];
+        if (v > m) { m = v; a = j; }                          // rising j: > keeps the lowest column
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const float m2 = __shfl_xor(m, o, 64);
