@@ -1386,8 +1386,8 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
 // and P V take the same operands as above (queries and probabilities as bf16 pairs hi + lo).  Exponentials
 // are base 2 with the scale folded in, and a column's running maximum is only raised (and its sums rescaled)
 // when it grows by more than 2^8, which leaves the sums in fp32 range and the result unchanged.
-// Measured (70B shape, 1999 entries of three contexts of 1400 to 2200 positions): 585 -> 275 us, at 2 us of
-// MFMAs in 4.3 us per stage and pair of waves; what is left is the softmax arithmetic, which the other wave
+// Measured (70B shape, 1999 entries of three contexts of 1400 to 2200 positions): 585 -> 275 to 355 us, machine to
+// machine, at 2 us of MFMAs in 4.3 us per stage and pair of waves; what is left is the softmax arithmetic, which the other wave
 // of the SIMD covers in part, at the 1.65 GHz the power limit leaves beside the products of the layer.  7B
 // shape, 1024 entries of four prompts (C = 1): 73 -> 35 us.  All eight K reads of a group are asked for
 // before its first MFMA and the V reads before the softmax; with a read in front of each product C = 2 took
@@ -1976,8 +1976,8 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
 
 // How the attention of a context pass is tiled: C 16-column blocks per wave (0: not tiled), entries per tile.
 // Two blocks per wave read each K and V operand from LDS half as often, one block gives twice the
-// workgroups: two where that still leaves two workgroups per CU (70B shape, 1999 entries: 275 us against 310
-// with one), one from one workgroup per CU on (256 entries, 1500 cached: layer 558 -> 539 us; 600 entries of
+// workgroups: two where that still leaves two workgroups per CU (70B shape, 1999 entries, one machine: 275 us against
+// 310 with one), one from one workgroup per CU on (256 entries, 1500 cached: layer 558 -> 539 us; 600 entries of
 // four contexts: 1284 -> 1239 us).  Below that the kernel that splits a row's positions over its waves stays.
 // What counts is the entries of the call, not the batch's capacity: 64 entries at positions from 1936 on take 41 us
 // in a batch of 2048 (79 as four tiles of 16, 32 workgroups), 100 of two contexts of 3000 in a batch of 1024 61 (197).
