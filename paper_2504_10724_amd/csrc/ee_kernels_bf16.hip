@@ -975,6 +975,133 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     else cols_wave<EPI, NT, 1>(c, 2 * (NT - 4) + (wn - (NT - 4)), ep);
 }
 
+// ------------------------------------------------------------------ few rows: each wave streams on its own
+// Products of at most 64 rows are a stream of weights, and what the tile kernels above lose there is depth: their
+// stages are shared by the waves of a workgroup, so each ends in a barrier, and with room for 256 rows in a stage
+// three of them (30 KiB at 32 rows) are on their way at a time, while a CU can keep more.  Here nothing is shared:
+// wave w of a workgroup takes the K tiles 4 i + w of the workgroup's K slice (so that all waves of a launch walk K
+// together), with the NS tile-rows of W and the MS row tiles of X of each in a ring of its own, filled by LDS-DMA
+// loads up to D tiles ahead and waited for by the wave's own load counter; the four partial sums are added in wave
+// order through LDS at the end.  Two workgroups fit on a CU.  Of an X tile only the 8-row pieces (whole lines)
+// that hold live rows are fetched; the rest of its slot keeps what was there, and reaches only results that
+// are not written.  K is a multiple of 64, the last workgroup of a slice re-reads its last tile-row in place of
+// missing ones.
+constexpr int few_depth(int MS, int NS) { return 80 / (4 * (MS + NS)); }     // ring of a wave: at most 20 KiB
+
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// the wait before a wave's last tiles: `left` more of L loads each may be under way (left < D)
+template <int L, int D>
+__device__ __forceinline__ void wait_tail(int left) {
+    if constexpr (D > 1) {
+        if (left >= D - 1) { wait_loads<(D - 1) * L>(); return; }
+        wait_tail<L, D - 1>(left);
+    } else {
+        wait_loads<0>();
+    }
+}
+
+template <int MS, int NS, int EPI>
+__global__ void __launch_bounds__(256, 2)
+k_bf16_gemm_few(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, int NBs, int nb_off, int NB_total, int splits,
+                const int32_t* __restrict__ n_ptr, int B, float* __restrict__ partial, int64_t part_plane, int part_ld, EpiArgs ep,
+                ZBatch zb) {
+    constexpr int T = NS + MS, D = few_depth(MS, NS);
+    __shared__ uint4 lds[4 * D * T * 64];
+    static_assert(4 * D * T >= 16 * NS, "the partial sums of a row tile share the rings");
+    const int n = min(*n_ptr, B);
+    if (n <= 0) return;
+    if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
+    Xp += (int64_t)blockIdx.z * zb.x_stride;
+    ep.out += (int64_t)blockIdx.z * zb.out_stride;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = blockIdx.x / splits, sp = blockIdx.x % splits;
+    const int nb0 = tile * NS, nt_live = min(NS, NB_total - nb0);
+    const int quads = KB >> 2;                               // a step of the workgroup: one K tile per wave
+    const int q_lo = (int)((int64_t)quads * sp / splits), S = (int)((int64_t)quads * (sp + 1) / splits) - q_lo;
+    const unsigned lane_bytes = (unsigned)lane * 16u, ring = (unsigned)(size_t)&lds[wave * D * T * 64];
+    const uint4* wp = Wp + ((int64_t)(4 * q_lo + wave) * NBs + nb_off + nb0) * 64;   // tile (r, c) of W sits at slot c * NBs + r
+    const uint4* xp = Xp + (int64_t)(4 * q_lo + wave) * 64;
+    unsigned wv[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) wv[j] = lane_bytes + ((unsigned)min(j, nt_live - 1) << 10);
+
+    floatx16 acc[MS][NS];
+#pragma unroll
+    for (int m = 0; m < MS; ++m)
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][j][r] = 0.f;
+
+    auto stream = [&](auto live_) {                          // live_: row tiles that hold rows
+        constexpr int ML = decltype(live_)::value, L = NS + ML;
+        auto issue = [&](int slot) {
+            const unsigned at = ring + (unsigned)(slot * T << 10);
+#pragma unroll
+            for (int j = 0; j < NS; ++j) dma_tile<true>(wp, wv[j], at + (unsigned)(j << 10));
+#pragma unroll
+            for (int m = 0; m < ML; ++m)
+                if ((lane & 31) < ((n - 32 * m + 7) & ~7))   // lanes of the first eight rows always: the load is counted
+                    dma_tile(xp, lane_bytes + ((unsigned)(m * KB) << 10), at + (unsigned)((NS + m) << 10));
+            wp += (int64_t)4 * NBs * 64;
+            xp += 4 * 64;
+        };
+        for (int i = 0; i < min(D, S); ++i) issue(i);
+        int slot = 0;
+        for (int s = 0; s < S; ++s) {
+            if (s + D <= S) wait_loads<(D - 1) * L>();
+            else wait_tail<L, D>(S - 1 - s);
+            const uint4* t = &lds[(wave * D + slot) * T * 64 + lane];
+            uint4 w[NS], x[ML];
+#pragma unroll
+            for (int j = 0; j < NS; ++j) w[j] = t[j * 64];
+#pragma unroll
+            for (int m = 0; m < ML; ++m) x[m] = t[(NS + m) * 64];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the slot is filled again
+            if (s + D < S) issue(slot);
+#pragma unroll
+            for (int m = 0; m < ML; ++m)
+#pragma unroll
+                for (int j = 0; j < NS; ++j) acc[m][j] = tile_mfma<EPI>(x[m], w[j], acc[m][j]);
+            slot = slot + 1 == D ? 0 : slot + 1;
+        }
+    };
+    if (MS == 1 || n > 32 * (MS - 1)) stream(std::integral_constant<int, MS>{});
+    else stream(std::integral_constant<int, 1>{});
+    float* red = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int m = 0; m < MS; ++m) {
+        if (32 * m >= n) break;
+        __syncthreads();                                     // the rings, or the row tile before, have been read
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[((wave * NS + j) * 16 + r) * 64 + lane] = acc[m][j][r];
+        __syncthreads();
+        if (wave < nt_live) {                                // tile-row `wave`
+            floatx16 v;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float s = red[(wave * 16 + r) * 64 + lane];
+#pragma unroll
+                for (int k = 1; k < 4; ++k) s += red[((k * NS + wave) * 16 + r) * 64 + lane];
+                v[r] = s;
+            }
+            if (splits > 1) {
+                EpiArgs pe = ep;
+                pe.out = partial + (int64_t)sp * part_plane;
+                pe.ldo = part_ld;
+                epilogue_one<EPI_STORE>(pe, v, 32 * m, n, nb0 + wave, lane);
+            } else {
+                epilogue_one<EPI>(ep, v, 32 * m, n, nb0 + wave, lane);
+            }
+        }
+    }
+}
+
 // What a workgroup of the decode attention has to know before its first load from the cache.  The RoPE kernel
 // leaves one per list entry, in launch order, so that the attention kernel starts with a single load instead of
 // the chain order -> row -> position -> cache row -> capacity, offset (each a trip to memory).
@@ -1815,6 +1942,32 @@ k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, in
     if (gain != nullptr) rmsnorm_row(hrow, gain, eps, N, xout, i, red);   // reads back this thread's own chunks
 }
 
+// Tile-rows per workgroup (NS) and K slices of k_bf16_gemm_few: the pair with the shortest estimate.  Workgroups are
+// taken in rounds of one per CU; a round lasts as long as its slowest bound, softened (4-norm), of what a CU gets at most
+// (50 GB/s, weights and live lines of X), memory (6.3 TB/s of weights) and both kinds over all CUs (15 TB/s).  The constants
+// are fitted to products of four shapes at 1, 16 and 48 rows, each with NS 1 .. 4 and 1 .. 16 slices: of the 48, the pair
+// chosen is on average 0.7 % and at most 4 % above the best one (q|k|v of the 70B shape, 1 row: 30.9 us with 3 and two
+// slices; 40.3 with 1 and one, 47.6 with 4 and one).  A slice keeps 32 K tiles, eight per wave.
+struct FewShape { int NS = 4, splits = 1; };
+static FewShape few_shape(int tile_rows, int KB, int rows, int nz, int max_splits) {
+    const int quads = KB / 4;
+    const float x_kib = (rows + 7) / 8 * 0.25f;              // KiB of X per K tile
+    FewShape best;
+    float best_t = 1e30f;
+    for (int NS = 1; NS <= 4; ++NS)
+        for (int sp = 1; sp <= max_splits && (sp == 1 || quads / sp >= 8); ++sp) {
+            const float steps = 4.0f * ((quads + sp - 1) / sp), w = steps * NS, wx = w + steps * x_kib;    // KiB of a workgroup
+            float t = 0.3f * sp + (sp > 1 ? sp * rows * tile_rows * (32 * 8) / 4.0e6f : 0.f);              // us
+            int left = (tile_rows + NS - 1) / NS * sp * nz;
+            for (int round = 0; left > 0; ++round, left -= 256) {
+                const float c = (float)std::min(left, 256), a = wx / 50.f, m = c * w / 6300.f, x = c * wx / 15000.f;
+                t += std::sqrt(std::sqrt(a * a * a * a + m * m * m * m + x * x * x * x)) + (round >= 2 ? 1.f : 0.f);
+            }
+            if (t < best_t) { best_t = t; best = FewShape{NS, sp}; }
+        }
+    return best;
+}
+
 // what the caller wants done with the K-slice planes of a product
 struct SliceTail {
     const float* norm_gain = nullptr;   // RESID: also normalise the updated rows with this gain ...
@@ -1826,23 +1979,78 @@ struct SliceTail {
     int*         from_out = nullptr;    // ... and the first column that is in planes (those before it are in out)
 };
 
+// the launch that adds the K-slice planes of a product, where there are any and the caller does not do it itself
+template <int EPI>
+static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n_ptr, int B, const EpiArgs& ep, hipStream_t s,
+                          const SliceTail& tail) {
+    if (tail.splits_out) *tail.splits_out = splits;
+    if (splits == 1) return;
+    const int64_t plane = (int64_t)((B + 31) / 32 * 32) * N;
+    if (EPI == EPI_RESID) {
+        hipLaunchKernelGGL(k_splitk_resid_norm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->wsp<float>(b->W.gemm_part),
+                           plane, N, splits, N, n_ptr, B, entry_near(B), ep.out, ep.ldo, ep.idx, tail.norm_gain, tail.eps, tail.norm_out);
+        if (tail.norm_gain && tail.norm_done) *tail.norm_done = true;
+    } else if (!tail.defer_store) {
+        hipLaunchKernelGGL((k_splitk_finish<EPI_STORE>), dim3((N / 4 + 255) / 256, B), dim3(256), 0, s,
+                           b->wsp<float>(b->W.gemm_part), plane, N, splits, N, n_ptr, B, ep);
+    }
+}
+
+// Whether a product takes k_bf16_gemm_few: up to 64 rows, from 4 MiB of weights on (32 MiB over several layers; below,
+// launches wait for memory once or twice whatever the kernel: O of a 576-wide model 6.7 us on the weight-streaming kernel
+// and its norm 3.3, 9.5 here; two layers of 4 MiB 17.1 and 17.6).  Where the 256-column tiles fill their rounds to 80 %
+// gate/up and the K/V of several layers stay with them: they read X once per 256 columns (gate/up of the 70B shape, 224
+// workgroups, 48 rows 143 us, 149 here, 16 rows 141 and 142; 34B 230 of 192 columns, 115 and 117; seven layers of the 7B
+// shape for 64 rows 95 and 99).  Elsewhere, tile kernels with the streaming kernel / this one, whole launches with the
+// finish: 7B shape 16 rows q|k|v 25.1 / 21.6 us, O 17.4 / 15.3, gate/up 39.8 / 31.2 (172 workgroups / 230), down 25.1 / 22.7;
+// 2048-wide model gate/up 22.6 / 13.5; 70B shape 16 rows q|k|v 33.8 / 30.9, O 34.1 / 30.4, down 82.3 / 76.9; exit head of the 7B
+// shape 1 row 44 / 43, of the 70B shape 64 rows 89 / 86; K/V of five layers of the 7B shape 64 rows 93 / 76.
+template <int EPI>
+static bool few_rows(int N, int K, int rows, int nz) {
+    if (rows > 64 || (int64_t)N * K * nz < ((int64_t)(nz > 1 ? 16 : 2) << 20)) return false;
+    if ((EPI != EPI_SWIGLU && nz == 1) || N % 256 != 0 || K % 128 != 0) return true;
+    const int wide = N / 256 * nz;
+    return (float)wide / (float)((wide + 255) / 256 * 256) < 0.8f;
+}
+
 // the 256-row tile kernels, 128 or 256 columns wide, K sliced so that about one workgroup per CU
 // runs; returns false where the weight-streaming kernel is the better choice
 template <int EPI>
 static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, int K, int NBs, int nb_off,
                      const int32_t* n_ptr, int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{},
                      int nz = 1, const SliceTail& tail = SliceTail{}) {
+    const int rows = b->n_entries > 0 ? b->n_entries : B;    // in a context pass what the call has, not what the batch could hold
+    if (few_rows<EPI>(N, K, rows, nz)) {
+        const int Mpad = (B + 31) / 32 * 32;
+        float* part = b->wsp<float>(b->W.gemm_part);
+        int most = 1;                                        // slices: only where somebody adds the planes
+        if (nz == 1 && (EPI == EPI_RESID || (EPI == EPI_STORE && tail.defer_store)))
+            most = (int)std::min<size_t>(16, b->W.gemm_part_bytes / ((size_t)Mpad * N * sizeof(float)));
+        const FewShape f = few_shape(N / 32, K / 16, rows, nz, most);
+        const dim3 grid((N / 32 + f.NS - 1) / f.NS * f.splits, 1, nz);
+        auto go = [&](auto ms_, auto ns_) {
+            hipLaunchKernelGGL((k_bf16_gemm_few<decltype(ms_)::value, decltype(ns_)::value, EPI>), grid, dim3(256), 0, s, (const uint4*)X,
+                               (const uint4*)W, K / 16, NBs, nb_off, N / 32, f.splits, n_ptr, B, part, (int64_t)Mpad * N, N, ep, zb);
+        };
+        auto go_ns = [&](auto ms_) {
+            if (f.NS == 4) go(ms_, std::integral_constant<int, 4>{});
+            else if (f.NS == 3) go(ms_, std::integral_constant<int, 3>{});
+            else if (f.NS == 2) go(ms_, std::integral_constant<int, 2>{});
+            else go(ms_, std::integral_constant<int, 1>{});
+        };
+        if (rows <= 32) go_ns(std::integral_constant<int, 1>{});
+        else go_ns(std::integral_constant<int, 2>{});
+        finish_slices<EPI>(b, N, f.splits, n_ptr, B, ep, s, tail);
+        if (tail.from_out) *tail.from_out = 0;
+        return true;
+    }
     if (N % 128 != 0 || K % 128 != 0) return false;
-    // One product at a time: the tile kernels at every batch size (at 1 to 32 rows, measured on the
-    // 70B shapes against the weight-streaming kernel plus the normalisation launch that the finish of
-    // a sliced product saves: QKV 36 against 46 us, O 34 against 37, down 84 against 87, exit head 94
-    // against 95-100, and 99 against 149 at 64 rows).
+    // One product at a time: the tile kernels at every batch size.
     if (nz > 1) {
         // Several layers in one launch (K/V of skipped layers) are not sliced.  The whole fill, streaming / tile
-        // kernel: up to 64 rows the tile kernel needs the 256-column tiles of all layers (rule `wide` below) to fill
-        // the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape (224 tiles) 1 row
-        // 90 / 79 us, 40 rows 144 / 94; nine (288, two rounds) 1 row 109 / 134, 40 rows 175 / 153; 40 layers of the
-        // 70B shape (320) 1 row 240 / 274, 16 rows 254 / 285, 40 rows 376 / 316.  From 65
+        // kernel: up to 64 rows (where few_rows leaves them) the tile kernel needs the 256-column tiles of all layers
+        // (rule `wide` below) to fill the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B
+        // shape (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.  From 65
         // rows on the streaming kernel stays where the tiles are few: three layers of the 70B shape (48 tiles of
         // 128) 40 of 65 rows 70 / 81, 128 rows 94 / 91; eight (128 tiles) 128 rows 112 / 103, ten 188 / 113; three
         // layers of the 7B shape (192 tiles) 40 of 65 rows 76 / 52.
@@ -1959,18 +2167,7 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         hipLaunchKernelGGL((k_bf16_gemm_dma2<EPI>), grid, dim3(BIG_THREADS), 0, s, (const uint4*)X, (const uint4*)W,
                            K / 16, NBs, nb_off, n_tiles, splits, n_ptr, B, b->wsp<float>(b->W.gemm_part),
                            (int64_t)Mpad * N, N, ep, zb);
-    if (tail.splits_out) *tail.splits_out = splits;
-    if (splits > 1) {
-        if (EPI == EPI_RESID) {
-            hipLaunchKernelGGL(k_splitk_resid_norm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->wsp<float>(b->W.gemm_part),
-                               (int64_t)Mpad * N, N, splits, N, n_ptr, B, entry_near(B), ep.out, ep.ldo, ep.idx, tail.norm_gain,
-                               tail.eps, tail.norm_out);
-            if (tail.norm_gain && tail.norm_done) *tail.norm_done = true;
-        } else if (!tail.defer_store) {
-            hipLaunchKernelGGL((k_splitk_finish<EPI_STORE>), dim3((N / 4 + 255) / 256, B), dim3(256), 0, s,
-                               b->wsp<float>(b->W.gemm_part), (int64_t)Mpad * N, N, splits, N, n_ptr, B, ep);
-        }
-    }
+    finish_slices<EPI>(b, N, splits, n_ptr, B, ep, s, tail);
     return true;
 }
 
@@ -2185,13 +2382,17 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     EpiArgs ep{};
     ep.out = kvb; ep.ldo = kv_n; ep.idx = idx;
     int NBs = (c.n_q_heads + 2 * c.n_kv_heads) * hd / 32, nb_off = c.n_q_heads * hd / 32;
-    if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl))
+    int splits = 1, from = 0;
+    SliceTail st;                                       // one layer's K-slice planes are added up by the append kernel
+    st.defer_store = nl == 1; st.splits_out = &splits; st.from_out = &from;
+    if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl, st))
         gemm<1, EPI_STORE>(x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl);
+    if (splits == 1) from = kv_n;                       // nothing is in planes
     const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(0, c.n_kv_heads, B * nl), nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, 1, (int64_t)0, kvb, kv_n, kv_n);
+                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, splits, (int64_t)b->Mpad * kv_n, b->wsp<float>(b->W.gemm_part), kv_n, from);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
