@@ -976,17 +976,17 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 }
 
 // ------------------------------------------------------------------ few rows: each wave streams on its own
-// Products of at most 64 rows are a stream of weights, and what the tile kernels above lose there is depth: their
+// Products of at most 128 rows are a stream of weights, and what the tile kernels above lose there is depth: their
 // stages are shared by the waves of a workgroup, so each ends in a barrier, and with room for 256 rows in a stage
 // three of them (30 KiB at 32 rows) are on their way at a time, while a CU can keep more.  Here nothing is shared:
 // wave w of a workgroup takes the K tiles 4 i + w of the workgroup's K slice (so that all waves of a launch walk K
 // together), with the NS tile-rows of W and the MS row tiles of X of each in a ring of its own, filled by LDS-DMA
 // loads up to D tiles ahead and waited for by the wave's own load counter; the four partial sums are added in wave
-// order through LDS at the end.  Two workgroups fit on a CU.  Of an X tile only the 8-row pieces (whole lines)
-// that hold live rows are fetched; the rest of its slot keeps what was there, and reaches only results that
+// order through LDS at the end.  Up to 64 rows two workgroups fit on a CU.  Of an X tile only the 8-row pieces (whole
+// lines) that hold live rows are fetched; the rest of its slot keeps what was there, and reaches only results that
 // are not written.  K is a multiple of 64, the last workgroup of a slice re-reads its last tile-row in place of
-// missing ones.
-constexpr int few_depth(int MS, int NS) { return 80 / (4 * (MS + NS)); }     // ring of a wave: at most 20 KiB
+// missing ones.  More rows than 32 MS are taken in row groups (tile_of_block).
+constexpr int few_depth(int MS, int NS) { return (MS > 2 ? 40 : 20) / (MS + NS); }     // KiB of a wave's ring
 
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -1003,21 +1003,23 @@ __device__ __forceinline__ void wait_tail(int left) {
 }
 
 template <int MS, int NS, int EPI>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, MS > 2 ? 1 : 2)
 k_bf16_gemm_few(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, int NBs, int nb_off, int NB_total, int splits,
                 const int32_t* __restrict__ n_ptr, int B, float* __restrict__ partial, int64_t part_plane, int part_ld, EpiArgs ep,
                 ZBatch zb) {
     constexpr int T = NS + MS, D = few_depth(MS, NS);
     __shared__ uint4 lds[4 * D * T * 64];
     static_assert(4 * D * T >= 16 * NS, "the partial sums of a row tile share the rings");
-    const int n = min(*n_ptr, B);
-    if (n <= 0) return;
+    int rg, unit;
+    tile_of_block((NB_total + NS - 1) / NS * splits, rg, unit);
+    const int row_base = rg * (32 * MS), n = min(*n_ptr, B) - row_base;      // rows of this row group and after it
+    if (unit < 0 || n <= 0) return;
     if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
-    Xp += (int64_t)blockIdx.z * zb.x_stride;
+    Xp += (int64_t)blockIdx.z * zb.x_stride + (int64_t)rg * MS * KB * 64;
     ep.out += (int64_t)blockIdx.z * zb.out_stride;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = blockIdx.x / splits, sp = blockIdx.x % splits;
+    const int tile = unit / splits, sp = unit % splits;
     const int nb0 = tile * NS, nt_live = min(NS, NB_total - nb0);
     const int quads = KB >> 2;                               // a step of the workgroup: one K tile per wave
     const int q_lo = (int)((int64_t)quads * sp / splits), S = (int)((int64_t)quads * (sp + 1) / splits) - q_lo;
@@ -1070,8 +1072,10 @@ k_bf16_gemm_few(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int 
         }
     };
     if (MS == 1 || n > 32 * (MS - 1)) stream(std::integral_constant<int, MS>{});
+    else if (MS > 2 && n > 32 * (MS - 2)) stream(std::integral_constant<int, (MS > 2 ? MS - 1 : 1)>{});
+    else if (MS > 3 && n > 32) stream(std::integral_constant<int, (MS > 3 ? 2 : 1)>{});
     else stream(std::integral_constant<int, 1>{});
-    float* red = reinterpret_cast<float*>(lds);
+    float4* red = reinterpret_cast<float4*>(lds);            // [wave][tile-row][4 registers][lane]
 #pragma unroll
     for (int m = 0; m < MS; ++m) {
         if (32 * m >= n) break;
@@ -1079,24 +1083,28 @@ k_bf16_gemm_few(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int 
 #pragma unroll
         for (int j = 0; j < NS; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) red[((wave * NS + j) * 16 + r) * 64 + lane] = acc[m][j][r];
+            for (int q = 0; q < 4; ++q)
+                red[((wave * NS + j) * 4 + q) * 64 + lane] = make_float4(acc[m][j][4 * q], acc[m][j][4 * q + 1], acc[m][j][4 * q + 2], acc[m][j][4 * q + 3]);
         __syncthreads();
         if (wave < nt_live) {                                // tile-row `wave`
             floatx16 v;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                float s = red[(wave * 16 + r) * 64 + lane];
+            for (int q = 0; q < 4; ++q) {
+                float4 t = red[(wave * 4 + q) * 64 + lane];
 #pragma unroll
-                for (int k = 1; k < 4; ++k) s += red[((k * NS + wave) * 16 + r) * 64 + lane];
-                v[r] = s;
+                for (int k = 1; k < 4; ++k) {
+                    const float4 u = red[((k * NS + wave) * 4 + q) * 64 + lane];
+                    t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+                }
+                v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
             }
             if (splits > 1) {
                 EpiArgs pe = ep;
                 pe.out = partial + (int64_t)sp * part_plane;
                 pe.ldo = part_ld;
-                epilogue_one<EPI_STORE>(pe, v, 32 * m, n, nb0 + wave, lane);
+                epilogue_one<EPI_STORE>(pe, v, row_base + 32 * m, row_base + n, nb0 + wave, lane);
             } else {
-                epilogue_one<EPI>(ep, v, 32 * m, n, nb0 + wave, lane);
+                epilogue_one<EPI>(ep, v, row_base + 32 * m, row_base + n, nb0 + wave, lane);
             }
         }
     }
@@ -1826,22 +1834,18 @@ static int rope_blocks(int n_q, int n_kv, int rows) {
 
 template <int MS, int NS, int WK, int WN, int EPI>
 static void gemm_launch(const void* X, const void* W, int K, int NB_total, int NBs, int nb_off, const int32_t* n_ptr,
-                        int B, int row_groups, const EpiArgs& ep, hipStream_t s, const ZBatch& zb, int nz) {
-    dim3 grid((NB_total + WN * NS - 1) / (WN * NS), row_groups, nz);
+                        int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb, int nz) {
+    dim3 grid((NB_total + WN * NS - 1) / (WN * NS), 1, nz);
     hipLaunchKernelGGL((k_bf16_gemm<MS, NS, WK, WN, EPI>), grid, dim3(64 * WK * WN), 0, s, (const uint4*)X,
                        (const uint4*)W, K / 16, NB_total, NBs, nb_off, n_ptr, B, ep, zb);
 }
 
-// picks the tile configuration from the row capacity of the batch
+// picks the tile configuration from the row capacity of the batch: at most 64 rows come here (gemm_tiled)
 template <int NS, int EPI>
 static void gemm(const void* X, const void* W, int N, int K, int NBs, int nb_off, const int32_t* n_ptr, int B,
                  const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{}, int nz = 1) {
-    int NB = N / 32;
-    int Mpad = (B + 31) / 32 * 32;
-    if (Mpad <= 32)       gemm_launch<1, NS, 8, 1, EPI>(X, W, K, NB, NBs, nb_off, n_ptr, B, 1, ep, s, zb, nz);
-    else if (Mpad <= 64)  gemm_launch<2, NS, 8, 1, EPI>(X, W, K, NB, NBs, nb_off, n_ptr, B, 1, ep, s, zb, nz);
-    else if (Mpad <= 128) gemm_launch<4, NS, 2, 2, EPI>(X, W, K, NB, NBs, nb_off, n_ptr, B, 1, ep, s, zb, nz);
-    else                  gemm_launch<8, NS, 1, 4, EPI>(X, W, K, NB, NBs, nb_off, n_ptr, B, (Mpad + 255) / 256, ep, s, zb, nz);
+    if (B <= 32) gemm_launch<1, NS, 8, 1, EPI>(X, W, K, N / 32, NBs, nb_off, n_ptr, B, ep, s, zb, nz);
+    else         gemm_launch<2, NS, 8, 1, EPI>(X, W, K, N / 32, NBs, nb_off, n_ptr, B, ep, s, zb, nz);
 }
 
 // Adds the K-slice planes in slice order and applies the epilogue: plain store, or
@@ -1950,15 +1954,15 @@ k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, in
 // slices; 40.3 with 1 and one, 47.6 with 4 and one).  A slice keeps 32 K tiles, eight per wave.
 struct FewShape { int NS = 4, splits = 1; };
 static FewShape few_shape(int tile_rows, int KB, int rows, int nz, int max_splits) {
-    const int quads = KB / 4;
-    const float x_kib = (rows + 7) / 8 * 0.25f;              // KiB of X per K tile
+    const int quads = KB / 4, groups = (rows + 127) / 128;
+    const float x_kib = (std::min(rows, 128) + 7) / 8 * 0.25f;      // KiB of X per K tile
     FewShape best;
     float best_t = 1e30f;
     for (int NS = 1; NS <= 4; ++NS)
         for (int sp = 1; sp <= max_splits && (sp == 1 || quads / sp >= 8); ++sp) {
             const float steps = 4.0f * ((quads + sp - 1) / sp), w = steps * NS, wx = w + steps * x_kib;    // KiB of a workgroup
-            float t = 0.3f * sp + (sp > 1 ? sp * rows * tile_rows * (32 * 8) / 4.0e6f : 0.f);              // us
-            int left = (tile_rows + NS - 1) / NS * sp * nz;
+            float t = (rows > 64 ? 0.7f : 0.3f) * sp + (sp > 1 ? sp * rows * tile_rows * (32 * 8) / 4.0e6f : 0.f);              // us
+            int left = (tile_rows + NS - 1) / NS * sp * nz * groups;
             for (int round = 0; left > 0; ++round, left -= 256) {
                 const float c = (float)std::min(left, 256), a = wx / 50.f, m = c * w / 6300.f, x = c * wx / 15000.f;
                 t += std::sqrt(std::sqrt(a * a * a * a + m * m * m * m + x * x * x * x)) + (round >= 2 ? 1.f : 0.f);
@@ -1996,21 +2000,62 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
     }
 }
 
-// Whether a product takes k_bf16_gemm_few: up to 64 rows, from 4 MiB of weights on (32 MiB over several layers; below,
-// launches wait for memory once or twice whatever the kernel: O of a 576-wide model 6.7 us on the weight-streaming kernel
-// and its norm 3.3, 9.5 here; two layers of 4 MiB 17.1 and 17.6).  Where the 256-column tiles fill their rounds to 80 %
-// gate/up and the K/V of several layers stay with them: they read X once per 256 columns (gate/up of the 70B shape, 224
-// workgroups, 48 rows 143 us, 149 here, 16 rows 141 and 142; 34B 230 of 192 columns, 115 and 117; seven layers of the 7B
-// shape for 64 rows 95 and 99).  Elsewhere, tile kernels with the streaming kernel / this one, whole launches with the
-// finish: 7B shape 16 rows q|k|v 25.1 / 21.6 us, O 17.4 / 15.3, gate/up 39.8 / 31.2 (172 workgroups / 230), down 25.1 / 22.7;
-// 2048-wide model gate/up 22.6 / 13.5; 70B shape 16 rows q|k|v 33.8 / 30.9, O 34.1 / 30.4, down 82.3 / 76.9; exit head of the 7B
-// shape 1 row 44 / 43, of the 70B shape 64 rows 89 / 86; K/V of five layers of the 7B shape 64 rows 93 / 76.
+// Whether a product takes k_bf16_gemm_few: up to 128 rows, from 4 MiB of weights on (32 MiB over several layers up to 64
+// rows; below, launches wait for memory once or twice whatever the kernel: O of a 576-wide model 6.7 us on the
+// weight-streaming kernel and its norm 3.3, 9.5 here; two layers of 4 MiB 17.1 and 17.6).  Where a tile width fills its
+// rounds to 80 % gate/up and the K/V of several layers stay with the tile kernels: they read X once per 192 or 256 columns
+// (gate/up of the 70B shape, 224 workgroups, 16 rows 141 and 142 us, 48 rows 143 and 149, 128 rows 157 and 189; seven
+// layers of the 7B shape for 64 rows 95 and 99).  Elsewhere, tile kernels with the streaming kernel / this one, whole
+// launches with the finish: 7B shape 16 rows q|k|v 25.1 / 21.6 us, O 17.4 / 15.3, gate/up 39.8 / 31.2 (172 workgroups / 230),
+// down 25.1 / 22.7, 72 rows 31.3 / 27.1, 22.4 / 21.3, 48.4 / 38.7, 30.4 / 29.3; 2048-wide model gate/up 16 rows 22.6 / 13.5, 72
+// rows 28.5 / 21.0; 70B shape 16 rows q|k|v 33.8 / 30.9, O 34.1 / 30.4, down 82.3 / 76.9, 128 rows 46.3 / 44.4, 47.4 / 45.3,
+// 101 / 94; exit head of the 70B shape 64 rows 89 / 86, 72 rows 106 / 93; K/V of five layers of the 7B shape 64 rows 93 / 76.
+// Above 128 rows an X tile per 128 columns is too much (head of the 7B shape 144 rows 65 / 115) where the tile kernels can
+// run (N and K multiples of 128); for other shapes the whole range is here: layer of 576 / 2880 values and 72 rows 79 / 56
+// and 211 / 100 us on the streaming kernel / here, 400 rows 293 / 76 and 977 / 227, context pass of 2048 entries 392 / 143
+// and 1518 / 696.
 template <int EPI>
-static bool few_rows(int N, int K, int rows, int nz) {
-    if (rows > 64 || (int64_t)N * K * nz < ((int64_t)(nz > 1 ? 16 : 2) << 20)) return false;
-    if ((EPI != EPI_SWIGLU && nz == 1) || N % 256 != 0 || K % 128 != 0) return true;
-    const int wide = N / 256 * nz;
-    return (float)wide / (float)((wide + 255) / 256 * 256) < 0.8f;
+static bool few_rows(int N, int K, int rows, int B, int nz) {
+    const bool on_grid = N % 128 == 0 && K % 128 == 0;
+    if (!on_grid && B > 64) return true;
+    if (rows > 128) return false;
+    if ((int64_t)N * K * nz < ((int64_t)(nz > 1 ? 16 : 2) << 20) && !(nz > 1 && B > 64)) return false;
+    if ((EPI != EPI_SWIGLU && nz == 1) || !on_grid) return true;
+    float fill = 0.f;                                        // widths: as gate/up takes them below; 256 columns for several layers
+    for (int t = 8; t >= (nz > 1 ? 8 : 4); t -= 2) {
+        const int wgs = (N / 32 + t - 1) / t * nz;
+        if (t < 8 || N % 256 == 0) fill = std::max(fill, (float)(N / 32 * nz) / (float)((wgs + 255) / 256 * 256 * t));
+    }
+    return fill < 0.8f;
+}
+
+template <int EPI>
+static void launch_few(const ee_batch* b, const void* X, const void* W, int N, int K, int NBs, int nb_off, const int32_t* n_ptr, int B,
+                       int rows, const EpiArgs& ep, hipStream_t s, const ZBatch& zb, int nz, const SliceTail& tail) {
+    const int Mpad = (B + 31) / 32 * 32, groups = (rows + 127) / 128;
+    float* part = b->wsp<float>(b->W.gemm_part);
+    int most = 1;                                            // slices: only where somebody adds the planes
+    if (nz == 1 && (EPI == EPI_RESID || (EPI == EPI_STORE && tail.defer_store)))
+        most = (int)std::min<size_t>(16, b->W.gemm_part_bytes / ((size_t)Mpad * N * sizeof(float)));
+    const FewShape f = few_shape(N / 32, K / 16, rows, nz, most);
+    const int units = (N / 32 + f.NS - 1) / f.NS * f.splits;
+    const dim3 grid(groups > 1 ? (units + 7) / 8 * 8 * groups : units, 1, nz);      // see tile_of_block
+    auto go = [&](auto ms_, auto ns_) {
+        hipLaunchKernelGGL((k_bf16_gemm_few<decltype(ms_)::value, decltype(ns_)::value, EPI>), grid, dim3(256), 0, s, (const uint4*)X,
+                           (const uint4*)W, K / 16, NBs, nb_off, N / 32, f.splits, n_ptr, B, part, (int64_t)Mpad * N, N, ep, zb);
+    };
+    auto go_ns = [&](auto ms_) {
+        if (f.NS == 4) go(ms_, std::integral_constant<int, 4>{});
+        else if (f.NS == 3) go(ms_, std::integral_constant<int, 3>{});
+        else if (f.NS == 2) go(ms_, std::integral_constant<int, 2>{});
+        else go(ms_, std::integral_constant<int, 1>{});
+    };
+    if (rows <= 32) go_ns(std::integral_constant<int, 1>{});
+    else if (rows <= 64) go_ns(std::integral_constant<int, 2>{});
+    else if (rows <= 96) go_ns(std::integral_constant<int, 3>{});
+    else go_ns(std::integral_constant<int, 4>{});
+    finish_slices<EPI>(b, N, f.splits, n_ptr, B, ep, s, tail);
+    if (tail.from_out) *tail.from_out = 0;
 }
 
 // the 256-row tile kernels, 128 or 256 columns wide, K sliced so that about one workgroup per CU
@@ -2020,28 +2065,8 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
                      const int32_t* n_ptr, int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{},
                      int nz = 1, const SliceTail& tail = SliceTail{}) {
     const int rows = b->n_entries > 0 ? b->n_entries : B;    // in a context pass what the call has, not what the batch could hold
-    if (few_rows<EPI>(N, K, rows, nz)) {
-        const int Mpad = (B + 31) / 32 * 32;
-        float* part = b->wsp<float>(b->W.gemm_part);
-        int most = 1;                                        // slices: only where somebody adds the planes
-        if (nz == 1 && (EPI == EPI_RESID || (EPI == EPI_STORE && tail.defer_store)))
-            most = (int)std::min<size_t>(16, b->W.gemm_part_bytes / ((size_t)Mpad * N * sizeof(float)));
-        const FewShape f = few_shape(N / 32, K / 16, rows, nz, most);
-        const dim3 grid((N / 32 + f.NS - 1) / f.NS * f.splits, 1, nz);
-        auto go = [&](auto ms_, auto ns_) {
-            hipLaunchKernelGGL((k_bf16_gemm_few<decltype(ms_)::value, decltype(ns_)::value, EPI>), grid, dim3(256), 0, s, (const uint4*)X,
-                               (const uint4*)W, K / 16, NBs, nb_off, N / 32, f.splits, n_ptr, B, part, (int64_t)Mpad * N, N, ep, zb);
-        };
-        auto go_ns = [&](auto ms_) {
-            if (f.NS == 4) go(ms_, std::integral_constant<int, 4>{});
-            else if (f.NS == 3) go(ms_, std::integral_constant<int, 3>{});
-            else if (f.NS == 2) go(ms_, std::integral_constant<int, 2>{});
-            else go(ms_, std::integral_constant<int, 1>{});
-        };
-        if (rows <= 32) go_ns(std::integral_constant<int, 1>{});
-        else go_ns(std::integral_constant<int, 2>{});
-        finish_slices<EPI>(b, N, f.splits, n_ptr, B, ep, s, tail);
-        if (tail.from_out) *tail.from_out = 0;
+    if (few_rows<EPI>(N, K, rows, B, nz)) {
+        launch_few<EPI>(b, X, W, N, K, NBs, nb_off, n_ptr, B, rows, ep, s, zb, nz, tail);
         return true;
     }
     if (N % 128 != 0 || K % 128 != 0) return false;
@@ -2050,14 +2075,10 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         // Several layers in one launch (K/V of skipped layers) are not sliced.  The whole fill, streaming / tile
         // kernel: up to 64 rows (where few_rows leaves them) the tile kernel needs the 256-column tiles of all layers
         // (rule `wide` below) to fill the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B
-        // shape (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.  From 65
-        // rows on the streaming kernel stays where the tiles are few: three layers of the 70B shape (48 tiles of
-        // 128) 40 of 65 rows 70 / 81, 128 rows 94 / 91; eight (128 tiles) 128 rows 112 / 103, ten 188 / 113; three
-        // layers of the 7B shape (192 tiles) 40 of 65 rows 76 / 52.
+        // shape (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.
         const int wide_tiles = N % 256 == 0 ? N / 256 * nz : 0;
         const float fill = (float)wide_tiles / (float)((wide_tiles + 255) / 256 * 256);
         if (B <= 64 && (wide_tiles < 200 || (B <= 32 && fill < 0.75f))) return false;
-        if (B > 64 && B <= 128 && N / 128 * nz <= 64) return false;
     }
     int row_groups = (B + 255) / 256;
     int Mpad = (B + 31) / 32 * 32;
@@ -2128,6 +2149,12 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     }
     int n_tiles = wide ? N / 256 : N / 128;
     if (splits == 0) splits = sliceable && n_tiles * row_groups < 200 ? fit_slices(slices_for(n_tiles * row_groups)) : 1;
+    if (rows <= 256 && n_tiles * splits * row_groups * nz <= 128 && (int64_t)N * K * nz >= ((int64_t)2 << 20)) {
+        // half of the CUs would idle: two row groups of 128 (2048-wide model, 192 rows: q|k|v 20.2 us in 96 workgroups, 18.0
+        // here, O 22.7 / 19.8, gate/up 30.3 / 27.2; with 172 workgroups the tiles stay: gate/up of the 7B shape 54.8 / 85)
+        launch_few<EPI>(b, X, W, N, K, NBs, nb_off, n_ptr, B, rows, ep, s, zb, nz, tail);
+        return true;
+    }
     if (tail.from_out) *tail.from_out = 0;
     // row groups that have rows: known in a context pass; in a decode step the rows that have left may leave one
     const int live_groups = (b->n_entries + 255) / 256;
