@@ -2275,9 +2275,12 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     bf16_t* act = b->wsp<bf16_t>(b->W.act);
     KvView view = make_view(m, kv, layer, b);
     const CtxTiles ctx = ctx_tiles(c, b);
-    // most workgroups per (row, kv head) of the decode attention (attn_shares)
+    // Most workgroups per (row, kv head) of the decode attention (attn_shares).  Positions are shared only where the longest
+    // row is worth the launch that merges them: 672 positions (attention and merge of 8 kv heads, 1 row of 500: layer 1 us
+    // longer shared, of 950: 3 us shorter), with 192 pairs 1024 (60 rows of 4 kv heads, 650: 78.5 us shared, 75.3 whole,
+    // 950: 84.1 and 81.1; 12 rows of 32, 650: 120.5 and 117.6).
     const int pairs = c.n_kv_heads * B;
-    int most = pairs >= 512 ? 1 : std::min({16, (1024 + pairs - 1) / pairs, std::max(1, kv->max_cap / 256)});
+    int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, kv->max_cap / 256});
     while (most > 1 && (size_t)b->Mpad * c.n_kv_heads * most * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --most;
 
     if (!x_ready) {
