@@ -7,6 +7,7 @@
 #include "ee_device.h"
 
 #include <float.h>
+#include <algorithm>
 
 // ------------------------------------------------------------------ GEMM
 // out[i][j] = sum_k x[i][k] W[j][k] for list entries i < n, 16 x 16 results per workgroup.
@@ -19,17 +20,30 @@
 // NORM: x = RMSNorm(h[idx[i]]; gain): the waves also sum the squares of what they load, and the sum over k of
 // h[k] gain[k] W[j][k] is multiplied by the row's 1 / sqrt(mean + eps) at the end, so no launch normalises.
 // VEC: 16-byte loads (K a multiple of 4, all operands aligned); otherwise element by element.
-enum { F32_EPI_STORE = 0, F32_EPI_RESID = 1, F32_EPI_SCALE = 2, F32_EPI_SWIGLU = 3 };
+// ROPE: the q|k|v product, rotation and cache append in one launch.  A workgroup has 16 rotation pairs of one head: columns
+// j and j + hd / 2, as SWIGLU has gate and up.  Rotated queries go to out, rotated keys and the values to the
+// cache at the row's position.  As a launch of its own rotation and append took 2.6 of the 147 us of the fp32 workload's
+// step six times; the K/V of all skipped layers are one launch (blockIdx.z = layer offset).
+// What a launch waits for is a chain of trips to memory, so everything that does not depend on the number of live
+// rows is asked for beside it: the row ids, and of the epilogue's operands row id, old value, scale or position.
+enum { F32_EPI_RESID = 0, F32_EPI_SCALE = 1, F32_EPI_SWIGLU = 2, F32_EPI_ROPE = 3 };
 #define F32_WAVES 8
 
 struct F32Gemm {
     const float* X; int ldx;             // NORM: the residual stream, indexed by row id
-    const float* W; int N, K;            // SWIGLU: N = F, up row j follows gate row j by F rows
+    const float* W; int N, K;            // SWIGLU: N = F, up row j follows gate row j by F rows; ROPE: N = all columns of W
     const int32_t* n_ptr; int B;
     float* out; int ldo;
     const int32_t* idx;
     const float* row_scale;              // SCALE: per row id
     const float* gain; float eps;        // NORM
+};
+struct F32Rope {                         // ROPE
+    int n_q, head0;                      // query heads of W, first head of the launch
+    const int32_t* pos; const float* rope; int max_pos;
+    KvView kv;
+    int32_t* status;
+    const void* const* w_tab; const float* const* g_tab; int z0;      // several layers: W and gain of layer z0 + blockIdx.z
 };
 
 template <bool VEC>
@@ -40,21 +54,66 @@ __device__ __forceinline__ float4 f32_load4(const float* p, int k, int K) {
 
 template <int EPI, bool NORM, bool VEC>
 __global__ void __launch_bounds__(64 * F32_WAVES)
-k_f32_gemm(F32Gemm g) {
+k_f32_gemm(F32Gemm g, F32Rope p) {
     typedef float floatx4 __attribute__((ext_vector_type(4)));
-    constexpr int NW = EPI == F32_EPI_SWIGLU ? 2 : 1;      // weight rows per result
-    __shared__ float red[NW][F32_WAVES][64][4];
+    constexpr bool ROPE = EPI == F32_EPI_ROPE;
+    constexpr int NW = EPI == F32_EPI_SWIGLU || ROPE ? 2 : 1;      // weight rows per result
+    constexpr bool BY_ID = NORM || EPI == F32_EPI_RESID || EPI == F32_EPI_SCALE || ROPE;
+    __shared__ float4 red[NW][F32_WAVES][64];
     __shared__ float ssq[F32_WAVES][16];
-    const int n = min(*g.n_ptr, g.B);
-    const int row0 = blockIdx.y * 16;
-    if (row0 >= n) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int m = lane & 15, kq = lane >> 4;
-    const int col0 = blockIdx.x * 16;
-    const int xrow = min(row0 + m, n - 1), wrow = min(col0 + m, g.N - 1);   // rows past the end: computed, not written
-    const float* x = g.X + (int64_t)(NORM ? g.idx[xrow] : xrow) * g.ldx;
+    const int row0 = blockIdx.y * 16;
+    // thread = 4 * lane + r of the result registers: row 4 (lane / 16) + r, column lane % 16
+    const int el = (threadIdx.x & 255) >> 2, er = threadIdx.x & 3, erl = 4 * (el >> 4) + er, erow = row0 + erl;
+    int id = 0, eid = 0;                                   // row ids: of the row this lane loads, and of the one it writes
+    if constexpr (BY_ID) {
+        id = g.idx[min(row0 + m, g.B - 1)];
+        eid = g.idx[min(erow, g.B - 1)];
+        asm volatile("" : "+v"(id), "+v"(eid));            // under way together with the number of rows, not after it
+    }
+    const int n = min(*g.n_ptr, g.B);
+    if (row0 >= n) return;
+    // rows past the end are computed, not written: they load the first row
+    const int first_id = __builtin_amdgcn_readfirstlane(id);
+    const bool in_rows = row0 + m < n, out_row = erow < n;
+    if (!in_rows) id = first_id;
+    if (!out_row) eid = first_id;
+    int col, wrow;                                         // column of the result this thread writes, row of W this lane loads
+    int half = 0, head = 0;
+    if constexpr (ROPE) {
+        half = p.kv.head_dim >> 1;
+        const int per_head = (half + 15) >> 4;
+        head = p.head0 + blockIdx.x / per_head;
+        const int j0 = blockIdx.x % per_head * 16;
+        col = j0 + (el & 15);
+        wrow = head * 2 * half + min(j0 + m, half - 1);
+        if (p.w_tab) {
+            g.W = reinterpret_cast<const float*>(p.w_tab[p.z0 + blockIdx.z]);
+            g.gain = p.g_tab[p.z0 + blockIdx.z];
+            p.kv.layer0 += blockIdx.z;
+        }
+    } else {
+        col = blockIdx.x * 16 + (el & 15);
+        wrow = min((int)blockIdx.x * 16 + m, g.N - 1);
+    }
+    const float* x = g.X + (int64_t)(NORM ? id : (in_rows ? row0 + m : row0)) * g.ldx;
     const float* wp = g.W + (int64_t)wrow * g.K;
-    const float* wu = wp + (int64_t)g.N * g.K;             // SWIGLU only
+    const float* wu = wp + (int64_t)(ROPE ? half : g.N) * g.K;      // second weight row
+    // what the epilogue needs
+    float old = 0.f;
+    int at = 0, sq = 0, cap = 0;
+    int64_t off = 0;
+    float2 cs = make_float2(1.f, 0.f);
+    const bool col_ok = col < (ROPE ? half : g.N);
+    if constexpr (EPI == F32_EPI_RESID) { if (col_ok) old = g.out[(int64_t)eid * g.ldo + col]; }
+    if constexpr (EPI == F32_EPI_SCALE) old = g.row_scale[eid];
+    if constexpr (ROPE) {
+        at = p.pos[eid];
+        sq = kv_row(p.kv, eid);
+        cap = p.kv.cap[sq];
+        off = p.kv.off[sq];
+    }
     floatx4 acc[NW] = {};
     float ss = 0.f;
     const int chunks = (g.K + 15) >> 4;
@@ -87,101 +146,191 @@ k_f32_gemm(F32Gemm g) {
             }
         }
     }
+    const bool pos_ok = at >= 0 && at < cap && at < p.max_pos;
+    if constexpr (ROPE) {
+        if (pos_ok && col_ok) cs = *reinterpret_cast<const float2*>(p.rope + ((int64_t)at * half + col) * 2);
+    }
 #pragma unroll
-    for (int q = 0; q < NW; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[q][w][lane][r] = acc[q][r];
+    for (int q = 0; q < NW; ++q) red[q][w][lane] = make_float4(acc[q][0], acc[q][1], acc[q][2], acc[q][3]);
     if constexpr (NORM) {
         ss += __shfl_xor(ss, 16, 64);
         ss += __shfl_xor(ss, 32, 64);
         if (kq == 0) ssq[w][m] = ss;
     }
     __syncthreads();
-    if (threadIdx.x >= 256) return;
-    // thread = 4 * lane + r of the result registers: row 4 (lane / 16) + r, column lane % 16
-    const int l = threadIdx.x >> 2, r = threadIdx.x & 3;
-    const int rl = 4 * (l >> 4) + r, row = row0 + rl, col = col0 + (l & 15);
-    if (row >= n || col >= g.N) return;
+    if (threadIdx.x >= 256 || !out_row || !col_ok) return;
     float v[NW];
 #pragma unroll
     for (int q = 0; q < NW; ++q) {
         v[q] = 0.f;
 #pragma unroll
-        for (int k = 0; k < F32_WAVES; ++k) v[q] += red[q][k][l][r];
+        for (int k = 0; k < F32_WAVES; ++k) v[q] += reinterpret_cast<const float*>(&red[q][k][el])[er];
     }
     if constexpr (NORM) {
         float t = 0.f;
 #pragma unroll
-        for (int k = 0; k < F32_WAVES; ++k) t += ssq[k][rl];
+        for (int k = 0; k < F32_WAVES; ++k) t += ssq[k][erl];
         const float inv = 1.0f / sqrtf(t / (float)g.K + g.eps);
 #pragma unroll
         for (int q = 0; q < NW; ++q) v[q] *= inv;
     }
-    if constexpr (EPI == F32_EPI_STORE) g.out[(int64_t)row * g.ldo + col] = v[0];
-    else if constexpr (EPI == F32_EPI_RESID) g.out[(int64_t)g.idx[row] * g.ldo + col] += v[0];
-    else if constexpr (EPI == F32_EPI_SCALE) g.out[(int64_t)row * g.ldo + col] = v[0] * g.row_scale[g.idx[row]];
-    else g.out[(int64_t)row * g.ldo + col] = (v[0] / (1.0f + expf(-v[0]))) * v[NW - 1];
-}
-
-// ------------------------------------------------------------------ RoPE + cache append
-// buf[i] holds [q (n_q*hd, may be empty) | k (Hkv*hd) | v (Hkv*hd)] of list entry i.
-// Rotates q in place and k on its way into the cache, at the row's position.
-__global__ void __launch_bounds__(256)
-k_f32_rope_append(float* __restrict__ buf, int ld, int n_q, const int32_t* __restrict__ idx,
-                  const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos,
-                  const float* __restrict__ rope, int max_pos, KvView kv, int32_t* __restrict__ status) {
-    int i = blockIdx.x;
-    int n = min(*n_ptr, B);
-    if (i >= n) return;
-    int b = idx[i];
-    int p = pos[b];
-    int hd = kv.head_dim, half = hd >> 1, Hkv = kv.n_kv_heads;
-    const int sq = kv_row(kv, b);
-    int cap = kv.cap[sq];
-    bool ok = p >= 0 && p < cap && p < max_pos;
-    if (!ok) {
-        if (threadIdx.x == 0) atomicOr(status, 1);
-        return;
-    }
-    float* r = buf + (int64_t)i * ld;
-    const float* cs = rope + (int64_t)p * half * 2;
-    for (int t = threadIdx.x; t < n_q * half; t += 256) {
-        int hh = t / half, j = t % half;
-        float c = cs[2 * j], s = cs[2 * j + 1];
-        float a = r[hh * hd + j], bb = r[hh * hd + j + half];
-        r[hh * hd + j] = a * c - bb * s;
-        r[hh * hd + j + half] = bb * c + a * s;
-    }
-    float* kin = r + n_q * hd;
-    float* vin = kin + Hkv * hd;
-    for (int t = threadIdx.x; t < Hkv * half; t += 256) {
-        int g = t / half, j = t % half;
-        float c = cs[2 * j], s = cs[2 * j + 1];
-        float a = kin[g * hd + j], bb = kin[g * hd + j + half];
-        float* base = reinterpret_cast<float*>(kv.pool) + kv_block(kv, sq, g, cap);
-        base[(int64_t)p * hd + j] = a * c - bb * s;
-        base[(int64_t)p * hd + j + half] = bb * c + a * s;
-    }
-    for (int t = threadIdx.x; t < Hkv * hd; t += 256) {
-        int g = t / hd, j = t % hd;
-        float* base = reinterpret_cast<float*>(kv.pool) + kv_block(kv, sq, g, cap);
-        base[(int64_t)cap * hd + (int64_t)p * hd + j] = vin[g * hd + j];
+    if constexpr (EPI == F32_EPI_RESID) g.out[(int64_t)eid * g.ldo + col] = old + v[0];
+    else if constexpr (EPI == F32_EPI_SCALE) g.out[(int64_t)erow * g.ldo + col] = v[0] * old;
+    else if constexpr (EPI == F32_EPI_SWIGLU) g.out[(int64_t)erow * g.ldo + col] = (v[0] / (1.0f + expf(-v[0]))) * v[NW - 1];
+    else {
+        const int hd = 2 * half;
+        const bool is_q = head < p.n_q, is_v = head >= p.n_q + p.kv.n_kv_heads;
+        const float a = v[0], b = v[NW - 1];
+        if (!pos_ok) {                                     // refused: nothing is appended, the queries stay as they are
+            if (blockIdx.x == 0 && col == 0) atomicOr(p.status, 1);
+            cs = make_float2(1.f, 0.f);
+            if (!is_q) return;
+        }
+        const float x0 = is_v ? a : a * cs.x - b * cs.y, x1 = is_v ? b : b * cs.x + a * cs.y;
+        float* dst;
+        if (is_q) {
+            dst = g.out + (int64_t)erow * g.ldo + head * hd;
+        } else {
+            const int kvh = head - p.n_q - (is_v ? p.kv.n_kv_heads : 0);
+            dst = reinterpret_cast<float*>(p.kv.pool) + ((int64_t)p.kv.layer0 * p.kv.T + off) * (2LL * p.kv.n_kv_heads * hd) +
+                  (int64_t)kvh * 2LL * cap * hd + (is_v ? (int64_t)cap * hd : 0) + (int64_t)at * hd;
+        }
+        dst[col] = x0;
+        dst[col + half] = x1;
     }
 }
 
 // ------------------------------------------------------------------ attention
-// One block per (query head, list entry): softmax(q.K^T / sqrt(hd)) V over positions 0..pos.
-// VEC (hd a multiple of 4): L lanes (the power of two from hd / 4 up) share a position and take 16 bytes of its
-// key or value each, the 256 / L groups take positions in turn, so a wave reads whole cache rows and as many
-// positions are in flight as there are groups.  Before, a thread walked one key on its own and hd threads walked
-// all values: 9.9 -> 8.4 us at 65 positions of 64 values, and far more beyond (64 rows of up to 1500
-// positions: the whole layer 268 -> 88 us).  Other hd: one position per thread, one value per thread.
-template <bool VEC>
-__global__ void __launch_bounds__(256)
+// softmax(q.K^T / sqrt(hd)) V over positions 0..pos, one workgroup per (query head, list entry, share of the positions),
+// hd a multiple of 4.  L lanes (the power of two from hd / 4 up) share a position and take 16 bytes of its key and of its
+// value each, asked for together, four positions per group of lanes at a time; each group keeps a running maximum, sum
+// and output, which are merged over the groups of a wave, over the waves through LDS, and over the shares by
+// k_f32_attn_merge.  What bounds it is memory latency.  Before, all scores were written to LDS, then the
+// maximum, the exponentials and the sum taken over the workgroup, then the values asked for.  Layer of 20 rows of 200 to 900
+// positions: 53 -> 34 us; of 1000 to 2000: 87 -> 42; of one row of 2000: 63 -> 32.
+#define F32_ATTN_PART(hd) ((hd) + 4)      /* floats of a share: outputs (not divided by the sum), maximum, sum, two unused */
+
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
 k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restrict__ idx,
            const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv,
-           float* __restrict__ out /* [i][Hq*hd] */, int L) {
-    extern __shared__ float sm[];   // VEC: partial outputs [256 / L][hd] (at most 4 * 256) | scores; else q[hd] | scores
+           float* __restrict__ out /* [i][Hq*hd] */, int L, int shares, float* __restrict__ part) {
+    constexpr int W = THREADS / 64;
+    __shared__ float4 s_o[W][64];
+    __shared__ float s_m[W], s_l[W];
+    const int hq = blockIdx.x, i = blockIdx.y, z = blockIdx.z;
+    int b = idx[i];                                         // i < B; beside the number of rows, not after it
+    asm volatile("" : "+v"(b));
+    const int n = min(*n_ptr, B);
+    if (i >= n) return;
+    b = __builtin_amdgcn_readfirstlane(b);
+    const int hd = kv.head_dim;
+    const int sq = kv_row(kv, b);
+    const int cap = kv.cap[sq];
+    const int n_pos = min(pos[b] + 1, cap);
+    const int g = hq / (Hq / kv.n_kv_heads);
+    const float* Kb = reinterpret_cast<const float*>(kv.pool) + kv_block(kv, sq, g, cap);
+    const float* Vb = Kb + (int64_t)cap * hd;
+    const float inv_sqrt = 1.0f / sqrtf((float)hd);
+    const int c = 4 * (threadIdx.x & (L - 1)), grp = threadIdx.x / L, groups = THREADS / L;
+    const bool has = c < hd;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 q = has ? *reinterpret_cast<const float4*>(qkv + (int64_t)i * ld + hq * hd + c) : zero;
+    const int t_lo = (int)((int64_t)n_pos * z / shares), t_hi = (int)((int64_t)n_pos * (z + 1) / shares);
+    float m = -FLT_MAX, l = 0.f;
+    float4 acc = zero;
+    for (int t0 = t_lo + grp; t0 < t_hi; t0 += 4 * groups) {
+        float4 k[4], v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = t0 + u * groups;
+            const bool ok = has && t < t_hi;
+            k[u] = ok ? *reinterpret_cast<const float4*>(Kb + (int64_t)t * hd + c) : zero;
+            v[u] = ok ? *reinterpret_cast<const float4*>(Vb + (int64_t)t * hd + c) : zero;
+        }
+        float a[4], m_new = m;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a[u] = (q.x * k[u].x + q.y * k[u].y) + (q.z * k[u].z + q.w * k[u].w);
+            for (int o = L >> 1; o > 0; o >>= 1) a[u] += __shfl_xor(a[u], o, 64);
+            a[u] *= inv_sqrt;
+            if (t0 + u * groups < t_hi) m_new = fmaxf(m_new, a[u]);
+        }
+        const float keep = expf(m - m_new);
+        l *= keep;
+        acc.x *= keep; acc.y *= keep; acc.z *= keep; acc.w *= keep;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float e = t0 + u * groups < t_hi ? expf(a[u] - m_new) : 0.f;
+            l += e;
+            acc.x += e * v[u].x; acc.y += e * v[u].y; acc.z += e * v[u].z; acc.w += e * v[u].w;
+        }
+        m = m_new;
+    }
+    for (int o = L; o < 64; o <<= 1) {                      // the wave's groups
+        const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64);
+        const float4 a2 = make_float4(__shfl_xor(acc.x, o, 64), __shfl_xor(acc.y, o, 64), __shfl_xor(acc.z, o, 64), __shfl_xor(acc.w, o, 64));
+        const float mm = fmaxf(m, m2), w1 = expf(m - mm), w2 = expf(m2 - mm);
+        l = l * w1 + l2 * w2;
+        acc.x = acc.x * w1 + a2.x * w2; acc.y = acc.y * w1 + a2.y * w2;
+        acc.z = acc.z * w1 + a2.z * w2; acc.w = acc.w * w1 + a2.w * w2;
+        m = mm;
+    }
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane < L) s_o[w][lane] = acc;
+    if (lane == 0) { s_m[w] = m; s_l[w] = l; }
+    __syncthreads();
+    if ((int)threadIdx.x >= L || !has) return;              // the lanes of group 0: four features each
+    float mm = s_m[0];
+#pragma unroll
+    for (int k = 1; k < W; ++k) mm = fmaxf(mm, s_m[k]);
+    float sum = 0.f;
+    acc = zero;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const float wk = expf(s_m[k] - mm);
+        const float4 o = s_o[k][lane];
+        sum += s_l[k] * wk;
+        acc.x += o.x * wk; acc.y += o.y * wk; acc.z += o.z * wk; acc.w += o.w * wk;
+    }
+    if (shares == 1) {
+        *reinterpret_cast<float4*>(out + (int64_t)i * (Hq * hd) + hq * hd + c) = make_float4(acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
+    } else {
+        float* pp = part + (((int64_t)i * Hq + hq) * shares + z) * F32_ATTN_PART(hd);
+        *reinterpret_cast<float4*>(pp + c) = acc;
+        if (c == 0) { pp[hd] = mm; pp[hd + 1] = sum; }
+    }
+}
+
+// the shares of a (query head, list entry) in order; one workgroup of a wave each
+__global__ void __launch_bounds__(64)
+k_f32_attn_merge(const float* __restrict__ part, int Hq, int hd, int shares, const int32_t* __restrict__ n_ptr, int B,
+                 float* __restrict__ out) {
+    const int hq = blockIdx.x, i = blockIdx.y;
+    if (i >= min(*n_ptr, B)) return;
+    const float* p = part + ((int64_t)i * Hq + hq) * shares * F32_ATTN_PART(hd);
+    float mm = -FLT_MAX;
+    for (int z = 0; z < shares; ++z) mm = fmaxf(mm, p[z * F32_ATTN_PART(hd) + hd]);
+    float sum = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int c = 4 * threadIdx.x;
+    if (c >= hd) return;
+    for (int z = 0; z < shares; ++z) {
+        const float* pz = p + z * F32_ATTN_PART(hd);
+        const float w = expf(pz[hd] - mm);
+        const float4 o = *reinterpret_cast<const float4*>(pz + c);
+        sum += pz[hd + 1] * w;
+        acc.x += o.x * w; acc.y += o.y * w; acc.z += o.z * w; acc.w += o.w * w;
+    }
+    *reinterpret_cast<float4*>(out + (int64_t)i * (Hq * hd) + hq * hd + c) = make_float4(acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
+}
+
+// other hd: one position per thread, then one value per thread
+__global__ void __launch_bounds__(256)
+k_f32_attn_any(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restrict__ idx,
+               const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv,
+               float* __restrict__ out /* [i][Hq*hd] */) {
+    extern __shared__ float sm[];   // q[hd] | scores
     __shared__ float red[4];
     int hq = blockIdx.x, i = blockIdx.y;
     int n = min(*n_ptr, B);
@@ -195,43 +344,17 @@ k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restr
     const float* Kb = reinterpret_cast<const float*>(kv.pool) + kv_block(kv, sq, g, cap);
     const float* Vb = Kb + (int64_t)cap * hd;
     const float* qrow = qkv + (int64_t)i * ld + hq * hd;
-    float* sc = sm + (VEC ? 1024 : hd);
+    float *q = sm, *sc = sm + hd;
     const float inv_sqrt = 1.0f / sqrtf((float)hd);
-    const int c = 4 * (threadIdx.x & (L - 1)), grp = threadIdx.x / L, groups = 256 / L;     // VEC
-    const bool has = c < hd;
     float mx = -FLT_MAX;
-    if constexpr (VEC) {
-        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 q = has ? *reinterpret_cast<const float4*>(qrow + c) : zero;
-        for (int t0 = grp; t0 < n_pos; t0 += 4 * groups) {
-            float4 k[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int t = t0 + u * groups;
-                k[u] = has && t < n_pos ? *reinterpret_cast<const float4*>(Kb + (int64_t)t * hd + c) : zero;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float a = (q.x * k[u].x + q.y * k[u].y) + (q.z * k[u].z + q.w * k[u].w);
-                for (int o = L >> 1; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-                const int t = t0 + u * groups;
-                if (t >= n_pos) continue;
-                a *= inv_sqrt;
-                if (c == 0) sc[t] = a;
-                mx = fmaxf(mx, a);
-            }
-        }
-    } else {
-        float* q = sm;
-        for (int t = threadIdx.x; t < hd; t += 256) q[t] = qrow[t];
-        __syncthreads();
-        for (int t = threadIdx.x; t < n_pos; t += 256) {
-            float a = 0.f;
-            for (int j = 0; j < hd; ++j) a += q[j] * Kb[(int64_t)t * hd + j];
-            a *= inv_sqrt;
-            sc[t] = a;
-            mx = fmaxf(mx, a);
-        }
+    for (int t = threadIdx.x; t < hd; t += 256) q[t] = qrow[t];
+    __syncthreads();
+    for (int t = threadIdx.x; t < n_pos; t += 256) {
+        float a = 0.f;
+        for (int j = 0; j < hd; ++j) a += q[j] * Kb[(int64_t)t * hd + j];
+        a *= inv_sqrt;
+        sc[t] = a;
+        mx = fmaxf(mx, a);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
@@ -247,29 +370,10 @@ k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restr
     }
     sum = block_sum<256>(sum, red);   // also makes sc[] visible to all threads
     float* orow = out + (int64_t)i * (Hq * hd) + hq * hd;
-    if constexpr (VEC) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (has) {
-#pragma unroll 4
-            for (int t = grp; t < n_pos; t += groups) {
-                const float p = sc[t];
-                const float4 v = *reinterpret_cast<const float4*>(Vb + (int64_t)t * hd + c);
-                acc.x += p * v.x; acc.y += p * v.y; acc.z += p * v.z; acc.w += p * v.w;
-            }
-            *reinterpret_cast<float4*>(sm + grp * hd + c) = acc;
-        }
-        __syncthreads();
-        for (int j = threadIdx.x; j < hd; j += 256) {
-            float a = 0.f;
-            for (int k = 0; k < groups; ++k) a += sm[k * hd + j];
-            orow[j] = a / sum;
-        }
-    } else {
-        for (int j = threadIdx.x; j < hd; j += 256) {
-            float acc = 0.f;
-            for (int t = 0; t < n_pos; ++t) acc += sc[t] * Vb[(int64_t)t * hd + j];
-            orow[j] = acc / sum;
-        }
+    for (int j = threadIdx.x; j < hd; j += 256) {
+        float acc = 0.f;
+        for (int t = 0; t < n_pos; ++t) acc += sc[t] * Vb[(int64_t)t * hd + j];
+        orow[j] = acc / sum;
     }
 }
 
@@ -330,11 +434,30 @@ static KvView make_view(const ee_model* m, const ee_kv* kv, int layer, const ee_
 }
 
 template <int EPI, bool NORM>
-static void gemm(const F32Gemm& g, hipStream_t s) {
-    const dim3 grid((g.N + 15) / 16, (g.B + 15) / 16), block(64 * F32_WAVES);
+static void gemm(const F32Gemm& g, hipStream_t s, const F32Rope& p = F32Rope{}, int cols = 0, int nz = 1, bool tab_aligned = true) {
+    const dim3 grid(cols ? cols : (g.N + 15) / 16, (g.B + 15) / 16, nz), block(64 * F32_WAVES);
     const uintptr_t a = (uintptr_t)g.X | (uintptr_t)g.W | (NORM ? (uintptr_t)g.gain : 0);
-    if (g.K % 4 == 0 && g.ldx % 4 == 0 && a % 16 == 0) hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, true>), grid, block, 0, s, g);
-    else hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, false>), grid, block, 0, s, g);
+    if (g.K % 4 == 0 && g.ldx % 4 == 0 && a % 16 == 0 && tab_aligned) hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, true>), grid, block, 0, s, g, p);
+    else hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, false>), grid, block, 0, s, g, p);
+}
+
+// the launch that makes queries, keys and values of the rows of a list: heads head0 .. of layers first .. first + nl - 1
+static void rope_gemm(const ee_model* m, const ee_kv* kv, ee_batch* b, int first, int nl, int head0, const int32_t* idx,
+                      const int32_t* n_ptr, hipStream_t s) {
+    const ee_model_config& c = m->cfg;
+    const int heads = c.n_q_heads + 2 * c.n_kv_heads, per_head = (c.head_dim / 2 + 15) / 16;
+    const ee_layer_weights& w = m->layers[first - 1];
+    F32Gemm g{b->st<float>(b->L.h), c.d_model, (const float*)w.w_qkv, heads * c.head_dim, c.d_model, n_ptr, b->B, b->wsp<float>(b->W.qkv),
+              heads * c.head_dim, idx, nullptr, w.g_attn, c.rms_eps};
+    F32Rope p{c.n_q_heads, head0, b->st<int32_t>(b->L.pos), m->d_rope, c.max_pos, make_view(m, kv, first, b), b->st<int32_t>(b->L.status),
+              nullptr, nullptr, 0};
+    bool aligned = true;
+    if (nl > 1) {
+        p.w_tab = m->d_wqkv_tab; p.g_tab = m->d_gattn_tab; p.z0 = first - 1;
+        for (int l = first; l < first + nl; ++l)
+            aligned = aligned && (((uintptr_t)m->layers[l - 1].w_qkv | (uintptr_t)m->layers[l - 1].g_attn) & 15) == 0;
+    }
+    gemm<F32_EPI_ROPE, true>(g, s, p, (heads - head0) * per_head, nl, aligned);
 }
 
 int f32_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipStream_t s) {
@@ -351,17 +474,31 @@ int f32_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipS
     float* act = b->wsp<float>(b->W.act);
     KvView view = make_view(m, kv, layer, b);
 
-    gemm<F32_EPI_STORE, true>(F32Gemm{h, d, (const float*)w.w_qkv, qkv_n, d, n_ptr, B, qkv, qkv_n, idx, nullptr, w.g_attn, c.rms_eps}, s);
-    hipLaunchKernelGGL(k_f32_rope_append, dim3(B), dim3(256), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B,
-                       b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->st<int32_t>(L.status));
-    int lanes = 1;                            // lanes that share a position: a power of two that holds hd / 4
-    while (4 * lanes < hd) lanes *= 2;
-    if (hd % 4 == 0)
-        hipLaunchKernelGGL(k_f32_attn<true>, dim3(c.n_q_heads, B), dim3(256), (size_t)(1024 + c.max_pos) * sizeof(float), s, qkv,
-                           qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao, lanes);
-    else
-        hipLaunchKernelGGL(k_f32_attn<false>, dim3(c.n_q_heads, B), dim3(256), (size_t)(hd + c.max_pos) * sizeof(float), s, qkv,
-                           qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao, 1);
+    rope_gemm(m, kv, b, layer, 1, 0, idx, n_ptr, s);
+    if (hd % 4 == 0) {
+        int lanes = 1;                        // lanes that share a position: a power of two that holds hd / 4
+        while (4 * lanes < hd) lanes *= 2;
+        // Few (row, head) pairs and long rows: the positions are shared out, so that a CU does not stream a whole row (layer of
+        // one row of 2000 positions 41.4 us unshared, 32.5 in seven shares; of 4 rows of up to 900 30.9 and 31.1 in three).  The
+        // shares lie where the layout keeps room for keys and values of a fill.
+        const int pairs = B * c.n_q_heads;
+        float* part = b->wsp<float>(b->W.fill_kv);
+        const size_t room = (size_t)b->Mpad * 2 * c.n_kv_heads * hd / ((size_t)pairs * F32_ATTN_PART(hd));
+        int shares = pairs < 128 ? (int)std::min<size_t>({16, (size_t)256 / pairs, (size_t)kv->max_cap / 256, room}) : 1;
+        shares = std::max(1, shares);
+        // Waves of a workgroup: as many as have work at once (16 lanes per position, four positions each: 64 positions on 4
+        // waves), fewer where the pairs alone fill the chip.  Layer, 4 / 8 / 16 waves: 20 rows of 60 positions 26.1 / 26.5 / 28.1
+        // us, of 120 27.8 / 26.8 / 28.1, of 200 to 900 37.7 / 34.9 / 34.4; 100 entries of 1500 62 / 49 / 52, 200 71 / 73 / 75.
+        const int cap = kv->max_cap;
+        const int waves = pairs > 512 || cap <= 64 ? 4 : pairs > 256 || cap <= 256 ? 8 : 16;
+        auto kern = waves == 4 ? k_f32_attn<256> : waves == 8 ? k_f32_attn<512> : k_f32_attn<1024>;
+        hipLaunchKernelGGL(kern, dim3(c.n_q_heads, B, shares), dim3(64 * waves), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B,
+                           b->st<int32_t>(L.pos), view, ao, lanes, shares, part);
+        if (shares > 1) hipLaunchKernelGGL(k_f32_attn_merge, dim3(c.n_q_heads, B), dim3(64), 0, s, part, c.n_q_heads, hd, shares, n_ptr, B, ao);
+    } else {
+        hipLaunchKernelGGL(k_f32_attn_any, dim3(c.n_q_heads, B), dim3(256), (size_t)(hd + c.max_pos) * sizeof(float), s, qkv,
+                           qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao);
+    }
     gemm<F32_EPI_RESID, false>(F32Gemm{ao, qd, (const float*)w.w_o, d, qd, n_ptr, B, h, d, idx, nullptr, nullptr, 0.f}, s);
     gemm<F32_EPI_SWIGLU, true>(F32Gemm{h, d, (const float*)w.w_gate_up, F, d, n_ptr, B, act, F, idx, nullptr, w.g_ffn, c.rms_eps}, s);
     gemm<F32_EPI_RESID, false>(F32Gemm{act, F, (const float*)w.w_down, d, F, n_ptr, B, h, d, idx, nullptr, nullptr, 0.f}, s);
@@ -386,21 +523,8 @@ int f32_exit_head(const ee_model* m, int e, float th, int force, ee_batch* b, fl
 }
 
 int f32_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_batch* b, hipStream_t s) {
-    const ee_model_config& c = m->cfg;
-    const ee_batch_layout& L = b->L;
-    int B = b->B, d = c.d_model, hd = c.head_dim;
-    int kv_n = 2 * c.n_kv_heads * hd;
-    const int32_t* idx = b->st<int32_t>(L.exited_idx);
-    const int32_t* n_ptr = b->st<int32_t>(L.n_exited);
-    float* kvb = b->wsp<float>(b->W.fill_kv);
-    for (int l = from_excl + 1; l <= to_incl; ++l) {
-        const ee_layer_weights& w = m->layers[l - 1];
-        const float* Wkv = (const float*)w.w_qkv + (int64_t)c.n_q_heads * hd * d;
-        gemm<F32_EPI_STORE, true>(F32Gemm{b->st<float>(L.h), d, Wkv, kv_n, d, n_ptr, B, kvb, kv_n, idx, nullptr, w.g_attn, c.rms_eps}, s);
-        hipLaunchKernelGGL(k_f32_rope_append, dim3(B), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B,
-                           b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, l, b),
-                           b->st<int32_t>(L.status));
-    }
+    // key and value heads follow the query heads
+    rope_gemm(m, kv, b, from_excl + 1, to_incl - from_excl, m->cfg.n_q_heads, b->st<int32_t>(b->L.exited_idx), b->st<int32_t>(b->L.n_exited), s);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
