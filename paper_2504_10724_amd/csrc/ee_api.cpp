@@ -505,7 +505,7 @@ int ee_exit_head(const ee_model* m, int exit_idx, float threshold, int force_exi
 int ee_compact_active(ee_batch* b, int exit_idx, int exit_layer, void* stream) {
     if (!b) return ee_fail(EE_ERR_INVALID_ARG, "ee_compact_active: null batch");
     if (exit_idx < 0 || exit_idx >= EE_MAX_EXITS) return ee_fail(EE_ERR_INVALID_ARG, "ee_compact_active: exit index out of range");
-    return launch_compact(b, exit_idx, exit_layer, as_stream(stream));
+    return launch_compact(b, exit_idx, exit_layer, false, as_stream(stream));
 }
 
 int ee_fill_skipped_kv(const ee_model* m, int from_layer_excl, int to_layer_incl, ee_kv* kv, ee_batch* b,
@@ -751,7 +751,8 @@ static int check_step(const char* who, const ee_model* m, const ee_kv* kv, const
 
 // Segment e of a step: the layers after exit e - 1 up to exit layer e (segment 0 starts with the embedding), the
 // exit head there, the compaction, and the K/V of the layers up to the next exit for the rows that have left.
-static int step_segment(const ee_model* m, ee_kv* kv, ee_batch* b, const float* host_thresholds, int e, int R, void* s) {
+// ends: the compaction at layer R also ends the step.
+static int step_segment(const ee_model* m, ee_kv* kv, ee_batch* b, const float* host_thresholds, int e, int R, bool ends, void* s) {
     const ee_model_config& c = m->cfg;
     // bf16: the kernel that finishes a layer can leave the normalised operand of whatever comes
     // next (the exit head, or the next layer when no compaction lies between), and the kernel that
@@ -775,7 +776,7 @@ static int step_segment(const ee_model* m, ee_kv* kv, ee_batch* b, const float* 
         rc = bf16_exit_head(m, e, host_thresholds[e], last == R ? 1 : 0, b, nullptr, as_stream(s), x_ready);
     else
         rc = ee_exit_head(m, e, host_thresholds[e], last == R, b, nullptr, s);
-    if (rc == EE_OK) rc = ee_compact_active(b, e, last, s);    // renumbers the list entries
+    if (rc == EE_OK) rc = launch_compact(b, e, last, ends && last == R, as_stream(s));    // renumbers the list entries
     if (rc != EE_OK || last == R) return rc;
     if (c.dtype == EE_BF16) {
         // Sec. 2.2 asks for the skipped layers' K/V of every row that left; when they are computed
@@ -794,8 +795,7 @@ int ee_decode_step(const ee_model* m, ee_kv* kv, ee_batch* b, const float* host_
                    void* stream) {
     int R = 0, n_res = 0;
     int rc = check_step("ee_decode_step", m, kv, b, host_thresholds, n_thresholds, &R, &n_res);
-    for (int e = 0; e < n_res && rc == EE_OK; ++e) rc = step_segment(m, kv, b, host_thresholds, e, R, stream);
-    if (rc == EE_OK) rc = launch_end_step(b, as_stream(stream));
+    for (int e = 0; e < n_res && rc == EE_OK; ++e) rc = step_segment(m, kv, b, host_thresholds, e, R, true, stream);
     return rc;
 }
 
@@ -805,7 +805,7 @@ int ee_decode_segment(const ee_model* m, ee_kv* kv, ee_batch* b, const float* ho
     int rc = check_step("ee_decode_segment", m, kv, b, host_thresholds, n_thresholds, &R, &n_res);
     if (rc != EE_OK) return rc;
     if (segment < 0 || segment >= n_res) return ee_fail(EE_ERR_INVALID_ARG, "ee_decode_segment: no such segment");
-    return step_segment(m, kv, b, host_thresholds, segment, R, stream);
+    return step_segment(m, kv, b, host_thresholds, segment, R, false, stream);
 }
 
 int ee_decode_finish(const ee_model* m, ee_kv* kv, ee_batch* b, int last_segment, void* stream) {

@@ -115,7 +115,8 @@ int launch_begin_step(const ee_model* m, ee_batch* b, hipStream_t s);
 int launch_end_step(ee_batch* b, hipStream_t s);
 int launch_reset(ee_batch* b, const int32_t* tok, const int32_t* pos, const float* scale, hipStream_t s);
 int launch_set_scale(ee_batch* b, const float* scale, hipStream_t s);
-int launch_compact(ee_batch* b, int exit_idx, int exit_layer, hipStream_t s);
+// end_step: also what launch_end_step does, for the last compaction of a step
+int launch_compact(ee_batch* b, int exit_idx, int exit_layer, bool end_step, hipStream_t s);
 int launch_exit_decide(ee_batch* b, int n_part, float th, int force, hipStream_t s);
 int launch_prefill_begin(const ee_model* m, const ee_kv* kv, ee_batch* b, const int32_t* tok, const int32_t* pos,
                          const int32_t* seq, int n, hipStream_t s);

@@ -370,7 +370,8 @@ k_compact(int32_t* __restrict__ active_idx, int32_t* __restrict__ n_active, int3
           const uint8_t* __restrict__ head_breach, int32_t* __restrict__ out_tok,
           int32_t* __restrict__ out_layer, float* __restrict__ out_conf, uint8_t* __restrict__ out_breach,
           int32_t* __restrict__ exit_counts, int32_t* __restrict__ breach_count, int exit_idx, int exit_layer,
-          int B, int32_t* __restrict__ gone_idx, int32_t* __restrict__ n_gone) {
+          int B, int32_t* __restrict__ gone_idx, int32_t* __restrict__ n_gone, int32_t* __restrict__ pos,
+          int32_t* __restrict__ tok_in) {
     __shared__ int s_keep[COMPACT_THREADS / 64];
     __shared__ int s_gone[COMPACT_THREADS / 64];
     __shared__ int s_brch[COMPACT_THREADS / 64];
@@ -417,9 +418,15 @@ k_compact(int32_t* __restrict__ active_idx, int32_t* __restrict__ n_active, int3
         exit_counts[exit_idx] += gone_base;
         *breach_count += breaches;
     }
+    // the last compaction of a step: what k_end_step does (the stores to out_tok above are this workgroup's own)
+    if (pos != nullptr)
+        for (int b = threadIdx.x; b < B; b += COMPACT_THREADS) {
+            pos[b] += 1;
+            tok_in[b] = out_tok[b];
+        }
 }
 
-int launch_compact(ee_batch* b, int exit_idx, int exit_layer, hipStream_t s) {
+int launch_compact(ee_batch* b, int exit_idx, int exit_layer, bool end_step, hipStream_t s) {
     const ee_batch_layout& L = b->L;
     TimedScope t(EE_K_COMPACT, s);
     hipLaunchKernelGGL(k_compact, dim3(1), dim3(COMPACT_THREADS), 0, s, b->st<int32_t>(L.active_idx),
@@ -428,7 +435,8 @@ int launch_compact(ee_batch* b, int exit_idx, int exit_layer, hipStream_t s) {
                        b->st<uint8_t>(L.head_breach), b->st<int32_t>(L.out_tok), b->st<int32_t>(L.out_layer),
                        b->st<float>(L.out_conf), b->st<uint8_t>(L.out_breach), b->st<int32_t>(L.exit_counts),
                        b->st<int32_t>(L.breach_count), exit_idx, exit_layer, b->B, b->wsp<int32_t>(b->W.gone_idx),
-                       b->wsp<int32_t>(b->W.n_gone));
+                       b->wsp<int32_t>(b->W.n_gone), end_step ? b->st<int32_t>(L.pos) : nullptr,
+                       end_step ? b->st<int32_t>(L.tok_in) : nullptr);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
