@@ -819,17 +819,20 @@ k_bf16_gemm_dma8(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 }
 
 // ------------------------------------------------------------------ tile of 192 columns
-// k_bf16_gemm_cols<EPI, NT>: 256 rows x 32 NT columns per workgroup (NT = 5 .. 7; 6 is used), for products whose
-// column tiles fill the 256 CUs badly at 128 or 256 columns (gate/up of the 34B shape has 1376
-// tile-rows: 344 workgroups of 4 take two rounds, 172 of 8 leave a third of the CUs idle, 230 of 6 run
-// in one round).  Same operand path, staging and waits as k_bf16_gemm_dma8, same wave layout: wave
-// (wm, wn) = (w / 4, w % 4) owns row tiles 4 wm .. 4 wm + 3, and the NT column tiles are dealt out
-// over wn (the four SIMDs) as evenly as they go, one or two each, so that whatever the number of
-// live row tiles every SIMD with the same number of column tiles carries the same MFMA work.  LDS: 5
-// stage buffers of 32 slots, X tile (row tile m, K half kk) at 2 m + kk, W tile (column tile nb, K half
+// 256 rows x 192 columns per workgroup, for products whose column tiles fill the 256 CUs badly at 128 or 256 columns
+// (gate/up of the 34B shape has 1376 tile-rows: 344 workgroups of 4 take two rounds, 172 of 8 leave a third of the
+// CUs idle, 230 of 6 run in one round; with several row groups gate/up of 1024 entries at the 7B shape is 344
+// workgroups of 8, two rounds of 90 us, and 460 of 6, two rounds of 76).  Same operand path, staging and waits as
+// k_bf16_gemm_dma8; eight waves as 4 x 2, wave (wm, wn) owns row tiles 2 wm, 2 wm + 1 and column tiles 3 wn .. 3 wn + 2: six
+// MFMA tiles each, two waves per SIMD.  (Before, the six column tiles were dealt out 2, 2, 1, 1 over the SIMDs, which at full rows
+// ran at the pace of the fuller ones: 256 rows 175 -> 169 us, and no faster than 256 columns with several row groups.)
+// LDS: 5 stage buffers of 32 slots, X tile (row tile m, K half kk) at 2 m + kk, W tile (column tile nb, K half
 // kk) at 16 + 2 nb + kk; wave w sends the X tiles of row tile w (if live) and the W tiles of column
-// tile w (if w < NT), four stages ahead.  The last workgroup of a product whose tile-rows are no
-// multiple of NT re-reads its last tile-row in place of the missing ones and drops their results.
+// tile w (if w < 6), four stages ahead.  The last workgroup of a product whose tile-rows are no
+// multiple of 6 re-reads its last tile-row in place of the missing ones and drops their results.
+#define COLS_NT 6       /* column tiles of a workgroup */
+#define COLS_NR 2       /* row tiles of a wave */
+#define COLS_NC 3       /* column tiles of a wave */
 struct ColsCtx {
     uint4*       lds;        // [5][32][64]
     const uint4* xg;
@@ -837,19 +840,19 @@ struct ColsCtx {
     int KB, NBs, ks_lo, T, mbs, nt_live, wave, lane, row_base, n, nb0;
 };
 
-template <int EPI, int NT, int NC>
-__device__ __forceinline__ void cols_wave(const ColsCtx& c, const int c0, const EpiArgs& ep) {
-    const int wave = c.wave, lane = c.lane, wm = wave >> 2;
-    const int cnt = max(0, min(4, c.mbs - 4 * wm));           // live row tiles among 4 wm .. 4 wm + 3
+template <int EPI>
+__device__ __forceinline__ void cols_wave(const ColsCtx& c, const int r0, const int c0, const EpiArgs& ep) {
+    const int wave = c.wave, lane = c.lane;
+    const int cnt = max(0, min(COLS_NR, c.mbs - r0));              // live row tiles among the wave's
     const unsigned lane_bytes = (unsigned)lane * 16u;
     const unsigned lds0 = (unsigned)(size_t)c.lds;
-    const bool sends_x = wave < c.mbs, sends_w = wave < NT;
+    const bool sends_x = wave < c.mbs, sends_w = wave < COLS_NT;
 
-    floatx16 acc[4][NC];
+    floatx16 acc[COLS_NR][COLS_NC];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < COLS_NR; ++i)
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
+        for (int j = 0; j < COLS_NC; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
@@ -867,9 +870,9 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int c0, const 
         if (j < 2) dma_tile(xs, voff[j], lds0 + (unsigned)((buf * 32 + wave * 2 + j) << 10));
         else dma_tile<true>(ws, voff[j], lds0 + (unsigned)((buf * 32 + 16 + wave * 2 + (j - 2)) << 10));
     };
-    uint4 a[2][4], b[2][NC];                                  // [K half][row tile], [K half][column tile]
+    uint4 a[2][COLS_NR], b[2][COLS_NC];                                 // [K half][row tile], [K half][column tile]
     auto slot = [&](int buf, int s_) { return (c.lds + lane + buf * (32 * 64))[s_ * 64]; };
-    auto rd_a = [&](int buf, int kk, int i) { a[kk][i] = slot(buf, (4 * wm + i) * 2 + kk); };
+    auto rd_a = [&](int buf, int kk, int i) { a[kk][i] = slot(buf, (r0 + i) * 2 + kk); };
     auto rd_b = [&](int buf, int kk, int j) { b[kk][j] = slot(buf, 16 + (c0 + j) * 2 + kk); };
 
     int bc = 0, bn = 1, bi = 4;   // buffers of the current stage, the next one and the one being requested (stage + 4)
@@ -886,19 +889,18 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int c0, const 
             const int rb = kk == 0 ? bc : bn;                 // buffer the other K half is read from
             const int ok = 1 - kk;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < COLS_NR; ++g) {
                 if (ALL || g < cnt) {
 #pragma unroll
-                    for (int j = 0; j < NC; ++j) acc[g][j] = tile_mfma<EPI>(a[kk][g], b[kk][j], acc[g][j]);
+                    for (int j = 0; j < COLS_NC; ++j) acc[g][j] = tile_mfma<EPI>(a[kk][g], b[kk][j], acc[g][j]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (g == 0) {
                     if (kk == 0 ? XL : WL) issue(xs, ws, bi, 2 * kk);
-                    rd_a(rb, ok, 0); rd_a(rb, ok, 1); rd_b(rb, ok, 0);
-                    if (NC > 1) rd_b(rb, ok, 1);
-                } else if (g == 1) {
+                    rd_a(rb, ok, 0); rd_b(rb, ok, 0); rd_b(rb, ok, 1);
+                } else {
                     if (kk == 0 ? XL : WL) issue(xs, ws, bi, 2 * kk + 1);
-                    rd_a(rb, ok, 2); rd_a(rb, ok, 3);
+                    rd_a(rb, ok, 1); rd_b(rb, ok, 2);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -916,9 +918,9 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int c0, const 
         // stages 0 and 1 have landed
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (2 * (XL ? 1 : 0) + 2 * (WL ? 1 : 0))) : "memory");
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { rd_a(0, 0, i); a[1][i] = a[0][i]; }
+        for (int i = 0; i < COLS_NR; ++i) { rd_a(0, 0, i); a[1][i] = a[0][i]; }
 #pragma unroll
-        for (int j = 0; j < NC; ++j) { rd_b(0, 0, j); b[1][j] = b[0][j]; }
+        for (int j = 0; j < COLS_NC; ++j) { rd_b(0, 0, j); b[1][j] = b[0][j]; }
         for (int t0 = 0; t0 < c.T; t0 += 4) {
             stage(xl_, wl_, all_, t0 + 4); stage(xl_, wl_, all_, t0 + 5); stage(xl_, wl_, all_, t0 + 6); stage(xl_, wl_, all_, t0 + 7);
         }
@@ -929,27 +931,26 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int c0, const 
     // the count of loads a wave may leave in flight is per wave and follows from what it sends, so each
     // combination runs its own copy of the loop; a wave whose four row tiles are live (the common case)
     // runs a copy without the live-tile test
-    const bool all = cnt == 4;
+    const bool all = cnt == COLS_NR;
     if (sends_x && sends_w) { if (all) slice(Yes{}, Yes{}, Yes{}); else slice(Yes{}, Yes{}, No{}); }
     else if (sends_x)       { if (all) slice(Yes{}, No{}, Yes{});  else slice(Yes{}, No{}, No{}); }
     else if (sends_w)       { slice(No{}, Yes{}, No{}); }
     else                    { slice(No{}, No{}, No{}); }
 
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < COLS_NR; ++i) {
         if (i >= cnt) continue;
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
+        for (int j = 0; j < COLS_NC; ++j)
             if (c0 + j < c.nt_live)
-                epilogue_one<EPI>(ep, acc[i][j], c.row_base + 32 * (4 * wm + i), c.n, c.nb0 + c0 + j, lane);
+                epilogue_one<EPI>(ep, acc[i][j], c.row_base + 32 * (r0 + i), c.n, c.nb0 + c0 + j, lane);
     }
 }
 
-template <int EPI, int NT>
+template <int EPI>
 __global__ void __launch_bounds__(512, 2)
 k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, int NBs, int nb_off, int NB_total,
                  int n_tiles, const int32_t* __restrict__ n_ptr, int B, EpiArgs ep) {
-    static_assert(NT >= 5 && NT <= 7, "column tiles per workgroup");
     __shared__ uint4 lds[5][32][64];
     const int n = min(*n_ptr, B);
     int rg, tile;
@@ -963,16 +964,13 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     c.ks_lo = 0;
     c.T = KB >> 1;                                            // stages: a positive multiple of 4 (K is a multiple of 128)
     c.mbs = min(8, (n - row_base + 31) >> 5);
-    c.nt_live = min(NT, NB_total - tile * NT);
+    c.nt_live = min(COLS_NT, NB_total - tile * COLS_NT);
     c.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     c.lane = threadIdx.x & 63;
-    c.row_base = row_base; c.n = n; c.nb0 = tile * NT;
+    c.row_base = row_base; c.n = n; c.nb0 = tile * COLS_NT;
     c.xg = Xp + ((int64_t)rg * 8 * KB) * 64;
-    c.wg = Wp + (int64_t)(nb_off + tile * NT) * 64;            // the tile's NT tile-rows of W
-    // column tiles of SIMD wn: two for wn < NT - 4, one for the others, in rising order
-    const int wn = c.wave & 3;
-    if (wn < NT - 4) cols_wave<EPI, NT, 2>(c, 2 * wn, ep);
-    else cols_wave<EPI, NT, 1>(c, 2 * (NT - 4) + (wn - (NT - 4)), ep);
+    c.wg = Wp + (int64_t)(nb_off + tile * COLS_NT) * 64;            // the tile's COLS_NT tile-rows of W
+    cols_wave<EPI>(c, COLS_NR * (c.wave >> 1), COLS_NC * (c.wave & 1), ep);
 }
 
 // ------------------------------------------------------------------ few rows: each wave streams on its own
@@ -2080,15 +2078,24 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         const float fill = (float)wide_tiles / (float)((wide_tiles + 255) / 256 * 256);
         if (B <= 64 && (wide_tiles < 200 || (B <= 32 && fill < 0.75f))) return false;
     }
-    int row_groups = (B + 255) / 256;
+    int row_groups = (rows + 255) / 256;
     int Mpad = (B + 31) / 32 * 32;
     int KS = K / 32;
+    auto launch_cols = [&]() {
+        const int n_tiles = (N / 32 + 5) / 6;
+        const dim3 grid(row_groups > 1 ? (n_tiles + 7) / 8 * 8 * row_groups : n_tiles, 1, 1);      // see tile_of_block
+        hipLaunchKernelGGL((k_bf16_gemm_cols<EPI>), grid, dim3(512), 0, s, (const uint4*)X, (const uint4*)W, K / 16, NBs, nb_off,
+                           N / 32, n_tiles, n_ptr, B, ep);
+        if (tail.splits_out) *tail.splits_out = 1;
+        if (tail.from_out) *tail.from_out = 0;
+        return true;
+    };
     // the 256-column tile loads each activation tile once per 256 columns instead of once per 128;
     // worth it when it still gives every CU a workgroup, or when K is long enough that a deeper K
     // slicing costs little
     // (long K: with more than 128 rows the 256-column tile's halved activation traffic outweighs its
     // doubled K-slice planes; up to 128 rows the 128-column tile is 2-8 % faster on the down projection)
-    bool wide = (N % 256 == 0) && ((N / 256) * row_groups * nz >= 200 || (EPI == EPI_RESID && K >= 2 * N && Mpad > 128));
+    bool wide = (N % 256 == 0) && ((N / 256) * row_groups * nz >= 200 || (EPI == EPI_RESID && K >= 2 * N && rows > 128));
     // K slices of a narrow product when the launch is left to itself: about one workgroup per CU
     auto slices_for = [&](int tiles) {
         int sp = (256 + tiles / 2) / tiles;
@@ -2137,14 +2144,7 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
             const int wgs = (NB + t - 1) / t * row_groups * nz, cost = (wgs + 255) / 256 * t;
             if (cost < best) { best = cost; nt = t; }
         }
-        if (nt == 6) {
-            const int n_tiles = (NB + 5) / 6;
-            dim3 grid(n_tiles, 1, 1);
-            hipLaunchKernelGGL((k_bf16_gemm_cols<EPI, 6>), grid, dim3(512), 0, s, (const uint4*)X, (const uint4*)W, K / 16,
-                               NBs, nb_off, NB, n_tiles, n_ptr, B, ep);
-            if (tail.splits_out) *tail.splits_out = 1;
-            return true;
-        }
+        if (nt == 6) return launch_cols();
         wide = nt == 8;
     }
     int n_tiles = wide ? N / 256 : N / 128;
@@ -2183,6 +2183,18 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
             *tail.from_out = full * 256;
             return true;
         }
+    }
+    if (EPI != EPI_RESID && splits == 1 && nz == 1 && row_groups > 1) {
+        // Several row groups: 192 columns where they cost fewer rounds of workgroups times a round's length.  A round of
+        // 256 / 192 / 128 columns takes 1 / 0.82 / 0.73, the last one down to 0.85 of that when it is nearly empty.  Gate/up 256 / 192
+        // columns: 7B shape 400 rows 93 / 80 us (172 / 230 workgroups), 768 entries 180 / 147, 1536 277 / 227, 2048 292 / 303 (688 /
+        // 920, not taken); 34B 512 entries 342 / 290, 1024 544 / 576 (not taken); 70B 512 371 / 428 (not taken).  q|k|v: 7B shape 1536
+        // entries 180 / 151, 70B 1024 166 / 151.
+        auto cost = [](int wgs, float round) {
+            const int full = (wgs - 1) / 256;
+            return round * ((float)full + 0.85f + 0.15f * (float)(wgs - 256 * full) / 256.f);
+        };
+        if (cost((N / 32 + 5) / 6 * row_groups, 0.82f) < cost(n_tiles * row_groups, wide ? 1.0f : 0.73f)) return launch_cols();
     }
     dim3 grid(n_tiles * splits, row_groups, nz);
     if (row_groups > 1) grid = dim3((n_tiles * splits + 7) / 8 * 8 * row_groups, 1, nz);   // see tile_of_block

@@ -120,3 +120,13 @@ def test_shared_positions_against_unshared(rows, hq, hkv, live):
     assert np.isfinite(out[0]).all()
     worst, ok = rows_close(out[0], out[1], TOL["bf16"])
     assert ok, worst
+
+
+# two row groups (the second with 4, 44 and 256 rows): 576, 688 and 688 tile-rows of q|k|v, gate/up and head are one round of
+# 192, 230 and 230 workgroups at 192 columns (the last of 688 with 4 of 6 tile-rows) and 144, 172 and 172 at 256
+@pytest.mark.parametrize("rows", [260, 300, 512])
+def test_products_of_several_row_groups_on_192_columns(rows):
+    from test_gpu_parity import test_calls_one_by_one as calls_one_by_one
+    calls_one_by_one(synth.CONFIGS["llama2_7b"].with_(
+        name=f"cols_b{rows}", n_layers=2, resident=2, d_model=256, n_q_heads=112, n_kv_heads=16, d_ffn=11008, vocab=22016,
+        exit_layers=(1, 2), thresholds=(0.5, 0.0), batch=rows, ctx_lo=1, ctx_hi=12, steps=1))
