@@ -676,16 +676,31 @@ k_exit_decide(const float* __restrict__ part_max, const float* __restrict__ part
         for (int u = 0; u < 4; ++u) sum += s[u] * expf(m[u] - mx);
         st = Stat{mx, sum, arg};
     }
+    // over the lanes, then the waves: the maximum, then every sum once to that maximum, and the lowest column that has it (merged
+    // pair by pair, each step waits for two exponentials)
+    auto over_lanes = [](Stat x) {
+        float m = x.m;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        Stat y{__shfl_xor(st.m, o, 64), __shfl_xor(st.s, o, 64), __shfl_xor(st.a, o, 64)};
-        st = stat_merge(st, y);
-    }
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        float sum = x.s * expf(x.m - m);
+        int arg = x.m == m ? x.a : 0x7fffffff;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            sum += __shfl_xor(sum, o, 64);
+            arg = min(arg, __shfl_xor(arg, o, 64));
+        }
+        return Stat{m, sum, arg};
+    };
+    st = over_lanes(st);
     if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = st;
     __syncthreads();
     if (threadIdx.x == 0) {
-        Stat r = sw[0];
-        for (int w = 1; w < 4; ++w) r = stat_merge(r, sw[w]);
+        Stat r{fmaxf(fmaxf(sw[0].m, sw[1].m), fmaxf(sw[2].m, sw[3].m)), 0.f, 0x7fffffff};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            r.s += sw[w].s * expf(sw[w].m - r.m);
+            if (sw[w].m == r.m) r.a = min(r.a, sw[w].a);
+        }
         float conf = 1.0f / r.s;
         bool met = conf >= threshold;
         head_conf[i] = conf;
