@@ -1958,13 +1958,16 @@ static FewShape few_shape(int tile_rows, int KB, int rows, int nz, int max_split
     float best_t = 1e30f;
     for (int NS = 1; NS <= 4; ++NS)
         for (int sp = 1; sp <= max_splits && (sp == 1 || quads / sp >= 8); ++sp) {
+            const int wgs = (tile_rows + NS - 1) / NS * sp * nz * groups, full = wgs / 256, last = wgs % 256;
             const float steps = 4.0f * ((quads + sp - 1) / sp), w = steps * NS, wx = w + steps * x_kib;    // KiB of a workgroup
+            auto round = [&](int c) {
+                const float a = wx / 50.f, m = c * w / 6300.f, x = c * wx / 15000.f;
+                return std::sqrt(std::sqrt(a * a * a * a + m * m * m * m + x * x * x * x));
+            };
             float t = (rows > 64 ? 0.7f : 0.3f) * sp + (sp > 1 ? sp * rows * tile_rows * (32 * 8) / 4.0e6f : 0.f);              // us
-            int left = (tile_rows + NS - 1) / NS * sp * nz * groups;
-            for (int round = 0; left > 0; ++round, left -= 256) {
-                const float c = (float)std::min(left, 256), a = wx / 50.f, m = c * w / 6300.f, x = c * wx / 15000.f;
-                t += std::sqrt(std::sqrt(a * a * a * a + m * m * m * m + x * x * x * x)) + (round >= 2 ? 1.f : 0.f);
-            }
+            t += std::max(0, full + (last > 0) - 2);
+            if (full > 0) t += full * round(256);
+            if (last > 0) t += round(last);
             if (t < best_t) { best_t = t; best = FewShape{NS, sp}; }
         }
     return best;
