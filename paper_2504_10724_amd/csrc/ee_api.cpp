@@ -652,7 +652,7 @@ int ee_draft_step(const ee_model* m, ee_kv* kv, ee_batch* b, int draft_exit, int
     if (rc != EE_OK) return rc;
     hipStream_t s = as_stream(stream);
     bool x_ready = false;
-    rc = m->cfg.dtype == EE_BF16 ? bf16_begin_step(m, b, s, &x_ready) : launch_begin_step(m, b, s);
+    rc = m->cfg.dtype == EE_BF16 ? bf16_begin_step(m, kv, b, s, &x_ready) : launch_begin_step(m, b, s);
     if (rc == EE_OK) rc = run_layers(m, 1, Le, kv, b, (const float*)m->exits[draft_exit].gain, s, &x_ready, x_ready);
     if (rc == EE_OK) rc = head_on(m, draft_exit, b, s, x_ready);
     if (rc == EE_OK) rc = ee_compact_active(b, draft_exit, Le, stream);          // every row leaves: out_tok = its draft
@@ -759,7 +759,7 @@ static int step_segment(const ee_model* m, ee_kv* kv, ee_batch* b, const float* 
     // begins the step that of the first layer: one launch less
     bool x_ready = false;
     int rc = EE_OK;
-    if (e == 0) rc = c.dtype == EE_BF16 ? bf16_begin_step(m, b, as_stream(s), &x_ready) : launch_begin_step(m, b, as_stream(s));
+    if (e == 0) rc = c.dtype == EE_BF16 ? bf16_begin_step(m, kv, b, as_stream(s), &x_ready) : launch_begin_step(m, b, as_stream(s));
     const int first = e == 0 ? 1 : c.exit_layers[e - 1] + 1, last = c.exit_layers[e];
     for (int l = first; l <= last && rc == EE_OK; ++l) {
         if (c.dtype == EE_BF16) {

@@ -145,7 +145,7 @@ int f32_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_bat
 
 // bf16 path (ee_kernels_bf16.hip)
 // step begin and context-pass begin that also leave the first layer's normalised operand where *x_ready says so
-int bf16_begin_step(const ee_model* m, ee_batch* b, hipStream_t s, bool* x_ready);
+int bf16_begin_step(const ee_model* m, const ee_kv* kv, ee_batch* b, hipStream_t s, bool* x_ready);
 int bf16_prefill_begin(const ee_model* m, const ee_kv* kv, ee_batch* b, const int32_t* tok, const int32_t* pos,
                        const int32_t* seq, int n, hipStream_t s, bool* x_ready);
 int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipStream_t s, bool x_ready = false,

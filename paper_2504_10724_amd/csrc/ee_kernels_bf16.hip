@@ -50,13 +50,66 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 // is rounded as a product with log2 e, an error that grows with |g|: 2.5e-6 of the value at -80.
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
+// ------------------------------------------------------------------ what the decode attention works on
+// What a workgroup of the decode attention has to know before its first load from the cache.  The kernel that normalises a
+// row for the q|k|v product, or the append kernel where there is one, leaves one per list entry, in launch order, so that
+// the attention kernel starts with a single load instead of the chain order -> row -> position -> cache row -> capacity,
+// offset (each a trip to memory).
+struct AttnJob {
+    int32_t entry;      // list entry
+    int32_t n_pos;      // positions read
+    int32_t cap;        // capacity of the cache row
+    int32_t shares;     // workgroups that share its positions, per kv head
+    int64_t off;        // positions of the rows before it
+    int32_t pos;        // the row's position
+    int32_t pad;
+};
+
+// Workgroups that share the positions of one list entry and kv head: as many as keep the live (entry, kv head) pairs
+// within the 512 that run at a time (two per CU), but two up to 384 pairs, and no more than leave each of the four
+// waves two groups of 32 positions.  `most`: what the host launched, from the capacity.  Taken on the device, because
+// only there it is known how many rows are left and how long they are: by the capacities alone, 4 of 16 rows of the
+// 70B shape took 24 us with their merge (19 now; 19 with twice the shares whatever is live), one row of 2000
+// positions 19 (16).  All rows live, attention and merge: 16 rows of the 70B shape 34 us at 1024 workgroups, 31
+// here; 37 rows of 2 kv heads, up to 900 positions, 27 and 17; 12 entries of four contexts at the 7B shape (384
+// pairs) 64 unshared, 55 in two; 60 entries (480 pairs) of the 70B shape 46 in two, 41 unshared.
+__device__ __forceinline__ int attn_shares(int pairs, int n_pos, int most) {
+    return max(1, min(min(most, n_pos >> 8), max(512 / pairs, pairs <= 384 ? 2 : 1)));
+}
+
+struct JobArgs {        // jobs == nullptr: none are left
+    const int32_t* pos; const int32_t* cap; const int64_t* off;
+    AttnJob* jobs;
+    int n_kv_heads, most;
+};
+
+// Called by every thread of a block of NORM_THREADS that works on list entry i of n: its last wave leaves the entry's job
+// at the entry's rank by falling position (ties by entry), so that the longest rows start first and the last round of
+// workgroups is short.  Batch row b is cache row b.
+#define NORM_THREADS 1024
+template <class Row>
+__device__ __forceinline__ void leave_job(const JobArgs& a, int i, int n, Row row_of) {
+    if (a.jobs == nullptr || threadIdx.x < NORM_THREADS - 64) return;
+    const int row = row_of(i), mine = a.pos[row];
+    int before = 0;
+    for (int j = threadIdx.x - (NORM_THREADS - 64); j < n; j += 64) {
+        const int kj = a.pos[row_of(j)];
+        before += (kj > mine || (kj == mine && j < i)) ? 1 : 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    if (threadIdx.x == NORM_THREADS - 64) {
+        const int cap = a.cap[row], n_pos = max(1, min(mine + 1, cap));
+        a.jobs[before] = AttnJob{i, n_pos, cap, attn_shares(n * a.n_kv_heads, n_pos, a.most), a.off[row], mine, 0};
+    }
+}
+
 // ------------------------------------------------------------------ RMSNorm -> A tiles
 // The NORM_THREADS threads of a block normalise one row (hr: d floats) and write it as list entry
 // i of the [Mpad][d] activation matrix in tile order.  Every thread reads only the 8-float chunks
 // c = threadIdx.x + NORM_THREADS j, so a caller may have written those same chunks just before.
 // (1024 threads: one chunk each at d = 8192; the kernels here are latency bound, and every
 // user of this routine takes the same thread count so that all give the same bits.)
-#define NORM_THREADS 1024
 // Sum of the squares of a chunk, its fused multiply-adds written out: every kernel that normalises a row (here, the
 // finish of a sliced product, the step begin) has to give the same bits, and left to the compiler which of the
 // products of a sum are fused differs from kernel to kernel.
@@ -122,11 +175,12 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
 // one block per list entry i; out is the [Mpad][d] activation matrix in tile order
 __global__ void __launch_bounds__(NORM_THREADS)
 k_bf16_rmsnorm(const float* __restrict__ h, const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr,
-               int B, int near, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ out, ZBatch zb) {
+               int B, int near, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ out, ZBatch zb, JobArgs ja) {
     __shared__ float red[NORM_THREADS / 64];
     int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
     if (i >= n) return;
+    leave_job(ja, i, n, [&](int j) { return idx[j]; });
     if (zb.g_tab) gain = zb.g_tab[zb.z0 + blockIdx.z];
     out += (int64_t)blockIdx.z * zb.x_stride;
     rmsnorm_row(h + (int64_t)idx[i] * d, gain, eps, d, out, i, red);
@@ -146,10 +200,11 @@ struct BeginArgs {
 
 template <bool CTX>
 __global__ void __launch_bounds__(NORM_THREADS)
-k_bf16_begin_norm(BeginArgs g, int near, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ xout) {
+k_bf16_begin_norm(BeginArgs g, int near, const float* __restrict__ gain, float eps, int d, uint4* __restrict__ xout, JobArgs ja) {
     __shared__ float red[NORM_THREADS / 64];
     const int i = entry_of_block(blockIdx.x, near);
     if (i >= g.n) return;
+    if constexpr (!CTX) leave_job(ja, i, g.n, [](int j) { return j; });
     int t = g.tok[i];
     const bool bad = t < 0 || t >= g.V;
     if (threadIdx.x == 0) {
@@ -1108,30 +1163,6 @@ k_bf16_gemm_few(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int 
     }
 }
 
-// What a workgroup of the decode attention has to know before its first load from the cache.  The RoPE kernel
-// leaves one per list entry, in launch order, so that the attention kernel starts with a single load instead of
-// the chain order -> row -> position -> cache row -> capacity, offset (each a trip to memory).
-struct AttnJob {
-    int32_t entry;      // list entry
-    int32_t n_pos;      // positions read
-    int32_t cap;        // capacity of the cache row
-    int32_t shares;     // workgroups that share its positions, per kv head
-    int64_t off;        // positions of the rows before it
-    int64_t pad2;
-};
-
-// Workgroups that share the positions of one list entry and kv head: as many as keep the live (entry, kv head) pairs
-// within the 512 that run at a time (two per CU), but two up to 384 pairs, and no more than leave each of the four
-// waves two groups of 32 positions.  `most`: what the host launched, from the capacity.  Taken on the device, because
-// only there it is known how many rows are left and how long they are: by the capacities alone, 4 of 16 rows of the
-// 70B shape took 24 us with their merge (19 now; 19 with twice the shares whatever is live), one row of 2000
-// positions 19 (16).  All rows live, attention and merge: 16 rows of the 70B shape 34 us at 1024 workgroups, 31
-// here; 37 rows of 2 kv heads, up to 900 positions, 27 and 17; 12 entries of four contexts at the 7B shape (384
-// pairs) 64 unshared, 55 in two; 60 entries (480 pairs) of the 70B shape 46 in two, 41 unshared.
-__device__ __forceinline__ int attn_shares(int pairs, int n_pos, int most) {
-    return max(1, min(min(most, n_pos >> 8), max(512 / pairs, pairs <= 384 ? 2 : 1)));
-}
-
 // ------------------------------------------------------------------ RoPE + cache append
 // buf[i] = [q (n_q heads, may be 0) | k (Hkv heads) | v (Hkv heads)], fp32, hd = 128.
 // Queries are rotated and written as a bf16 pair (hi, lo) with hi + lo = q to 16
@@ -1172,7 +1203,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
         if (threadIdx.x == 0) {
             if (jobs != nullptr) {
                 const int n_pos = max(1, min(p + 1, cap));
-                jobs[before] = AttnJob{tile, n_pos, cap, attn_shares(n * kv.n_kv_heads, n_pos, most_shares), kv.off[sq], 0};
+                jobs[before] = AttnJob{tile, n_pos, cap, attn_shares(n * kv.n_kv_heads, n_pos, most_shares), kv.off[sq], p, 0};
             } else {
                 order[before] = tile;
             }
@@ -1290,12 +1321,115 @@ struct AttnShared {
     float o[4][16][128];
 };
 
-template <bool PAIR, bool AHEAD>
+// Rotation and append in the attention of a decode step (FUSED): the q|k|v product's result is taken as it is (its columns
+// before `from` from buf, the others as `splits` K-slice planes, as in k_bf16_rope_append).  Wave 0 and 1 rotate the queries of
+// the workgroup's heads (features 32 c + .. and 32 c + 64 + .. are pairs, c = 0 and 1) and leave them as (hi, lo) pairs in
+// LDS, wave 3 rotates and appends the key and appends the value, all while the other waves' first cached keys and values are
+// on their way.  The group that holds the new position is read after the barrier, from L2.  As a launch of its own this took 3.5 to 4 us on a few
+// rows; which calls come here: append_in_attn.
+struct QkvIn {
+    const float* buf; int ld, from;
+    const float* planes; int ld_planes, splits; int64_t plane;
+    const float* rope; int max_pos;
+    int32_t* status;
+    // N times 4 columns of entry i (x[k] a multiple of 4, all on one side of `from`): the loads of two planes under way together
+    template <int N>
+    __device__ __forceinline__ void rd4(int i, const int (&x)[N], float4 (&v)[N]) const {
+        const bool done = x[0] < from;
+        const float* p = done ? buf + (int64_t)i * ld : planes + (int64_t)i * ld_planes - from;
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = *reinterpret_cast<const float4*>(p + x[k]);
+        if (done) return;
+        for (int q = 1; q < splits; q += 2) {
+            float4 u[2][N];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int k = 0; k < N; ++k) u[h][k] = *reinterpret_cast<const float4*>(p + x[k] + min(q + h, splits - 1) * plane);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (q + h >= splits) break;
+#pragma unroll
+                for (int k = 0; k < N; ++k) { v[k].x += u[h][k].x; v[k].y += u[h][k].y; v[k].z += u[h][k].z; v[k].w += u[h][k].w; }
+            }
+        }
+    }
+};
+
+// four rotation pairs: columns j .. j + 3 (a) with j + 64 .. (b), cs = cos, sin of the first
+__device__ __forceinline__ void rotate4(const float4& a, const float4& b, const float* cs, float (&x0)[4], float (&x1)[4]) {
+    const float4 c0 = *reinterpret_cast<const float4*>(cs), c1 = *reinterpret_cast<const float4*>(cs + 4);
+    x0[0] = a.x * c0.x - b.x * c0.y; x0[1] = a.y * c0.z - b.y * c0.w; x0[2] = a.z * c1.x - b.z * c1.y; x0[3] = a.w * c1.z - b.w * c1.w;
+    x1[0] = b.x * c0.x + a.x * c0.y; x1[1] = b.y * c0.z + a.y * c0.w; x1[2] = b.z * c1.x + a.z * c1.y; x1[3] = b.w * c1.z + a.w * c1.w;
+}
+
+// what wave w of the workgroup (kv head g, job) does of it; qs: [c][hi, lo][lane]
+__device__ __forceinline__ void rotate_append(uint4 (&qs)[4][2][64], const QkvIn& in, const KvView& kv, const AttnJob& job, int Hq, int g,
+                                              bool appends) {
+    const int G = Hq / kv.n_kv_heads, i = job.entry, p = job.pos;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n16 = lane & 15, gq = lane >> 4;
+    const bool ok = p >= 0 && p < job.cap && p < in.max_pos;
+    const float* cs = in.rope + (int64_t)(ok ? p : 0) * 128;
+    if (w < 2) {
+        const int x = (g * G + (n16 < G ? n16 : 0)) * 128 + 32 * w + 8 * gq;      // columns without a head read head 0
+        float lo[8], hi[8];
+        const int xs[4] = {x, x + 4, x + 64, x + 68};
+        float4 v[4];
+        in.rd4(i, xs, v);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float x0[4], x1[4];
+            rotate4(v[h], v[2 + h], cs + 2 * (32 * w + 8 * gq + 4 * h), x0, x1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { lo[4 * h + k] = x0[k]; hi[4 * h + k] = x1[k]; }
+        }
+        auto put = [&](int c, const float (&v)[8]) {
+            uint32_t a[4], b[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                a[k] = pack2(v[2 * k], v[2 * k + 1]);
+                b[k] = pack2(v[2 * k] - __uint_as_float(a[k] << 16), v[2 * k + 1] - __uint_as_float(a[k] & 0xffff0000u));
+            }
+            qs[c][0][lane] = make_uint4(a[0], a[1], a[2], a[3]);
+            qs[c][1][lane] = make_uint4(b[0], b[1], b[2], b[3]);
+        };
+        put(w, lo);
+        put(w + 2, hi);
+        return;
+    }
+    if (!appends || w != 3) return;
+    if (!ok) {
+        if (lane == 0 && g == 0) atomicOr(in.status, 1);
+        return;
+    }
+    bf16_t* base = reinterpret_cast<bf16_t*>(kv.pool) + ((int64_t)kv.layer0 * kv.T + job.off) * (2LL * kv.n_kv_heads * 128) +
+                   (int64_t)g * 2LL * job.cap * 128;
+    // lanes 0 .. 15 four pairs of the key each, lanes 32 .. 63 four values each
+    if (lane < 16) {
+        const int j0 = 4 * lane, x = (Hq + g) * 128 + j0;
+        const int xs[2] = {x, x + 64};
+        float4 v[2];
+        in.rd4(i, xs, v);
+        float x0[4], x1[4];
+        rotate4(v[0], v[1], cs + 2 * j0, x0, x1);
+        *reinterpret_cast<uint2*>(base + k_bf16_offset(p, j0, 128)) = make_uint2(pack2(x0[0], x0[1]), pack2(x0[2], x0[3]));
+        *reinterpret_cast<uint2*>(base + k_bf16_offset(p, j0 + 64, 128)) = make_uint2(pack2(x1[0], x1[1]), pack2(x1[2], x1[3]));
+    } else if (lane >= 32) {
+        const int f = 4 * (lane - 32);
+        const int xs[1] = {(Hq + kv.n_kv_heads + g) * 128 + f};
+        float4 v[1];
+        in.rd4(i, xs, v);
+        bf16_t* at = base + v_bf16_offset(p, f, 128);         // neighbouring features are 8 positions apart
+        at[0] = f32_to_bf16(v[0].x); at[8] = f32_to_bf16(v[0].y); at[16] = f32_to_bf16(v[0].z); at[24] = f32_to_bf16(v[0].w);
+    }
+}
+
+template <bool PAIR, bool AHEAD, bool FUSED = false>
 __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo,
                                              int Hq, const int32_t* __restrict__ idx, const int32_t* __restrict__ pos,
                                              const KvView& kv, uint4* __restrict__ ao, int KB_ao, int n_splits, int share,
                                              float* __restrict__ part, int most, int g, int first, int cnt,
-                                             const AttnJob& job = AttnJob{}) {
+                                             const AttnJob& job = AttnJob{}, const QkvIn& in = QkvIn{}, uint4 (*qs)[2][64] = nullptr) {
     const int G = Hq / kv.n_kv_heads;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int n16 = lane & 15, gq = lane >> 4;
@@ -1324,7 +1458,7 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     const int my_head = n16 - my_ent * G;
 
     bf16x8 qh[4], ql[4];
-    {
+    if constexpr (!FUSED) {
         // Columns without a head read head 0 (their results are not written): eight 16-byte loads.  With a condition
         // on them they became 32 loads of 4 bytes, each with a branch of its own, at the start of every run of
         // entries: 1024 rows of 30 to 100 positions at the 7B shape 438 us, 362 now; 16 rows of the 70B shape in
@@ -1362,7 +1496,21 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     // equal at 256).  Context pass with two entries per workgroup: three workgroups, no prefetch
     // (0.8 % faster there).
     KVTiles nxt;
-    if constexpr (AHEAD) nxt = load_kv(min(g_lo + w, max(g_hi - 1, 0)));   // a group this workgroup's row has
+    if constexpr (AHEAD) {
+        const int t0 = min(g_lo + w, max(g_hi - 1, 0));                     // a group this workgroup's row has
+        // it holds the position that is appended below, or belongs to the wave that appends and waits for its stores
+        const bool late = FUSED && (t0 == n_groups - 1 || w == 3);
+        if (!late) nxt = load_kv(t0);
+        if constexpr (FUSED) {
+            rotate_append(*reinterpret_cast<uint4 (*)[4][2][64]>(qs), in, kv, job, Hq, g, share == n_splits - 1);
+            // the appending wave: key and value have arrived in L2
+            if (w == 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (late) nxt = load_kv(t0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { qh[c] = as_bf16x8(qs[c][0][lane]); ql[c] = as_bf16x8(qs[c][1][lane]); }
+        }
+    }
 
     const float inv_sqrt = 1.0f / sqrtf(128.0f);
     const float NEG = -1.0e30f;
@@ -1508,6 +1656,20 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
         attn_streams<false, true>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, job.shares, blockIdx.z, part, most, blockIdx.x,
                                   job.entry, 1, job);
     }
+}
+
+// The attention of a decode step with rotation and append: batch row b owns cache row b, and no workgroup reads what another
+// one appends.
+__global__ void __launch_bounds__(256, 2)
+k_bf16_attn_decode(QkvIn in, int Hq, const int32_t* __restrict__ n_ptr, int B, KvView kv, uint4* __restrict__ ao, int KB_ao, int most,
+                   float* __restrict__ part, const AttnJob* __restrict__ jobs) {
+    __shared__ AttnShared sm;
+    __shared__ uint4 qs[4][2][64];
+    const int n = min(*n_ptr, B);
+    const AttnJob job = jobs[blockIdx.y];      // longest contexts first; slots from n on are not read further
+    if ((int)blockIdx.y >= n || (int)blockIdx.z >= job.shares) return;
+    attn_streams<false, true, true>(sm, nullptr, nullptr, Hq, nullptr, nullptr, kv, ao, KB_ao, job.shares, blockIdx.z, part, most,
+                                    blockIdx.x, job.entry, 1, job, in, qs);
 }
 
 // ------------------------------------------------------------------ context-pass attention
@@ -1879,11 +2041,12 @@ k_splitk_finish(const float* __restrict__ partial, int64_t plane, int ld, int sp
 __global__ void __launch_bounds__(NORM_THREADS)
 k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, int splits, int N,
                     const int32_t* __restrict__ n_ptr, int B, int near, float* h, int ldh, const int32_t* __restrict__ idx,
-                    const float* gain, float eps, uint4* xout) {
+                    const float* gain, float eps, uint4* xout, JobArgs ja) {
     __shared__ float red[NORM_THREADS / 64];
     const int n = min(*n_ptr, B);
     const int i = entry_of_block(blockIdx.x, near);
     if (i >= n) return;
+    leave_job(ja, i, n, [&](int j) { return idx[j]; });
     float* hrow = h + (int64_t)idx[i] * ldh;
     const float* prow = partial + (int64_t)i * ld;
     if ((N >> 3) <= NORM_THREADS) {
@@ -1982,6 +2145,7 @@ struct SliceTail {
     bool         defer_store = false;   // STORE: leave the planes to the caller ...
     int*         splits_out = nullptr;  // ... who gets their number (1 = the result is in out already)
     int*         from_out = nullptr;    // ... and the first column that is in planes (those before it are in out)
+    JobArgs      jobs = {};             // RESID: the attention jobs to leave beside the norm
 };
 
 // the launch that adds the K-slice planes of a product, where there are any and the caller does not do it itself
@@ -1993,7 +2157,7 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
     const int64_t plane = (int64_t)((B + 31) / 32 * 32) * N;
     if (EPI == EPI_RESID) {
         hipLaunchKernelGGL(k_splitk_resid_norm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->wsp<float>(b->W.gemm_part),
-                           plane, N, splits, N, n_ptr, B, entry_near(B), ep.out, ep.ldo, ep.idx, tail.norm_gain, tail.eps, tail.norm_out);
+                           plane, N, splits, N, n_ptr, B, entry_near(B), ep.out, ep.ldo, ep.idx, tail.norm_gain, tail.eps, tail.norm_out, tail.jobs);
         if (tail.norm_gain && tail.norm_done) *tail.norm_done = true;
     } else if (!tail.defer_store) {
         hipLaunchKernelGGL((k_splitk_finish<EPI_STORE>), dim3((N / 4 + 255) / 256, B), dim3(256), 0, s,
@@ -2235,11 +2399,35 @@ static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
     return r;
 }
 
+// Most workgroups per (row, kv head) of the decode attention (attn_shares).  Positions are shared only where the longest
+// row is worth the launch that merges them: 672 positions (attention and merge of 8 kv heads, 1 row of 500: layer 1 us
+// longer shared, of 950: 3 us shorter), with 192 pairs 1024 (60 rows of 4 kv heads, 650: 78.5 us shared, 75.3 whole,
+// 950: 84.1 and 81.1; 12 rows of 32, 650: 120.5 and 117.6).
+static int attn_most(const ee_model_config& c, const ee_kv* kv, const ee_batch* b) {
+    const int pairs = c.n_kv_heads * b->B;
+    int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, kv->max_cap / 256});
+    while (most > 1 && (size_t)b->Mpad * c.n_kv_heads * most * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --most;
+    return most;
+}
+
+// Whether rotation and append are part of the attention (k_bf16_attn_decode): in a decode step (with entries that name their
+// cache row one may read what another appends), up to 768 (row, kv head) pairs.  Beyond, the workgroups' start is no longer hidden
+// and costs more than the launch.  Layer, separate / together: 7B shape 8 rows (256 pairs) 103.7 / 101.0 us, 20 rows (640)
+// 121.6 / 119.5, 40 (1280) 118.7 / 122.5, 512 1106 / 1141; 34B 128 rows (1024) 419 / 422; 2048-wide model 100 rows (400) 98.1 /
+// 93.4; 576-wide model 20 rows (40) 43.1 / 41.0.
+static bool append_in_attn(const ee_model_config& c, const ee_batch* b) { return b->kv_seq == nullptr && c.n_kv_heads * b->B <= 768; }
+
+// the jobs that the kernel which normalises for a layer's q|k|v product leaves; elsewhere the append kernel does
+static JobArgs attn_jobs(const ee_model_config& c, const ee_kv* kv, const ee_batch* b) {
+    if (!append_in_attn(c, b)) return JobArgs{};
+    return JobArgs{b->st<int32_t>(b->L.pos), kv->d_cap, kv->d_off, b->wsp<AttnJob>(b->W.attn_order), c.n_kv_heads, attn_most(c, kv, b)};
+}
+
 static bool begin_norm_fits(const ee_model* m) {
     return m->cfg.d_model <= 8 * NORM_THREADS && (uintptr_t)m->emb % 16 == 0;
 }
 
-int bf16_begin_step(const ee_model* m, ee_batch* b, hipStream_t s, bool* x_ready) {
+int bf16_begin_step(const ee_model* m, const ee_kv* kv, ee_batch* b, hipStream_t s, bool* x_ready) {
     *x_ready = begin_norm_fits(m);
     if (!*x_ready) return launch_begin_step(m, b, s);
     const ee_batch_layout& L = b->L;
@@ -2249,7 +2437,7 @@ int bf16_begin_step(const ee_model* m, ee_batch* b, hipStream_t s, bool* x_ready
     g.active_idx = b->st<int32_t>(L.active_idx); g.n_active = b->st<int32_t>(L.n_active);
     g.n_exited = b->st<int32_t>(L.n_exited); g.out_layer = b->st<int32_t>(L.out_layer); g.status = b->st<int32_t>(L.status);
     hipLaunchKernelGGL(k_bf16_begin_norm<false>, dim3(entry_grid(b->B)), dim3(NORM_THREADS), 0, s, g, entry_near(b->B),
-                       (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x));
+                       (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x), attn_jobs(m->cfg, kv, b));
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
@@ -2266,7 +2454,7 @@ int bf16_prefill_begin(const ee_model* m, const ee_kv* kv, ee_batch* b, const in
     g.kv_seq = b->wsp<int32_t>(b->W.kv_seq); g.active_idx = b->st<int32_t>(L.active_idx);
     g.n_active = b->st<int32_t>(L.n_active); g.n_exited = b->st<int32_t>(L.n_exited); g.status = b->st<int32_t>(L.status);
     hipLaunchKernelGGL(k_bf16_begin_norm<true>, dim3(entry_grid(n)), dim3(NORM_THREADS), 0, s, g, entry_near(n),
-                       (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x));
+                       (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x), JobArgs{});
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
@@ -2290,17 +2478,12 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     bf16_t* act = b->wsp<bf16_t>(b->W.act);
     KvView view = make_view(m, kv, layer, b);
     const CtxTiles ctx = ctx_tiles(c, b);
-    // Most workgroups per (row, kv head) of the decode attention (attn_shares).  Positions are shared only where the longest
-    // row is worth the launch that merges them: 672 positions (attention and merge of 8 kv heads, 1 row of 500: layer 1 us
-    // longer shared, of 950: 3 us shorter), with 192 pairs 1024 (60 rows of 4 kv heads, 650: 78.5 us shared, 75.3 whole,
-    // 950: 84.1 and 81.1; 12 rows of 32, 650: 120.5 and 117.6).
-    const int pairs = c.n_kv_heads * B;
-    int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, kv->max_cap / 256});
-    while (most > 1 && (size_t)b->Mpad * c.n_kv_heads * most * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --most;
+    const int pairs = c.n_kv_heads * B, most = attn_most(c, kv, b);
+    const JobArgs jobs = attn_jobs(c, kv, b);
 
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_attn, c.rms_eps, d, x, ZBatch{});
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_attn, c.rms_eps, d, x, ZBatch{}, jobs);
     }
     EpiArgs e1{};
     e1.out = qkv; e1.ldo = qkv_n; e1.idx = idx;
@@ -2312,11 +2495,12 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         if (!gemm_tiled<EPI_STORE>(b, x, w.w_qkv, qkv_n, d, qkv_n / 32, 0, n_ptr, B, e1, s, ZBatch{}, 1, st))
             gemm<1, EPI_STORE>(x, w.w_qkv, qkv_n, d, qkv_n / 32, 0, n_ptr, B, e1, s);
     }
-    {
+    if (qkv_splits == 1) qkv_from = qkv_n;             // nothing is in planes
+    const bool together = append_in_attn(c, b);
+    if (!together) {
         TimedScope t(EE_K_ROPE_APPEND, s);
         // neighbouring entries share lines of the cache only where they are positions of one row (context pass)
         const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
-        if (qkv_splits == 1) qkv_from = qkv_n;         // nothing is in planes
         hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(c.n_q_heads, c.n_kv_heads, B)), dim3(256), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B, near,
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
@@ -2329,7 +2513,12 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         // context pass: 16 / G entries per workgroup, which share the K/V stream where they sit in the same cache row
         const int G = c.n_q_heads / c.n_kv_heads;
         const bool pair = b->kv_seq != nullptr && pairs >= 512 && 2 * G <= 16;
-        if (ctx.C) {
+        if (together) {
+            const QkvIn in{qkv, qkv_n, qkv_from, b->wsp<float>(b->W.gemm_part), qkv_n - qkv_from, qkv_splits,
+                           (int64_t)b->Mpad * (qkv_n - qkv_from), m->d_rope, c.max_pos, b->st<int32_t>(L.status)};
+            hipLaunchKernelGGL(k_bf16_attn_decode, dim3(c.n_kv_heads, B, most), dim3(256), 0, s, in, c.n_q_heads, n_ptr, B, view, ao, qd / 16,
+                               most, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
+        } else if (ctx.C) {
             auto kern = ctx.C == 2 ? k_bf16_attn_ctx<2> : k_bf16_attn_ctx<1>;
             hipLaunchKernelGGL(kern, dim3(c.n_kv_heads, ctx.tiles * 4 * ctx.C), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
@@ -2358,7 +2547,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     }
     if (!ffn_x_done) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_ffn, c.rms_eps, d, x, ZBatch{});
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_ffn, c.rms_eps, d, x, ZBatch{}, JobArgs{});
     }
     EpiArgs e3{};
     e3.act = act; e3.KB_act = F / 16; e3.idx = idx;
@@ -2371,6 +2560,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         TimedScope t(EE_K_GEMM_DOWN, s);
         SliceTail st;
         st.norm_gain = tail_gain; st.eps = c.rms_eps; st.norm_out = x; st.norm_done = x_done;
+        if (tail_gain) st.jobs = jobs;
         if (!gemm_tiled<EPI_RESID>(b, act, w.w_down, d, F, d / 32, 0, n_ptr, B, e2, s, ZBatch{}, 1, st))
             gemm<1, EPI_RESID>(act, w.w_down, d, F, d / 32, 0, n_ptr, B, e2, s);
     }
@@ -2389,7 +2579,7 @@ int bf16_exit_head(const ee_model* m, int e, float th, int force, ee_batch* b, f
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
         hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
-                           m->exits[e].gain, c.rms_eps, d, x, ZBatch{});
+                           m->exits[e].gain, c.rms_eps, d, x, ZBatch{}, JobArgs{});
     }
     EpiArgs ep{};
     ep.idx = idx; ep.row_scale = b->st<float>(L.row_scale);
@@ -2422,7 +2612,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     zb.w_tab = m->d_wqkv_tab; zb.g_tab = m->d_gattn_tab; zb.z0 = from_excl;
     zb.x_stride = (int64_t)b->Mpad * d / 8; zb.out_stride = (int64_t)b->Mpad * kv_n;
     hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B), 1, nl), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
-                       (const float*)nullptr, c.rms_eps, d, x, zb);
+                       (const float*)nullptr, c.rms_eps, d, x, zb, JobArgs{});
     // key and value rows are the last 2*H_kv*hd rows of W_qkv: tile-rows H_q*hd/32 onwards
     EpiArgs ep{};
     ep.out = kvb; ep.ldo = kv_n; ep.idx = idx;
