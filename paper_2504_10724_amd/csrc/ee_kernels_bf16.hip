@@ -496,9 +496,12 @@ __device__ __forceinline__ void epilogue_one(const EpiArgs& ep, const floatx16& 
         const float m2 = __shfl_xor(mx, 32, 64);
         const int a2 = __shfl_xor(arg, 32, 64);
         if (m2 > mx || (m2 == mx && a2 < arg)) { mx = m2; arg = a2; }
+        // On the hardware's base-2 exponential: its argument -a is rounded as a product with log2 e, a relative error of about
+        // 6e-8 a on a term of size exp(-a), at most 3e-8 of the sum, which holds exp(0).  expf takes about 20 instructions for
+        // each of a lane's up to 128 logits: head of 192 rows at the 70B shape 132 us with it, 128 so, of 200 rows at 7B 86 and 82.
         float se = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) se += expf(z[r] - mx);
+        for (int r = 0; r < 16; ++r) se += __builtin_amdgcn_exp2f((z[r] - mx) * 1.44269504088896340736f);
         se += __shfl_xor(se, 32, 64);
         if (live && lane < 32) {
             const int64_t at = (int64_t)row * ep.n_part + nb;
