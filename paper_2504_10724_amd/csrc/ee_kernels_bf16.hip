@@ -1305,7 +1305,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
 }
 
 // ------------------------------------------------------------------ decode attention
-// One workgroup per (kv head g, list entry i); its 4 waves take the 32-position
+// One workgroup per (kv head g, list entry i); its waves (four, or one for short rows) take the 32-position
 // groups of the row's cache round-robin and are merged at the end.  Per group:
 //   S^T[pos][head] = K[pos][:] . q[head][:]   two 16x16x32 MFMAs per 32 features
 //   online softmax over positions (fp32, per head)
@@ -1318,10 +1318,11 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
 // The work of one workgroup: list entries first .. first + cnt - 1 of kv head g, share `share` of n_splits of
 // the position groups.  AHEAD: a wave asks for its next group before it works on the current one.
 #define ATTN_SHARE 132      /* floats of one head's share of a row: a multiple of four, so that they move 16 bytes at a time */
+template <int WAVES>
 struct AttnShared {
-    float m[4][16];
-    float l[4][16];
-    float o[4][16][128];
+    float m[WAVES][16];
+    float l[WAVES][16];
+    float o[WAVES][16][132];    // 128 features; rows of 132 floats put a 16-byte access of the 16 columns into different banks
 };
 
 // Rotation and append in the attention of a decode step (FUSED): the q|k|v product's result is taken as it is (its columns
@@ -1427,8 +1428,8 @@ __device__ __forceinline__ void rotate_append(uint4 (&qs)[4][2][64], const QkvIn
     }
 }
 
-template <bool PAIR, bool AHEAD, bool FUSED = false>
-__device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo,
+template <bool PAIR, bool AHEAD, bool FUSED, int WAVES>
+__device__ __forceinline__ void attn_streams(AttnShared<WAVES>& sm, const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo,
                                              int Hq, const int32_t* __restrict__ idx, const int32_t* __restrict__ pos,
                                              const KvView& kv, uint4* __restrict__ ao, int KB_ao, int n_splits, int share,
                                              float* __restrict__ part, int most, int g, int first, int cnt,
@@ -1522,12 +1523,12 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
 #pragma unroll
     for (int hb = 0; hb < 8; ++hb) O[hb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    for (int t = g_lo + w; t < g_hi; t += 4) {
+    for (int t = g_lo + w; t < g_hi; t += WAVES) {
         const int p0 = t << 5;
         KVTiles cur;
         if constexpr (AHEAD) {
             cur = nxt;
-            if (t + 4 < g_hi) nxt = load_kv(t + 4);
+            if (t + WAVES < g_hi) nxt = load_kv(t + WAVES);
         } else {
             cur = load_kv(t);
         }
@@ -1594,40 +1595,39 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
     if (gq == 0) { sm.m[w][n16] = m_run; sm.l[w][n16] = l_run; }
+    if (n16 < n_col) {
 #pragma unroll
-    for (int hb = 0; hb < 8; ++hb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sm.o[w][n16][16 * hb + 4 * gq + r] = O[hb][r];
+        for (int hb = 0; hb < 8; ++hb)
+            *reinterpret_cast<float4*>(&sm.o[w][n16][16 * hb + 4 * gq]) = make_float4(O[hb][0], O[hb][1], O[hb][2], O[hb][3]);
+    }
     __syncthreads();
-    {
-        const int head = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 8;     // head = MFMA column
-        if (head < n_col) {
-            const int i = first + r0 + head / G;
-            const int hq = head % G;
-            float M = fmaxf(fmaxf(sm.m[0][head], sm.m[1][head]), fmaxf(sm.m[2][head], sm.m[3][head]));
-            float wgt[4], Lsum = 0.f;
+    for (int tt = threadIdx.x; tt < n_col * 16; tt += 64 * WAVES) {
+        const int head = tt >> 4, c0 = (tt & 15) * 8;      // head = MFMA column
+        const int i = first + r0 + head / G;
+        const int hq = head % G;
+        float M = sm.m[0][head];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { wgt[k] = __expf(sm.m[k][head] - M); Lsum += sm.l[k][head] * wgt[k]; }
-            float o[8];
+        for (int k = 1; k < WAVES; ++k) M = fmaxf(M, sm.m[k][head]);
+        float Lsum = 0.f, o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                float acc = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) acc += sm.o[k][head][c0 + j] * wgt[k];
-                o[j] = acc;
-            }
-            if (n_splits == 1) {
-                uint4 pk = make_uint4(pack2(o[0] / Lsum, o[1] / Lsum), pack2(o[2] / Lsum, o[3] / Lsum),
-                                      pack2(o[4] / Lsum, o[5] / Lsum), pack2(o[6] / Lsum, o[7] / Lsum));
-                int col = (g * G + hq) * 128 + c0;
-                ao[afrag_chunk(i, col, KB_ao)] = pk;
-            } else {
-                // unnormalised share: [i][kv head][share, `most` of them][head][132] = 128 features, max, sum, two unused
-                float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * most + share) * 16 + hq) * ATTN_SHARE;
-                *reinterpret_cast<float4*>(p + c0) = make_float4(o[0], o[1], o[2], o[3]);
-                *reinterpret_cast<float4*>(p + c0 + 4) = make_float4(o[4], o[5], o[6], o[7]);
-                if (c0 == 0) { p[128] = M; p[129] = Lsum; }
-            }
+        for (int k = 0; k < WAVES; ++k) {
+            const float wgt = __expf(sm.m[k][head] - M);
+            Lsum += sm.l[k][head] * wgt;
+            const float4 u = *reinterpret_cast<const float4*>(&sm.o[k][head][c0]), v = *reinterpret_cast<const float4*>(&sm.o[k][head][c0 + 4]);
+            o[0] += u.x * wgt; o[1] += u.y * wgt; o[2] += u.z * wgt; o[3] += u.w * wgt;
+            o[4] += v.x * wgt; o[5] += v.y * wgt; o[6] += v.z * wgt; o[7] += v.w * wgt;
+        }
+        if (n_splits == 1) {
+            uint4 pk = make_uint4(pack2(o[0] / Lsum, o[1] / Lsum), pack2(o[2] / Lsum, o[3] / Lsum),
+                                  pack2(o[4] / Lsum, o[5] / Lsum), pack2(o[6] / Lsum, o[7] / Lsum));
+            int col = (g * G + hq) * 128 + c0;
+            ao[afrag_chunk(i, col, KB_ao)] = pk;
+        } else {
+            // unnormalised share: [i][kv head][share, `most` of them][head][132] = 128 features, max, sum, two unused
+            float* p = part + ((((int64_t)i * kv.n_kv_heads + g) * most + share) * 16 + hq) * ATTN_SHARE;
+            *reinterpret_cast<float4*>(p + c0) = make_float4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<float4*>(p + c0 + 4) = make_float4(o[4], o[5], o[6], o[7]);
+            if (c0 == 0) { p[128] = M; p[129] = Lsum; }
         }
     }
     r0 = r1;
@@ -1635,13 +1635,13 @@ __device__ __forceinline__ void attn_streams(AttnShared& sm, const bf16_t* __res
     }
 }
 
-template <bool PAIR>
-__global__ void __launch_bounds__(256, PAIR ? 3 : 2)
+template <bool PAIR, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, PAIR ? 3 : 2)
 k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, int Hq,
             const int32_t* __restrict__ idx, const int32_t* __restrict__ n_ptr, int B,
             const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao, int KB_ao, int most,
             float* __restrict__ part, const AttnJob* __restrict__ jobs) {
-    __shared__ AttnShared sm;
+    __shared__ AttnShared<WAVES> sm;
     const int n = min(*n_ptr, B);
     // PAIR (context pass and other passes over list entries, 2 G <= 16): the workgroup serves the E = 16 / G
     // list entries E y .. E y + E - 1.  Consecutive entries that read the same cache row (a context passed
@@ -1652,11 +1652,11 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
     if constexpr (PAIR) {
         const int E = 16 / (Hq / kv.n_kv_heads), first = E * (int)blockIdx.y;
         if (first >= n) return;
-        attn_streams<true, false>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr, 1, blockIdx.x, first, min(E, n - first));
+        attn_streams<true, false, false, WAVES>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr, 1, blockIdx.x, first, min(E, n - first));
     } else {
         const AttnJob job = jobs[blockIdx.y];  // longest contexts first; slots from n on are not read further
         if ((int)blockIdx.y >= n || (int)blockIdx.z >= job.shares) return;
-        attn_streams<false, true>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, job.shares, blockIdx.z, part, most, blockIdx.x,
+        attn_streams<false, true, false, WAVES>(sm, q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, job.shares, blockIdx.z, part, most, blockIdx.x,
                                   job.entry, 1, job);
     }
 }
@@ -1666,12 +1666,12 @@ k_bf16_attn(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo, in
 __global__ void __launch_bounds__(256, 2)
 k_bf16_attn_decode(QkvIn in, int Hq, const int32_t* __restrict__ n_ptr, int B, KvView kv, uint4* __restrict__ ao, int KB_ao, int most,
                    float* __restrict__ part, const AttnJob* __restrict__ jobs) {
-    __shared__ AttnShared sm;
+    __shared__ AttnShared<4> sm;
     __shared__ uint4 qs[4][2][64];
     const int n = min(*n_ptr, B);
     const AttnJob job = jobs[blockIdx.y];      // longest contexts first; slots from n on are not read further
     if ((int)blockIdx.y >= n || (int)blockIdx.z >= job.shares) return;
-    attn_streams<false, true, true>(sm, nullptr, nullptr, Hq, nullptr, nullptr, kv, ao, KB_ao, job.shares, blockIdx.z, part, most,
+    attn_streams<false, true, true, 4>(sm, nullptr, nullptr, Hq, nullptr, nullptr, kv, ao, KB_ao, job.shares, blockIdx.z, part, most,
                                     blockIdx.x, job.entry, 1, job, in, qs);
 }
 
@@ -1927,7 +1927,7 @@ k_bf16_attn_ctx(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo
                 const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv, uint4* __restrict__ ao,
                 int KB_ao, const int32_t* __restrict__ order) {
     __shared__ uint4 lds[2 * CTX_STAGE];
-    static_assert(sizeof(AttnShared) <= sizeof(lds), "the merge arrays share the stage buffers");
+    static_assert(sizeof(AttnShared<4>) <= sizeof(lds), "the merge arrays share the stage buffers");
     const int n = min(*n_ptr, B);
     const int E = 16 / (Hq / kv.n_kv_heads), TE = 4 * C * E;
     const int tiles = gridDim.y / (4 * C);                   // of the batch's capacity; n entries fill the first ones
@@ -1946,7 +1946,7 @@ k_bf16_attn_ctx(const bf16_t* __restrict__ q_hi, const bf16_t* __restrict__ q_lo
         __syncthreads();                                     // what the tile wrote comes before what follows
     }
     for (; k < k_end && k * E < cnt; ++k) {
-        attn_streams<true, true>(*reinterpret_cast<AttnShared*>(lds), q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr,
+        attn_streams<true, true, false, 4>(*reinterpret_cast<AttnShared<4>*>(lds), q_hi, q_lo, Hq, idx, pos, kv, ao, KB_ao, 1, 0, nullptr,
                                  1, blockIdx.x, first + k * E, min(E, cnt - k * E));
         __syncthreads();                                     // the merge has read the shared arrays
     }
@@ -2527,13 +2527,21 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
                                qd / 16, b->wsp<int32_t>(b->W.attn_order));
         } else if (pair)
-            hipLaunchKernelGGL(k_bf16_attn<true>, dim3(c.n_kv_heads, (B + 16 / G - 1) / (16 / G), 1), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
+            hipLaunchKernelGGL((k_bf16_attn<true, 4>), dim3(c.n_kv_heads, (B + 16 / G - 1) / (16 / G), 1), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
                                qd / 16, 1, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
         else
-            hipLaunchKernelGGL(k_bf16_attn<false>, dim3(c.n_kv_heads, B, most), dim3(256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
+        {
+            // Rows of at most 8 groups of 32 positions and many of them: a wave takes a whole row, so that nothing is merged and eight
+            // rows start on a CU at a time.  Layer, four waves / one: 7B shape 300 rows of 20 to 30 positions 330 / 287 us, of 125
+            // to 250 439 / 436, 40 rows of 60 117.5 / 113.5; 34B 400 rows of 60 746 / 729; longer rows 0.5 to 2 % the other way (two
+            // waves lie between).
+            const bool one = pairs > 768 && kv->max_cap <= 256;
+            auto kern = one ? k_bf16_attn<false, 1> : k_bf16_attn<false, 4>;
+            hipLaunchKernelGGL(kern, dim3(c.n_kv_heads, B, most), dim3(one ? 64 : 256), 0, s, b->wsp<bf16_t>(b->W.q_hi),
                                b->wsp<bf16_t>(b->W.q_lo), c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao,
                                qd / 16, most, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
+        }
         if (most > 1 && ctx.C == 0)
             hipLaunchKernelGGL(k_bf16_attn_merge, dim3(c.n_kv_heads, B), dim3(256), 0, s, b->wsp<float>(b->W.attn_part),
                                c.n_q_heads, c.n_kv_heads, most, b->wsp<AttnJob>(b->W.attn_order), n_ptr, B, ao, qd / 16);

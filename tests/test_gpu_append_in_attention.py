@@ -1,7 +1,8 @@
 """Decode attention that rotates and appends itself (few (row, kv head) pairs) against the append kernel and the attention
 behind it: the same rows in a batch whose capacity takes the separate launches.  One, four and sixteen query heads per kv head,
 rows whose new position opens or closes a group of 32 positions, lies in the first group or behind several, rows left of a
-batch, and rows whose position is refused."""
+batch, and rows whose position is refused; capacities on both sides of the one from which the attention behind the append
+kernel has four waves per row."""
 import numpy as np
 import pytest
 import torch
@@ -14,8 +15,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("hq,hkv", [(16, 16), (64, 16), (256, 16)])
 @pytest.mark.parametrize("live", [40, 7])
-def test_append_in_attention_equals_its_own_launch(hq, hkv, live):
-    print(f"[case] append in attention {hq}/{hkv} heads, {live} rows", flush=True)
+@pytest.mark.parametrize("longest", [255, 300])
+def test_append_in_attention_equals_its_own_launch(hq, hkv, live, longest):
+    print(f"[case] append in attention {hq}/{hkv} heads, {live} rows of up to {longest}", flush=True)
     gen = torch.Generator().manual_seed(9)
     d, rows = 256, 40                                        # 640 pairs; 64 rows are 1024
     rnd = lambda *shape: (torch.randn(*shape, generator=gen) * 0.05).bfloat16()      # noqa: E731
@@ -25,7 +27,7 @@ def test_append_in_attention_equals_its_own_launch(hq, hkv, live):
     m.set_layer(1, g_attn=one, W_qkv=rnd((hq + 2 * hkv) * 128, d), W_o=rnd(d, hq * 128), g_ffn=one, W_gate=rnd(64, d),
                 W_up=rnd(64, d), W_down=rnd(d, 64))
     m.set_embed(rnd(64, d))
-    pos = [(0, 1, 30, 31, 32, 33, 95, 96, 127, 128, 200, 255, 256, 300)[r % 14] for r in range(rows)]
+    pos = [min(longest, (0, 1, 30, 31, 32, 33, 95, 96, 127, 128, 200, 255, 256, 300)[r % 14]) for r in range(rows)]
     cap = [(p + 32) // 32 * 32 for p in pos]
     refused = [2, 5]                                         # at their capacity: nothing may be appended
     for r in refused:
