@@ -2226,8 +2226,9 @@ static void launch_few(const ee_batch* b, const void* X, const void* W, int N, i
     if (tail.from_out) *tail.from_out = 0;
 }
 
-// the 256-row tile kernels, 128 or 256 columns wide, K sliced so that about one workgroup per CU
-// runs; returns false where the weight-streaming kernel is the better choice
+// A product on the kernel whose waves stream alone (few_rows) or on the 256-row tile kernels, 128, 192 or 256 columns
+// wide, K sliced so that about one workgroup per CU runs; returns false where the weight-streaming kernel is the better
+// choice (at most 64 rows)
 template <int EPI>
 static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, int K, int NBs, int nb_off,
                      const int32_t* n_ptr, int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{},
@@ -2238,7 +2239,6 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         return true;
     }
     if (N % 128 != 0 || K % 128 != 0) return false;
-    // One product at a time: the tile kernels at every batch size.
     if (nz > 1) {
         // Several layers in one launch (K/V of skipped layers) are not sliced.  The whole fill, streaming / tile
         // kernel: up to 64 rows (where few_rows leaves them) the tile kernel needs the 256-column tiles of all layers
