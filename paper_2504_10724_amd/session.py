@@ -209,10 +209,12 @@ class Batch:
             count = {"h": self.B * self.model.cfg.d_model, "n_active": 1, "n_exited": 1, "breach_count": 1,
                      "status": 1, "exit_counts": ee.EE_MAX_EXITS}.get(name, self.B)
             nbytes = count * torch.empty(0, dtype=dt).element_size()
-            with torch.inference_mode(False):      # a view made in inference mode could not be written outside it later
-                v = self.state[off:off + nbytes].view(dt)
-                if name == "h":
-                    v = v.view(self.B, -1)
+            if torch.is_inference_mode_enabled():  # a view made in inference mode could not be written outside it later
+                with torch.inference_mode(False):
+                    return self.field(name)
+            v = self.state[off:off + nbytes].view(dt)
+            if name == "h":
+                v = v.view(self.B, -1)
             self._views[name] = v
         return v
 
