@@ -1008,7 +1008,7 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int r0, const 
 template <int EPI>
 __global__ void __launch_bounds__(512, 2)
 k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, int NBs, int nb_off, int NB_total,
-                 int n_tiles, const int32_t* __restrict__ n_ptr, int B, EpiArgs ep) {
+                 int n_tiles, const int32_t* __restrict__ n_ptr, int B, EpiArgs ep, ZBatch zb) {
     __shared__ uint4 lds[5][32][64];
     const int n = min(*n_ptr, B);
     int rg, tile;
@@ -1016,6 +1016,9 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     if (tile < 0) return;
     const int row_base = rg * 256;
     if (row_base >= n) return;
+    if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
+    Xp += (int64_t)blockIdx.z * zb.x_stride;
+    ep.out += (int64_t)blockIdx.z * zb.out_stride;
     ColsCtx c;
     c.lds = &lds[0][0][0];
     c.KB = KB; c.NBs = NBs;
@@ -2255,7 +2258,7 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         const int n_tiles = (N / 32 + 5) / 6;
         const dim3 grid(row_groups > 1 ? (n_tiles + 7) / 8 * 8 * row_groups : n_tiles, 1, 1);      // see tile_of_block
         hipLaunchKernelGGL((k_bf16_gemm_cols<EPI>), grid, dim3(512), 0, s, (const uint4*)X, (const uint4*)W, K / 16, NBs, nb_off,
-                           N / 32, n_tiles, n_ptr, B, ep);
+                           N / 32, n_tiles, n_ptr, B, ep, zb);
         if (tail.splits_out) *tail.splits_out = 1;
         if (tail.from_out) *tail.from_out = 0;
         return true;

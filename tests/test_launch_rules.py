@@ -1,0 +1,37 @@
+"""The launch rules, on the library's host code alone (no GPU): what is launched for a call, and with which arguments."""
+import pytest
+
+from host_launches import launches
+
+# query heads, kv heads, d, FFN: the widths of the workloads, heads between them, a smaller model, one off the 128-wide tile grid
+SHAPES = [(32, 32, 4096, 11008), (64, 8, 8192, 28672), (40, 40, 5120, 13824), (48, 48, 6144, 16384), (24, 24, 3072, 8192), (16, 4, 2048, 5632),
+          (32, 32, 512, 1024), (4, 2, 576, 1088)]
+ROWS = [1, 7, 32, 33, 64, 65, 96, 128, 129, 200, 256, 257, 400, 512, 513, 600, 768, 769, 1000, 1024, 1025, 1100, 1280, 1281, 1537, 1792, 2048,
+        2049, 2304, 2816, 2817, 4096, 4097, 4352, 5000, 5888, 8192, 20000, 65535]
+
+
+def _cfg(shape, layers, exits):
+    hq, hkv, d, f = shape
+    return dict(n_layers=layers, d_model=d, n_q_heads=hq, n_kv_heads=hkv, d_ffn=f, vocab=32000, exit_layers=exits)
+
+
+def _arg(launch, kind, nth=0):
+    return [a for a, t in zip(launch["args"], launch["types"]) if t == kind][nth]
+
+
+def _products(launches_):
+    return [x for x in launches_ if x["kernel"].startswith("k_bf16_gemm")]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_every_product_is_given_its_weights(shape):
+    """the weights as an address, or a table of addresses on a kernel that reads it: keys and values of one skipped layer and of
+    several, of few entries in a large batch, of a step with exits on neighbouring layers, and every product of a context pass"""
+    calls = [["fill_skipped_kv", 1, 2], ["fill_skipped_kv", 1, 4], ["backfill_kv", 3, 4, 1], ["decode_step"], ["prefill", 1], ["exit_head", 0]]
+    got = launches([dict(cfg=_cfg(shape, 4, [1, 2, 4]), rows=n, calls=calls + [["prefill", n]]) for n in ROWS])
+    for n, per_call in zip(ROWS, got):
+        for call, (rc, ran) in zip(calls + [["prefill", n]], per_call):
+            assert rc == 0 and _products(ran), (n, call)
+            for x in _products(ran):
+                weights, table = _arg(x, "HIP_vector_type const*", 1), _arg(x, "ZBatch") if "ZBatch" in x["types"] else 0
+                assert weights or table, (n, call, x["kernel"])
