@@ -462,6 +462,19 @@ __device__ __forceinline__ floatx16 tile_mfma(const uint4& x, const uint4& w, co
     else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(x), as_bf16x8(w), acc, 0, 0, 0);
 }
 
+// exp(d), d <= 0 (or NaN) a logit's distance to the tile's maximum: the hardware's base-2 exponential of t = d log2 e, rounded,
+// times 1 + r with r = d - t ln 2 what the rounding left; within 1.4e-7 of the value.  (The base-2 exponential alone is off by the
+// rounding of t, up to 6e-8 d, and equal distances make the same error, so that it does not average out of a sum.)
+// d = -infinity: t is too, r is clipped, the result is 0.  expf, which reduces its argument and tests its range, takes two to
+// three times the instructions for each of a lane's up to 128 logits: head of 192 rows at the 70B shape 134.4 us with it, 132.0 so,
+// of 200 rows at the 7B shape 86.2 and 84.1.
+__device__ __forceinline__ float exp_below(float d) {
+    const float t = d * 1.44269504088896340736f;
+    const float r = fmaf(-t, -1.90465429995776e-9f, fmaf(-t, 0.693147182464599609f, d));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return fmaf(e, fminf(r, 1.0f), e);
+}
+
 // v: the 32x32 result of tile-row nb (columns 32 nb ..) for rows row0 .. row0+31; every lane of the wave calls it
 template <int EPI>
 __device__ __forceinline__ void epilogue_one(const EpiArgs& ep, const floatx16& v, int row0, int n, int nb, int lane) {
@@ -496,12 +509,14 @@ __device__ __forceinline__ void epilogue_one(const EpiArgs& ep, const floatx16& 
         const float m2 = __shfl_xor(mx, 32, 64);
         const int a2 = __shfl_xor(arg, 32, 64);
         if (m2 > mx || (m2 == mx && a2 < arg)) { mx = m2; arg = a2; }
-        // On the hardware's base-2 exponential: its argument -a is rounded as a product with log2 e, a relative error of about
-        // 6e-8 a on a term of size exp(-a), at most 3e-8 of the sum, which holds exp(0).  expf takes about 20 instructions for
-        // each of a lane's up to 128 logits: head of 192 rows at the 70B shape 132 us with it, 128 so, of 200 rows at 7B 86 and 82.
-        float se = 0.f;
+        float ex[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) se += __builtin_amdgcn_exp2f((z[r] - mx) * 1.44269504088896340736f);
+        for (int r = 0; r < 16; ++r) ex[r] = exp_below(z[r] - mx);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1)                       // in pairs: four roundings on a term's way; one by one fifteen
+#pragma unroll
+            for (int r = 0; r < o; ++r) ex[r] += ex[r + o];
+        float se = ex[0];
         se += __shfl_xor(se, 32, 64);
         if (live && lane < 32) {
             const int64_t at = (int64_t)row * ep.n_part + nb;
