@@ -2165,7 +2165,7 @@ struct SliceTail {
     bool*        norm_done = nullptr;   // set when that happened
     bool         defer_store = false;   // STORE: leave the planes to the caller ...
     int*         splits_out = nullptr;  // ... who gets their number (1 = the result is in out already)
-    int*         from_out = nullptr;    // ... and the first column that is in planes (those before it are in out)
+    int*         from_out = nullptr;    // ... and, from a caller that can take a part of the columns so, the first one in planes
     JobArgs      jobs = {};             // RESID: the attention jobs to leave beside the norm
 };
 
@@ -2646,17 +2646,17 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     EpiArgs ep{};
     ep.out = kvb; ep.ldo = kv_n; ep.idx = idx;
     int NBs = (c.n_q_heads + 2 * c.n_kv_heads) * hd / 32, nb_off = c.n_q_heads * hd / 32;
-    int splits = 1, from = 0;
-    SliceTail st;                                       // one layer's K-slice planes are added up by the append kernel
-    st.defer_store = nl == 1; st.splits_out = &splits; st.from_out = &from;
+    int splits = 1;
+    SliceTail st;                                       // one layer's K-slice planes, of all columns, are added up by the append kernel
+    st.defer_store = nl == 1; st.splits_out = &splits;
     if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl, st))
         gemm<1, EPI_STORE>(x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl);
-    if (splits == 1) from = kv_n;                       // nothing is in planes
     const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(0, c.n_kv_heads, B * nl), nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, splits, (int64_t)b->Mpad * kv_n, b->wsp<float>(b->W.gemm_part), kv_n, from);
+                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, splits, (int64_t)b->Mpad * kv_n, b->wsp<float>(b->W.gemm_part), kv_n,
+                       splits == 1 ? kv_n : 0);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }

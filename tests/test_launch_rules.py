@@ -35,3 +35,27 @@ def test_every_product_is_given_its_weights(shape):
             for x in _products(ran):
                 weights, table = _arg(x, "HIP_vector_type const*", 1), _arg(x, "ZBatch") if "ZBatch" in x["types"] else 0
                 assert weights or table, (n, call, x["kernel"])
+
+
+@pytest.mark.parametrize("shape", [x for x in SHAPES if x[2] >= 2048], ids=str)      # narrower products are not sliced
+def test_the_append_kernel_reads_the_planes_the_product_wrote(shape):
+    """q|k|v of a context pass and of a step, keys and values of one skipped layer and of several"""
+    calls = [["fill_skipped_kv", 1, 2], ["fill_skipped_kv", 1, 4], ["backfill_kv", 3, 4, 1], ["layer_forward", 1]]
+    got = launches([dict(cfg=_cfg(shape, 4, [1, 2, 4]), rows=n, calls=calls + [["prefill", n]]) for n in ROWS])
+    qkv, sliced = (shape[0] + 2 * shape[1]) * 128, 0
+    for n, per_call in zip(ROWS, got):
+        for call, (rc, ran) in zip(calls + [["prefill", n]], per_call):
+            columns = qkv if call[0] in ("layer_forward", "prefill") else 2 * shape[1] * 128
+            for i, x in enumerate(ran):
+                if x["kernel"] != "k_bf16_rope_append":
+                    continue
+                splits, plane, planes, ld, start = x["args"][-5:]
+                made = next(y for y in reversed(ran[:i]) if y["kernel"].startswith("k_bf16_gemm"))
+                if "long" not in made["types"] or made["args"][made["types"].index("int const*") - 1] == 1:
+                    assert splits == 1 and start == columns, (n, call)
+                    continue
+                at = made["types"].index("long")
+                sliced += 1
+                assert made["args"][at - 3 - 1] == splits > 1 and made["args"][at - 1:at + 2] == [planes, plane, ld], (n, call)
+                assert ld == columns - start and plane >= n * ld, (n, call)
+    assert sliced
