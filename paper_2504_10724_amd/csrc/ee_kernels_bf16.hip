@@ -2148,7 +2148,7 @@ static FewShape few_shape(int tile_rows, int KB, int rows, int nz, int max_split
                 const float a = wx / 50.f, m = c * w / 6300.f, x = c * wx / 15000.f;
                 return std::sqrt(std::sqrt(a * a * a * a + m * m * m * m + x * x * x * x));
             };
-            float t = (rows > 64 ? 0.7f : 0.3f) * sp + (sp > 1 ? sp * rows * tile_rows * (32 * 8) / 4.0e6f : 0.f);              // us
+            float t = (rows > 64 ? 0.7f : 0.3f) * sp + (sp > 1 ? (float)sp * rows * tile_rows * (32 * 8) / 4.0e6f : 0.f);       // us
             t += std::max(0, full + (last > 0) - 2);
             if (full > 0) t += full * round(256);
             if (last > 0) t += round(last);

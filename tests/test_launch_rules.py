@@ -59,3 +59,14 @@ def test_the_append_kernel_reads_the_planes_the_product_wrote(shape):
                 assert made["args"][at - 3 - 1] == splits > 1 and made["args"][at - 1:at + 2] == [planes, plane, ld], (n, call)
                 assert ld == columns - start and plane >= n * ld, (n, call)
     assert sliced
+
+
+def test_large_batches_are_not_sliced():
+    """products off the 128-wide tile grid: K is sliced where few rows give few workgroups; 2000 rows of 130 tile-rows give two for
+    every CU, and up to the largest batch only a last round that is nearly empty is worth a second plane"""
+    rows = [65, 2000, 3000, 4000, 4100, 6000, 8000, 12000, 20000, 40000, 65535]
+    got = launches([dict(cfg=dict(n_layers=1, d_model=4160, n_q_heads=32, n_kv_heads=32, d_ffn=11008, vocab=32000, exit_layers=[1]), rows=n, cap=32,
+                         calls=[["layer_forward", 1]]) for n in rows])
+    for nth in (0, 1, 3):                                    # q|k|v, O and down
+        slices = [_products(c[0][1])[nth]["args"][6] for c in got]
+        assert slices[0] > 1 and max(slices[1:]) <= 2 and slices[-1] == 1, slices
