@@ -1,5 +1,5 @@
-"""The views of a batch's state: one per field, of the state itself, also when it is first asked for in inference mode; calls go
-to the current stream."""
+"""The views of a batch's state: of the state itself, each caller's own, also where a field is first asked for in inference mode;
+calls go to the current stream."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +19,13 @@ def test_fields_are_views_of_the_state_on_any_stream():
         b.field("h")
     for name in S._FIELD_TYPES:
         v, off = b.field(name), getattr(b.layout, name)
-        assert v is b.field(name) and v.data_ptr() == b.state.data_ptr() + off and v.dtype == S._FIELD_TYPES[name]
+        assert v.data_ptr() == b.state.data_ptr() + off and v.dtype == S._FIELD_TYPES[name]
+        shape, changed = v.shape, b.field(name)
+        changed.unsqueeze_(0)                                # in place, of this view alone
+        assert v.shape == shape and b.field(name).shape == shape and b.field(name).is_contiguous()
+        if v.is_floating_point():
+            b.field(name).requires_grad_()
+            assert not b.field(name).requires_grad
     assert b.field("h").shape == (5, s.d_model) and b.field("tok_in").shape == (5,) and b.field("status").shape == (1,)
     b.reset(np.arange(5), np.zeros(5, np.int32))
     side = torch.cuda.Stream()
