@@ -820,10 +820,15 @@ int ee_decode_finish(const ee_model* m, ee_kv* kv, ee_batch* b, int last_segment
     if (last_segment < 0 || last_segment >= n_res) return ee_fail(EE_ERR_INVALID_ARG, "ee_decode_finish: no such segment");
     if (kv->n_layers < R) return ee_fail(EE_ERR_CAPACITY, "ee_decode_finish: cache was bound for fewer layers than are resident");
     // the segments that were not run would have filled the K/V of their layers for the rows that have left
-    // (all of them, if the caller stops here rightly); an fp32 segment fills through layer R itself
-    if (c.dtype == EE_BF16 && last_segment + 1 < n_res && c.exit_layers[last_segment + 1] < R)
-        rc = bf16_fill_kv(m, c.exit_layers[last_segment + 1], R, kv, b, as_stream(stream), b->wsp<int32_t>(b->W.gone_idx),
-                          b->wsp<int32_t>(b->W.n_gone));
+    // (all of them, if the caller stops here rightly), each up to the next exit layer; an fp32 segment fills through layer R itself
+    if (c.dtype == EE_BF16) {
+        int32_t bounds[EE_MAX_EXITS + 1];
+        int n = 0;
+        for (int e = last_segment + 1; e < n_res; ++e) bounds[n++] = c.exit_layers[e];
+        if (n > 0 && bounds[n - 1] < R) bounds[n++] = R;
+        rc = bf16_fill_ranges(m, bounds, n - 1, kv, b, as_stream(stream), b->wsp<int32_t>(b->W.gone_idx),
+                              b->wsp<int32_t>(b->W.n_gone));
+    }
     if (rc == EE_OK) rc = launch_end_step(b, as_stream(stream));
     return rc;
 }

@@ -2244,28 +2244,43 @@ static void launch_few(const ee_batch* b, const void* X, const void* W, int N, i
     if (tail.from_out) *tail.from_out = 0;
 }
 
+static int product_rows(const ee_batch* b) { return b->n_entries > 0 ? b->n_entries : b->B; }     // in a context pass what the call has
+
+// Whether the products of one launch take the 256-column tile: it loads each activation tile once per 256 columns instead
+// of once per 128, which is worth it when it still gives every CU a workgroup
+static bool wide_tiles(int N, int row_groups, int nz) { return N % 256 == 0 && N / 256 * row_groups * nz >= 200; }
+
+// Several layers in one launch (K/V of skipped layers): the kernel whose waves stream alone (few_rows), the tile
+// kernels, or the weight-streaming one.  They add K up in different orders, so that this choice decides the bits; which
+// tile does not, and such a launch is never sliced.
+enum class Fill { stream, few, tiles };
+static Fill fill_kernel(int N, int K, int rows, int B, int nz) {
+    if (few_rows<EPI_STORE>(N, K, rows, B, nz)) return Fill::few;
+    if (N % 128 != 0 || K % 128 != 0) return Fill::stream;
+    // The whole fill, streaming / tile kernel: up to 64 rows (where few_rows leaves them) the tile kernel needs the 256-column
+    // tiles of all layers to fill the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape
+    // (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.
+    const int wide = N % 256 == 0 ? N / 256 * nz : 0;
+    const float fill = (float)wide / (float)((wide + 255) / 256 * 256);
+    if (B <= 64 && (wide < 200 || (B <= 32 && fill < 0.75f))) return Fill::stream;
+    if (rows <= 256 && N / (wide_tiles(N, 1, nz) ? 256 : 128) * nz <= 128 && (int64_t)N * K * nz >= ((int64_t)2 << 20)) return Fill::few;   // see gemm_tiled
+    return Fill::tiles;
+}
+
 // A product on the kernel whose waves stream alone (few_rows) or on the 256-row tile kernels, 128, 192 or 256 columns
 // wide, K sliced so that about one workgroup per CU runs; returns false where the weight-streaming kernel is the better
-// choice (at most 64 rows)
+// choice (at most 64 rows).  nz > 1 layers in one launch: the kernel that a launch of nz_as of them would take.
 template <int EPI>
 static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, int K, int NBs, int nb_off,
                      const int32_t* n_ptr, int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{},
-                     int nz = 1, const SliceTail& tail = SliceTail{}) {
-    const int rows = b->n_entries > 0 ? b->n_entries : B;    // in a context pass what the call has, not what the batch could hold
-    if (few_rows<EPI>(N, K, rows, B, nz)) {
+                     int nz = 1, const SliceTail& tail = SliceTail{}, int nz_as = 1) {
+    const int rows = product_rows(b);
+    const Fill fill_as = nz > 1 ? fill_kernel(N, K, rows, B, nz_as) : Fill::tiles;
+    if (nz > 1 ? fill_as == Fill::few : few_rows<EPI>(N, K, rows, B, 1)) {
         launch_few<EPI>(b, X, W, N, K, NBs, nb_off, n_ptr, B, rows, ep, s, zb, nz, tail);
         return true;
     }
-    if (N % 128 != 0 || K % 128 != 0) return false;
-    if (nz > 1) {
-        // Several layers in one launch (K/V of skipped layers) are not sliced.  The whole fill, streaming / tile
-        // kernel: up to 64 rows (where few_rows leaves them) the tile kernel needs the 256-column tiles of all layers
-        // (rule `wide` below) to fill the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B
-        // shape (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.
-        const int wide_tiles = N % 256 == 0 ? N / 256 * nz : 0;
-        const float fill = (float)wide_tiles / (float)((wide_tiles + 255) / 256 * 256);
-        if (B <= 64 && (wide_tiles < 200 || (B <= 32 && fill < 0.75f))) return false;
-    }
+    if (N % 128 != 0 || K % 128 != 0 || fill_as == Fill::stream) return false;
     int row_groups = (rows + 255) / 256;
     int Mpad = (B + 31) / 32 * 32;
     int KS = K / 32;
@@ -2278,12 +2293,10 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         if (tail.from_out) *tail.from_out = 0;
         return true;
     };
-    // the 256-column tile loads each activation tile once per 256 columns instead of once per 128;
-    // worth it when it still gives every CU a workgroup, or when K is long enough that a deeper K
-    // slicing costs little
+    // or when K is long enough that a deeper K slicing costs little
     // (long K: with more than 128 rows the 256-column tile's halved activation traffic outweighs its
     // doubled K-slice planes; up to 128 rows the 128-column tile is 2-8 % faster on the down projection)
-    bool wide = (N % 256 == 0) && ((N / 256) * row_groups * nz >= 200 || (EPI == EPI_RESID && K >= 2 * N && rows > 128));
+    bool wide = wide_tiles(N, row_groups, nz) || (N % 256 == 0 && EPI == EPI_RESID && K >= 2 * N && rows > 128);
     // K slices of a narrow product when the launch is left to itself: about one workgroup per CU
     auto slices_for = [&](int tiles) {
         int sp = (256 + tiles / 2) / tiles;
@@ -2337,7 +2350,7 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     }
     int n_tiles = wide ? N / 256 : N / 128;
     if (splits == 0) splits = sliceable && n_tiles * row_groups < 200 ? fit_slices(slices_for(n_tiles * row_groups)) : 1;
-    if (rows <= 256 && n_tiles * splits * row_groups * nz <= 128 && (int64_t)N * K * nz >= ((int64_t)2 << 20)) {
+    if (nz == 1 && rows <= 256 && n_tiles * splits <= 128 && (int64_t)N * K >= ((int64_t)2 << 20)) {
         // half of the CUs would idle: two row groups of 128 (2048-wide model, 192 rows: q|k|v 20.2 us in 96 workgroups, 18.0
         // here, O 22.7 / 19.8, gate/up 30.3 / 27.2; with 172 workgroups the tiles stay: gate/up of the 7B shape 54.8 / 85)
         launch_few<EPI>(b, X, W, N, K, NBs, nb_off, n_ptr, B, rows, ep, s, zb, nz, tail);
@@ -2624,8 +2637,9 @@ int bf16_exit_head(const ee_model* m, int e, float th, int force, ee_batch* b, f
     return launch_exit_decide(b, V / 32, th, force, s);
 }
 
-int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_batch* b, hipStream_t s,
-                 const int32_t* idx, const int32_t* n_ptr) {
+// layers_as: the keys and values are those of fills of so many layers, bit for bit
+static int fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_batch* b, hipStream_t s, const int32_t* idx,
+                   const int32_t* n_ptr, int layers_as) {
     const ee_model_config& c = m->cfg;
     const ee_batch_layout& L = b->L;
     int B = b->B, d = c.d_model, hd = c.head_dim;
@@ -2649,7 +2663,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     int splits = 1;
     SliceTail st;                                       // one layer's K-slice planes, of all columns, are added up by the append kernel
     st.defer_store = nl == 1; st.splits_out = &splits;
-    if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl, st))
+    if (!gemm_tiled<EPI_STORE>(b, x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl, st, layers_as))
         gemm<1, EPI_STORE>(x, nullptr, kv_n, d, NBs, nb_off, n_ptr, B, ep, s, zb, nl);
     const int near = b->kv_seq != nullptr ? entry_near(B) : 1;
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(0, c.n_kv_heads, B * nl), nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
@@ -2659,4 +2673,23 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
                        splits == 1 ? kv_n : 0);
     EE_LAUNCH_CHECK();
     return EE_OK;
+}
+
+int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_batch* b, hipStream_t s, const int32_t* idx,
+                 const int32_t* n_ptr) {
+    return fill_kv(m, from_excl, to_incl, kv, b, s, idx, n_ptr, to_incl - from_excl);
+}
+
+int bf16_fill_ranges(const ee_model* m, const int32_t* bounds, int n, ee_kv* kv, ee_batch* b, hipStream_t s, const int32_t* idx,
+                     const int32_t* n_ptr) {
+    const ee_model_config& c = m->cfg;
+    auto kernel = [&](int layers) { return fill_kernel(2 * c.n_kv_heads * c.head_dim, c.d_model, product_rows(b), b->B, layers); };
+    int rc = EE_OK;
+    for (int i = 0, j; i < n && rc == EE_OK; i = j) {
+        // neighbouring ranges that run on the same kernel are one launch; a single layer may be sliced and stays by itself
+        const int layers = bounds[i + 1] - bounds[i];
+        for (j = i + 1; j < n && layers > 1 && bounds[j + 1] - bounds[j] > 1 && kernel(bounds[j + 1] - bounds[j]) == kernel(layers);) ++j;
+        rc = fill_kv(m, bounds[i], bounds[j], kv, b, s, idx, n_ptr, layers);
+    }
+    return rc;
 }

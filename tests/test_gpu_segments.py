@@ -75,6 +75,17 @@ def test_step_in_segments_equals_the_step(s):
     _same_cache(g1, g2, len(plans))
 
 
+# the layers after the second exit: ten at a time on one kernel (up to 128 rows, 129 to 256), thirty together would be on another;
+# ranges of one, two, seven and thirty layers; no range at all
+@pytest.mark.parametrize("rows", [3, 70, 150])
+@pytest.mark.parametrize("exits", [(1, 11, 21, 31, 41), (1, 2, 4, 5, 12, 42), (1, 3)], ids=str)
+def test_layers_not_run_are_filled_as_the_step_fills_them(exits, rows):
+    n = len(exits)
+    test_step_in_segments_equals_the_step(synth.CONFIGS["llama2_7b"].with_(
+        name=f"many_layers_{exits[-1]}_b{rows}", n_layers=exits[-1], resident=exits[-1], d_model=512, n_q_heads=8, n_kv_heads=8, d_ffn=64, vocab=512,
+        exit_layers=exits, thresholds=(0.5,) * (n - 1) + (0.0,), batch=rows, ctx_lo=3, ctx_hi=20, steps=4))
+
+
 def test_segment_calls_reject_bad_arguments():
     s = SMALL
     g = GpuSide(s)

@@ -70,3 +70,26 @@ def test_large_batches_are_not_sliced():
     for nth in (0, 1, 3):                                    # q|k|v, O and down
         slices = [_products(c[0][1])[nth]["args"][6] for c in got]
         assert slices[0] > 1 and max(slices[1:]) <= 2 and slices[-1] == 1, slices
+
+
+def _sums(launch):
+    """the order in which a product adds its columns up: kernels of one kind differ in the tiles they take, not in this"""
+    kind = next(k for k in ("few", "cols", "dma") if k in launch["kernel"]) if "_gemm_" in launch["kernel"] else "stream"
+    splits = 1 if kind in ("cols", "stream") else launch["args"][6]
+    return "tile" if kind in ("cols", "dma") else kind, splits
+
+
+@pytest.mark.parametrize("exits", [[1, 11, 21, 31, 41], [2, 3, 4, 5, 41], [1, 3, 5, 9, 12, 13, 40, 41], [8, 16, 24, 32]], ids=str)
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_the_end_of_a_step_in_pieces_fills_layers_as_the_step_does(shape, exits):
+    """keys and values of skipped layers: per layer the same kind of sums after ee_decode_finish as in ee_decode_step"""
+    rows = [1, 33, 64, 65, 128, 129, 256, 300, 1100]
+    cfg = dict(_cfg(shape, exits[-1], exits), vocab=512)
+    calls = [["decode_step"]] + [["decode_finish", e] for e in range(len(exits))]
+    for n, ((rc, step), *finish) in zip(rows, launches([dict(cfg=cfg, rows=n, cap=32, calls=calls) for n in rows])):
+        fills = lambda ran: [_sums(x) for x in _products(ran) if _arg(x, "HIP_vector_type const*", 1) == 0 for _ in range(x["grid"][2])]   # noqa: E731
+        want = fills(step)
+        assert rc == 0 and len(want) == exits[-1] - exits[0]
+        for e, (rc, ran) in enumerate(finish):
+            left = exits[-1] - exits[min(e + 1, len(exits) - 1)]
+            assert rc == 0 and fills(ran) == want[len(want) - left:], (n, e)
