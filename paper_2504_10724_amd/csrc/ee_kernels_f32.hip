@@ -201,24 +201,23 @@ k_f32_gemm(F32Gemm g, F32Rope p) {
 }
 
 // ------------------------------------------------------------------ attention
-// softmax(q.K^T / sqrt(hd)) V over positions 0..pos, one workgroup per (query head, list entry, share of the positions),
-// hd a multiple of 4.  L lanes (the power of two from hd / 4 up) share a position and take 16 bytes of its key and of its
-// value each, asked for together, four positions per group of lanes at a time; each group keeps a running maximum, sum
-// and output, which are merged over the groups of a wave, over the waves through LDS, and over the shares by
-// k_f32_attn_merge.  What bounds it is memory latency.  Before, all scores were written to LDS, then the
-// maximum, the exponentials and the sum taken over the workgroup, then the values asked for.  Layer of 20 rows of 200 to 900
-// positions: 53 -> 34 us; of 1000 to 2000: 87 -> 42; of one row of 2000: 63 -> 32.
-#define F32_ATTN_PART(hd) ((hd) + 4)      /* floats of a share: outputs (not divided by the sum), maximum, sum, two unused */
-
+// softmax(q.K^T / sqrt(hd)) V over positions 0..pos, one workgroup per (query head, list entry), hd a multiple of 4.  L
+// lanes (the power of two from hd / 4 up) share a position and take 16 bytes of its key and of its value each, asked for
+// together, four positions per group of lanes at a time; each group keeps a running maximum, sum and output, which are
+// merged over the groups of a wave and over the waves through LDS.  What bounds it is memory latency.  Layer, all scores to
+// LDS, then maximum, exponentials and sum over the workgroup, then the values / so: 20 rows of 4 heads of 64, 62 positions 27.0 /
+// 25.4 us, 300 33.5 / 27.5, 1500 71.4 / 37.4; one row of 1500 59.8 / 34.7.  (A long row's positions shared out over workgroups
+// and merged by another launch: 30 us there, but the host does not know how long rows are, and by the cache's capacity a row
+// of 20 positions in room for 2000 paid for it too, 28.4 us instead of 22.1.)
 template <int THREADS>
 __global__ void __launch_bounds__(THREADS)
 k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restrict__ idx,
            const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv,
-           float* __restrict__ out /* [i][Hq*hd] */, int L, int shares, float* __restrict__ part) {
+           float* __restrict__ out /* [i][Hq*hd] */, int L) {
     constexpr int W = THREADS / 64;
     __shared__ float4 s_o[W][64];
     __shared__ float s_m[W], s_l[W];
-    const int hq = blockIdx.x, i = blockIdx.y, z = blockIdx.z;
+    const int hq = blockIdx.x, i = blockIdx.y;
     int b = idx[i];                                         // i < B; beside the number of rows, not after it
     asm volatile("" : "+v"(b));
     const int n = min(*n_ptr, B);
@@ -236,15 +235,14 @@ k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restr
     const bool has = c < hd;
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     const float4 q = has ? *reinterpret_cast<const float4*>(qkv + (int64_t)i * ld + hq * hd + c) : zero;
-    const int t_lo = (int)((int64_t)n_pos * z / shares), t_hi = (int)((int64_t)n_pos * (z + 1) / shares);
     float m = -FLT_MAX, l = 0.f;
     float4 acc = zero;
-    for (int t0 = t_lo + grp; t0 < t_hi; t0 += 4 * groups) {
+    for (int t0 = grp; t0 < n_pos; t0 += 4 * groups) {
         float4 k[4], v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int t = t0 + u * groups;
-            const bool ok = has && t < t_hi;
+            const bool ok = has && t < n_pos;
             k[u] = ok ? *reinterpret_cast<const float4*>(Kb + (int64_t)t * hd + c) : zero;
             v[u] = ok ? *reinterpret_cast<const float4*>(Vb + (int64_t)t * hd + c) : zero;
         }
@@ -254,14 +252,14 @@ k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restr
             a[u] = (q.x * k[u].x + q.y * k[u].y) + (q.z * k[u].z + q.w * k[u].w);
             for (int o = L >> 1; o > 0; o >>= 1) a[u] += __shfl_xor(a[u], o, 64);
             a[u] *= inv_sqrt;
-            if (t0 + u * groups < t_hi) m_new = fmaxf(m_new, a[u]);
+            if (t0 + u * groups < n_pos) m_new = fmaxf(m_new, a[u]);
         }
         const float keep = expf(m - m_new);
         l *= keep;
         acc.x *= keep; acc.y *= keep; acc.z *= keep; acc.w *= keep;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const float e = t0 + u * groups < t_hi ? expf(a[u] - m_new) : 0.f;
+            const float e = t0 + u * groups < n_pos ? expf(a[u] - m_new) : 0.f;
             l += e;
             acc.x += e * v[u].x; acc.y += e * v[u].y; acc.z += e * v[u].z; acc.w += e * v[u].w;
         }
@@ -292,35 +290,6 @@ k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restr
         const float4 o = s_o[k][lane];
         sum += s_l[k] * wk;
         acc.x += o.x * wk; acc.y += o.y * wk; acc.z += o.z * wk; acc.w += o.w * wk;
-    }
-    if (shares == 1) {
-        *reinterpret_cast<float4*>(out + (int64_t)i * (Hq * hd) + hq * hd + c) = make_float4(acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
-    } else {
-        float* pp = part + (((int64_t)i * Hq + hq) * shares + z) * F32_ATTN_PART(hd);
-        *reinterpret_cast<float4*>(pp + c) = acc;
-        if (c == 0) { pp[hd] = mm; pp[hd + 1] = sum; }
-    }
-}
-
-// the shares of a (query head, list entry) in order; one workgroup of a wave each
-__global__ void __launch_bounds__(64)
-k_f32_attn_merge(const float* __restrict__ part, int Hq, int hd, int shares, const int32_t* __restrict__ n_ptr, int B,
-                 float* __restrict__ out) {
-    const int hq = blockIdx.x, i = blockIdx.y;
-    if (i >= min(*n_ptr, B)) return;
-    const float* p = part + ((int64_t)i * Hq + hq) * shares * F32_ATTN_PART(hd);
-    float mm = -FLT_MAX;
-    for (int z = 0; z < shares; ++z) mm = fmaxf(mm, p[z * F32_ATTN_PART(hd) + hd]);
-    float sum = 0.f;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int c = 4 * threadIdx.x;
-    if (c >= hd) return;
-    for (int z = 0; z < shares; ++z) {
-        const float* pz = p + z * F32_ATTN_PART(hd);
-        const float w = expf(pz[hd] - mm);
-        const float4 o = *reinterpret_cast<const float4*>(pz + c);
-        sum += pz[hd + 1] * w;
-        acc.x += o.x * w; acc.y += o.y * w; acc.z += o.z * w; acc.w += o.w * w;
     }
     *reinterpret_cast<float4*>(out + (int64_t)i * (Hq * hd) + hq * hd + c) = make_float4(acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
 }
@@ -478,23 +447,21 @@ int f32_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipS
     if (hd % 4 == 0) {
         int lanes = 1;                        // lanes that share a position: a power of two that holds hd / 4
         while (4 * lanes < hd) lanes *= 2;
-        // Few (row, head) pairs and long rows: the positions are shared out, so that a CU does not stream a whole row (layer of
-        // one row of 2000 positions 41.4 us unshared, 32.5 in seven shares; of 4 rows of up to 900 30.9 and 31.1 in three).  The
-        // shares lie where the layout keeps room for keys and values of a fill.
         const int pairs = B * c.n_q_heads;
-        float* part = b->wsp<float>(b->W.fill_kv);
-        const size_t room = (size_t)b->Mpad * 2 * c.n_kv_heads * hd / ((size_t)pairs * F32_ATTN_PART(hd));
-        int shares = pairs < 128 ? (int)std::min<size_t>({16, (size_t)256 / pairs, (size_t)kv->max_cap / 256, room}) : 1;
-        shares = std::max(1, shares);
-        // Waves of a workgroup: as many as have work at once (16 lanes per position, four positions each: 64 positions on 4
-        // waves), fewer where the pairs alone fill the chip.  Layer, 4 / 8 / 16 waves: 20 rows of 60 positions 26.1 / 26.5 / 28.1
-        // us, of 120 27.8 / 26.8 / 28.1, of 200 to 900 37.7 / 34.9 / 34.4; 100 entries of 1500 62 / 49 / 52, 200 71 / 73 / 75.
+        // Waves of a workgroup, by what the host knows, the (row, head) pairs and the longest row that the cache has room for; rows
+        // may be much shorter, so that no choice may cost them what it gives long ones.  Layer, 4 / 8 / 16 waves: 32 pairs, 62
+        // positions 22.6 / 23.1 / 24.3 us, 700 39.5 / 32.4 / 28.9; 400 pairs 26.3 / 27.4 / 30.8 and 47.4 / 48.0 / 46.9; 528
+        // pairs, 1500 positions 230 / 253 / 255; 800 pairs 352 / 338 / 342, 40 positions 98.6 / 98.4 / 104; 4000 pairs, 40
+        // positions 47 / 56 / 73.
         const int cap = kv->max_cap;
-        const int waves = pairs > 512 || cap <= 64 ? 4 : pairs > 256 || cap <= 256 ? 8 : 16;
+        int waves;
+        if (cap <= 64) waves = 4;
+        else if (pairs <= 256) waves = cap <= 256 ? 8 : 16;
+        else if (pairs <= 512) waves = 8;
+        else waves = cap > 256 && pairs > 768 && pairs <= 2048 ? 8 : 4;
         auto kern = waves == 4 ? k_f32_attn<256> : waves == 8 ? k_f32_attn<512> : k_f32_attn<1024>;
-        hipLaunchKernelGGL(kern, dim3(c.n_q_heads, B, shares), dim3(64 * waves), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B,
-                           b->st<int32_t>(L.pos), view, ao, lanes, shares, part);
-        if (shares > 1) hipLaunchKernelGGL(k_f32_attn_merge, dim3(c.n_q_heads, B), dim3(64), 0, s, part, c.n_q_heads, hd, shares, n_ptr, B, ao);
+        hipLaunchKernelGGL(kern, dim3(c.n_q_heads, B), dim3(64 * waves), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B,
+                           b->st<int32_t>(L.pos), view, ao, lanes);
     } else {
         hipLaunchKernelGGL(k_f32_attn_any, dim3(c.n_q_heads, B), dim3(256), (size_t)(hd + c.max_pos) * sizeof(float), s, qkv,
                            qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao);

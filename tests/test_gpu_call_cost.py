@@ -133,3 +133,34 @@ def test_fill_of_layers_that_spill_into_a_second_round():
     t = {n: _time(_fill_call(m, 16, 1, n), FILL) for n in (20, 40)}
     print(f"[case] fill of one row: 20 layers {t[20]:.1f} us, 40 layers {t[40]:.1f}", flush=True)
     assert t[40] <= 2.02 * t[20]
+
+
+@pytest.mark.parametrize("rows,positions", [(1, 20), (8, 62), (20, 62), (64, 20)])
+def test_fp32_layer_of_short_rows_in_a_large_cache(rows, positions):
+    """room for 2000 positions more per row costs a layer of the fp32 workload's shape at most what more waves per row cost"""
+    d, heads, hd, ffn = 256, 4, 64, 688
+    m = S.Model(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=heads, head_dim=hd, d_ffn=ffn, vocab=64, dtype="f32", exit_layers=[1],
+                max_pos=4096)
+    rnd = lambda *s: torch.empty(s, device="cuda").normal_(0.0, 0.02)      # noqa: E731
+    one = torch.ones(d, device="cuda")
+    m.set_layer(1, g_attn=one, W_qkv=rnd(3 * heads * hd, d), W_o=rnd(d, heads * hd), g_ffn=one, W_gate=rnd(ffn, d), W_up=rnd(ffn, d), W_down=rnd(d, ffn))
+    m.set_embed(rnd(64, d))
+    t = {}
+    for room in (0, 2000):
+        kv, b = S.KVCache(m, 1, [positions + 8 + room] * rows), S.Batch(m, rows)
+        kv.pool.view(torch.float32).normal_()
+        b.reset(np.zeros(rows, np.int32), np.full(rows, positions - 1), None)
+        b.begin_step()
+        got = []
+        for _ in range(20):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            start.record()
+            for _ in range(100):
+                capi.check(S.layer_forward(m, 1, kv, b))
+            end.record()
+            torch.cuda.synchronize()
+            got.append(start.elapsed_time(end) * 10.0)
+        t[room] = min(got[3:])
+    print(f"[case] fp32 layer of {rows} rows of {positions} positions: {t[0]:.1f} us, {t[2000]:.1f} with room for 2000 more", flush=True)
+    assert t[2000] <= 1.15 * t[0]

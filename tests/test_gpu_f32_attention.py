@@ -1,6 +1,6 @@
-"""GPU parity of the fp32 attention where the positions of a row are shared out over workgroups and merged (few rows, long
-contexts, rows much shorter than the longest beside them) and on both sides of the cache size from which a workgroup has
-sixteen waves; head sizes of 1, 5, 16 and 64 lanes per position.  Whole steps against the oracle, bar of every fp32 step."""
+"""GPU parity of the fp32 attention on few rows with long contexts, rows much shorter than the longest beside them, and on both
+sides of the cache sizes and row counts from which a workgroup has eight or sixteen waves; head sizes of 1, 5, 16 and 64 lanes
+per position.  Whole steps against the oracle, bar of every fp32 step."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("hd,hq,hkv,batch,lo,hi", [
     (64, 4, 4, 1, 1500, 1500), (64, 4, 2, 8, 1, 1100), (20, 4, 2, 3, 500, 700), (256, 2, 1, 2, 300, 600), (4, 2, 2, 5, 2, 520),
-    (64, 4, 4, 40, 100, 127), (64, 4, 4, 40, 100, 130)])
+    (64, 4, 4, 40, 100, 127), (64, 4, 4, 40, 100, 130),
+    (64, 4, 4, 65, 100, 300), (16, 8, 8, 97, 100, 300), (16, 8, 8, 65, 20, 300)])
 def test_f32_attention_of_long_rows(hd, hq, hkv, batch, lo, hi):
     s = small_shape(name="f32_attention", d_model=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=96, vocab=128, batch=batch, ctx_lo=lo,
                     ctx_hi=hi, steps=2, thresholds=(0.05, 0.0))
