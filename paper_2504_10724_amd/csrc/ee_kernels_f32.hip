@@ -66,6 +66,8 @@ k_f32_gemm(F32Gemm g, F32Rope p) {
     const int row0 = blockIdx.y * 16;
     // thread = 4 * lane + r of the result registers: row 4 (lane / 16) + r, column lane % 16
     const int el = (threadIdx.x & 255) >> 2, er = threadIdx.x & 3, erl = 4 * (el >> 4) + er, erow = row0 + erl;
+    // in a large batch most row groups but the first may be empty: those look at the number of rows before anything else
+    if (row0 > 0 && row0 >= min(*g.n_ptr, g.B)) return;
     int id = 0, eid = 0;                                   // row ids: of the row this lane loads, and of the one it writes
     if constexpr (BY_ID) {
         id = g.idx[min(row0 + m, g.B - 1)];
