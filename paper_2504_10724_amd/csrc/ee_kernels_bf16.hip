@@ -2186,6 +2186,13 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
     }
 }
 
+// Whether the products of one launch take the 256-column tile: it loads each activation tile once per 256 columns instead
+// of once per 128, which is worth it when it still gives every CU a workgroup
+static bool wide_tiles(int N, int row_groups, int nz) { return N % 256 == 0 && N / 256 * row_groups * nz >= 200; }
+
+// how full the rounds of one workgroup per CU are
+static float rounds_filled(int wgs) { return (float)wgs / (float)((wgs + 255) / 256 * 256); }
+
 // Whether a product takes k_bf16_gemm_few: up to 128 rows, from 4 MiB of weights on (32 MiB over several layers up to 64
 // rows; below, launches wait for memory once or twice whatever the kernel: O of a 576-wide model 6.7 us on the
 // weight-streaming kernel and its norm 3.3, 9.5 here; two layers of 4 MiB 17.1 and 17.6).  Where a tile width fills its
@@ -2196,6 +2203,9 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
 // down 25.1 / 22.7, 72 rows 31.3 / 27.1, 22.4 / 21.3, 48.4 / 38.7, 30.4 / 29.3; 2048-wide model gate/up 16 rows 22.6 / 13.5, 72
 // rows 28.5 / 21.0; 70B shape 16 rows q|k|v 33.8 / 30.9, O 34.1 / 30.4, down 82.3 / 76.9, 128 rows 46.3 / 44.4, 47.4 / 45.3,
 // 101 / 94; exit head of the 70B shape 64 rows 89 / 86, 72 rows 106 / 93; K/V of five layers of the 7B shape 64 rows 93 / 76.
+// A head whose 256-column tiles fill their rounds to 77 % stays with them too: 4096 wide, tiles / here, 64 rows of 51200 logits
+// (200 tiles) 83.6 and 89.1 us, of 65536 (256) 99.7 and 103.3, of 102400 (400) 160 and 178, of 131072 (512) 206 and 220, 128 rows
+// 213 and 267, one row 202 and 235; of 98304 (384, 75 %) 160 / 147, of 76800 (300) 150 / 132, of 40960 (tiles of 128) 96.4 / 76.7.
 // Above 128 rows an X tile per 128 columns is too much (head of the 7B shape 144 rows 65 / 115) where the tile kernels can
 // run (N and K multiples of 128); for other shapes the whole range is here: layer of 576 / 2880 values and 72 rows 79 / 56
 // and 211 / 100 us on the streaming kernel / here, 400 rows 293 / 76 and 977 / 227, context pass of 2048 entries 392 / 143
@@ -2205,6 +2215,7 @@ static bool few_rows(int N, int K, int rows, int B, int nz) {
     const bool on_grid = N % 128 == 0 && K % 128 == 0;
     if (!on_grid && B > 64) return true;
     if (rows > 128) return false;
+    if (EPI == EPI_EXIT && on_grid && wide_tiles(N, 1, 1) && rounds_filled(N / 256) >= 0.77f) return false;
     if ((int64_t)N * K * nz < ((int64_t)(nz > 1 ? 16 : 2) << 20) && !(nz > 1 && B > 64)) return false;
     if ((EPI != EPI_SWIGLU && nz == 1) || !on_grid) return true;
     float fill = 0.f;                                        // widths: as gate/up takes them below; 256 columns for several layers
@@ -2246,10 +2257,6 @@ static void launch_few(const ee_batch* b, const void* X, const void* W, int N, i
 
 static int product_rows(const ee_batch* b) { return b->n_entries > 0 ? b->n_entries : b->B; }     // in a context pass what the call has
 
-// Whether the products of one launch take the 256-column tile: it loads each activation tile once per 256 columns instead
-// of once per 128, which is worth it when it still gives every CU a workgroup
-static bool wide_tiles(int N, int row_groups, int nz) { return N % 256 == 0 && N / 256 * row_groups * nz >= 200; }
-
 // Several layers in one launch (K/V of skipped layers): the kernel whose waves stream alone (few_rows), the tile
 // kernels, or the weight-streaming one.  They add K up in different orders, so that this choice decides the bits; which
 // tile does not, and such a launch is never sliced.
@@ -2261,8 +2268,7 @@ static Fill fill_kernel(int N, int K, int rows, int B, int nz) {
     // tiles of all layers to fill the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape
     // (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.
     const int wide = N % 256 == 0 ? N / 256 * nz : 0;
-    const float fill = (float)wide / (float)((wide + 255) / 256 * 256);
-    if (B <= 64 && (wide < 200 || (B <= 32 && fill < 0.75f))) return Fill::stream;
+    if (B <= 64 && (wide < 200 || (B <= 32 && rounds_filled(wide) < 0.75f))) return Fill::stream;
     if (rows <= 256 && N / (wide_tiles(N, 1, nz) ? 256 : 128) * nz <= 128 && (int64_t)N * K * nz >= ((int64_t)2 << 20)) return Fill::few;   // see gemm_tiled
     return Fill::tiles;
 }
@@ -2316,7 +2322,6 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
         // several row groups (context pass, batches above 256): the products are bound by the MFMAs and by
         // what a CU can pull from L2, and the 256-column tile moves a quarter less per MFMA issued
         const int ww = (N / 256) * row_groups, wn = (N / 128) * row_groups;
-        auto fill = [](int wgs) { return (float)wgs / (float)((wgs + 255) / 256 * 256); };
         if (sliceable && ww <= 256) {
             // a product that may be K-sliced: the 256-column tile with as many slices (at most 4) as keep
             // it inside one round of workgroups, against the 128-column tile with the slices it would get
@@ -2325,11 +2330,11 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
             // 1024 entries 219 -> 198 us; O projection at 768 entries 158 -> 124 us, at 1024 168 -> 148 us.)
             const int s_w = fit_slices(std::min(4, 256 / ww));
             const int s_n = fit_slices(wn < 200 ? slices_for(wn) : 1);
-            const float f_w = fill(ww * s_w), f_n = fill(wn * s_n);
+            const float f_w = rounds_filled(ww * s_w), f_n = rounds_filled(wn * s_n);
             wide = f_w > f_n || (f_w == f_n && s_w < 4);
             splits = wide ? s_w : s_n;
         } else {
-            wide = fill(ww) >= fill(wn);
+            wide = rounds_filled(ww) >= rounds_filled(wn);
         }
     }
     if constexpr (EPI == EPI_SWIGLU) if (row_groups == 1 && nz == 1) {

@@ -93,3 +93,12 @@ def test_the_end_of_a_step_in_pieces_fills_layers_as_the_step_does(shape, exits)
         for e, (rc, ran) in enumerate(finish):
             left = exits[-1] - exits[min(e + 1, len(exits) - 1)]
             assert rc == 0 and fills(ran) == want[len(want) - left:], (n, e)
+
+
+@pytest.mark.parametrize("vocab,tiles", [(32000, False), (40960, False), (51200, True), (65536, True), (76800, False), (98304, False),
+                                         (102400, True), (128256, True), (131072, True), (151936, False)])
+def test_heads_of_few_rows_whose_tiles_fill_their_rounds_keep_them(vocab, tiles):
+    rows = [1, 32, 64, 100, 128]
+    cfg = dict(n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=8, d_ffn=14336, vocab=vocab, exit_layers=[1])
+    for n, ((rc, ran),) in zip(rows, launches([dict(cfg=cfg, rows=n, calls=[["exit_head", 0]]) for n in rows])):
+        assert rc == 0 and _products(ran)[0]["kernel"].startswith("k_bf16_gemm_dma8" if tiles else "k_bf16_gemm_few"), n
