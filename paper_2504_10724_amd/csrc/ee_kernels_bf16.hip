@@ -2355,9 +2355,11 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     }
     int n_tiles = wide ? N / 256 : N / 128;
     if (splits == 0) splits = sliceable && n_tiles * row_groups < 200 ? fit_slices(slices_for(n_tiles * row_groups)) : 1;
-    if (nz == 1 && rows <= 256 && n_tiles * splits <= 128 && (int64_t)N * K >= ((int64_t)2 << 20)) {
+    if (nz == 1 && rows <= 256 && n_tiles * splits <= (rows > 160 ? 128 : 112) && (int64_t)N * K >= ((int64_t)2 << 20)) {
         // half of the CUs would idle: two row groups of 128 (2048-wide model, 192 rows: q|k|v 20.2 us in 96 workgroups, 18.0
-        // here, O 22.7 / 19.8, gate/up 30.3 / 27.2; with 172 workgroups the tiles stay: gate/up of the 7B shape 54.8 / 85)
+        // here, O 22.7 / 19.8, gate/up 30.3 / 27.2; with 172 workgroups the tiles stay: gate/up of the 7B shape 54.8 / 85).
+        // Little more than one group's rows: head of 16000 logits, 8192 wide (125 workgroups), 129 rows 107 / 113, 160 108 / 112, 180
+        // 113.0 / 112.3, 256 128 / 105; of 14080 (110) 129 rows 107.0 / 106.8.
         launch_few<EPI>(b, X, W, N, K, NBs, nb_off, n_ptr, B, rows, ep, s, zb, nz, tail);
         return true;
     }

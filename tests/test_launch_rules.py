@@ -102,3 +102,10 @@ def test_heads_of_few_rows_whose_tiles_fill_their_rounds_keep_them(vocab, tiles)
     cfg = dict(n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=8, d_ffn=14336, vocab=vocab, exit_layers=[1])
     for n, ((rc, ran),) in zip(rows, launches([dict(cfg=cfg, rows=n, calls=[["exit_head", 0]]) for n in rows])):
         assert rc == 0 and _products(ran)[0]["kernel"].startswith("k_bf16_gemm_dma8" if tiles else "k_bf16_gemm_few"), n
+
+
+@pytest.mark.parametrize("rows,vocab,tiles", [(129, 14080, False), (129, 16000, True), (160, 16000, True), (161, 16000, False), (256, 16384, False)])
+def test_two_row_groups_of_128_where_they_leave_fewer_cus_idle(rows, vocab, tiles):
+    cfg = dict(n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=8, d_ffn=14336, vocab=vocab, exit_layers=[1])
+    ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, calls=[["exit_head", 0]])])
+    assert rc == 0 and _products(ran)[0]["kernel"].startswith("k_bf16_gemm_dma2" if tiles else "k_bf16_gemm_few")
