@@ -2191,18 +2191,17 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
 static bool wide_tiles(int N, int row_groups, int nz) { return N % 256 == 0 && N / 256 * row_groups * nz >= 200; }
 
 // how full the rounds of one workgroup per CU are
-static float rounds_filled(int wgs) { return (float)wgs / (float)((wgs + 255) / 256 * 256); }
+static float rounds_filled(int wgs) { return wgs == 0 ? 0.f : (float)wgs / (float)((wgs + 255) / 256 * 256); }
 
-// Whether a product takes k_bf16_gemm_few: up to 128 rows, from 4 MiB of weights on (32 MiB over several layers up to 64
-// rows; below, launches wait for memory once or twice whatever the kernel: O of a 576-wide model 6.7 us on the
-// weight-streaming kernel and its norm 3.3, 9.5 here; two layers of 4 MiB 17.1 and 17.6).  Where a tile width fills its
-// rounds to 80 % gate/up and the K/V of several layers stay with the tile kernels: they read X once per 192 or 256 columns
-// (gate/up of the 70B shape, 224 workgroups, 16 rows 141 and 142 us, 48 rows 143 and 149, 128 rows 157 and 189; seven
-// layers of the 7B shape for 64 rows 95 and 99).  Elsewhere, tile kernels with the streaming kernel / this one, whole
+// Whether a product takes k_bf16_gemm_few: up to 128 rows, from 4 MiB of weights on (below, launches wait for memory
+// once or twice whatever the kernel: O of a 576-wide model 6.7 us on the weight-streaming kernel and its norm 3.3, 9.5
+// here).  Where a tile width fills its rounds to 80 % gate/up stays with the tile kernels: they read X once per 192 or 256
+// columns (gate/up of the 70B shape, 224 workgroups, 16 rows 141 and 142 us, 48 rows 143 and 149, 128 rows 157 and 189).
+// Elsewhere, tile kernels with the streaming kernel / this one, whole
 // launches with the finish: 7B shape 16 rows q|k|v 25.1 / 21.6 us, O 17.4 / 15.3, gate/up 39.8 / 31.2 (172 workgroups / 230),
 // down 25.1 / 22.7, 72 rows 31.3 / 27.1, 22.4 / 21.3, 48.4 / 38.7, 30.4 / 29.3; 2048-wide model gate/up 16 rows 22.6 / 13.5, 72
 // rows 28.5 / 21.0; 70B shape 16 rows q|k|v 33.8 / 30.9, O 34.1 / 30.4, down 82.3 / 76.9, 128 rows 46.3 / 44.4, 47.4 / 45.3,
-// 101 / 94; exit head of the 70B shape 64 rows 89 / 86, 72 rows 106 / 93; K/V of five layers of the 7B shape 64 rows 93 / 76.
+// 101 / 94; exit head of the 70B shape 64 rows 89 / 86, 72 rows 106 / 93.
 // A head whose 256-column tiles fill their rounds to 77 % stays with them too: 4096 wide, tiles / here, 64 rows of 51200 logits
 // (200 tiles) 83.6 and 89.1 us, of 65536 (256) 99.7 and 103.3, of 102400 (400) 160 and 178, of 131072 (512) 206 and 220, 128 rows
 // 213 and 267, one row 202 and 235; of 98304 (384, 75 %) 160 / 147, of 76800 (300) 150 / 132, of 40960 (tiles of 128) 96.4 / 76.7.
@@ -2211,17 +2210,17 @@ static float rounds_filled(int wgs) { return (float)wgs / (float)((wgs + 255) / 
 // and 211 / 100 us on the streaming kernel / here, 400 rows 293 / 76 and 977 / 227, context pass of 2048 entries 392 / 143
 // and 1518 / 696.
 template <int EPI>
-static bool few_rows(int N, int K, int rows, int B, int nz) {
+static bool few_rows(int N, int K, int rows, int B) {
     const bool on_grid = N % 128 == 0 && K % 128 == 0;
     if (!on_grid && B > 64) return true;
-    if (rows > 128) return false;
-    if (EPI == EPI_EXIT && on_grid && wide_tiles(N, 1, 1) && rounds_filled(N / 256) >= 0.77f) return false;
-    if ((int64_t)N * K * nz < ((int64_t)(nz > 1 ? 16 : 2) << 20) && !(nz > 1 && B > 64)) return false;
-    if ((EPI != EPI_SWIGLU && nz == 1) || !on_grid) return true;
-    float fill = 0.f;                                        // widths: as gate/up takes them below; 256 columns for several layers
-    for (int t = 8; t >= (nz > 1 ? 8 : 4); t -= 2) {
-        const int wgs = (N / 32 + t - 1) / t * nz;
-        if (t < 8 || N % 256 == 0) fill = std::max(fill, (float)(N / 32 * nz) / (float)((wgs + 255) / 256 * 256 * t));
+    if (rows > 128 || (int64_t)N * K < ((int64_t)2 << 20)) return false;
+    if (!on_grid) return true;
+    if (EPI == EPI_EXIT) return !(wide_tiles(N, 1, 1) && rounds_filled(N / 256) >= 0.77f);
+    if (EPI != EPI_SWIGLU) return true;
+    float fill = 0.f;                                        // widths: as gate/up takes them below
+    for (int t = 8; t >= 4; t -= 2) {
+        const int wgs = (N / 32 + t - 1) / t;
+        if (t < 8 || N % 256 == 0) fill = std::max(fill, (float)(N / 32) / (float)((wgs + 255) / 256 * 256 * t));
     }
     return fill < 0.8f;
 }
@@ -2255,21 +2254,29 @@ static void launch_few(const ee_batch* b, const void* X, const void* W, int N, i
     if (tail.from_out) *tail.from_out = 0;
 }
 
-static int product_rows(const ee_batch* b) { return b->n_entries > 0 ? b->n_entries : b->B; }     // in a context pass what the call has
-
-// Several layers in one launch (K/V of skipped layers): the kernel whose waves stream alone (few_rows), the tile
-// kernels, or the weight-streaming one.  They add K up in different orders, so that this choice decides the bits; which
-// tile does not, and such a launch is never sliced.
+// Several layers in one launch (K/V of skipped layers): the kernel whose waves stream alone, the tile kernels, or the
+// weight-streaming one.  They add K up in different orders, so that this choice decides the bits; which tile does not,
+// and such a launch is never sliced.
 enum class Fill { stream, few, tiles };
-static Fill fill_kernel(int N, int K, int rows, int B, int nz) {
-    if (few_rows<EPI_STORE>(N, K, rows, B, nz)) return Fill::few;
-    if (N % 128 != 0 || K % 128 != 0) return Fill::stream;
-    // The whole fill, streaming / tile kernel: up to 64 rows (where few_rows leaves them) the tile kernel needs the 256-column
-    // tiles of all layers to fill the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape
-    // (224 tiles) 1 row 90 / 79 us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274.
-    const int wide = N % 256 == 0 ? N / 256 * nz : 0;
-    if (B <= 64 && (wide < 200 || (B <= 32 && rounds_filled(wide) < 0.75f))) return Fill::stream;
-    if (rows <= 256 && N / (wide_tiles(N, 1, nz) ? 256 : 128) * nz <= 128 && (int64_t)N * K * nz >= ((int64_t)2 << 20)) return Fill::few;   // see gemm_tiled
+static Fill fill_kernel(int N, int K, int rows, int nz) {
+    const int64_t weights = (int64_t)N * K * nz;
+    const bool large = weights >= ((int64_t)16 << 20);       // 32 MiB; two layers of 4 MiB 17.1 us on the streaming kernel, 17.6 on few
+    if (N % 128 != 0 || K % 128 != 0) return rows > 64 || large ? Fill::few : Fill::stream;
+    const int wide = N % 256 == 0 ? N / 256 * nz : 0, narrow = N / 128 * nz;       // column tiles
+    if (rows <= 128) {
+        // Tiles of 256 columns read X once per 256 columns, if they fill their rounds (seven layers of the 7B shape, 64 rows
+        // 95 us and 99 on few); elsewhere few (five layers 93 / 76)
+        if ((rows > 64 || large) && rounds_filled(wide) < 0.8f) return Fill::few;
+        // The whole fill, streaming / tile kernel: up to 64 rows the tile kernel needs the 256-column tiles of all layers to fill
+        // the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape (224 tiles) 1 row 90 / 79
+        // us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274
+        if (rows <= 64 && (wide < 200 || (rows <= 32 && rounds_filled(wide) < 0.75f))) return Fill::stream;
+    } else if (rows <= 256 && weights >= ((int64_t)2 << 20)) {
+        // Two row groups of 128 on few where the tiles leave three quarters of the CUs idle.  Tiles / few, 129 and 256 rows: 64
+        // tiles, eight layers of 4 MiB 41.0 / 38.3 and 52.9 / 43.9 us; 80, five of the 70B shape 97 / 98 (200 rows 114 / 105) and
+        // 122 / 94; 96, twelve of 4 MiB 45.0 / 49.4 and 60.2 / 58.8; 128, eight of the 70B shape 106 / 132 and 138 / 134
+        if ((wide >= 200 ? wide : narrow) <= (rows > 192 ? 80 : 64)) return Fill::few;
+    }
     return Fill::tiles;
 }
 
@@ -2280,9 +2287,9 @@ template <int EPI>
 static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, int K, int NBs, int nb_off,
                      const int32_t* n_ptr, int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{},
                      int nz = 1, const SliceTail& tail = SliceTail{}, int nz_as = 1) {
-    const int rows = product_rows(b);
-    const Fill fill_as = nz > 1 ? fill_kernel(N, K, rows, B, nz_as) : Fill::tiles;
-    if (nz > 1 ? fill_as == Fill::few : few_rows<EPI>(N, K, rows, B, 1)) {
+    const int rows = b->n_entries > 0 ? b->n_entries : B;    // in a context pass what the call has, not what the batch could hold
+    const Fill fill_as = nz > 1 ? fill_kernel(N, K, rows, nz_as) : Fill::tiles;
+    if (nz > 1 ? fill_as == Fill::few : few_rows<EPI>(N, K, rows, B)) {
         launch_few<EPI>(b, X, W, N, K, NBs, nb_off, n_ptr, B, rows, ep, s, zb, nz, tail);
         return true;
     }
@@ -2690,7 +2697,7 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
 int bf16_fill_ranges(const ee_model* m, const int32_t* bounds, int n, ee_kv* kv, ee_batch* b, hipStream_t s, const int32_t* idx,
                      const int32_t* n_ptr) {
     const ee_model_config& c = m->cfg;
-    auto kernel = [&](int layers) { return fill_kernel(2 * c.n_kv_heads * c.head_dim, c.d_model, product_rows(b), b->B, layers); };
+    auto kernel = [&](int layers) { return fill_kernel(2 * c.n_kv_heads * c.head_dim, c.d_model, b->B, layers); };
     int rc = EE_OK;
     for (int i = 0, j; i < n && rc == EE_OK; i = j) {
         // neighbouring ranges that run on the same kernel are one launch; a single layer may be sliced and stays by itself

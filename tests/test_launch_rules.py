@@ -109,3 +109,14 @@ def test_two_row_groups_of_128_where_they_leave_fewer_cus_idle(rows, vocab, tile
     cfg = dict(n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=8, d_ffn=14336, vocab=vocab, exit_layers=[1])
     ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, calls=[["exit_head", 0]])])
     assert rc == 0 and _products(ran)[0]["kernel"].startswith("k_bf16_gemm_dma2" if tiles else "k_bf16_gemm_few")
+
+
+@pytest.mark.parametrize("shape,layers,rows,kind", [
+    # 129 to 256 rows: by the tiles of 128 columns, 16 per layer (70B), 64 (7B), 8
+    ((64, 8, 8192, 28672), 4, 129, "few"), ((64, 8, 8192, 28672), 5, 192, "dma"), ((64, 8, 8192, 28672), 5, 193, "few"),
+    ((64, 8, 8192, 28672), 6, 256, "dma"), ((32, 32, 4096, 11008), 2, 129, "dma"), ((16, 4, 2048, 5632), 8, 160, "few"),
+    ((16, 4, 2048, 5632), 12, 129, "dma")])
+def test_kernel_of_a_fill_of_several_layers(shape, layers, rows, kind):
+    cfg = dict(_cfg(shape, layers + 1, [1, layers + 1]), vocab=512)
+    ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, cap=32, calls=[["fill_skipped_kv", 1, layers + 1]])])
+    assert rc == 0 and ("_gemm_" + kind if kind != "stream" else "k_bf16_gemm<") in _products(ran)[0]["kernel"]
