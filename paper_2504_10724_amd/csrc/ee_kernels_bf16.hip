@@ -2265,8 +2265,10 @@ static Fill fill_kernel(int N, int K, int rows, int nz) {
     const int wide = N % 256 == 0 ? N / 256 * nz : 0, narrow = N / 128 * nz;       // column tiles
     if (rows <= 128) {
         // Tiles of 256 columns read X once per 256 columns, if they fill their rounds (seven layers of the 7B shape, 64 rows
-        // 95 us and 99 on few); elsewhere few (five layers 93 / 76)
-        if ((rows > 64 || large) && rounds_filled(wide) < 0.8f) return Fill::few;
+        // 95 us and 99 on few), and with more than 96 rows so do tiles of 128 (three layers of the 7B shape, 128 rows 68.9 / 72.7,
+        // sixteen of 1 MiB 41.1 / 43.0; ten of the 70B shape, 62 %, 113.5 / 111.8); elsewhere few (five layers of the 7B shape, 64 rows 93 / 76)
+        const bool filled = rounds_filled(wide) >= 0.8f || (rows > 96 && wide < 200 && rounds_filled(narrow) >= 0.75f);
+        if ((rows > 64 || large) && !filled) return Fill::few;
         // The whole fill, streaming / tile kernel: up to 64 rows the tile kernel needs the 256-column tiles of all layers to fill
         // the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape (224 tiles) 1 row 90 / 79
         // us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274

@@ -115,7 +115,10 @@ def test_two_row_groups_of_128_where_they_leave_fewer_cus_idle(rows, vocab, tile
     # 129 to 256 rows: by the tiles of 128 columns, 16 per layer (70B), 64 (7B), 8
     ((64, 8, 8192, 28672), 4, 129, "few"), ((64, 8, 8192, 28672), 5, 192, "dma"), ((64, 8, 8192, 28672), 5, 193, "few"),
     ((64, 8, 8192, 28672), 6, 256, "dma"), ((32, 32, 4096, 11008), 2, 129, "dma"), ((16, 4, 2048, 5632), 8, 160, "few"),
-    ((16, 4, 2048, 5632), 12, 129, "dma")])
+    ((16, 4, 2048, 5632), 12, 129, "dma"),
+    # 97 to 128 rows: tiles of 128 columns that fill three quarters of their rounds, 192 and 160
+    ((32, 32, 4096, 11008), 3, 96, "few"), ((32, 32, 4096, 11008), 3, 97, "dma"), ((64, 8, 8192, 28672), 12, 128, "dma"),
+    ((64, 8, 8192, 28672), 10, 128, "few"), ((32, 32, 4096, 11008), 5, 128, "few")])
 def test_kernel_of_a_fill_of_several_layers(shape, layers, rows, kind):
     cfg = dict(_cfg(shape, layers + 1, [1, layers + 1]), vocab=512)
     ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, cap=32, calls=[["fill_skipped_kv", 1, layers + 1]])])
