@@ -2268,7 +2268,13 @@ static Fill fill_kernel(int N, int K, int rows, int nz) {
         // 95 us and 99 on few), and with more than 96 rows so do tiles of 128 (three layers of the 7B shape, 128 rows 68.9 / 72.7,
         // sixteen of 1 MiB 41.1 / 43.0; ten of the 70B shape, 62 %, 113.5 / 111.8); elsewhere few (five layers of the 7B shape, 64 rows 93 / 76)
         const bool filled = rounds_filled(wide) >= 0.8f || (rows > 96 && wide < 200 && rounds_filled(narrow) >= 0.75f);
-        if ((rows > 64 || large) && !filled) return Fill::few;
+        // Few workgroups and few rows: one per tile-row on the streaming kernel, one round of them, is the shorter start up to 96 MiB
+        // of weights, 64 up to 16 rows where they are more than 128.  Streaming / few: eight layers of 4 MiB (256 tile-rows) 1 row 14.2 /
+        // 15.9 us, 32 rows 17.0 / 18.9; two of 16 MiB (128) 16.9 / 19.1 and 18.8 / 20.9, four (256) 20.9 / 20.2 and 24.1 / 25.0; two of
+        // the 70B shape (128) 27.1 / 28.3 and 30.8 / 32.2, three 32.0 / 29.9 and 36.4 / 37.0; ten of 4 MiB 18.7 / 17.5 and 22.6 / 21.9
+        const int tile_rows = N / 32 * nz;
+        const bool short_start = rows <= 32 && tile_rows <= 256 && weights < ((int64_t)(rows <= 16 && tile_rows > 128 ? 32 : 48) << 20);
+        if ((rows > 64 || large) && !filled && !short_start) return Fill::few;
         // The whole fill, streaming / tile kernel: up to 64 rows the tile kernel needs the 256-column tiles of all layers to fill
         // the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape (224 tiles) 1 row 90 / 79
         // us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274

@@ -118,7 +118,11 @@ def test_two_row_groups_of_128_where_they_leave_fewer_cus_idle(rows, vocab, tile
     ((16, 4, 2048, 5632), 12, 129, "dma"),
     # 97 to 128 rows: tiles of 128 columns that fill three quarters of their rounds, 192 and 160
     ((32, 32, 4096, 11008), 3, 96, "few"), ((32, 32, 4096, 11008), 3, 97, "dma"), ((64, 8, 8192, 28672), 12, 128, "dma"),
-    ((64, 8, 8192, 28672), 10, 128, "few"), ((32, 32, 4096, 11008), 5, 128, "few")])
+    ((64, 8, 8192, 28672), 10, 128, "few"), ((32, 32, 4096, 11008), 5, 128, "few"),
+    # up to 32 rows: 64 tile-rows per layer (70B), 32
+    ((64, 8, 8192, 28672), 2, 32, "stream"), ((64, 8, 8192, 28672), 2, 33, "few"), ((64, 8, 8192, 28672), 3, 32, "few"),
+    ((16, 4, 2048, 5632), 8, 16, "stream"), ((16, 4, 2048, 5632), 8, 32, "stream"), ((16, 4, 2048, 5632), 10, 1, "few"),
+    ((32, 8, 4096, 14336), 4, 16, "few"), ((32, 8, 4096, 14336), 4, 17, "stream")])
 def test_kernel_of_a_fill_of_several_layers(shape, layers, rows, kind):
     cfg = dict(_cfg(shape, layers + 1, [1, layers + 1]), vocab=512)
     ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, cap=32, calls=[["fill_skipped_kv", 1, layers + 1]])])
