@@ -17,10 +17,12 @@ def test_one_skipped_layer(rows):
     fill_and_compare(2, 32, rows)
 
 
-@pytest.mark.parametrize("capacity,entries", [(1100, 5), (1100, 300), (1100, 1100)])
-def test_one_more_layer_for_cached_tokens(capacity, entries):
+# 4608 values and 8 kv heads: nine slices, added up by a launch of their own (129 rows and more)
+@pytest.mark.parametrize("capacity,entries,d,hkv", [(1100, 5, 512, 32), (1100, 300, 512, 32), (1100, 1100, 512, 32), (129, 129, 4608, 8),
+                                                    (250, 40, 4608, 8)])
+def test_one_more_layer_for_cached_tokens(capacity, entries, d, hkv):
     print(f"[case] backfill of one layer, {entries} entries in a batch of {capacity}", flush=True)
-    d, hd, hkv, n_kv = 512, 128, 32, 40
+    hd, n_kv = 128, 40
     gen = torch.Generator().manual_seed(capacity + entries)
     rnd = lambda *shape, std=0.02: (torch.randn(*shape, generator=gen) * std).bfloat16()      # noqa: E731
     m = S.Model(n_layers=2, d_model=d, n_q_heads=hkv, n_kv_heads=hkv, head_dim=hd, d_ffn=64, vocab=64, dtype="bf16", exit_layers=[1, 2],

@@ -39,7 +39,8 @@ def test_every_product_is_given_its_weights(shape):
 
 @pytest.mark.parametrize("shape", [x for x in SHAPES if x[2] >= 2048], ids=str)      # narrower products are not sliced
 def test_the_append_kernel_reads_the_planes_the_product_wrote(shape):
-    """q|k|v of a context pass and of a step, keys and values of one skipped layer and of several"""
+    """q|k|v of a context pass and of a step, keys and values of one skipped layer and of several; or none, where a launch has added
+    them up"""
     calls = [["fill_skipped_kv", 1, 2], ["fill_skipped_kv", 1, 4], ["backfill_kv", 3, 4, 1], ["layer_forward", 1]]
     got = launches([dict(cfg=_cfg(shape, 4, [1, 2, 4]), rows=n, calls=calls + [["prefill", n]]) for n in ROWS])
     qkv, sliced = (shape[0] + 2 * shape[1]) * 128, 0
@@ -50,8 +51,8 @@ def test_the_append_kernel_reads_the_planes_the_product_wrote(shape):
                 if x["kernel"] != "k_bf16_rope_append":
                     continue
                 splits, plane, planes, ld, start = x["args"][-5:]
-                made = next(y for y in reversed(ran[:i]) if y["kernel"].startswith("k_bf16_gemm"))
-                if "long" not in made["types"] or made["args"][made["types"].index("int const*") - 1] == 1:
+                made = next(y for y in reversed(ran[:i]) if y["kernel"].startswith(("k_bf16_gemm", "k_splitk_finish")))
+                if made["kernel"].startswith("k_splitk") or "long" not in made["types"] or made["args"][made["types"].index("int const*") - 1] == 1:
                     assert splits == 1 and start == columns, (n, call)
                     continue
                 at = made["types"].index("long")
@@ -127,3 +128,12 @@ def test_kernel_of_a_fill_of_several_layers(shape, layers, rows, kind):
     cfg = dict(_cfg(shape, layers + 1, [1, layers + 1]), vocab=512)
     ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, cap=32, calls=[["fill_skipped_kv", 1, layers + 1]])])
     assert rc == 0 and ("_gemm_" + kind if kind != "stream" else "k_bf16_gemm<") in _products(ran)[0]["kernel"]
+
+
+@pytest.mark.parametrize("rows,planes", [(128, "few"), (129, 16), (256, 16), (257, 8), (1000, 4)])
+def test_many_planes_of_one_skipped_layer_are_added_up_before_the_append(rows, planes):
+    cfg = dict(_cfg((64, 8, 8192, 28672), 2, [1, 2]), vocab=512)
+    ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, cap=32, calls=[["fill_skipped_kv", 1, 2]])])
+    splits = _products(ran)[0]["args"][6]
+    assert rc == 0 and (planes == "few" or splits == planes)
+    assert any(x["kernel"].startswith("k_splitk_finish") for x in ran) == (splits > 8)
