@@ -23,7 +23,7 @@
 // ROPE: the q|k|v product, rotation and cache append in one launch.  A workgroup has 16 rotation pairs of one head: columns
 // j and j + hd / 2, as SWIGLU has gate and up.  Rotated queries go to out, rotated keys and the values to the
 // cache at the row's position.  As a launch of its own rotation and append took 2.6 of the 147 us of the fp32 workload's
-// step six times; the K/V of all skipped layers are one launch (blockIdx.z = layer offset).
+// step six times; the K/V of the skipped layers are one launch for 32 layers (blockIdx.z).
 // What a launch waits for is a chain of trips to memory, so everything that does not depend on the number of live
 // rows is asked for beside it: the row ids, and of the epilogue's operands row id, old value, scale or position.
 enum { F32_EPI_RESID = 0, F32_EPI_SCALE = 1, F32_EPI_SWIGLU = 2, F32_EPI_ROPE = 3 };
@@ -38,13 +38,16 @@ struct F32Gemm {
     const float* row_scale;              // SCALE: per row id
     const float* gain; float eps;        // NORM
 };
+#define F32_ROPE_LAYERS 32
 struct F32Rope {                         // ROPE
     int n_q, head0;                      // query heads of W, first head of the launch
     const int32_t* pos; const float* rope; int max_pos;
     KvView kv;
     int32_t* status;
-    const void* const* w_tab; const float* const* g_tab; int z0;      // several layers: W and gain of layer z0 + blockIdx.z
+    // W and gain of each layer (blockIdx.z).  By value: what the layers were when the call was made, as for every other product
+    const float* w[F32_ROPE_LAYERS]; const float* gain[F32_ROPE_LAYERS];
 };
+struct F32None {};
 
 template <bool VEC>
 __device__ __forceinline__ float4 f32_load4(const float* p, int k, int K) {
@@ -52,9 +55,9 @@ __device__ __forceinline__ float4 f32_load4(const float* p, int k, int K) {
     else return make_float4(k < K ? p[k] : 0.f, k + 1 < K ? p[k + 1] : 0.f, k + 2 < K ? p[k + 2] : 0.f, k + 3 < K ? p[k + 3] : 0.f);
 }
 
-template <int EPI, bool NORM, bool VEC>
+template <int EPI, bool NORM, bool VEC, class P>      // P: F32Rope for ROPE, else F32None
 __global__ void __launch_bounds__(64 * F32_WAVES)
-k_f32_gemm(F32Gemm g, F32Rope p) {
+k_f32_gemm(F32Gemm g, P p) {
     typedef float floatx4 __attribute__((ext_vector_type(4)));
     constexpr bool ROPE = EPI == F32_EPI_ROPE;
     constexpr int NW = EPI == F32_EPI_SWIGLU || ROPE ? 2 : 1;      // weight rows per result
@@ -90,11 +93,8 @@ k_f32_gemm(F32Gemm g, F32Rope p) {
         const int j0 = blockIdx.x % per_head * 16;
         col = j0 + (el & 15);
         wrow = head * 2 * half + min(j0 + m, half - 1);
-        if (p.w_tab) {
-            g.W = reinterpret_cast<const float*>(p.w_tab[p.z0 + blockIdx.z]);
-            g.gain = p.g_tab[p.z0 + blockIdx.z];
-            p.kv.layer0 += blockIdx.z;
-        }
+        g.W = p.w[blockIdx.z];
+        g.gain = p.gain[blockIdx.z];
     } else {
         col = blockIdx.x * 16 + (el & 15);
         wrow = min((int)blockIdx.x * 16 + m, g.N - 1);
@@ -148,8 +148,9 @@ k_f32_gemm(F32Gemm g, F32Rope p) {
             }
         }
     }
-    const bool pos_ok = at >= 0 && at < cap && at < p.max_pos;
+    bool pos_ok = true;
     if constexpr (ROPE) {
+        pos_ok = at >= 0 && at < cap && at < p.max_pos;
         if (pos_ok && col_ok) cs = *reinterpret_cast<const float2*>(p.rope + ((int64_t)at * half + col) * 2);
     }
 #pragma unroll
@@ -179,7 +180,7 @@ k_f32_gemm(F32Gemm g, F32Rope p) {
     if constexpr (EPI == F32_EPI_RESID) g.out[(int64_t)eid * g.ldo + col] = old + v[0];
     else if constexpr (EPI == F32_EPI_SCALE) g.out[(int64_t)erow * g.ldo + col] = v[0] * old;
     else if constexpr (EPI == F32_EPI_SWIGLU) g.out[(int64_t)erow * g.ldo + col] = (v[0] / (1.0f + expf(-v[0]))) * v[NW - 1];
-    else {
+    else if constexpr (ROPE) {
         const int hd = 2 * half;
         const bool is_q = head < p.n_q, is_v = head >= p.n_q + p.kv.n_kv_heads;
         const float a = v[0], b = v[NW - 1];
@@ -194,7 +195,7 @@ k_f32_gemm(F32Gemm g, F32Rope p) {
             dst = g.out + (int64_t)erow * g.ldo + head * hd;
         } else {
             const int kvh = head - p.n_q - (is_v ? p.kv.n_kv_heads : 0);
-            dst = reinterpret_cast<float*>(p.kv.pool) + ((int64_t)p.kv.layer0 * p.kv.T + off) * (2LL * p.kv.n_kv_heads * hd) +
+            dst = reinterpret_cast<float*>(p.kv.pool) + ((int64_t)(p.kv.layer0 + blockIdx.z) * p.kv.T + off) * (2LL * p.kv.n_kv_heads * hd) +
                   (int64_t)kvh * 2LL * cap * hd + (is_v ? (int64_t)cap * hd : 0) + (int64_t)at * hd;
         }
         dst[col] = x0;
@@ -404,31 +405,32 @@ static KvView make_view(const ee_model* m, const ee_kv* kv, int layer, const ee_
     return KvView{kv->pool, kv->d_cap, kv->d_off, kv->T, m->cfg.n_kv_heads, m->cfg.head_dim, layer - 1, b->kv_seq};
 }
 
-template <int EPI, bool NORM>
-static void gemm(const F32Gemm& g, hipStream_t s, const F32Rope& p = F32Rope{}, int cols = 0, int nz = 1, bool tab_aligned = true) {
+template <int EPI, bool NORM, class P = F32None>
+static void gemm(const F32Gemm& g, hipStream_t s, const P& p = P{}, int cols = 0, int nz = 1, bool w_aligned = true) {
     const dim3 grid(cols ? cols : (g.N + 15) / 16, (g.B + 15) / 16, nz), block(64 * F32_WAVES);
     const uintptr_t a = (uintptr_t)g.X | (uintptr_t)g.W | (NORM ? (uintptr_t)g.gain : 0);
-    if (g.K % 4 == 0 && g.ldx % 4 == 0 && a % 16 == 0 && tab_aligned) hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, true>), grid, block, 0, s, g, p);
-    else hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, false>), grid, block, 0, s, g, p);
+    if (g.K % 4 == 0 && g.ldx % 4 == 0 && a % 16 == 0 && w_aligned) hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, true, P>), grid, block, 0, s, g, p);
+    else hipLaunchKernelGGL((k_f32_gemm<EPI, NORM, false, P>), grid, block, 0, s, g, p);
 }
 
-// the launch that makes queries, keys and values of the rows of a list: heads head0 .. of layers first .. first + nl - 1
+// queries, keys and values of the rows of a list: heads head0 .. of layers first .. first + nl - 1, one launch per F32_ROPE_LAYERS layers
 static void rope_gemm(const ee_model* m, const ee_kv* kv, ee_batch* b, int first, int nl, int head0, const int32_t* idx,
                       const int32_t* n_ptr, hipStream_t s) {
     const ee_model_config& c = m->cfg;
     const int heads = c.n_q_heads + 2 * c.n_kv_heads, per_head = (c.head_dim / 2 + 15) / 16;
-    const ee_layer_weights& w = m->layers[first - 1];
-    F32Gemm g{b->st<float>(b->L.h), c.d_model, (const float*)w.w_qkv, heads * c.head_dim, c.d_model, n_ptr, b->B, b->wsp<float>(b->W.qkv),
-              heads * c.head_dim, idx, nullptr, w.g_attn, c.rms_eps};
-    F32Rope p{c.n_q_heads, head0, b->st<int32_t>(b->L.pos), m->d_rope, c.max_pos, make_view(m, kv, first, b), b->st<int32_t>(b->L.status),
-              nullptr, nullptr, 0};
-    bool aligned = true;
-    if (nl > 1) {
-        p.w_tab = m->d_wqkv_tab; p.g_tab = m->d_gattn_tab; p.z0 = first - 1;
-        for (int l = first; l < first + nl; ++l)
-            aligned = aligned && (((uintptr_t)m->layers[l - 1].w_qkv | (uintptr_t)m->layers[l - 1].g_attn) & 15) == 0;
+    for (const int end = first + nl; first < end; first += F32_ROPE_LAYERS) {
+        F32Gemm g{b->st<float>(b->L.h), c.d_model, nullptr, heads * c.head_dim, c.d_model, n_ptr, b->B, b->wsp<float>(b->W.qkv),
+                  heads * c.head_dim, idx, nullptr, nullptr, c.rms_eps};
+        F32Rope p{c.n_q_heads, head0, b->st<int32_t>(b->L.pos), m->d_rope, c.max_pos, make_view(m, kv, first, b), b->st<int32_t>(b->L.status), {}, {}};
+        const int n = std::min(end - first, F32_ROPE_LAYERS);
+        bool aligned = true;
+        for (int z = 0; z < n; ++z) {
+            const ee_layer_weights& w = m->layers[first - 1 + z];
+            p.w[z] = (const float*)w.w_qkv; p.gain[z] = w.g_attn;
+            aligned = aligned && (((uintptr_t)w.w_qkv | (uintptr_t)w.g_attn) & 15) == 0;
+        }
+        gemm<F32_EPI_ROPE, true>(g, s, p, (heads - head0) * per_head, n, aligned);
     }
-    gemm<F32_EPI_ROPE, true>(g, s, p, (heads - head0) * per_head, nl, aligned);
 }
 
 int f32_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipStream_t s) {
