@@ -240,10 +240,10 @@ k_bf16_begin_norm(BeginArgs g, int near, const float* __restrict__ gain, float e
 }
 
 // ------------------------------------------------------------------ weight-streaming MFMA GEMM
-// out[i][j] = sum_k X[i][k] W[j][k] for the first n rows of X (n read on the device).
-// A workgroup has WK x WN waves.  Wave (wk, wn) owns NS consecutive 32-column
-// tile-rows of W, all MS 32-row tiles of X, and the wk-th slice of the K range;
-// the WK partial sums of a tile are added in a fixed order through LDS.
+// out[i][j] = sum_k X[i][k] W[j][k] for the first n rows of X (n read on the device), at most 64.
+// A workgroup has WK waves and owns NS consecutive 32-column tile-rows of W and all MS 32-row tiles
+// of X; wave wk takes the wk-th slice of the K range, and the WK partial sums of a tile are added in
+// a fixed order through LDS.
 // 16 bytes that this launch reads once (weights, cached keys and values): a non-temporal load.
 // Measured: streams of such loads run 10-13 % faster than ordinary ones, which hold a line of
 // the vector cache while they are in flight.
@@ -269,27 +269,25 @@ struct EpiArgs {
     int            KB_act;    // F / 16
 };
 
-template <int MS, int NS, int WK, int WN, int EPI>
-__global__ void __launch_bounds__(64 * WK * WN)
+template <int MS, int NS, int WK, int EPI>
+__global__ void __launch_bounds__(64 * WK)
 k_bf16_gemm(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, int NB_total, int NBs, int nb_off,
             const int32_t* __restrict__ n_ptr, int B, EpiArgs ep, ZBatch zb) {
     constexpr int IPW = 16 / WK;   // accumulator registers each wave finishes after the reduction
     constexpr int GD = 4;          // K tiles per load group
-    __shared__ float red[(WK > 1) ? (WK * WN * NS * 16 * 64) : 1];
+    __shared__ float red[WK * NS * 16 * 64];
     const int n = min(*n_ptr, B);
-    const int row_base = blockIdx.y * (32 * MS);
-    if (row_base >= n) return;
+    if (n <= 0) return;
     if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
     Xp += (int64_t)blockIdx.z * zb.x_stride;
     ep.out += (int64_t)blockIdx.z * zb.out_stride;
-    const int mbs = min(MS, (n - row_base + 31) >> 5);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wk = wave % WK, wn = wave / WK;
-    const int nb0 = (blockIdx.x * WN + wn) * NS;
+    const int mbs = min(MS, (n + 31) >> 5);
+    const int lane = threadIdx.x & 63, wk = threadIdx.x >> 6;
+    const int nb0 = blockIdx.x * NS;
     const int kb_lo = (int)(((int64_t)KB * wk) / WK), kb_hi = (int)(((int64_t)KB * (wk + 1)) / WK);
-    const uint4* xw = Xp + ((int64_t)blockIdx.y * MS * KB) * 64 + lane;
+    const uint4* xw = Xp + lane;
     const uint4* ww = Wp + (int64_t)(nb_off + nb0) * 64 + lane;   // tile (r, c) sits at slot c * NBs + r
-    const bool has_cols = nb0 + NS <= NB_total;   // uniform per wave
+    const bool has_cols = nb0 + NS <= NB_total;   // uniform over the workgroup
 
     floatx16 acc[MS][NS];
 #pragma unroll
@@ -362,34 +360,26 @@ k_bf16_gemm(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int KB, 
     for (int ms = 0; ms < MS; ++ms) {
         if (ms >= mbs) break;              // uniform over the workgroup
         float v[NS][IPW];
-        if (WK > 1) {
 #pragma unroll
-            for (int ns = 0; ns < NS; ++ns)
+        for (int ns = 0; ns < NS; ++ns)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) red[((wave * NS + ns) * 16 + r) * 64 + lane] = acc[ms][ns][r];
-            __syncthreads();
+            for (int r = 0; r < 16; ++r) red[((wk * NS + ns) * 16 + r) * 64 + lane] = acc[ms][ns][r];
+        __syncthreads();
 #pragma unroll
-            for (int ns = 0; ns < NS; ++ns)
+        for (int ns = 0; ns < NS; ++ns)
 #pragma unroll
-                for (int ii = 0; ii < IPW; ++ii) {
-                    float s = 0.f;
+            for (int ii = 0; ii < IPW; ++ii) {
+                float s = 0.f;
 #pragma unroll
-                    for (int k2 = 0; k2 < WK; ++k2)
-                        s += red[(((wn * WK + k2) * NS + ns) * 16 + (wk * IPW + ii)) * 64 + lane];
-                    v[ns][ii] = s;
-                }
-            __syncthreads();
-        } else {
-#pragma unroll
-            for (int ns = 0; ns < NS; ++ns)
-#pragma unroll
-                for (int ii = 0; ii < IPW; ++ii) v[ns][ii] = acc[ms][ns][ii];
-        }
+                for (int k2 = 0; k2 < WK; ++k2) s += red[((k2 * NS + ns) * 16 + (wk * IPW + ii)) * 64 + lane];
+                v[ns][ii] = s;
+            }
+        __syncthreads();
         if (!has_cols) continue;
 #pragma unroll
         for (int ii = 0; ii < IPW; ++ii) {
             const int r = wk * IPW + ii;   // accumulator register index 0..15
-            const int row = row_base + 32 * ms + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            const int row = 32 * ms + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
             const bool live = row < n;
             const int cl = lane & 31;
             if (EPI == EPI_STORE) {
@@ -1002,7 +992,7 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int r0, const 
     using Yes = std::true_type;
     using No = std::false_type;
     // the count of loads a wave may leave in flight is per wave and follows from what it sends, so each
-    // combination runs its own copy of the loop; a wave whose four row tiles are live (the common case)
+    // combination runs its own copy of the loop; a wave whose two row tiles are live (the common case)
     // runs a copy without the live-tile test
     const bool all = cnt == COLS_NR;
     if (sends_x && sends_w) { if (all) slice(Yes{}, Yes{}, Yes{}); else slice(Yes{}, Yes{}, No{}); }
@@ -1343,22 +1333,22 @@ struct AttnShared {
     float o[WAVES][16][132];    // 128 features; rows of 132 floats put a 16-byte access of the 16 columns into different banks
 };
 
-// Rotation and append in the attention of a decode step (FUSED): the q|k|v product's result is taken as it is (its columns
-// before `from` from buf, the others as `splits` K-slice planes, as in k_bf16_rope_append).  Wave 0 and 1 rotate the queries of
+// Rotation and append in the attention of a decode step (FUSED): the q|k|v product's result is taken as it is (from buf, or
+// as `splits` K-slice planes, as in k_bf16_rope_append; some columns so and others so is for context passes).  Wave 0 and 1 rotate the queries of
 // the workgroup's heads (features 32 c + .. and 32 c + 64 + .. are pairs, c = 0 and 1) and leave them as (hi, lo) pairs in
 // LDS, wave 3 rotates and appends the key and appends the value, all while the other waves' first cached keys and values are
 // on their way.  The group that holds the new position is read after the barrier, from L2.  As a launch of its own this took 3.5 to 4 us on a few
 // rows; which calls come here: append_in_attn.
 struct QkvIn {
-    const float* buf; int ld, from;
-    const float* planes; int ld_planes, splits; int64_t plane;
+    const float* buf; int ld;                               // of the planes too
+    const float* planes; int splits; int64_t plane;
     const float* rope; int max_pos;
     int32_t* status;
-    // N times 4 columns of entry i (x[k] a multiple of 4, all on one side of `from`): the loads of two planes under way together
+    // N times 4 columns of entry i (x[k] a multiple of 4): the loads of two planes under way together
     template <int N>
     __device__ __forceinline__ void rd4(int i, const int (&x)[N], float4 (&v)[N]) const {
-        const bool done = x[0] < from;
-        const float* p = done ? buf + (int64_t)i * ld : planes + (int64_t)i * ld_planes - from;
+        const bool done = splits == 1;
+        const float* p = (done ? buf : planes) + (int64_t)i * ld;
 #pragma unroll
         for (int k = 0; k < N; ++k) v[k] = *reinterpret_cast<const float4*>(p + x[k]);
         if (done) return;
@@ -2013,28 +2003,19 @@ static int rope_blocks(int n_q, int n_kv, int rows) {
     return std::min({8, (items + 255) / 256, std::max(4, 8192 / rows)});
 }
 
-template <int MS, int NS, int WK, int WN, int EPI>
-static void gemm_launch(const void* X, const void* W, int K, int NB_total, int NBs, int nb_off, const int32_t* n_ptr,
-                        int B, const EpiArgs& ep, hipStream_t s, const ZBatch& zb, int nz) {
-    dim3 grid((NB_total + WN * NS - 1) / (WN * NS), 1, nz);
-    hipLaunchKernelGGL((k_bf16_gemm<MS, NS, WK, WN, EPI>), grid, dim3(64 * WK * WN), 0, s, (const uint4*)X,
-                       (const uint4*)W, K / 16, NB_total, NBs, nb_off, n_ptr, B, ep, zb);
-}
-
 // picks the tile configuration from the row capacity of the batch: at most 64 rows come here (gemm_tiled)
 template <int NS, int EPI>
 static void gemm(const void* X, const void* W, int N, int K, int NBs, int nb_off, const int32_t* n_ptr, int B,
                  const EpiArgs& ep, hipStream_t s, const ZBatch& zb = ZBatch{}, int nz = 1) {
-    if (B <= 32) gemm_launch<1, NS, 8, 1, EPI>(X, W, K, N / 32, NBs, nb_off, n_ptr, B, ep, s, zb, nz);
-    else         gemm_launch<2, NS, 8, 1, EPI>(X, W, K, N / 32, NBs, nb_off, n_ptr, B, ep, s, zb, nz);
+    auto kern = B <= 32 ? k_bf16_gemm<1, NS, 8, EPI> : k_bf16_gemm<2, NS, 8, EPI>;
+    hipLaunchKernelGGL(kern, dim3((N / 32 + NS - 1) / NS, 1, nz), dim3(64 * 8), 0, s, (const uint4*)X, (const uint4*)W, K / 16, N / 32, NBs, nb_off,
+                       n_ptr, B, ep, zb);
 }
 
-// Adds the K-slice planes in slice order and applies the epilogue: plain store, or
-// residual update h[row id] += sum.  One thread per 4 consecutive columns.
-template <int EPI>
+// Adds the K-slice planes in slice order into out.  One thread per 4 consecutive columns.
 __global__ void __launch_bounds__(256)
 k_splitk_finish(const float* __restrict__ partial, int64_t plane, int ld, int splits, int N,
-                const int32_t* __restrict__ n_ptr, int B, EpiArgs ep) {
+                const int32_t* __restrict__ n_ptr, int B, float* __restrict__ out, int ldo) {
     const int n = min(*n_ptr, B);
     const int row = blockIdx.y;
     if (row >= n) return;
@@ -2046,14 +2027,7 @@ k_splitk_finish(const float* __restrict__ partial, int64_t plane, int ld, int sp
         float4 v = *reinterpret_cast<const float4*>(p + (int64_t)q * plane);
         sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
     }
-    if (EPI == EPI_STORE) {
-        *reinterpret_cast<float4*>(ep.out + (int64_t)row * ep.ldo + col) = sum;
-    } else {
-        float4* h = reinterpret_cast<float4*>(ep.out + (int64_t)ep.idx[row] * ep.ldo + col);
-        float4 o = *h;
-        o.x += sum.x; o.y += sum.y; o.z += sum.z; o.w += sum.w;
-        *h = o;
-    }
+    *reinterpret_cast<float4*>(out + (int64_t)row * ldo + col) = sum;
 }
 
 // Residual finish of a K-sliced product, one block per list entry: h[row id] += sum of the
@@ -2182,8 +2156,8 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
         if (tail.norm_gain && tail.norm_done) *tail.norm_done = true;
     } else if (splits > tail.defer_most) {
         if (tail.splits_out) *tail.splits_out = 1;
-        hipLaunchKernelGGL((k_splitk_finish<EPI_STORE>), dim3((N / 4 + 255) / 256, B), dim3(256), 0, s,
-                           b->wsp<float>(b->W.gemm_part), plane, N, splits, N, n_ptr, B, ep);
+        hipLaunchKernelGGL(k_splitk_finish, dim3((N / 4 + 255) / 256, B), dim3(256), 0, s, b->wsp<float>(b->W.gemm_part), plane, N, splits, N,
+                           n_ptr, B, ep.out, ep.ldo);
     }
 }
 
@@ -2545,15 +2519,15 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     EpiArgs e1{};
     e1.out = qkv; e1.ldo = qkv_n; e1.idx = idx;
     int qkv_splits = 1, qkv_from = 0;
+    const bool together = append_in_attn(c, b);
     {
         TimedScope t(EE_K_GEMM_QKV, s);
-        SliceTail st;                  // K-slice planes of q|k|v are added up by the RoPE kernel
-        st.defer_most = 16; st.splits_out = &qkv_splits; st.from_out = &qkv_from;
+        SliceTail st;                  // K-slice planes of q|k|v are added up by the append kernel, or the attention, which takes all columns so
+        st.defer_most = 1 << 30; st.splits_out = &qkv_splits; st.from_out = together ? nullptr : &qkv_from;
         if (!gemm_tiled<EPI_STORE>(b, x, w.w_qkv, qkv_n, d, qkv_n / 32, 0, n_ptr, B, e1, s, ZBatch{}, 1, st))
             gemm<1, EPI_STORE>(x, w.w_qkv, qkv_n, d, qkv_n / 32, 0, n_ptr, B, e1, s);
     }
     if (qkv_splits == 1) qkv_from = qkv_n;             // nothing is in planes
-    const bool together = append_in_attn(c, b);
     if (!together) {
         TimedScope t(EE_K_ROPE_APPEND, s);
         // neighbouring entries share lines of the cache only where they are positions of one row (context pass)
@@ -2571,8 +2545,8 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
         const int G = c.n_q_heads / c.n_kv_heads;
         const bool pair = b->kv_seq != nullptr && pairs >= 512 && 2 * G <= 16;
         if (together) {
-            const QkvIn in{qkv, qkv_n, qkv_from, b->wsp<float>(b->W.gemm_part), qkv_n - qkv_from, qkv_splits,
-                           (int64_t)b->Mpad * (qkv_n - qkv_from), m->d_rope, c.max_pos, b->st<int32_t>(L.status)};
+            const QkvIn in{qkv, qkv_n, b->wsp<float>(b->W.gemm_part), qkv_splits, (int64_t)b->Mpad * qkv_n, m->d_rope, c.max_pos,
+                           b->st<int32_t>(L.status)};
             hipLaunchKernelGGL(k_bf16_attn_decode, dim3(c.n_kv_heads, B, most), dim3(256), 0, s, in, c.n_q_heads, n_ptr, B, view, ao, qd / 16,
                                most, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
         } else if (ctx.C) {
