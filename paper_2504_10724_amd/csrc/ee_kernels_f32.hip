@@ -297,12 +297,15 @@ k_f32_attn(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restr
     *reinterpret_cast<float4*>(out + (int64_t)i * (Hq * hd) + hq * hd + c) = make_float4(acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
 }
 
-// other hd: one position per thread, then one value per thread
+// The same through the scores of all positions in LDS: maximum, exponentials and sum over the workgroup, then the values.  One
+// exponential per position, where the kernel above has one per lane: for many pairs on long rows (two_passes below), and, one
+// position and then one value per thread, for other hd.
+template <bool VEC>
 __global__ void __launch_bounds__(256)
-k_f32_attn_any(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restrict__ idx,
-               const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv,
-               float* __restrict__ out /* [i][Hq*hd] */) {
-    extern __shared__ float sm[];   // q[hd] | scores
+k_f32_attn_scores(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __restrict__ idx,
+           const int32_t* __restrict__ n_ptr, int B, const int32_t* __restrict__ pos, KvView kv,
+           float* __restrict__ out /* [i][Hq*hd] */, int L) {
+    extern __shared__ float sm[];   // VEC: partial outputs [256 / L][hd] (at most 4 * 256) | scores; else q[hd] | scores
     __shared__ float red[4];
     int hq = blockIdx.x, i = blockIdx.y;
     int n = min(*n_ptr, B);
@@ -316,17 +319,43 @@ k_f32_attn_any(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __r
     const float* Kb = reinterpret_cast<const float*>(kv.pool) + kv_block(kv, sq, g, cap);
     const float* Vb = Kb + (int64_t)cap * hd;
     const float* qrow = qkv + (int64_t)i * ld + hq * hd;
-    float *q = sm, *sc = sm + hd;
+    float* sc = sm + (VEC ? 1024 : hd);
     const float inv_sqrt = 1.0f / sqrtf((float)hd);
+    const int c = 4 * (threadIdx.x & (L - 1)), grp = threadIdx.x / L, groups = 256 / L;     // VEC
+    const bool has = c < hd;
     float mx = -FLT_MAX;
-    for (int t = threadIdx.x; t < hd; t += 256) q[t] = qrow[t];
-    __syncthreads();
-    for (int t = threadIdx.x; t < n_pos; t += 256) {
-        float a = 0.f;
-        for (int j = 0; j < hd; ++j) a += q[j] * Kb[(int64_t)t * hd + j];
-        a *= inv_sqrt;
-        sc[t] = a;
-        mx = fmaxf(mx, a);
+    if constexpr (VEC) {
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 q = has ? *reinterpret_cast<const float4*>(qrow + c) : zero;
+        for (int t0 = grp; t0 < n_pos; t0 += 4 * groups) {
+            float4 k[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = t0 + u * groups;
+                k[u] = has && t < n_pos ? *reinterpret_cast<const float4*>(Kb + (int64_t)t * hd + c) : zero;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float a = (q.x * k[u].x + q.y * k[u].y) + (q.z * k[u].z + q.w * k[u].w);
+                for (int o = L >> 1; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+                const int t = t0 + u * groups;
+                if (t >= n_pos) continue;
+                a *= inv_sqrt;
+                if (c == 0) sc[t] = a;
+                mx = fmaxf(mx, a);
+            }
+        }
+    } else {
+        float* q = sm;
+        for (int t = threadIdx.x; t < hd; t += 256) q[t] = qrow[t];
+        __syncthreads();
+        for (int t = threadIdx.x; t < n_pos; t += 256) {
+            float a = 0.f;
+            for (int j = 0; j < hd; ++j) a += q[j] * Kb[(int64_t)t * hd + j];
+            a *= inv_sqrt;
+            sc[t] = a;
+            mx = fmaxf(mx, a);
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
@@ -342,10 +371,29 @@ k_f32_attn_any(const float* __restrict__ qkv, int ld, int Hq, const int32_t* __r
     }
     sum = block_sum<256>(sum, red);   // also makes sc[] visible to all threads
     float* orow = out + (int64_t)i * (Hq * hd) + hq * hd;
-    for (int j = threadIdx.x; j < hd; j += 256) {
-        float acc = 0.f;
-        for (int t = 0; t < n_pos; ++t) acc += sc[t] * Vb[(int64_t)t * hd + j];
-        orow[j] = acc / sum;
+    if constexpr (VEC) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (has) {
+#pragma unroll 4
+            for (int t = grp; t < n_pos; t += groups) {
+                const float p = sc[t];
+                const float4 v = *reinterpret_cast<const float4*>(Vb + (int64_t)t * hd + c);
+                acc.x += p * v.x; acc.y += p * v.y; acc.z += p * v.z; acc.w += p * v.w;
+            }
+            *reinterpret_cast<float4*>(sm + grp * hd + c) = acc;
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < hd; j += 256) {
+            float a = 0.f;
+            for (int k = 0; k < groups; ++k) a += sm[k * hd + j];
+            orow[j] = a / sum;
+        }
+    } else {
+        for (int j = threadIdx.x; j < hd; j += 256) {
+            float acc = 0.f;
+            for (int t = 0; t < n_pos; ++t) acc += sc[t] * Vb[(int64_t)t * hd + j];
+            orow[j] = acc / sum;
+        }
     }
 }
 
@@ -448,16 +496,20 @@ int f32_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipS
     KvView view = make_view(m, kv, layer, b);
 
     rope_gemm(m, kv, b, layer, 1, 0, idx, n_ptr, s);
-    if (hd % 4 == 0) {
-        int lanes = 1;                        // lanes that share a position: a power of two that holds hd / 4
-        while (4 * lanes < hd) lanes *= 2;
-        const int pairs = B * c.n_q_heads;
+    int lanes = 1;                            // lanes that share a position: a power of two that holds hd / 4
+    while (4 * lanes < hd) lanes *= 2;
+    const int pairs = (b->n_entries > 0 ? b->n_entries : B) * c.n_q_heads, cap = kv->max_cap;
+    // Many pairs and room for long rows.  Layer, one pass / two: context passes, 4 heads, 100 entries from 1500 on 55 / 70 us, 200
+    // 88 / 84, 300 from 100 on 55 / 58, 600 from 0 on 88 / 85, from 1500 on 210 / 172; 16 heads of 32, 300 entries from 500 on 103 /
+    // 93, from 1500 on 178 / 138.  Decode steps, whose rows come from memory: 100 rows of 8 heads of 128, 1500 positions 338 / 322,
+    // 150 455 / 450, 250 433 / 456 (700 positions).
+    const bool two_passes = cap > 512 && pairs > 768 && (b->kv_seq != nullptr || pairs <= 1100);
+    if (hd % 4 == 0 && !two_passes) {
         // Waves of a workgroup, by what the host knows, the (row, head) pairs and the longest row that the cache has room for; rows
         // may be much shorter, so that no choice may cost them what it gives long ones.  Layer, 4 / 8 / 16 waves: 32 pairs, 62
         // positions 22.6 / 23.1 / 24.3 us, 700 39.5 / 32.4 / 28.9; 400 pairs 26.3 / 27.4 / 30.8 and 47.4 / 48.0 / 46.9; 528
         // pairs, 1500 positions 230 / 253 / 255; 800 pairs 352 / 338 / 342, 40 positions 98.6 / 98.4 / 104; 4000 pairs, 40
         // positions 47 / 56 / 73.
-        const int cap = kv->max_cap;
         int waves;
         if (cap <= 64) waves = 4;
         else if (pairs <= 256) waves = cap <= 256 ? 8 : 16;
@@ -466,9 +518,12 @@ int f32_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hipS
         auto kern = waves == 4 ? k_f32_attn<256> : waves == 8 ? k_f32_attn<512> : k_f32_attn<1024>;
         hipLaunchKernelGGL(kern, dim3(c.n_q_heads, B), dim3(64 * waves), 0, s, qkv, qkv_n, c.n_q_heads, idx, n_ptr, B,
                            b->st<int32_t>(L.pos), view, ao, lanes);
+    } else if (hd % 4 == 0) {
+        hipLaunchKernelGGL(k_f32_attn_scores<true>, dim3(c.n_q_heads, B), dim3(256), (size_t)(1024 + c.max_pos) * sizeof(float), s, qkv,
+                           qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao, lanes);
     } else {
-        hipLaunchKernelGGL(k_f32_attn_any, dim3(c.n_q_heads, B), dim3(256), (size_t)(hd + c.max_pos) * sizeof(float), s, qkv,
-                           qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao);
+        hipLaunchKernelGGL(k_f32_attn_scores<false>, dim3(c.n_q_heads, B), dim3(256), (size_t)(hd + c.max_pos) * sizeof(float), s, qkv,
+                           qkv_n, c.n_q_heads, idx, n_ptr, B, b->st<int32_t>(L.pos), view, ao, 1);
     }
     gemm<F32_EPI_RESID, false>(F32Gemm{ao, qd, (const float*)w.w_o, d, qd, n_ptr, B, h, d, idx, nullptr, nullptr, 0.f}, s);
     gemm<F32_EPI_SWIGLU, true>(F32Gemm{h, d, (const float*)w.w_gate_up, F, d, n_ptr, B, act, F, idx, nullptr, w.g_ffn, c.rms_eps}, s);
