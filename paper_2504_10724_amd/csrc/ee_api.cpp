@@ -508,6 +508,16 @@ int ee_compact_active(ee_batch* b, int exit_idx, int exit_layer, void* stream) {
     return launch_compact(b, exit_idx, exit_layer, false, as_stream(stream));
 }
 
+// from, the exit layers between, to: the ranges a decode step fills one by one; returns how many
+static int exit_bounds(const ee_model* m, int from, int to, int32_t* bounds) {
+    int n = 0;
+    bounds[n++] = from;
+    for (int e = 0; e < m->cfg.n_exits; ++e)
+        if (m->cfg.exit_layers[e] > from && m->cfg.exit_layers[e] < to) bounds[n++] = m->cfg.exit_layers[e];
+    bounds[n] = to;
+    return n;
+}
+
 int ee_fill_skipped_kv(const ee_model* m, int from_layer_excl, int to_layer_incl, ee_kv* kv, ee_batch* b,
                        void* stream) {
     int rc = check_pair("ee_fill_skipped_kv", m, kv, b);
@@ -518,8 +528,10 @@ int ee_fill_skipped_kv(const ee_model* m, int from_layer_excl, int to_layer_incl
         if (!m->resident[l - 1]) return ee_fail(EE_ERR_LAYER_NOT_RESIDENT, "ee_fill_skipped_kv: layer is not resident");
     if (to_layer_incl > kv->n_layers) return ee_fail(EE_ERR_CAPACITY, "ee_fill_skipped_kv: cache holds fewer layers");
     if (from_layer_excl >= to_layer_incl) return EE_OK;
-    return m->cfg.dtype == EE_BF16 ? bf16_fill_kv(m, from_layer_excl, to_layer_incl, kv, b, as_stream(stream))
-                                   : f32_fill_kv(m, from_layer_excl, to_layer_incl, kv, b, as_stream(stream));
+    if (m->cfg.dtype != EE_BF16) return f32_fill_kv(m, from_layer_excl, to_layer_incl, kv, b, as_stream(stream));
+    int32_t bounds[EE_MAX_EXITS + 2];
+    const int n = exit_bounds(m, from_layer_excl, to_layer_incl, bounds);
+    return bf16_fill_ranges(m, bounds, n, false, kv, b, as_stream(stream));
 }
 
 int ee_prefill(const ee_model* m, ee_kv* kv, ee_batch* b, const int32_t* dev_tok, const int32_t* dev_pos,
@@ -821,13 +833,10 @@ int ee_decode_finish(const ee_model* m, ee_kv* kv, ee_batch* b, int last_segment
     if (kv->n_layers < R) return ee_fail(EE_ERR_CAPACITY, "ee_decode_finish: cache was bound for fewer layers than are resident");
     // the segments that were not run would have filled the K/V of their layers for the rows that have left
     // (all of them, if the caller stops here rightly), each up to the next exit layer; an fp32 segment fills through layer R itself
-    if (c.dtype == EE_BF16) {
-        int32_t bounds[EE_MAX_EXITS + 1];
-        int n = 0;
-        for (int e = last_segment + 1; e < n_res; ++e) bounds[n++] = c.exit_layers[e];
-        if (n > 0 && bounds[n - 1] < R) bounds[n++] = R;
-        rc = bf16_fill_ranges(m, bounds, n - 1, kv, b, as_stream(stream), b->wsp<int32_t>(b->W.gone_idx),
-                              b->wsp<int32_t>(b->W.n_gone));
+    if (c.dtype == EE_BF16 && last_segment + 1 < n_res && c.exit_layers[last_segment + 1] < R) {
+        int32_t bounds[EE_MAX_EXITS + 2];
+        const int n = exit_bounds(m, c.exit_layers[last_segment + 1], R, bounds);
+        rc = bf16_fill_ranges(m, bounds, n, true, kv, b, as_stream(stream), b->wsp<int32_t>(b->W.gone_idx), b->wsp<int32_t>(b->W.n_gone));
     }
     if (rc == EE_OK) rc = launch_end_step(b, as_stream(stream));
     return rc;

@@ -155,6 +155,7 @@ int bf16_exit_head(const ee_model* m, int e, float th, int force, ee_batch* b, f
 // rows: the batch's exited_idx / n_exited unless another device list (idx, n_ptr) is given
 int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_batch* b, hipStream_t s,
                  const int32_t* idx = nullptr, const int32_t* n_ptr = nullptr);
-// the fills of layers (bounds[i], bounds[i + 1]], i < n, in as few launches as give the bits of one after the other
-int bf16_fill_ranges(const ee_model* m, const int32_t* bounds, int n, ee_kv* kv, ee_batch* b, hipStream_t s, const int32_t* idx,
-                     const int32_t* n_ptr);
+// The fills of layers (bounds[i], bounds[i + 1]], i < n, in as few launches as give the bits of one after the other.  A range of one
+// layer is sliced when it is by itself (singles_apart), else it goes along with its neighbours.
+int bf16_fill_ranges(const ee_model* m, const int32_t* bounds, int n, bool singles_apart, ee_kv* kv, ee_batch* b, hipStream_t s,
+                     const int32_t* idx = nullptr, const int32_t* n_ptr = nullptr);

@@ -2254,12 +2254,9 @@ static Fill fill_kernel(int N, int K, int rows, int nz) {
         // the chip, up to 32 also well filled rounds of workgroups: seven layers of the 7B shape (224 tiles) 1 row 90 / 79
         // us, 40 rows 144 / 94; 40 layers of the 70B shape (320) 1 row 240 / 274
         if (rows <= 64 && (wide < 200 || (rows <= 32 && rounds_filled(wide) < 0.75f))) return Fill::stream;
-    } else if (rows <= 256 && weights >= ((int64_t)2 << 20)) {
-        // Two row groups of 128 on few where the tiles leave three quarters of the CUs idle.  Tiles / few, 129 and 256 rows: 64
-        // tiles, eight layers of 4 MiB 41.0 / 38.3 and 52.9 / 43.9 us; 80, five of the 70B shape 97 / 98 (200 rows 114 / 105) and
-        // 122 / 94; 96, twelve of 4 MiB 45.0 / 49.4 and 60.2 / 58.8; 128, eight of the 70B shape 106 / 132 and 138 / 134
-        if ((wide >= 200 ? wide : narrow) <= (rows > 192 ? 80 : 64)) return Fill::few;
     }
+    // more than 128 rows: always the tiles, so that a range gives the same bits in one launch or several.  (Two row groups of 128 on
+    // few: 256 rows, two layers of the 70B shape 109 / 59 us, but eight, at 129 rows, 106 / 132.)
     return Fill::tiles;
 }
 
@@ -2679,16 +2676,19 @@ int bf16_fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_ba
     return fill_kv(m, from_excl, to_incl, kv, b, s, idx, n_ptr, to_incl - from_excl);
 }
 
-int bf16_fill_ranges(const ee_model* m, const int32_t* bounds, int n, ee_kv* kv, ee_batch* b, hipStream_t s, const int32_t* idx,
-                     const int32_t* n_ptr) {
+int bf16_fill_ranges(const ee_model* m, const int32_t* bounds, int n, bool singles_apart, ee_kv* kv, ee_batch* b, hipStream_t s,
+                     const int32_t* idx, const int32_t* n_ptr) {
     const ee_model_config& c = m->cfg;
     auto kernel = [&](int layers) { return fill_kernel(2 * c.n_kv_heads * c.head_dim, c.d_model, b->B, layers); };
     int rc = EE_OK;
     for (int i = 0, j; i < n && rc == EE_OK; i = j) {
-        // neighbouring ranges that run on the same kernel are one launch; a single layer may be sliced and stays by itself
-        const int layers = bounds[i + 1] - bounds[i];
-        for (j = i + 1; j < n && layers > 1 && bounds[j + 1] - bounds[j] > 1 && kernel(bounds[j + 1] - bounds[j]) == kernel(layers);) ++j;
-        rc = fill_kv(m, bounds[i], bounds[j], kv, b, s, idx, n_ptr, layers);
+        int layers = bounds[i + 1] - bounds[i];              // of a range of several whose kernel the launch takes
+        for (j = i + 1; j < n && !(layers == 1 && singles_apart); ++j) {
+            const int next = bounds[j + 1] - bounds[j];
+            if (next == 1 ? singles_apart : layers > 1 && kernel(next) != kernel(layers)) break;
+            if (layers == 1) layers = next;
+        }
+        rc = fill_kv(m, bounds[i], bounds[j], kv, b, s, idx, n_ptr, layers > 1 ? layers : bounds[j] - bounds[i]);
     }
     return rc;
 }

@@ -86,6 +86,31 @@ def test_layers_not_run_are_filled_as_the_step_fills_them(exits, rows):
         exit_layers=exits, thresholds=(0.5,) * (n - 1) + (0.0,), batch=rows, ctx_lo=3, ctx_hi=20, steps=4))
 
 
+@pytest.mark.parametrize("rows", [3, 70, 150])
+def test_step_equals_its_calls_over_many_layers(rows):
+    """every exit filled up to the last resident layer by a call of its own, against the step, which fills from exit to exit"""
+    exits = (1, 11, 21, 31, 41)
+    s = synth.CONFIGS["llama2_7b"].with_(
+        name=f"many_calls_b{rows}", n_layers=41, resident=41, d_model=512, n_q_heads=8, n_kv_heads=8, d_ffn=64, vocab=512, exit_layers=exits,
+        thresholds=(0.5,) * 4 + (0.0,), batch=rows, ctx_lo=3, ctx_hi=20, steps=1)
+    _say(f"[case] step vs calls {s.name}")
+    g1, g2 = GpuSide(s), GpuSide(s)
+    sc = synth.row_scale(s, 0)
+    g1.step(0, scale=sc)
+    g2.batch.set_row_scale(sc)
+    g2.batch.begin_step()
+    for l in range(1, 42):
+        assert S.layer_forward(g2.model, l, g2.kv, g2.batch) == 0
+        if l in exits:
+            e = exits.index(l)
+            assert S.exit_head(g2.model, e, float(s.thresholds[e]), l == 41, g2.batch) == 0
+            assert S.compact_active(g2.batch, e, l) == 0 and S.fill_skipped_kv(g2.model, l, 41, g2.kv, g2.batch) == 0
+    torch.cuda.synchronize()
+    for k in ("out_tok", "out_layer", "out_conf", "out_breach", "h"):
+        assert torch.equal(g1.batch.field(k), g2.batch.field(k)), k
+    _same_cache(g1, g2, 1)
+
+
 def test_segment_calls_reject_bad_arguments():
     s = SMALL
     g = GpuSide(s)

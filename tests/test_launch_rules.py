@@ -6,6 +6,7 @@ from host_launches import launches
 # query heads, kv heads, d, FFN: the widths of the workloads, heads between them, a smaller model, one off the 128-wide tile grid
 SHAPES = [(32, 32, 4096, 11008), (64, 8, 8192, 28672), (40, 40, 5120, 13824), (48, 48, 6144, 16384), (24, 24, 3072, 8192), (16, 4, 2048, 5632),
           (32, 32, 512, 1024), (4, 2, 576, 1088)]
+FILLS = [SHAPES[0], SHAPES[1], SHAPES[5], SHAPES[7]]
 ROWS = [1, 7, 32, 33, 64, 65, 96, 128, 129, 200, 256, 257, 400, 512, 513, 600, 768, 769, 1000, 1024, 1025, 1100, 1280, 1281, 1537, 1792, 2048,
         2049, 2304, 2816, 2817, 4096, 4097, 4352, 5000, 5888, 8192, 20000, 65535]
 
@@ -81,7 +82,7 @@ def _sums(launch):
 
 
 @pytest.mark.parametrize("exits", [[1, 11, 21, 31, 41], [2, 3, 4, 5, 41], [1, 3, 5, 9, 12, 13, 40, 41], [8, 16, 24, 32]], ids=str)
-@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("shape", FILLS, ids=str)
 def test_the_end_of_a_step_in_pieces_fills_layers_as_the_step_does(shape, exits):
     """keys and values of skipped layers: per layer the same kind of sums after ee_decode_finish as in ee_decode_step"""
     rows = [1, 33, 64, 65, 128, 129, 256, 300, 1100]
@@ -113,10 +114,8 @@ def test_two_row_groups_of_128_where_they_leave_fewer_cus_idle(rows, vocab, tile
 
 
 @pytest.mark.parametrize("shape,layers,rows,kind", [
-    # 129 to 256 rows: by the tiles of 128 columns, 16 per layer (70B), 64 (7B), 8
-    ((64, 8, 8192, 28672), 4, 129, "few"), ((64, 8, 8192, 28672), 5, 192, "dma"), ((64, 8, 8192, 28672), 5, 193, "few"),
-    ((64, 8, 8192, 28672), 6, 256, "dma"), ((32, 32, 4096, 11008), 2, 129, "dma"), ((16, 4, 2048, 5632), 8, 160, "few"),
-    ((16, 4, 2048, 5632), 12, 129, "dma"),
+    # more than 128 rows: the tile kernels whatever the number of layers
+    ((64, 8, 8192, 28672), 2, 129, "dma"), ((64, 8, 8192, 28672), 40, 129, "dma"), ((16, 4, 2048, 5632), 2, 256, "dma"),
     # 97 to 128 rows: tiles of 128 columns that fill three quarters of their rounds, 192 and 160
     ((32, 32, 4096, 11008), 3, 96, "few"), ((32, 32, 4096, 11008), 3, 97, "dma"), ((64, 8, 8192, 28672), 12, 128, "dma"),
     ((64, 8, 8192, 28672), 10, 128, "few"), ((32, 32, 4096, 11008), 5, 128, "few"),
@@ -137,3 +136,18 @@ def test_many_planes_of_one_skipped_layer_are_added_up_before_the_append(rows, p
     splits = _products(ran)[0]["args"][6]
     assert rc == 0 and (planes == "few" or splits == planes)
     assert any(x["kernel"].startswith("k_splitk_finish") for x in ran) == (splits > 8)
+
+
+@pytest.mark.parametrize("exits", [[1, 11, 21, 31, 41], [8, 16, 24, 32], [2, 4, 6, 8], [3, 5, 12, 42]], ids=str)
+@pytest.mark.parametrize("shape", FILLS, ids=str)
+def test_fills_up_to_the_last_exit_are_those_of_the_step(shape, exits):
+    """a step made of its calls fills (exit, R] at every exit, ee_decode_step from one exit to the next: the same kind of sums"""
+    rows = [1, 33, 64, 65, 128, 129, 256, 300, 1100]
+    cfg = dict(_cfg(shape, exits[-1], exits), vocab=512)
+    calls = [["decode_step"]] + [["fill_skipped_kv", l, exits[-1]] for l in exits[:-1]]
+    for n, ((rc, step), *fill) in zip(rows, launches([dict(cfg=cfg, rows=n, cap=32, calls=calls) for n in rows])):
+        fills = lambda ran: [_sums(x) for x in _products(ran) if _arg(x, "HIP_vector_type const*", 1) == 0 for _ in range(x["grid"][2])]   # noqa: E731
+        want = fills(step)
+        assert rc == 0 and len(want) == exits[-1] - exits[0]
+        for l, (rc, ran) in zip(exits, fill):
+            assert rc == 0 and fills(ran) == want[len(want) - (exits[-1] - l):], (n, l)
