@@ -2427,10 +2427,11 @@ static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
     return r;
 }
 
-// Most workgroups per (row, kv head) of the decode attention (attn_shares).  Positions are shared only where the longest
-// row is worth the launch that merges them: 672 positions (attention and merge of 8 kv heads, 1 row of 500: layer 1 us
+// Most workgroups per (row, kv head) of the decode attention (attn_shares).  Positions are shared only where a row may be worth
+// the launch that merges them: room for 672 positions (attention and merge of 8 kv heads, 1 row of 500: layer 1 us
 // longer shared, of 950: 3 us shorter), with 192 pairs 1024 (60 rows of 4 kv heads, 650: 78.5 us shared, 75.3 whole,
-// 950: 84.1 and 81.1; 12 rows of 32, 650: 120.5 and 117.6).
+// 950: 84.1 and 81.1; 12 rows of 32, 650: 120.5 and 117.6).  The host knows the room, not the rows: short ones in a large cache
+// pay for the merge launch too (4 rows of 40 to 200 positions of the 70B shape, layer 273 us, 282 with room for 3000 more).
 static int attn_most(const ee_model_config& c, const ee_kv* kv, const ee_batch* b) {
     const int pairs = c.n_kv_heads * b->B;
     int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, kv->max_cap / 256});
@@ -2557,7 +2558,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
                                qd / 16, 1, b->wsp<float>(b->W.attn_part), b->wsp<AttnJob>(b->W.attn_order));
         else
         {
-            // Rows of at most 8 groups of 32 positions and many of them: a wave takes a whole row, so that nothing is merged and eight
+            // Room for at most 8 groups of 32 positions per row and many rows: a wave takes a whole row, so that nothing is merged and eight
             // rows start on a CU at a time.  Layer, four waves / one: 7B shape 300 rows of 20 to 30 positions 330 / 287 us, of 125
             // to 250 439 / 436, 40 rows of 60 117.5 / 113.5; 34B 400 rows of 60 746 / 729; longer rows 0.5 to 2 % the other way (two
             // waves lie between).

@@ -47,8 +47,9 @@ def test_qkv_of_a_context_pass_in_one_and_two_launches(n, hq, hkv):
             assert ok, f"cache row {r}: worst cache error {worst:.2e}"
 
 
-# 32 tiles of 256 columns per layer: 7 layers are 224 (tile kernel from the first row on), 6 are 192 (streaming kernel up
-# to 64 rows), 10 are 320 (streaming up to 32 rows); of 8 kv heads 3 layers are 48 tiles of 128 (streaming up to 128 rows)
+# 32 tiles of 256 columns per layer: 7 layers are 224 (tile kernel from the first row on), 6 are 192 (75 % of a round:
+# streaming up to 64 rows, then the kernel whose waves stream alone), 10 are 320 and 40 MiB (that kernel from the first
+# row up to 128); of 8 kv heads 3 layers are 48 tiles of 128 (streaming up to 64 rows); from 129 rows on the tiles take all
 @pytest.mark.parametrize("layers,hkv", [(7, 32), (8, 32), (11, 32), (4, 8)])
 @pytest.mark.parametrize("rows", [1, 33, 64, 65, 129])
 def test_skipped_layers_of_few_rows(layers, hkv, rows):
