@@ -2241,7 +2241,8 @@ static Fill fill_kernel(int N, int K, int rows, int nz) {
     if (rows <= 128) {
         // Tiles of 256 columns read X once per 256 columns, if they fill their rounds (seven layers of the 7B shape, 64 rows
         // 95 us and 99 on few), and with more than 96 rows so do tiles of 128 (three layers of the 7B shape, 128 rows 68.9 / 72.7,
-        // sixteen of 1 MiB 41.1 / 43.0; ten of the 70B shape, 62 %, 113.5 / 111.8); elsewhere few (five layers of the 7B shape, 64 rows 93 / 76)
+        // sixteen of 1 MiB 41.1 / 43.0); elsewhere few (five layers of the 7B shape, 62 %, 64 rows 93 / 76, 128 rows 117.8 / 113.7, 60
+        // of 128 leaving 97.8 / 86.0; ten of the 70B shape, 62 %, 113.0 / 117.2 with all 128 rows leaving, 94.2 / 91.5 with 60)
         const bool filled = rounds_filled(wide) >= 0.8f || (rows > 96 && wide < 200 && rounds_filled(narrow) >= 0.75f);
         // Few workgroups and few rows: one per tile-row on the streaming kernel, one round of them, is the shorter start up to 96 MiB
         // of weights, 64 up to 16 rows where they are more than 128.  Streaming / few: eight layers of 4 MiB (256 tile-rows) 1 row 14.2 /
@@ -2431,7 +2432,7 @@ static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
 // the launch that merges them: room for 672 positions (attention and merge of 8 kv heads, 1 row of 500: layer 1 us
 // longer shared, of 950: 3 us shorter), with 192 pairs 1024 (60 rows of 4 kv heads, 650: 78.5 us shared, 75.3 whole,
 // 950: 84.1 and 81.1; 12 rows of 32, 650: 120.5 and 117.6).  The host knows the room, not the rows: short ones in a large cache
-// pay for the merge launch too (4 rows of 40 to 200 positions of the 70B shape, layer 273 us, 282 with room for 3000 more).
+// pay for the merge launch too (4 rows of 40 to 200 positions of the 70B shape, attention 11.2 us, 12.7 with room for 3000 more).
 static int attn_most(const ee_model_config& c, const ee_kv* kv, const ee_batch* b) {
     const int pairs = c.n_kv_heads * b->B;
     int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, kv->max_cap / 256});
