@@ -560,6 +560,138 @@ __device__ __forceinline__ void epilogue_tile(const EpiArgs& ep, const floatx16&
     epilogue_one<EPI>(ep, v1, row0, n, nb + 1, lane);
 }
 
+// ------------------------------------------------------------------ results of 16x16x32 MFMAs
+// A 32 x 32 block of results as 2 x 2 transposed 16x16 tiles (W is the first operand): v[i][u], lane l: batch row 16 i + l % 16,
+// columns 16 u + 4 (l / 16) + s of the block in register s.  What epilogue_one does with a 32x32 tile, to the same bits:
+// a 16x16x32 MFMA adds up its 32 products as two 32x32x16 do.
+__device__ __forceinline__ floatx4 mfma16(const uint4& x, const uint4& w, const floatx4& acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w), as_bf16x8(x), acc, 0, 0, 0);
+}
+// lanes below 32: a of both halves of the wave in (x, y), lanes from 32 on: b
+__device__ __forceinline__ void halves(float a, float b, float& x, float& y) {
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    x = __uint_as_float(t[0]); y = __uint_as_float(t[1]);
+}
+// the value of lane ^ 16
+__device__ __forceinline__ uint32_t other_row(uint32_t v) {
+    const auto t = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? t[0] : t[1];
+}
+
+// v: NB blocks of rows row0 .. row0 + 31, columns 32 nb .. ; every lane of the wave calls it
+template <int EPI, int NB>
+__device__ __forceinline__ void epilogue_blocks(const EpiArgs& ep, const floatx4 (&v)[2][2 * NB], int row0, int n, int nb0, int nb_live,
+                                                int lane) {
+    const int r16 = lane & 15, g = lane >> 4;
+    if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (b >= nb_live) break;
+            // a lane has outputs 2 g, 2 g + 1 of the 8 of a tile, for four tiles k = 2 i + u; the lanes of a row swap so that
+            // group k has all of tile k: one 16-byte chunk of the next product's operand tiles
+            uint32_t d[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const floatx4& t = v[k >> 1][2 * b + (k & 1)];
+                d[k] = pack2(silu_mul(t[0], t[1]), silu_mul(t[2], t[3]));
+            }
+            const auto a = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false), c = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+            const auto lo = __builtin_amdgcn_permlane16_swap(a[0], c[0], false, false), hi = __builtin_amdgcn_permlane16_swap(a[1], c[1], false, false);
+            const int row = row0 + 16 * (g >> 1) + r16;
+            if (row < n)
+                reinterpret_cast<uint4*>(ep.act)[afrag_chunk(row, 16 * (nb0 + b) + 8 * (g & 1), ep.KB_act)] = make_uint4(lo[0], lo[1], hi[0], hi[1]);
+        }
+    } else if constexpr (EPI == EPI_EXIT) {
+        float sc[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) sc[i] = row0 + 16 * i + r16 < n ? ep.row_scale[ep.idx[row0 + 16 * i + r16]] : 0.f;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (b >= nb_live) break;
+            const int col0 = 32 * (nb0 + b) + 4 * g;
+            float z[2][8], mx[2];
+            int arg[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                mx[i] = -FLT_MAX;
+                arg[i] = col0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {                 // column 16 (k / 4) + k % 4 from col0: rising, > keeps the lowest
+                    z[i][k] = v[i][2 * b + (k >> 2)][k & 3] * sc[i];
+                    if (z[i][k] > mx[i]) { mx[i] = z[i][k]; arg[i] = col0 + 16 * (k >> 2) + (k & 3); }
+                }
+                if (ep.dbg_logits && row0 + 16 * i + r16 < n) {
+                    // 16 bytes per store (V is a multiple of 32; single values where the caller's array is not aligned for that)
+                    float* zp = ep.dbg_logits + (int64_t)(row0 + 16 * i + r16) * ep.ldo + col0;
+                    if (((uintptr_t)ep.dbg_logits & 15) == 0) {
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) *reinterpret_cast<float4*>(zp + 16 * u) = make_float4(z[i][4 * u], z[i][4 * u + 1], z[i][4 * u + 2], z[i][4 * u + 3]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) zp[16 * (k >> 2) + (k & 3)] = z[i][k];
+                    }
+                }
+            }
+            // lanes below 32 go on with the rows of i = 0, the others with those of i = 1
+            float ma, mb, m;
+            halves(mx[0], mx[1], ma, mb);
+            const auto ai = __builtin_amdgcn_permlane32_swap((uint32_t)arg[0], (uint32_t)arg[1], false, false);
+            int at = (int)ai[0];
+            m = ma;
+            if (mb > m || (mb == m && (int)ai[1] < at)) { m = mb; at = (int)ai[1]; }
+            const float mo = __uint_as_float(other_row(__float_as_uint(m)));
+            const int ao = (int)other_row((uint32_t)at);
+            if (mo > m || (mo == m && ao < at)) { m = mo; at = ao; }
+            float mr[2];
+            halves(m, m, mr[0], mr[1]);                       // the maximum of each lane's two rows
+            float e[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {                     // in pairs, in epilogue_one's order
+                float x, y;
+                halves(exp_below(z[0][s] - mr[0]) + exp_below(z[0][4 + s] - mr[0]), exp_below(z[1][s] - mr[1]) + exp_below(z[1][4 + s] - mr[1]), x, y);
+                e[s] = x + y;
+            }
+            float se = (e[0] + e[2]) + (e[1] + e[3]);
+            se += __uint_as_float(other_row(__float_as_uint(se)));
+            const int row = row0 + 16 * (lane >> 5) + r16;
+            if (row < n && !(lane & 16)) {
+                const int64_t o = (int64_t)row * ep.n_part + nb0 + b;
+                ep.part_max[o] = m; ep.part_sum[o] = se; ep.part_arg[o] = at;
+            }
+        }
+    } else if constexpr (EPI == EPI_RESID) {
+        // h[row id] += v: all old values, then the stores (see epilogue_one)
+        float* at[2];
+        float4 old[2][2 * NB];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) at[i] = ep.out + (int64_t)ep.idx[min(row0 + 16 * i + r16, n - 1)] * ep.ldo + 32 * nb0 + 4 * g;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int u = 0; u < 2 * NB; ++u)
+                if ((u >> 1) < nb_live) old[i][u] = *reinterpret_cast<const float4*>(at[i] + 16 * u);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (row0 + 16 * i + r16 < n) {
+#pragma unroll
+                for (int u = 0; u < 2 * NB; ++u)
+                    if ((u >> 1) < nb_live)
+                        *reinterpret_cast<float4*>(at[i] + 16 * u) = make_float4(old[i][u].x + v[i][u][0], old[i][u].y + v[i][u][1],
+                                                                                 old[i][u].z + v[i][u][2], old[i][u].w + v[i][u][3]);
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int row = row0 + 16 * i + r16;
+            if (row >= n) continue;
+            float* o = ep.out + (int64_t)row * ep.ldo + 32 * nb0 + 4 * g;
+#pragma unroll
+            for (int u = 0; u < 2 * NB; ++u)
+                if ((u >> 1) < nb_live) *reinterpret_cast<float4*>(o + 16 * u) = make_float4(v[i][u][0], v[i][u][1], v[i][u][2], v[i][u][3]);
+        }
+    }
+}
+
 // ------------------------------------------------------------------ tile GEMMs fed by LDS-DMA loads
 // No operand passes through registers on its way in: the waves of a workgroup send the X and W
 // tiles of a 32-wide K stage straight from global memory into LDS (global_load_lds_dwordx4: 64
@@ -750,12 +882,143 @@ k_bf16_gemm_dma2(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 #undef EPI_ROW
 }
 
+// ------------------------------------------------------------------ full tiles of 256 and 192 columns: two waves per SIMD in turns
+// 256 rows x 32 NT columns per workgroup, eight waves with NA x NB tiles of 16x16 each: as 2 x 4 with 8 x 4 (NT = 8), as 4 x 2
+// with 4 x 6 (NT = 6); a wave's 32-row tiles are r0, r0 + STEP, .. so that both waves of a SIMD, w and w + 4, have live rows.
+// LDS slots and loads as in the loops of k_bf16_gemm_dma8 and k_bf16_gemm_cols below, which take over where few row tiles are live.
+//
+// While waves 0 .. 3 multiply, waves 4 .. 7 read their operands of a stage from LDS and send their tiles of the stage four ahead;
+// then they change places, at a barrier.  The matrix pipes are busy 83 % of the time (66 % in the loops below), and what
+// limits the product then is power, of which 16x16x32 MFMAs take less than 32x32x16 (alone, on random data, 2.08 PFLOP/s against
+// 1.79 to 1.85; in this loop 1.47 at 1.69 GHz against 1.38 at 1.55).  2048 rows: down of the 70B shape 704 -> 654 us, gate/up
+// 1420..1507 -> 1402; exit head of 1024 entries at the 7B shape, with its new epilogue, 300..323 -> 258..267; 256 rows, gate/up
+// of the 70B shape 228..252 -> 218..243.
+// TURNS: the live row tiles from which on this is the faster loop.  With fewer, memory sets the pace and a wave's turn
+// holds up its requests: gate/up of the 70B shape (256 columns) below / here 128 rows 157 / 164..171 us, 160 174 / 195, 200 222 / 227,
+// 256 230 / 220, down 160 113 / 110, 200 128 / 124; of the 34B shape (192) 128 rows 127 / 143, 180 166 / 172,
+// 230 182 / 177.
+#define SB __builtin_amdgcn_sched_barrier(0)
+template <int NT>
+struct TurnShape;
+template <>
+struct TurnShape<8> { static constexpr int NA = 8, NB = 4, STEP = 2, TURNS = 7; };
+template <>
+struct TurnShape<6> { static constexpr int NA = 4, NB = 6, STEP = 4, TURNS = 7; };
+
+struct TurnCtx {
+    uint4*       lds;        // [5][32][64]
+    const uint4* xg;         // row tile 0, K tile 0 of the row group
+    const uint4* wg;         // column tile 0 of the workgroup, K tile 0
+    int KB, NBs, ks_lo, T;   // stages ks_lo .. ks_lo + T - 1
+    int row_base, n, nb0, nt_live;
+};
+
+template <int EPI, int NT>
+__device__ __forceinline__ void tile_in_turns(const TurnCtx& c, const EpiArgs& ep) {
+    using S = TurnShape<NT>;
+    constexpr int NA = S::NA, NB = S::NB;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int later = wave >> 2;
+    const int r0 = NT == 8 ? later : 2 * ((wave >> 1) & 1) + later, c0 = NB / 2 * (NT == 8 ? wave & 3 : wave & 1);
+    const int rows = c.n - c.row_base, mbs = min(8, (rows + 31) >> 5);
+    int cnt = 0;                                             // live 16-row tiles among the wave's
+#pragma unroll
+    for (int i = 0; i < NA / 2; ++i) cnt += max(0, min(2, (rows - 32 * (r0 + S::STEP * i) + 15) >> 4));
+    const unsigned lane_bytes = (unsigned)lane * 16u;
+    const unsigned lds0 = (unsigned)(size_t)c.lds;
+    const bool sends_x = wave < mbs, sends_w = wave < NT;
+
+    floatx4 acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    // j-th load of a stage: j = 0, 1 the X tile of row tile `wave`, K half j; j = 2, 3 the W tile of
+    // column tile `wave`, K half j - 2.  Address = the stage's base pointer (scalar, once per stage)
+    // plus a lane offset that is the same in every stage.
+    unsigned voff[4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) voff[j] = lane_bytes + ((unsigned)(min(wave, mbs - 1) * c.KB + j) << 10);
+#pragma unroll
+    for (int j = 2; j < 4; ++j) voff[j] = lane_bytes + ((unsigned)((j - 2) * c.NBs + min(wave, c.nt_live - 1)) << 10);
+    auto x_base = [&](int t) { return c.xg + (int64_t)(2 * (c.ks_lo + min(t, c.T - 1))) * 64; };
+    auto w_base = [&](int t) { return c.wg + (int64_t)(2 * (c.ks_lo + min(t, c.T - 1))) * c.NBs * 64; };
+    // Operand of a 16x16x32 MFMA from the two tiles (K halves, 1 KiB each) of 32 rows: lane l has row l % 16 and K octet l / 16,
+    // the tiles' lanes are 32 rows x 2 octets; rows 16 to 31 are 256 bytes further
+    const char* lane_at = reinterpret_cast<const char*>(c.lds) + (lane >> 5) * 1024 + ((lane >> 4) & 1) * 512 + (lane & 15) * 16;
+    auto next = [](int buf) { return buf == 4 ? 0 : buf + 1; };
+
+    // what a wave sends is fixed, and with it the count of loads it may leave in flight: each combination runs its own copy
+    auto loop = [&](auto xl_, auto wl_, auto all_) {
+        constexpr bool XL = decltype(xl_)::value, WL = decltype(wl_)::value, ALL = decltype(all_)::value;
+        constexpr int L = 2 * (XL ? 1 : 0) + 2 * (WL ? 1 : 0);
+        auto issue = [&](int t, int buf) {
+            const uint4 *xs = x_base(t), *ws = w_base(t);
+            const unsigned at = lds0 + (unsigned)((buf * 32 + wave * 2) << 10);
+            if constexpr (XL) { dma_tile(xs, voff[0], at); dma_tile(xs, voff[1], at + 1024); }
+            if constexpr (WL) { dma_tile<true>(ws, voff[2], at + 16384); dma_tile<true>(ws, voff[3], at + 17408); }
+        };
+#pragma unroll
+        for (int st = 0; st < 4; ++st) issue(st, st);
+        uint4 a[NA], b[NB];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a[i] = make_uint4(0, 0, 0, 0);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * L) : "memory");         // stage 0 has landed
+        if (later) asm volatile("s_barrier" ::: "memory");
+        int bc = 0, bi = 4;                                  // buffers of the current stage and of the one being requested
+        for (int t = 0; t < c.T; ++t) {
+            SB;
+            const char* at = lane_at + bc * 32768;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) b[j] = *reinterpret_cast<const uint4*>(at + 16384 + (c0 + (j >> 1)) * 2048 + (j & 1) * 256);
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if (ALL || i < cnt) a[i] = *reinterpret_cast<const uint4*>(at + (r0 + S::STEP * (i >> 1)) * 2048 + (i & 1) * 256);
+            issue(t + 4, bi);
+            // The operands have been read (their buffer is filled again from the phase after the next on).  Between the two phases
+            // of a stage every wave waits for its loads of the next stage, which is first read after this barrier or the one after.
+            if (later) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(3 * L) : "memory");
+            else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            SB;
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if (ALL || i < cnt) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) acc[i][j] = mfma16(a[i], b[j], acc[i][j]);
+                }
+            SB;
+            if (later) asm volatile("s_barrier" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * L) : "memory");
+            bc = next(bc); bi = next(bi);
+        }
+        if (!later) asm volatile("s_barrier" ::: "memory");  // as many barriers as the others
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    const bool all = cnt == NA;                              // only waves that send X have all their rows live
+    if (NT == 8 || sends_w) { if (!sends_x) loop(No{}, Yes{}, No{}); else if (all) loop(Yes{}, Yes{}, Yes{}); else loop(Yes{}, Yes{}, No{}); }
+    else { if (!sends_x) loop(No{}, No{}, No{}); else if (all) loop(Yes{}, No{}, Yes{}); else loop(Yes{}, No{}, No{}); }
+
+#pragma unroll
+    for (int i = 0; i < NA / 2; ++i) {
+        if (2 * i >= cnt) break;
+        floatx4 v[2][NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) { v[0][j] = acc[2 * i][j]; v[1][j] = acc[2 * i + 1][j]; }
+        epilogue_blocks<EPI, NB / 2>(ep, v, c.row_base + 32 * (r0 + S::STEP * i), c.n, c.nb0 + c0, c.nt_live - c0, lane);
+    }
+}
+
+#undef SB
+
 // ------------------------------------------------------------------ 256-column tile, two waves per SIMD
 // 256 rows x 256 columns per workgroup, eight waves (2 x 4): wave (wm, wn) owns rows
 // 128 wm .. +127 and columns 64 wn .. +63 (4 x 2 MFMA tiles, 128 accumulator registers), so two waves
 // share a SIMD and one computes while the other waits at a barrier or for LDS (an MFMA-only
-// kernel issues 10 % more per SIMD with two waves than with one; against four waves that own
-// 8 x 2 tiles each, gate/up is 4-6 % faster at 160 to 512 rows and the same at 64).  Used for the
+// kernel issues 10 % more per SIMD with two waves than with one).  Used for the
 // products with many columns (gate/up with the SwiGLU epilogue, down, the K/V of skipped layers).  LDS: 5 stage buffers x 32 slots
 // (X tile (row tile m, K half kk) at 2 m + kk, W tile (column tile nb of 8, K half kk) at
 // 16 + 2 nb + kk) = all 160 KiB.  A wave sends 2 X and 2 W tiles per stage, four stages ahead, and
@@ -787,6 +1050,16 @@ k_bf16_gemm_dma8(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     const int T = ks_hi - ks_lo;                             // stages of this slice: a positive multiple of 4
     const uint4* xg = Xp + ((int64_t)rg * 8 * KB) * 64;
     const uint4* wg = Wp + (int64_t)(nb_off + tile * 8) * 64;   // the tile's eight tile-rows of W
+    if (splits > 1) {
+        ep.out = partial + (int64_t)sp * part_plane;
+        ep.ldo = part_ld;
+    }
+    if (mbs >= TurnShape<8>::TURNS) {
+        const TurnCtx c{&lds[0][0][0], xg, wg, KB, NBs, ks_lo, T, row_base, n, tile * 8, 8};
+        if (splits > 1) tile_in_turns<EPI == EPI_RESID ? EPI_STORE : EPI, 8>(c, ep);     // others than these two are never sliced
+        else tile_in_turns<EPI, 8>(c, ep);
+        return;
+    }
     const unsigned lane_bytes = (unsigned)lane * 16u;
     const unsigned lds0 = (unsigned)(size_t)&lds[0][0][0];
 
@@ -871,10 +1144,7 @@ k_bf16_gemm_dma8(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 #define EPI_ROW(E, ARGS, I) \
     if (4 * wm + (I) < mbs) epilogue_tile<E>(ARGS, acc[I][0], acc[I][1], row_base + 32 * (4 * wm + (I)), n, nbw, lane);
     if (splits > 1) {
-        EpiArgs pe = ep;
-        pe.out = partial + (int64_t)sp * part_plane;
-        pe.ldo = part_ld;
-        EPI_ROW(EPI_STORE, pe, 0) EPI_ROW(EPI_STORE, pe, 1) EPI_ROW(EPI_STORE, pe, 2) EPI_ROW(EPI_STORE, pe, 3)
+        EPI_ROW(EPI_STORE, ep, 0) EPI_ROW(EPI_STORE, ep, 1) EPI_ROW(EPI_STORE, ep, 2) EPI_ROW(EPI_STORE, ep, 3)
         return;
     }
     EPI_ROW(EPI, ep, 0) EPI_ROW(EPI, ep, 1) EPI_ROW(EPI, ep, 2) EPI_ROW(EPI, ep, 3)
@@ -1024,6 +1294,12 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
     Xp += (int64_t)blockIdx.z * zb.x_stride;
     ep.out += (int64_t)blockIdx.z * zb.out_stride;
+    if (n - row_base > 32 * (TurnShape<6>::TURNS - 1)) {
+        const TurnCtx t{&lds[0][0][0], Xp + ((int64_t)rg * 8 * KB) * 64, Wp + (int64_t)(nb_off + tile * COLS_NT) * 64, KB, NBs, 0, KB >> 1,
+                        row_base, n, tile * COLS_NT, min(COLS_NT, NB_total - tile * COLS_NT)};
+        tile_in_turns<EPI, COLS_NT>(t, ep);
+        return;
+    }
     ColsCtx c;
     c.lds = &lds[0][0][0];
     c.KB = KB; c.NBs = NBs;

@@ -1,0 +1,70 @@
+"""The tile kernels' two loops (waves of a SIMD in turns where most row tiles are live, else each wave on its own) add up in one
+order: rows of the same token are the same bits, whichever loop and place in the tile they get.  Row tiles on both sides of
+the rule, a last 16-row tile with one row, row groups of which the last one takes the other loop; stores, residual updates,
+SwiGLU and exit statistics with logits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_10724_amd import session as S
+
+pytestmark = pytest.mark.gpu
+
+TOKENS = 61          # no divisor of a tile: equal rows sit at different places of their tiles
+
+
+def model(d, heads, kv_heads, ffn, vocab):
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    w = lambda n, k: torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=gen)      # noqa: E731
+    m = S.Model(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=128, d_ffn=ffn, vocab=vocab, dtype="bf16",
+                exit_layers=[1], max_pos=32)
+    one = torch.ones(d, device="cuda")
+    m.set_layer(1, g_attn=one, W_qkv=w((heads + 2 * kv_heads) * 128, d), W_o=w(d, heads * 128), g_ffn=one, W_gate=w(ffn, d), W_up=w(ffn, d),
+                W_down=w(d, ffn))
+    m.set_exit(0, g=one, W=w(vocab, d))
+    m.set_embed(w(vocab, d))
+    return m
+
+
+def same_rows(x, ref, what):
+    """row i of x is row i % TOKENS of ref, bit for bit"""
+    want = ref[torch.arange(len(x), device=x.device) % TOKENS]
+    assert torch.isfinite(x.float()).all(), what
+    differ = torch.nonzero((x != want).reshape(len(x), -1).any(-1)).flatten().tolist()
+    assert not differ, (what, differ[:8])
+
+
+# 224 tiles of 256 columns and the down projection in K slices; 230 workgroups of 192 columns, the last with two tile-rows of six
+@pytest.mark.parametrize("d,ffn", [(1024, 28672), (512, 22016)])
+def test_one_row_group(d, ffn):
+    m = model(d, 8, 8, ffn, 51200)
+    kv, b = S.KVCache(m, 1, [32] * 256), S.Batch(m, 256)
+    logits, ref = torch.empty((256, 51200), device="cuda"), None
+    for live in (160, 161, 176, 177, 192, 193, 208, 209, 224, 225, 240, 241, 256):
+        print(f"[case] one row group, d = {d}, {live} rows", flush=True)
+        b.reset(np.arange(256) % TOKENS, np.zeros(256, np.int32), None)
+        b.begin_step()
+        b.field("n_active").fill_(live)
+        assert S.layer_forward(m, 1, kv, b) == 0 and S.exit_head(m, 0, 0.5, False, b, logits) == 0
+        got = [b.field("h")[:live].clone(), logits[:live].clone(), b.field("head_conf")[:live].clone(), b.field("head_tok")[:live].clone()]
+        ref = ref or got                                     # 160 rows: no row tile in turns
+        for x, r, what in zip(got, ref, ("state", "logits", "confidence", "token")):
+            same_rows(x, r, (what, live))
+
+
+# the last row group has 100 rows (its own loop), 208 and 255; 1124 entries of the narrower model: 192 columns
+@pytest.mark.parametrize("d,heads,kv_heads,ffn,n", [(4096, 32, 32, 11008, 1124), (4096, 32, 32, 11008, 2047), (8192, 64, 8, 28672, 1892),
+                                                    (8192, 64, 8, 28672, 2000)])
+def test_several_row_groups(d, heads, kv_heads, ffn, n):
+    print(f"[case] {n} entries, d = {d}", flush=True)
+    m = model(d, heads, kv_heads, ffn, 32000)
+    kv, b = S.KVCache(m, 1, [32] * n), S.Batch(m, n)
+    b.reset(np.zeros(n, np.int32), np.zeros(n, np.int32), None)
+    logits = torch.empty((n, 32000), device="cuda")
+    assert S.prefill(m, kv, b, np.arange(n) % TOKENS, np.zeros(n, np.int32), np.arange(n)) == 0
+    assert S.exit_head(m, 0, 0.0, True, b, logits) == 0
+    tail = n // 256 * 256 // TOKENS * TOKENS + TOKENS        # rows of the last row group, the first token's first
+    for x, what in ((b.field("h"), "state"), (logits, "logits"), (b.field("head_conf"), "confidence"), (b.field("head_tok"), "token")):
+        same_rows(x, x, what)
+        if n - tail >= TOKENS:
+            same_rows(x, x[tail:], what)
