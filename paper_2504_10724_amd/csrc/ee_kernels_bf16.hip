@@ -83,33 +83,35 @@ struct JobArgs {        // jobs == nullptr: none are left
     int n_kv_heads, most;
 };
 
-// Called by every thread of a block of NORM_THREADS that works on list entry i of n: its last wave leaves the entry's job
+// Called by every thread of a block of norm_threads that works on list entry i of n: its last wave leaves the entry's job
 // at the entry's rank by falling position (ties by entry), so that the longest rows start first and the last round of
 // workgroups is short.  Batch row b is cache row b.
 #define NORM_THREADS 1024
 template <class Row>
 __device__ __forceinline__ void leave_job(const JobArgs& a, int i, int n, Row row_of) {
-    if (a.jobs == nullptr || threadIdx.x < NORM_THREADS - 64) return;
+    const int wave0 = blockDim.x - 64;
+    if (a.jobs == nullptr || (int)threadIdx.x < wave0) return;
     const int row = row_of(i), mine = a.pos[row];
     int before = 0;
-    for (int j = threadIdx.x - (NORM_THREADS - 64); j < n; j += 64) {
+    for (int j = threadIdx.x - wave0; j < n; j += 64) {
         const int kj = a.pos[row_of(j)];
         before += (kj > mine || (kj == mine && j < i)) ? 1 : 0;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
-    if (threadIdx.x == NORM_THREADS - 64) {
+    if ((int)threadIdx.x == wave0) {
         const int cap = a.cap[row], n_pos = max(1, min(mine + 1, cap));
         a.jobs[before] = AttnJob{i, n_pos, cap, attn_shares(n * a.n_kv_heads, n_pos, a.most), a.off[row], mine, 0};
     }
 }
 
 // ------------------------------------------------------------------ RMSNorm -> A tiles
-// The NORM_THREADS threads of a block normalise one row (hr: d floats) and write it as list entry
+// The threads of a block normalise one row (hr: d floats) and write it as list entry
 // i of the [Mpad][d] activation matrix in tile order.  Every thread reads only the 8-float chunks
 // c = threadIdx.x + NORM_THREADS j, so a caller may have written those same chunks just before.
-// (1024 threads: one chunk each at d = 8192; the kernels here are latency bound, and every
-// user of this routine takes the same thread count so that all give the same bits.)
+// One chunk per thread up to d = 8192, and no wave without one (norm_threads): a row's sum of squares adds up the waves' in their
+// order, so that waves without a chunk would add nothing, and the smaller blocks of narrower rows fit on a CU side by side
+// (1024 rows of 4096 values, 1024 threads / 512: begin and norm 14.2 / 12.7 us, norm 9.5 / 8.8, finish of two K slices 17.3 / 16.7).
 // Sum of the squares of a chunk, its fused multiply-adds written out: every kernel that normalises a row (here, the
 // finish of a sliced product, the step begin) has to give the same bits, and left to the compiler which of the
 // products of a sum are fused differs from kernel to kernel.
@@ -118,6 +120,16 @@ __device__ __forceinline__ float sum_sq8(const float4& a, const float4& b) {
     s = fmaf(a.y, a.y, s); s = fmaf(a.z, a.z, s); s = fmaf(a.w, a.w, s);
     s = fmaf(b.x, b.x, s); s = fmaf(b.y, b.y, s); s = fmaf(b.z, b.z, s); s = fmaf(b.w, b.w, s);
     return s;
+}
+// block_sum over the waves that the block has (up to NORM_THREADS / 64)
+__device__ __forceinline__ float waves_sum(float v, float* smem) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) smem[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float t = 0.f;
+    for (int i = 0; i < (int)blockDim.x >> 6; ++i) t += smem[i];
+    return t;
 }
 // the row as one 8-float chunk (a, b) per thread (d <= 8 NORM_THREADS; zeros in threads past the row)
 __device__ __forceinline__ void rmsnorm_chunk(const float4& a, const float4& b, const float* gain, float eps, int d, uint4* out, int i,
@@ -128,7 +140,7 @@ __device__ __forceinline__ void rmsnorm_chunk(const float4& a, const float4& b, 
     if (has) { ga = reinterpret_cast<const float4*>(gain)[2 * c]; gb = reinterpret_cast<const float4*>(gain)[2 * c + 1]; }
     float ss = 0.f;
     if (has) ss += sum_sq8(a, b);
-    ss = block_sum<NORM_THREADS>(ss, red);
+    ss = waves_sum(ss, red);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
     if (!has) return;
     uint4 o;
@@ -2345,7 +2357,7 @@ k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, in
         if (gain == nullptr) return;
         float ss = 0.f;
         if (has) ss += sum_sq8(o0, o1);
-        ss = block_sum<NORM_THREADS>(ss, red);
+        ss = waves_sum(ss, red);
         const float inv = 1.0f / sqrtf(ss / (float)N + eps);
         if (has) {
             const float4* g4 = reinterpret_cast<const float4*>(gain);
@@ -2407,6 +2419,12 @@ static FewShape few_shape(int tile_rows, int KB, int rows, int nz, int max_split
     return best;
 }
 
+// threads of a block that normalises a row of d values: one per chunk of 8, and a wave for the attention's job
+static int norm_threads(int d, const JobArgs& jobs) {
+    const int chunks = (d / 8 + 63) / 64 * 64;
+    return std::min(NORM_THREADS, chunks + (jobs.jobs != nullptr ? 64 : 0));
+}
+
 // what the caller wants done with the K-slice planes of a product
 struct SliceTail {
     const float* norm_gain = nullptr;   // RESID: also normalise the updated rows with this gain ...
@@ -2427,7 +2445,7 @@ static void finish_slices(const ee_batch* b, int N, int splits, const int32_t* n
     if (splits == 1) return;
     const int64_t plane = (int64_t)((B + 31) / 32 * 32) * N;
     if (EPI == EPI_RESID) {
-        hipLaunchKernelGGL(k_splitk_resid_norm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->wsp<float>(b->W.gemm_part),
+        hipLaunchKernelGGL(k_splitk_resid_norm, dim3(entry_grid(B)), dim3(norm_threads(N, tail.jobs)), 0, s, b->wsp<float>(b->W.gemm_part),
                            plane, N, splits, N, n_ptr, B, entry_near(B), ep.out, ep.ldo, ep.idx, tail.norm_gain, tail.eps, tail.norm_out, tail.jobs);
         if (tail.norm_gain && tail.norm_done) *tail.norm_done = true;
     } else if (splits > tail.defer_most) {
@@ -2742,7 +2760,7 @@ int bf16_begin_step(const ee_model* m, const ee_kv* kv, ee_batch* b, hipStream_t
     g.tok = b->st<int32_t>(L.tok_in); g.n = b->B; g.V = m->cfg.vocab; g.emb = (const uint4*)m->emb; g.h = b->st<float>(L.h);
     g.active_idx = b->st<int32_t>(L.active_idx); g.n_active = b->st<int32_t>(L.n_active);
     g.n_exited = b->st<int32_t>(L.n_exited); g.out_layer = b->st<int32_t>(L.out_layer); g.status = b->st<int32_t>(L.status);
-    hipLaunchKernelGGL(k_bf16_begin_norm<false>, dim3(entry_grid(b->B)), dim3(NORM_THREADS), 0, s, g, entry_near(b->B),
+    hipLaunchKernelGGL(k_bf16_begin_norm<false>, dim3(entry_grid(b->B)), dim3(norm_threads(m->cfg.d_model, attn_jobs(m->cfg, kv, b))), 0, s, g, entry_near(b->B),
                        (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x), attn_jobs(m->cfg, kv, b));
     EE_LAUNCH_CHECK();
     return EE_OK;
@@ -2759,7 +2777,7 @@ int bf16_prefill_begin(const ee_model* m, const ee_kv* kv, ee_batch* b, const in
     g.h = b->st<float>(L.h); g.s_tok = b->st<int32_t>(L.tok_in); g.s_pos = b->st<int32_t>(L.pos);
     g.kv_seq = b->wsp<int32_t>(b->W.kv_seq); g.active_idx = b->st<int32_t>(L.active_idx);
     g.n_active = b->st<int32_t>(L.n_active); g.n_exited = b->st<int32_t>(L.n_exited); g.status = b->st<int32_t>(L.status);
-    hipLaunchKernelGGL(k_bf16_begin_norm<true>, dim3(entry_grid(n)), dim3(NORM_THREADS), 0, s, g, entry_near(n),
+    hipLaunchKernelGGL(k_bf16_begin_norm<true>, dim3(entry_grid(n)), dim3(norm_threads(m->cfg.d_model, JobArgs{})), 0, s, g, entry_near(n),
                        (const float*)m->layers[0].g_attn, m->cfg.rms_eps, m->cfg.d_model, b->wsp<uint4>(b->W.x), JobArgs{});
     EE_LAUNCH_CHECK();
     return EE_OK;
@@ -2789,7 +2807,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
 
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_attn, c.rms_eps, d, x, ZBatch{}, jobs);
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(norm_threads(d, jobs)), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_attn, c.rms_eps, d, x, ZBatch{}, jobs);
     }
     EpiArgs e1{};
     e1.out = qkv; e1.ldo = qkv_n; e1.idx = idx;
@@ -2861,7 +2879,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
     }
     if (!ffn_x_done) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_ffn, c.rms_eps, d, x, ZBatch{}, JobArgs{});
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(norm_threads(d, JobArgs{})), 0, s, h, idx, n_ptr, B, entry_near(B), w.g_ffn, c.rms_eps, d, x, ZBatch{}, JobArgs{});
     }
     EpiArgs e3{};
     e3.act = act; e3.KB_act = F / 16; e3.idx = idx;
@@ -2892,7 +2910,7 @@ int bf16_exit_head(const ee_model* m, int e, float th, int force, ee_batch* b, f
     uint4* x = b->wsp<uint4>(b->W.x);
     if (!x_ready) {
         TimedScope t(EE_K_NORM, s);
-        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
+        hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B)), dim3(norm_threads(d, JobArgs{})), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
                            m->exits[e].gain, c.rms_eps, d, x, ZBatch{}, JobArgs{});
     }
     EpiArgs ep{};
@@ -2926,7 +2944,7 @@ static int fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_
     ZBatch zb{};
     zb.w_tab = m->d_wqkv_tab; zb.g_tab = m->d_gattn_tab; zb.z0 = from_excl;
     zb.x_stride = (int64_t)b->Mpad * d / 8; zb.out_stride = (int64_t)b->Mpad * kv_n;
-    hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B), 1, nl), dim3(NORM_THREADS), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
+    hipLaunchKernelGGL(k_bf16_rmsnorm, dim3(entry_grid(B), 1, nl), dim3(norm_threads(d, JobArgs{})), 0, s, b->st<float>(L.h), idx, n_ptr, B, entry_near(B),
                        (const float*)nullptr, c.rms_eps, d, x, zb, JobArgs{});
     // key and value rows are the last 2*H_kv*hd rows of W_qkv: tile-rows H_q*hd/32 onwards
     EpiArgs ep{};
