@@ -1468,13 +1468,29 @@ k_bf16_gemm_few(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int 
 // mantissa bits, so that the attention kernel can feed them to the bf16 matrix
 // cores without giving up fp32-grade scores.  Keys are rotated, rounded and
 // appended; values are rounded and appended in the grouped layout.
+// alone: no other entry's position shares a line of the cache with this one's (rows of a decode step).  An append then touches 32
+// lines of a row and kv head for 16 bytes of a key's and 2 of a value's each, half a million lines for 512 rows of the 7B shape.
+// As ordinary stores they stay in L2 until the attention's stream drives them out, one by one between its reads; non-temporal
+// ones leave at once.  512 rows of the 7B shape, append 32 -> 36 us, attention 807 -> 765..790, machine to machine (its loads alone
+// 776 before; without any append 703), 64 rows 117 -> 112..115, 256 rows of the 70B shape 233 -> 230.  In a context pass neighbours complete each other's lines in L2:
+// append of 1024 entries 25 us, 55 non-temporal.
+__device__ __forceinline__ void append8(bf16_t* at, uint2 v, bool alone) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    if (alone) __builtin_nontemporal_store((u32x2{v.x, v.y}), reinterpret_cast<u32x2*>(at));
+    else *reinterpret_cast<uint2*>(at) = v;
+}
+__device__ __forceinline__ void append2(bf16_t* at, bf16_t v, bool alone) {
+    if (alone) __builtin_nontemporal_store(v, at);
+    else *at = v;
+}
+
 __global__ void __launch_bounds__(256)
 k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t* __restrict__ idx,
                    const int32_t* __restrict__ n_ptr, int B, int near, const int32_t* __restrict__ pos,
                    const float* __restrict__ rope, int max_pos, KvView kv, bf16_t* __restrict__ q_hi,
                    bf16_t* __restrict__ q_lo, int32_t* __restrict__ status, int64_t z_stride,
                    int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int most_shares, int tile_entries, int splits, int64_t plane,
-                   const float* __restrict__ planes, int ld_planes, int from) {
+                   const float* __restrict__ planes, int ld_planes, int from, bool alone) {
     int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
     if (i >= n) return;
@@ -1567,8 +1583,8 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
             } else {
                 // four consecutive features of a key sit side by side in the cache (same octet)
                 bf16_t* base = reinterpret_cast<bf16_t*>(kv.pool) + kv_block(kv, sq, hh, cap);
-                *reinterpret_cast<uint2*>(base + k_bf16_offset(p, j0, hd)) = pack4(x0[0], x0[1], x0[2], x0[3]);
-                *reinterpret_cast<uint2*>(base + k_bf16_offset(p, j0 + half, hd)) = pack4(x1[0], x1[1], x1[2], x1[3]);
+                append8(base + k_bf16_offset(p, j0, hd), pack4(x0[0], x0[1], x0[2], x0[3]), alone);
+                append8(base + k_bf16_offset(p, j0 + half, hd), pack4(x1[0], x1[1], x1[2], x1[3]), alone);
             }
         } else {
             const int u = t - nq4 - nk4;
@@ -1594,7 +1610,7 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
                 const int f = f0 + 64 * k;
                 if (f >= Hkv * hd) break;
                 bf16_t* base = reinterpret_cast<bf16_t*>(kv.pool) + kv_block(kv, sq, f >> 7, cap);
-                base[v_bf16_offset(p, f & 127, hd)] = f32_to_bf16(v[k]);
+                append2(base + v_bf16_offset(p, f & 127, hd), f32_to_bf16(v[k]), alone);
             }
         }
     }
@@ -2830,7 +2846,7 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
                            ctx.C ? b->wsp<int32_t>(b->W.attn_order) : nullptr, ctx.C ? nullptr : b->wsp<AttnJob>(b->W.attn_order),
                            most, ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * (qkv_n - qkv_from), b->wsp<float>(b->W.gemm_part),
-                           qkv_n - qkv_from, qkv_from);
+                           qkv_n - qkv_from, qkv_from, b->kv_seq == nullptr);
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
@@ -2962,7 +2978,7 @@ static int fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
                        (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, splits, (int64_t)b->Mpad * kv_n, b->wsp<float>(b->W.gemm_part), kv_n,
-                       splits == 1 ? kv_n : 0);
+                       splits == 1 ? kv_n : 0, false);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
