@@ -1519,8 +1519,8 @@ k_bf16_rope_append(const float* __restrict__ buf, int ld, int n_q, const int32_t
                    const int32_t* __restrict__ n_ptr, int B, int near, const int32_t* __restrict__ pos,
                    const float* __restrict__ rope, int max_pos, KvView kv, bf16_t* __restrict__ q_hi,
                    bf16_t* __restrict__ q_lo, int32_t* __restrict__ status, int64_t z_stride,
-                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int most_shares, int tile_entries, int splits, int64_t plane,
-                   const float* __restrict__ planes, int ld_planes, int from, bool alone) {
+                   int32_t* __restrict__ order, AttnJob* __restrict__ jobs, int most_shares, int tile_entries, bool alone, int splits, int64_t plane,
+                   const float* __restrict__ planes, int ld_planes, int from) {
     int i = entry_of_block(blockIdx.x, near);
     int n = min(*n_ptr, B);
     if (i >= n) return;
@@ -2875,8 +2875,8 @@ int bf16_layer_forward(const ee_model* m, int layer, ee_kv* kv, ee_batch* b, hip
                            b->st<int32_t>(L.pos), m->d_rope, c.max_pos, view, b->wsp<bf16_t>(b->W.q_hi),
                            b->wsp<bf16_t>(b->W.q_lo), b->st<int32_t>(L.status), (int64_t)0,
                            ctx.C ? b->wsp<int32_t>(b->W.attn_order) : nullptr, ctx.C ? nullptr : b->wsp<AttnJob>(b->W.attn_order),
-                           most, ctx.tile_entries, qkv_splits, (int64_t)b->Mpad * (qkv_n - qkv_from), b->wsp<float>(b->W.gemm_part),
-                           qkv_n - qkv_from, qkv_from, b->kv_seq == nullptr);
+                           most, ctx.tile_entries, b->kv_seq == nullptr, qkv_splits, (int64_t)b->Mpad * (qkv_n - qkv_from), b->wsp<float>(b->W.gemm_part),
+                           qkv_n - qkv_from, qkv_from);
     }
     {
         TimedScope t(EE_K_ATTENTION, s);
@@ -3007,8 +3007,8 @@ static int fill_kv(const ee_model* m, int from_excl, int to_incl, ee_kv* kv, ee_
     hipLaunchKernelGGL(k_bf16_rope_append, dim3(near > 1 ? entry_grid(B) : B, rope_blocks(0, c.n_kv_heads, B * nl), nl), dim3(256), 0, s, kvb, kv_n, 0, idx, n_ptr, B, near,
                        b->st<int32_t>(L.pos), m->d_rope, c.max_pos, make_view(m, kv, from_excl + 1, b),
                        (bf16_t*)nullptr, (bf16_t*)nullptr, b->st<int32_t>(L.status), zb.out_stride,
-                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, splits, (int64_t)b->Mpad * kv_n, b->wsp<float>(b->W.gemm_part), kv_n,
-                       splits == 1 ? kv_n : 0, false);
+                       (int32_t*)nullptr, (AttnJob*)nullptr, 1, 1, false, splits, (int64_t)b->Mpad * kv_n, b->wsp<float>(b->W.gemm_part), kv_n,
+                       splits == 1 ? kv_n : 0);
     EE_LAUNCH_CHECK();
     return EE_OK;
 }
