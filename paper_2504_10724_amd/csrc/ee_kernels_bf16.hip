@@ -70,17 +70,11 @@ struct AttnJob {
 // waves two groups of 32 positions.  `most`: what the host launched, from the capacity.  Taken on the device, because
 // only there it is known how many rows are left and how long they are: by the capacities alone, 4 of 16 rows of the
 // 70B shape took 24 us with their merge (19 now; 19 with twice the shares whatever is live), one row of 2000
-// positions 19 (16).  Up to 96 pairs four shares may go down to one group per wave (share_limit): layer of 8 rows of 2 kv heads,
-// up to 900 positions, 41.1 us with shares of 256 positions, 38.8 so, 37 rows 50.1 and 49.4, 8 rows of 4 kv heads 59.4 and 56.8, one row of the 7B
-// shape 96.4 and 95.6; six of them lose it again (37 rows 50.7), and from 120 pairs on so do four (128 pairs 108.8 and 109.7).  All rows live, attention and merge: 16 rows of the 70B shape 34 us at 1024 workgroups, 31
+// positions 19 (16).  All rows live, attention and merge: 16 rows of the 70B shape 34 us at 1024 workgroups, 31
 // here; 37 rows of 2 kv heads, up to 900 positions, 27 and 17; 12 entries of four contexts at the 7B shape (384
 // pairs) 64 unshared, 55 in two; 60 entries (480 pairs) of the 70B shape 46 in two, 41 unshared.
-__host__ __device__ __forceinline__ int share_limit(int n_pos, int pairs) {
-    const int whole = n_pos >> 8, small = n_pos >> 7;
-    return pairs <= 96 && small > whole && whole < 4 ? (small < 4 ? small : 4) : whole;
-}
 __device__ __forceinline__ int attn_shares(int pairs, int n_pos, int most) {
-    return max(1, min(min(most, share_limit(n_pos, pairs)), max(512 / pairs, pairs <= 384 ? 2 : 1)));
+    return max(1, min(min(most, n_pos >> 8), max(512 / pairs, pairs <= 384 ? 2 : 1)));
 }
 
 struct JobArgs {        // jobs == nullptr: none are left
@@ -2775,7 +2769,7 @@ static CtxTiles ctx_tiles(const ee_model_config& c, const ee_batch* b) {
 // pay for the merge launch too (4 rows of 40 to 200 positions of the 70B shape, attention 11.2 us, 12.7 with room for 3000 more).
 static int attn_most(const ee_model_config& c, const ee_kv* kv, const ee_batch* b) {
     const int pairs = c.n_kv_heads * b->B;
-    int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, share_limit(kv->max_cap, pairs)});
+    int most = pairs >= 512 || kv->max_cap < (pairs >= 192 ? 1024 : 672) ? 1 : std::min({16, (1024 + pairs - 1) / pairs, kv->max_cap / 256});
     while (most > 1 && (size_t)b->Mpad * c.n_kv_heads * most * 16 * ATTN_SHARE * 4 > b->W.attn_part_bytes) --most;
     return most;
 }

@@ -151,3 +151,15 @@ def test_fills_up_to_the_last_exit_are_those_of_the_step(shape, exits):
         assert rc == 0 and len(want) == exits[-1] - exits[0]
         for l, (rc, ran) in zip(exits, fill):
             assert rc == 0 and fills(ran) == want[len(want) - (exits[-1] - l):], (n, l)
+
+
+# 16, 74, 96 and 32 (row, kv head) pairs: few enough that places stay empty, and still no share below two groups of 32 positions per wave
+@pytest.mark.parametrize("hq,hkv,rows,cap,most", [(4, 2, 8, 704, 2), (4, 2, 8, 928, 3), (4, 2, 37, 928, 3), (64, 8, 12, 736, 2), (32, 32, 1, 992, 3),
+                                                  (32, 32, 1, 1024, 4), (4, 2, 8, 640, 1)])
+def test_positions_are_shared_in_pieces_of_256(hq, hkv, rows, cap, most):
+    """how a row's positions are shared decides in which order its partial softmax sums are added, so it decides the bits"""
+    cfg = dict(_cfg((hq, hkv, 512, 1024), 1, [1]), vocab=512)
+    ((rc, ran),), = launches([dict(cfg=cfg, rows=rows, cap=cap, calls=[["layer_forward", 1]])])
+    attention = next(x for x in ran if x["kernel"] == "k_bf16_attn_decode")
+    assert rc == 0 and attention["grid"] == [hkv, rows, most]
+    assert any(x["kernel"] == "k_bf16_attn_merge" for x in ran) == (most > 1)
