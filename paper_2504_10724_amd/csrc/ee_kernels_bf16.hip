@@ -911,22 +911,34 @@ k_bf16_gemm_dma2(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 // LDS slots and loads as in the loops of k_bf16_gemm_dma8 and k_bf16_gemm_cols below, which take over where few row tiles are live.
 //
 // While waves 0 .. 3 multiply, waves 4 .. 7 read their operands of a stage from LDS and send their tiles of the stage four ahead;
-// then they change places, at a barrier.  The matrix pipes are busy 83 % of the time (66 % in the loops below), and what
-// limits the product then is power, of which 16x16x32 MFMAs take less than 32x32x16 (alone, on random data, 2.08 PFLOP/s against
-// 1.79 to 1.85; in this loop 1.47 at 1.69 GHz against 1.38 at 1.55).  2048 rows: down of the 70B shape 704 -> 654 us, gate/up
-// 1420..1507 -> 1402; exit head of 1024 entries at the 7B shape, with its new epilogue, 300..323 -> 258..267; 256 rows, gate/up
-// of the 70B shape 228..252 -> 218..243.
-// TURNS: the live row tiles from which on this is the faster loop.  With fewer, memory sets the pace and a wave's turn
-// holds up its requests: gate/up of the 70B shape (256 columns) below / here 128 rows 157 / 164..171 us, 160 174 / 195, 200 222 / 227,
-// 256 230 / 220, down 160 113 / 110, 200 128 / 124; of the 34B shape (192) 128 rows 127 / 143, 180 166 / 172,
-// 230 182 / 177.
+// then they change places, at a barrier.  What limits the product then is power, of which 16x16x32 MFMAs take less than 32x32x16
+// (alone, on random data, 2.08 PFLOP/s against 1.79 to 1.85; in this loop 1.47 at 1.69 GHz against 1.38 at 1.55).  2048 rows: down of
+// the 70B shape 704 -> 654 us, gate/up 1420..1507 -> 1402; exit head of 1024 entries at the 7B shape, with its new epilogue,
+// 300..323 -> 258..267.
 #define SB __builtin_amdgcn_sched_barrier(0)
 template <int NT>
 struct TurnShape;
 template <>
-struct TurnShape<8> { static constexpr int NA = 8, NB = 4, STEP = 2, TURNS = 7; };
+struct TurnShape<8> { static constexpr int NA = 8, NB = 4, STEP = 2; };
 template <>
-struct TurnShape<6> { static constexpr int NA = 4, NB = 6, STEP = 4, TURNS = 7; };
+struct TurnShape<6> { static constexpr int NA = 4, NB = 6, STEP = 4; };
+
+// Whether the workgroups of a row group take turns (below: the loops that follow / here).
+// One group: with seven live row tiles or more (layer of the 70B shape 200 rows, gate/up 197 / 191 us, down 119 / 112; of the 34B
+// shape, 192 columns, 200 rows 160 / 157).  With fewer, memory sets the pace and a wave's turn holds up its requests (gate/up of
+// the 70B shape 128 rows 157 / 164..171, 160 174 / 195, of the 34B shape 128 127 / 143, 180 166 / 172).
+// Several groups: the last one from five tiles on, as the groups of a column tile read the same weights and keep step only on one loop (layer
+// of 400 rows, 144 of them in the second group, that group below / here: 7B shape 354 / 330 us, 34B 718 / 658, 70B 840 / 764; 1700
+// rows 1074 / 1064, 2130 / 2076, 2622 / 2564).
+// Slices of K: a turn more at the start and at the end of each, and where the groups do not keep step short ones lose more than that.
+// All groups in turns, stages of a slice: down of the 2048-wide model 11 (512 rows) 35.5 / 37.7 us, 22 (1024) 49.3 / 50.0, of the 7B shape
+// 21 (256 rows) 54.5 / 56.7, 43 (512) 66.0 / 64.5, of the 70B shape 112 (512) 211 / 202; a last group of fewer tiles: 7B shape 300 rows, q|k|v
+// 64 54.5 / 57.5, down 43 59.5 / 61.8, 600 rows, down 68 79.0 / 80.3, 34B 300 rows, q|k|v 84 80.5 / 82.5; 7B 1100 rows, down 114 115 / 111.
+__device__ __forceinline__ bool takes_turns(int n, int row_base, int splits, int stages) {
+    const int groups = (n + 255) >> 8, from = groups > 1 ? 5 : 7;
+    const int live = (n - row_base + 31) >> 5, last = (n - 256 * (groups - 1) + 31) >> 5;      // row tiles from this group on, of the last one
+    return live >= from && (splits == 1 || stages >= (last >= from ? 40 : 96));
+}
 
 struct TurnCtx {
     uint4*       lds;        // [5][32][64]
@@ -1080,7 +1092,7 @@ k_bf16_gemm_dma8(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
         ep.out = partial + (int64_t)sp * part_plane;
         ep.ldo = part_ld;
     }
-    if (mbs >= TurnShape<8>::TURNS) {
+    if (takes_turns(n, row_base, splits, T)) {
         const TurnCtx c{&lds[0][0][0], xg, wg, KB, NBs, ks_lo, T, row_base, n, tile * 8, 8};
         if (splits > 1) tile_in_turns<EPI == EPI_RESID ? EPI_STORE : EPI, 8>(c, ep);     // others than these two are never sliced
         else tile_in_turns<EPI, 8>(c, ep);
@@ -1327,7 +1339,7 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
     Xp += (int64_t)blockIdx.z * zb.x_stride;
     ep.out += (int64_t)blockIdx.z * zb.out_stride;
-    if (n - row_base > 32 * (TurnShape<6>::TURNS - 1)) {
+    if (takes_turns(n, row_base, 1, KB >> 1)) {
         const TurnCtx t{&lds[0][0][0], Xp + ((int64_t)rg * 8 * KB) * 64, Wp + (int64_t)(nb_off + tile * COLS_NT) * 64, KB, NBs, 0, KB >> 1,
                         row_base, n, tile * COLS_NT, min(COLS_NT, NB_total - tile * COLS_NT)};
         tile_in_turns<EPI, COLS_NT>(t, ep);

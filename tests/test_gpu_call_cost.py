@@ -12,19 +12,19 @@ from paper_2504_10724_amd import session as S
 
 pytestmark = pytest.mark.gpu
 
-ATTENTION, QKV = (1 << capi.KERNEL_CLASSES.index(k) for k in ("attention", "gemm_qkv"))
-SHAPES = {"70b": (8192, 64, 8), "7b": (4096, 32, 32)}      # d, query heads, kv heads (the FFN is kept small)
+ATTENTION, QKV, DOWN = (1 << capi.KERNEL_CLASSES.index(k) for k in ("attention", "gemm_qkv", "gemm_down"))
+SHAPES = {"70b": (8192, 64, 8), "7b": (4096, 32, 32), "small": (2048, 16, 4)}      # d, query heads, kv heads (the FFN is kept small)
 
 
-def _model(shape, layers=1):
+def _model(shape, layers=1, ffn=256):
     d, hq, hkv = SHAPES[shape]
-    m = S.Model(n_layers=layers, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ffn=256, vocab=512, dtype="bf16",
+    m = S.Model(n_layers=layers, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ffn=ffn, vocab=512, dtype="bf16",
                 exit_layers=[layers], max_pos=4096)
     rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02)      # noqa: E731
     one = torch.ones(d, device="cuda")
     for l in range(1, layers + 1):
-        m.set_layer(l, g_attn=one, W_qkv=rnd((hq + 2 * hkv) * 128, d), W_o=rnd(d, hq * 128), g_ffn=one, W_gate=rnd(256, d),
-                    W_up=rnd(256, d), W_down=rnd(d, 256))
+        m.set_layer(l, g_attn=one, W_qkv=rnd((hq + 2 * hkv) * 128, d), W_o=rnd(d, hq * 128), g_ffn=one, W_gate=rnd(ffn, d),
+                    W_up=rnd(ffn, d), W_down=rnd(d, ffn))
     m.set_exit(0, g=one, W=rnd(512, d))
     m.set_embed(rnd(512, d))
     return m
@@ -164,3 +164,18 @@ def test_fp32_layer_of_short_rows_in_a_large_cache(rows, positions):
         t[room] = min(got[3:])
     print(f"[case] fp32 layer of {rows} rows of {positions} positions: {t[0]:.1f} us, {t[2000]:.1f} with room for 2000 more", flush=True)
     assert t[2000] <= 1.15 * t[0]
+
+
+# a second row group of 144 rows, and of 256.  With the two groups on two loops 400 rows took 1.05 times as long as 512, now 0.91 to 1.00
+@pytest.mark.parametrize("shape,ffn,kernels", [("small", 5632, DOWN), ("7b", 11008, DOWN), ("70b", 256, QKV)],
+                         ids=["2048-wide-down", "7b-down", "70b-qkv"])
+def test_products_of_400_rows_take_no_longer_than_of_512(shape, ffn, kernels):
+    print(f"[case] products of 400 and 512 rows, {shape}, FFN {ffn}", flush=True)
+    m, us = _model(shape, ffn=ffn), []
+    for rows in (400, 512):
+        kv, b = S.KVCache(m, 1, [32] * rows), S.Batch(m, rows)
+        b.reset(np.arange(rows), np.zeros(rows, np.int32), None)
+        b.begin_step()
+        us.append(_time(lambda: capi.check(S.layer_forward(m, 1, kv, b)), kernels))
+    print(f"[times] {us[0]:.1f} us, {us[1]:.1f} us", flush=True)
+    assert us[0] <= 1.03 * us[1], us

@@ -1,6 +1,6 @@
 """The tile kernels' two loops (waves of a SIMD in turns where most row tiles are live, else each wave on its own) add up in one
 order: rows of the same token are the same bits, whichever loop and place in the tile they get.  Row tiles on both sides of
-the rule, a last 16-row tile with one row, row groups of which the last one takes the other loop; stores, residual updates,
+the rule, a last 16-row tile with one row, row groups of which the last one takes the other loop or the same; stores, residual updates,
 SwiGLU and exit statistics with logits."""
 import numpy as np
 import pytest
@@ -34,15 +34,14 @@ def same_rows(x, ref, what):
     assert not differ, (what, differ[:8])
 
 
-# 224 tiles of 256 columns and the down projection in K slices; 230 workgroups of 192 columns, the last with two tile-rows of six
-@pytest.mark.parametrize("d,ffn", [(1024, 28672), (512, 22016)])
-def test_one_row_group(d, ffn):
+def live_rows(d, ffn, rows, counts):
+    """a layer and its head on the first `live` of the rows, for each of the counts: the rows of the first count again"""
     m = model(d, 8, 8, ffn, 51200)
-    kv, b = S.KVCache(m, 1, [32] * 256), S.Batch(m, 256)
-    logits, ref = torch.empty((256, 51200), device="cuda"), None
-    for live in (160, 161, 176, 177, 192, 193, 208, 209, 224, 225, 240, 241, 256):
-        print(f"[case] one row group, d = {d}, {live} rows", flush=True)
-        b.reset(np.arange(256) % TOKENS, np.zeros(256, np.int32), None)
+    kv, b = S.KVCache(m, 1, [32] * rows), S.Batch(m, rows)
+    logits, ref = torch.empty((rows, 51200), device="cuda"), None
+    for live in counts:
+        print(f"[case] d = {d}, {live} of {rows} rows", flush=True)
+        b.reset(np.arange(rows) % TOKENS, np.zeros(rows, np.int32), None)
         b.begin_step()
         b.field("n_active").fill_(live)
         assert S.layer_forward(m, 1, kv, b) == 0 and S.exit_head(m, 0, 0.5, False, b, logits) == 0
@@ -50,6 +49,18 @@ def test_one_row_group(d, ffn):
         ref = ref or got                                     # 160 rows: no row tile in turns
         for x, r, what in zip(got, ref, ("state", "logits", "confidence", "token")):
             same_rows(x, r, (what, live))
+
+
+# 224 tiles of 256 columns and the down projection in K slices; 230 workgroups of 192 columns, the last with two tile-rows of six
+@pytest.mark.parametrize("d,ffn", [(1024, 28672), (512, 22016)])
+def test_one_row_group(d, ffn):
+    live_rows(d, ffn, 256, (160, 161, 176, 177, 192, 193, 208, 209, 224, 225, 240, 241, 256))
+
+
+# the last group with fewer than five row tiles (its own loop), with five, six and seven; the down projection in slices of 56 stages and of 10 or 11
+@pytest.mark.parametrize("d,ffn", [(2048, 28672), (512, 22016)])
+def test_two_row_groups(d, ffn):
+    live_rows(d, ffn, 512, (160, 257, 300, 384, 385, 401, 416, 417, 433, 448, 449, 480, 512))
 
 
 # the last row group has 100 rows (its own loop), 208 and 255; 1124 entries of the narrower model: 192 columns
@@ -63,8 +74,5 @@ def test_several_row_groups(d, heads, kv_heads, ffn, n):
     logits = torch.empty((n, 32000), device="cuda")
     assert S.prefill(m, kv, b, np.arange(n) % TOKENS, np.zeros(n, np.int32), np.arange(n)) == 0
     assert S.exit_head(m, 0, 0.0, True, b, logits) == 0
-    tail = n // 256 * 256 // TOKENS * TOKENS + TOKENS        # rows of the last row group, the first token's first
     for x, what in ((b.field("h"), "state"), (logits, "logits"), (b.field("head_conf"), "confidence"), (b.field("head_tok"), "token")):
         same_rows(x, x, what)
-        if n - tail >= TOKENS:
-            same_rows(x, x[tail:], what)
