@@ -1309,11 +1309,11 @@ __device__ __forceinline__ void cols_wave(const ColsCtx& c, const int r0, const 
     // the count of loads a wave may leave in flight is per wave and follows from what it sends, so each
     // combination runs its own copy of the loop; a wave whose two row tiles are live (the common case)
     // runs a copy without the live-tile test
+    // (at most six row tiles are live here, so that a wave that sends X sends W too)
     const bool all = cnt == COLS_NR;
-    if (sends_x && sends_w) { if (all) slice(Yes{}, Yes{}, Yes{}); else slice(Yes{}, Yes{}, No{}); }
-    else if (sends_x)       { if (all) slice(Yes{}, No{}, Yes{});  else slice(Yes{}, No{}, No{}); }
-    else if (sends_w)       { slice(No{}, Yes{}, No{}); }
-    else                    { slice(No{}, No{}, No{}); }
+    if (sends_x)      { if (all) slice(Yes{}, Yes{}, Yes{}); else slice(Yes{}, Yes{}, No{}); }
+    else if (sends_w) { slice(No{}, Yes{}, No{}); }
+    else              { slice(No{}, No{}, No{}); }
 
 #pragma unroll
     for (int i = 0; i < COLS_NR; ++i) {
@@ -1350,7 +1350,7 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     c.KB = KB; c.NBs = NBs;
     c.ks_lo = 0;
     c.T = KB >> 1;                                            // stages: a positive multiple of 4 (K is a multiple of 128)
-    c.mbs = min(8, (n - row_base + 31) >> 5);
+    c.mbs = (n - row_base + 31) >> 5;                        // at most six (takes_turns)
     c.nt_live = min(COLS_NT, NB_total - tile * COLS_NT);
     c.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     c.lane = threadIdx.x & 63;
