@@ -108,9 +108,9 @@ __device__ __forceinline__ void leave_job(const JobArgs& a, int i, int n, Row ro
 // ------------------------------------------------------------------ RMSNorm -> A tiles
 // The threads of a block normalise one row (hr: d floats) and write it as list entry
 // i of the [Mpad][d] activation matrix in tile order.  Every thread reads only the 8-float chunks
-// c = threadIdx.x + NORM_THREADS j, so a caller may have written those same chunks just before.
-// One chunk per thread up to d = 8192, and no wave without one (norm_threads): a row's sum of squares adds up the waves' in their
-// order, so that waves without a chunk would add nothing, and the smaller blocks of narrower rows fit on a CU side by side
+// c = threadIdx.x + blockDim.x j, so a caller may have written those same chunks just before.
+// One chunk per thread up to d = 8192, and no wave without one but the one that leaves the attention's job (norm_threads): a row's sum
+// of squares adds up the waves' in their order, so that waves without a chunk would add nothing, and the smaller blocks of narrower rows fit on a CU side by side
 // (1024 rows of 4096 values, 1024 threads / 512: begin and norm 14.2 / 12.7 us, norm 9.5 / 8.8, finish of two K slices 17.3 / 16.7).
 // Sum of the squares of a chunk, its fused multiply-adds written out: every kernel that normalises a row (here, the
 // finish of a sliced product, the step begin) has to give the same bits, and left to the compiler which of the
@@ -166,13 +166,13 @@ __device__ __forceinline__ void rmsnorm_row(const float* hr_, const float* gain,
         return;
     }
     float ss = 0.f;
-    for (int c = threadIdx.x; c < n8; c += NORM_THREADS) {
+    for (int c = threadIdx.x; c < n8; c += blockDim.x) {
         float4 a = hr[2 * c], b = hr[2 * c + 1];
         ss += sum_sq8(a, b);
     }
-    ss = block_sum<NORM_THREADS>(ss, red);
+    ss = waves_sum(ss, red);
     float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int c = threadIdx.x; c < n8; c += NORM_THREADS) {
+    for (int c = threadIdx.x; c < n8; c += blockDim.x) {
         float4 a = hr[2 * c], b = hr[2 * c + 1];
         float4 ga = g4[2 * c], gb = g4[2 * c + 1];
         uint4 o;
@@ -2423,7 +2423,7 @@ k_splitk_resid_norm(const float* __restrict__ partial, int64_t plane, int ld, in
         }
         return;
     }
-    for (int c = threadIdx.x; c < (N >> 3); c += NORM_THREADS) {
+    for (int c = threadIdx.x; c < (N >> 3); c += blockDim.x) {
         const float* p = prow + c * 8;
         float4 s0 = *reinterpret_cast<const float4*>(p), s1 = *reinterpret_cast<const float4*>(p + 4);
 #pragma unroll 4
@@ -2471,7 +2471,7 @@ static FewShape few_shape(int tile_rows, int KB, int rows, int nz, int max_split
     return best;
 }
 
-// threads of a block that normalises a row of d values: one per chunk of 8, and a wave for the attention's job
+// threads of a block that normalises a row of d values: one per chunk of 8 up to NORM_THREADS, and a wave for the attention's job where there is room
 static int norm_threads(int d, const JobArgs& jobs) {
     const int chunks = (d / 8 + 63) / 64 * 64;
     return std::min(NORM_THREADS, chunks + (jobs.jobs != nullptr ? 64 : 0));
