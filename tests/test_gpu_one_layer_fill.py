@@ -1,7 +1,8 @@
 """GPU parity of the keys and values of ONE skipped layer in batches whose capacity takes the product to each of its kernels:
 the one whose waves stream alone (up to 128 rows, and up to 256 where the tiles are few), 128 columns (257 and 1024), 192
 columns (1025 to 1280; 43 column tiles of which the last has four of six tile-rows) and 256 columns (1281).  All
-rows have left, or a few entries of a large batch are filled from kept states."""
+rows have left, or a few entries of a large batch are filled from kept states.  And of seven and eight layers in one launch of
+256-column tiles whose row tiles are nearly all live."""
 import numpy as np
 import pytest
 import torch
@@ -15,6 +16,12 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("rows", [1, 65, 200, 257, 1024, 1025, 1100, 1280, 1281])
 def test_one_skipped_layer(rows):
     fill_and_compare(2, 32, rows)
+
+
+# 224 and 256 workgroups, a table of weights: full row groups, and seven row tiles of eight
+@pytest.mark.parametrize("layers,rows", [(8, 200), (8, 225), (8, 256), (9, 256)])
+def test_several_skipped_layers_of_many_rows(layers, rows):
+    fill_and_compare(layers, 32, rows)
 
 
 # 4608 values and 8 kv heads: nine slices, added up by a launch of their own (129 rows and more)
