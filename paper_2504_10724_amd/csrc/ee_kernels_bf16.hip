@@ -911,10 +911,11 @@ k_bf16_gemm_dma2(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
 // LDS slots and loads as in the loops of k_bf16_gemm_dma8 and k_bf16_gemm_cols below, which take over where few row tiles are live.
 //
 // While waves 0 .. 3 multiply, waves 4 .. 7 read their operands of a stage from LDS and send their tiles of the stage four ahead;
-// then they change places, at a barrier.  What limits the product then is power, of which 16x16x32 MFMAs take less than 32x32x16
-// (alone, on random data, 2.08 PFLOP/s against 1.79 to 1.85; in this loop 1.47 at 1.69 GHz against 1.38 at 1.55).  2048 rows: down of
-// the 70B shape 704 -> 654 us, gate/up 1420..1507 -> 1402; exit head of 1024 entries at the 7B shape, with its new epilogue,
-// 300..323 -> 258..267.
+// then they change places, at a barrier.  What limits full products is power, of which 16x16x32 MFMAs take less than 32x32x16
+// (alone, on random data, 2.08 PFLOP/s against 1.79 to 1.85).  2048 rows of the 70B shape, one machine, loops below / here: gate/up 1454 us,
+// matrix pipes busy 77 % of the time at 1.64 GHz / 1338, 76 % at 1.81; down with its K-slice finish 704 / 658; q|k|v, 192 columns, whose
+// operands take LDS longer than the MFMAs last, 305 / 311.  Exit head of 1024 entries at the 7B shape 211 / 201, with logits 300..323 /
+// 258..267 (the epilogue's 16-byte stores too).
 #define SB __builtin_amdgcn_sched_barrier(0)
 template <int NT>
 struct TurnShape;
@@ -2728,10 +2729,12 @@ static bool gemm_tiled(const ee_batch* b, const void* X, const void* W, int N, i
     }
     if (EPI != EPI_RESID && splits == 1 && nz == 1 && row_groups > 1) {
         // Several row groups: 192 columns where they cost fewer rounds of workgroups times a round's length.  A round of
-        // 256 / 192 / 128 columns takes 1 / 0.82 / 0.73, the last one down to 0.85 of that when it is nearly empty.  Gate/up 256 / 192
-        // columns: 7B shape 400 rows 93 / 80 us (172 / 230 workgroups), 768 entries 180 / 147, 1536 277 / 227, 2048 292 / 303 (688 /
-        // 920, not taken); 34B 512 entries 342 / 290, 1024 544 / 576 (not taken); 70B 512 371 / 428 (not taken).  q|k|v: 7B shape 1536
-        // entries 180 / 151, 70B 1024 166 / 151.
+        // 256 / 192 / 128 columns takes 1 / 0.82 / 0.73, the last one down to 0.85 of that when it is nearly empty.  (192: gate/up of 400
+        // to 2048 rows 0.79 to 0.83, q|k|v of the 70B shape 0.88.  128: 0.59 to 0.63 against full groups of 256 columns, which a choice
+        // between 192 and 128 has not hung on.)  Gate/up 256 / 192 columns: 7B shape 400 rows 89 / 76 us (172 / 230
+        // workgroups), 768 entries 176 / 146, 1024 182 / 157, 1536 271 / 228, 2048 282 / 300 (688 / 920, not taken); 34B 512 entries 345 / 303, 1024
+        // 543 / 588 (not taken); 70B 512 377 / 427 (not taken).  q|k|v: 7B shape 1536 entries 182 / 158, 2048 186 / 179, 70B 1024 174 / 156,
+        // 2048 355 / 318.
         auto cost = [](int wgs, float round) {
             const int full = (wgs - 1) / 256;
             return round * ((float)full + 0.85f + 0.15f * (float)(wgs - 256 * full) / 256.f);
