@@ -934,11 +934,12 @@ struct TurnShape<6> { static constexpr int NA = 4, NB = 6, STEP = 4; };
 // Slices of K: a turn more at the start and at the end of each, and where the groups do not keep step short ones lose more than that.
 // All groups in turns, stages of a slice: down of the 2048-wide model 11 (512 rows) 35.5 / 37.7 us, 22 (1024) 49.3 / 50.0, of the 7B shape
 // 21 (256 rows) 54.5 / 56.7, 43 (512) 66.0 / 64.5, of the 70B shape 112 (512) 211 / 202; a last group of fewer tiles: 7B shape 300 rows, q|k|v
-// 64 54.5 / 57.5, down 43 59.5 / 61.8, 600 rows, down 68 79.0 / 80.3, 34B 300 rows, q|k|v 84 80.5 / 82.5; 7B 1100 rows, down 114 115 / 111.
+// 64 54.5 / 57.5, down 43 59.5 / 61.8, 600 rows, down 68 79.0 / 80.3, on another machine 92 / 85, 34B 300 rows, q|k|v 84 80 / 82 and 90 / 86, 7B
+// 1100 rows, down 114 115 / 111.
 __device__ __forceinline__ bool takes_turns(int n, int row_base, int splits, int stages) {
     const int groups = (n + 255) >> 8, from = groups > 1 ? 5 : 7;
     const int live = (n - row_base + 31) >> 5, last = (n - 256 * (groups - 1) + 31) >> 5;      // row tiles from this group on, of the last one
-    return live >= from && (splits == 1 || stages >= (last >= from ? 40 : 96));
+    return live >= from && (splits == 1 || stages >= (last >= from ? 40 : 65));
 }
 
 struct TurnCtx {
