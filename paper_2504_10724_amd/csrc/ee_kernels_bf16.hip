@@ -933,13 +933,17 @@ struct TurnShape<6> { static constexpr int NA = 4, NB = 6, STEP = 4; };
 // rows 1074 / 1064, 2130 / 2076, 2622 / 2564).
 // Slices of K: a turn more at the start and at the end of each, and where the groups do not keep step short ones lose more than that.
 // All groups in turns, stages of a slice: down of the 2048-wide model 11 (512 rows) 35.5 / 37.7 us, 22 (1024) 49.3 / 50.0, of the 7B shape
-// 21 (256 rows) 54.5 / 56.7, 43 (512) 66.0 / 64.5, of the 70B shape 112 (512) 211 / 202; a last group of fewer tiles: 7B shape 300 rows, q|k|v
-// 64 54.5 / 57.5, down 43 59.5 / 61.8, 600 rows, down 68 79.0 / 80.3, on another machine 92 / 85, 34B 300 rows, q|k|v 84 80 / 82 and 90 / 86, 7B
-// 1100 rows, down 114 115 / 111.
+// 21 (256 rows) 54.5 / 56.7, 43 (512) 66.0 / 64.5, of the 70B shape 112 (512) 211 / 202.  Planes for the append kernel, whose launches
+// leave CUs idle, need longer ones if the last group has the seven tiles that the old loops are good at: q|k|v of the 7B shape 64 (512
+// rows) 58.2 / 59.8, (480) 57.0 / 58.4, but (440: six tiles) 59.3 / 57.1, of the 70B shape 85 (512) 85.3 / 83.2.  A last group of fewer tiles: 7B shape
+// 300 rows, q|k|v 64 54.5 / 57.5, down 43 59.5 / 61.8, 600 rows, down 68 79.0 / 80.3, on another machine 92 / 85, 34B 300 rows, q|k|v 84
+// 80 / 82 and 90 / 86, 7B 1100 rows, down 114 115 / 111.
+template <int EPI>
 __device__ __forceinline__ bool takes_turns(int n, int row_base, int splits, int stages) {
     const int groups = (n + 255) >> 8, from = groups > 1 ? 5 : 7;
     const int live = (n - row_base + 31) >> 5, last = (n - 256 * (groups - 1) + 31) >> 5;      // row tiles from this group on, of the last one
-    return live >= from && (splits == 1 || stages >= (last >= from ? 40 : 65));
+    const bool longer = last < from || (EPI == EPI_STORE && last >= 7);
+    return live >= from && (splits == 1 || stages >= (longer ? 65 : 40));
 }
 
 struct TurnCtx {
@@ -1094,7 +1098,7 @@ k_bf16_gemm_dma8(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
         ep.out = partial + (int64_t)sp * part_plane;
         ep.ldo = part_ld;
     }
-    if (takes_turns(n, row_base, splits, T)) {
+    if (takes_turns<EPI>(n, row_base, splits, T)) {
         const TurnCtx c{&lds[0][0][0], xg, wg, KB, NBs, ks_lo, T, row_base, n, tile * 8, 8};
         if (splits > 1) tile_in_turns<EPI == EPI_RESID ? EPI_STORE : EPI, 8>(c, ep);     // others than these two are never sliced
         else tile_in_turns<EPI, 8>(c, ep);
@@ -1341,7 +1345,7 @@ k_bf16_gemm_cols(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int
     if (zb.w_tab) Wp = reinterpret_cast<const uint4*>(zb.w_tab[zb.z0 + blockIdx.z]);
     Xp += (int64_t)blockIdx.z * zb.x_stride;
     ep.out += (int64_t)blockIdx.z * zb.out_stride;
-    if (takes_turns(n, row_base, 1, KB >> 1)) {
+    if (takes_turns<EPI>(n, row_base, 1, KB >> 1)) {
         const TurnCtx t{&lds[0][0][0], Xp + ((int64_t)rg * 8 * KB) * 64, Wp + (int64_t)(nb_off + tile * COLS_NT) * 64, KB, NBs, 0, KB >> 1,
                         row_base, n, tile * COLS_NT, min(COLS_NT, NB_total - tile * COLS_NT)};
         tile_in_turns<EPI, COLS_NT>(t, ep);
