@@ -28,8 +28,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # HBM bytes per launch of the gate/up GEMM at batch 256 from the rocprofv3 counter runs summarised in
 # profiles/llama2_70b_b256_hbm_traffic.md (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, KiB -> bytes); valid
 # only for the kernel source it was measured on.
-TRAFFIC_KERNEL_SHA1 = "7c744dc760523acd515bcdbc88edc6316acd0d91"
-TRAFFIC_GATE_UP_BYTES = (942352 + 9590) * 1024
+TRAFFIC_KERNEL_SHA1 = "c7812f83ba9b5cfb177a998c63ef316cc6999c9d"
+TRAFFIC_GATE_UP_BYTES = (944124 + 9352) * 1024
 
 
 def measured_traffic(batch):
